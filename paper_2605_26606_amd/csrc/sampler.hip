@@ -9,11 +9,21 @@
 // with an in-order double-precision CDF except within rounding of a boundary.
 //
 // Nucleus truncation (top_p < 1): the tokens in order of decreasing probability (ties: lower id first) until their
-// cumulative mass reaches top_p keep their weight, the rest get none; the passes above then run on the kept
-// tokens.  Decreasing probability is decreasing logit, so the cut is found by a radix select over an
-// order-preserving 32-bit key of the logit, four passes of 8 bits, each with a histogram of the MASS per bucket
-// (double, one histogram per wave, added up in wave order): the bucket in which the cumulative mass from the top
-// crosses top_p * Z is the one to refine.  The row is re-read from L2 for every pass.
+// cumulative mass reaches top_p keep their weight, the rest get none; the passes above then run on the kept tokens.
+// Two ways to the cut:
+//   binned (nucleus_binned): one pass over the row files every token in one of 4096 bins of 1/32 of a scaled logit, with
+//     its count and its mass relative to the bin's upper edge as a 25-bit fraction in ONE 64-bit LDS integer add (exact in
+//     any order), so neither the maximum nor Z is needed beforehand; the bin in which the mass from the top crosses
+//     top_p Z is known then, a second pass sums the tokens above it per wave segment (the sums the sampler needs anyway)
+//     and lists the bin's own tokens in LDS, and the exact cut is found in that list.  The row is read twice.
+//   radix (any row): a select over an order-preserving 32-bit key of the logit, four passes of 8 bits with a histogram of
+//     the mass per bucket (double, one histogram per wave, added up in wave order), between two summing passes.  The row
+//     is read six times and the few buckets in use make the LDS adds collide.  Taken when the binned way cannot be:
+//     a maximum more than 32 above that of 1024 sampled tokens, more than 5120 tokens in the crossing bin, or more than
+//     256 of them in one of its 4096 parts (logits almost all alike), scaled logits beyond 1e5.
+//   1024 rows of 151936 logits: 1470 us by the radix way, 271 us binned (read once at the copy rate: 121 us).
+#include <type_traits>
+
 #include "pc_internal.h"
 
 namespace pc {
@@ -95,8 +105,313 @@ __device__ inline void load_scaled(const float *__restrict__ x, int idx, int end
 
 __device__ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
+// ---- the binned way to the nucleus
+static constexpr int NUC_BINS = 4096;          // four per thread
+static constexpr float NUC_PER_UNIT = 32.0f;   // bins per unit of scaled logit
+static constexpr int NUC_LIST = 5120;          // tokens of the crossing bin that fit the list (72 KB in all: two blocks per CU)
+static constexpr int NUC_TIES = 256;           // tokens of one part of it that are ranked one against the other
+static constexpr int NUC_COUNT_SHIFT = 44;     // a bin: count above, sum of 25-bit fractions below (2^18 tokens fit either)
+
+struct NucleusBins {
+    union {
+        struct {
+            unsigned long long bin[NUC_BINS];
+            uint32_t key[NUC_LIST];
+            int32_t id[NUC_LIST];
+        };
+        struct {
+            double hist[SAMPLE_WAVES][256];
+            int cnt[SAMPLE_WAVES][256];
+            double comb[256];
+            int ccnt[256];
+        } radix;
+    };
+    double wave_sum[SAMPLE_WAVES];
+    float wave_max[SAMPLE_WAVES];
+    uint32_t wave_lo[SAMPLE_WAVES], wave_hi[SAMPLE_WAVES];
+    double above;
+    int sel, last, n, bad;
+    uint32_t tie_key[NUC_TIES], tie_part[NUC_TIES];
+    int32_t tie_id[NUC_TIES];
+    uint32_t kstar;
+    int tie_limit;
+};
+
+// From the bins (each thread owns four, in order of falling logit): the first one at which above + the running mass reaches
+// `want`, and the mass in front of it.  scale(bin) turns a bin's fraction sum into mass.  Leaves sb.sel (the last bin in
+// use if rounding leaves the total short) and sb.above; every thread must call it.  `total` (out): the mass of all bins.
+template <typename Scale>
+__device__ inline void nucleus_cross(NucleusBins &sb, double above, double top_p, double want, Scale scale, double &total) {
+    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
+    double m[4], own = 0.0;
+    int used = -1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned long long b = sb.bin[4 * tid + i];
+        m[i] = 0.0;
+        if (b >> NUC_COUNT_SHIFT) {
+            m[i] = (double)(b & ((1ull << NUC_COUNT_SHIFT) - 1)) * scale(4 * tid + i);
+            used = 4 * tid + i;
+        }
+        own += m[i];
+    }
+    double incl = own;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const double t = __shfl_up(incl, o, WAVE);
+        if (lane >= o) incl += t;
+    }
+    if (tid == 0) {
+        sb.sel = NUC_BINS;
+        sb.last = -1;
+    }
+    if (lane == WAVE - 1) sb.wave_sum[wave] = incl;
+    __syncthreads();
+    double before = above, all = 0.0;
+#pragma unroll
+    for (int w = 0; w < SAMPLE_WAVES; ++w) {
+        if (w < wave) before += sb.wave_sum[w];
+        all += sb.wave_sum[w];
+    }
+    total = all;
+    if (want < 0.0) want = top_p * all;
+    before += incl - own;
+    int mine = -1;
+    double run = before, at = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (mine < 0 && m[i] > 0.0 && run + m[i] >= want) {
+            mine = 4 * tid + i;
+            at = run;
+        }
+        run += m[i];
+    }
+    if (mine >= 0) atomicMin(&sb.sel, mine);
+    if (used >= 0) atomicMax(&sb.last, used);
+    __syncthreads();
+    if (sb.sel == NUC_BINS) {                  // (block-uniform)
+        if (used >= 0 && used == sb.last) {
+            double r = before;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (4 * tid + i < used) r += m[i];
+            sb.above = r;
+        }
+        __syncthreads();
+        if (tid == 0) sb.sel = sb.last;
+    } else if (mine == sb.sel) {
+        sb.above = at;
+    }
+    __syncthreads();
+}
+
+template <int VEC>
+__device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, int seg, float inv_t, float top_p, int eos_id,
+                                      float eos_bias, float eos_key_add, NucleusBins &sb, float *s_wm, double *s_ws,
+                                      Nucleus &nu) {
+    constexpr int STRIDE = WAVE * VEC, BLOCK = SAMPLE_WAVES * WAVE;
+    constexpr float LOG2E = 1.4426950408889634f;
+    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
+    if (vocab > (1 << 18)) return false;
+    auto raw_load = [&](int idx, int end, float (&v)[VEC]) {
+        if (VEC == 4 && idx + 3 < end) {
+            const float4 t = *(const float4 *)(x + idx);
+            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        } else {
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) v[c] = (idx + c) < end ? x[idx + c] : -INFINITY;
+        }
+    };
+    // ---- the top edge of the bins: 32 above the largest of 1024 tokens
+    {
+        const float v = x[(int)((int64_t)tid * vocab / BLOCK)] * inv_t;
+        const float wm = wave_max_f32(v);
+        if (lane == 0) sb.wave_max[wave] = wm;
+    }
+#pragma unroll
+    for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
+    if (tid == 0) sb.bad = sb.n = 0;
+    __syncthreads();
+    float top = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < SAMPLE_WAVES; ++w) top = fmaxf(top, sb.wave_max[w]);
+    if (!(fabsf(top) < 1e5f)) return false;
+    top = ceilf(top) + 32.0f;                  // every bin edge is then a multiple of 1/32 that fp32 holds exactly
+    __syncthreads();                           // (wave_max is written again below)
+    // place of a logit: (top - scaled logit) * 32; the EOS id's bias counts like in its key
+    auto place = [&](float raw, int idx) { return (top - (idx == eos_id ? raw + eos_key_add : raw) * inv_t) * NUC_PER_UNIT; };
+    auto scaled = [&](float raw, int idx) { return raw * inv_t + (idx == eos_id ? eos_bias : 0.f); };
+    auto fraction = [&](float v, int bin) {    // weight relative to the bin's upper edge, 25 bits
+        const float edge = top - (float)bin * (1.0f / NUC_PER_UNIT);
+        return (unsigned int)(__builtin_amdgcn_exp2f((v - edge) * LOG2E) * 33554432.0f + 0.5f);
+    };
+    // ---- pass 1: bins and maximum
+    float m = -INFINITY;
+    bool bad = false;
+    {
+        float cur[VEC], nxt[VEC];
+        raw_load(tid * VEC, vocab, nxt);
+        for (int base = tid * VEC; base < vocab; base += BLOCK * VEC) {
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) cur[c] = nxt[c];
+            if (base + BLOCK * VEC < vocab) raw_load(base + BLOCK * VEC, vocab, nxt);
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) {
+                const float p = place(cur[c], base + c);
+                if (p < (float)(NUC_BINS - 1)) {   // (96 below the top token's neighbourhood: no mass a double would notice)
+                    const float v = scaled(cur[c], base + c);
+                    m = fmaxf(m, v);
+                    if (p < 0.f) {
+                        bad = true;
+                    } else {
+                        const int b = (int)p;
+                        atomicAdd(&sb.bin[b], (1ull << NUC_COUNT_SHIFT) + fraction(v, b));
+                    }
+                }
+            }
+        }
+    }
+    const float wm = wave_max_f32(m);
+    if (lane == 0) sb.wave_max[wave] = wm;
+    if (bad) sb.bad = 1;
+    __syncthreads();
+    if (sb.bad) return false;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < SAMPLE_WAVES; ++w) M = fmaxf(M, sb.wave_max[w]);
+    if (!(fabsf(M) < 1e5f)) return false;
+    const double unit = 1.0 / 33554432.0;
+    double Z0, part_mass;
+    nucleus_cross(sb, 0.0, (double)top_p, -1.0, [&](int b) {
+        return unit * exp((double)top - (double)b / (double)NUC_PER_UNIT - (double)M);
+    }, Z0);
+    const int sel = sb.sel;
+    const double above = sb.above, want = (double)top_p * Z0;
+    const double scale = unit * exp((double)top - (double)sel / (double)NUC_PER_UNIT - (double)M);
+    const int n_list = (int)(sb.bin[sel] >> NUC_COUNT_SHIFT);
+    if (n_list > NUC_LIST) return false;
+    // ---- pass 2: this wave's segment: sum of the tokens above the crossing bin, the bin's own tokens into the list
+    double s = 0.0;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    {
+        const int b = min(vocab, wave * seg), e = min(vocab, b + seg);
+        constexpr int AHEAD = 2;
+        float cur[AHEAD][VEC], nxt[AHEAD][VEC];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) raw_load(b + u * STRIDE + lane * VEC, e, nxt[u]);
+        for (int base = b; base < e; base += AHEAD * STRIDE) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) cur[u][c] = nxt[u][c];
+            if (base + AHEAD * STRIDE < e) {
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) raw_load(base + (AHEAD + u) * STRIDE + lane * VEC, e, nxt[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) {
+                    const int idx = base + u * STRIDE + lane * VEC + c;
+                    const float p = place(cur[u][c], idx);
+                    if (p < (float)sel) {
+                        s += (double)expf(scaled(cur[u][c], idx) - M);
+                    } else if (p < (float)(sel + 1)) {
+                        const int at = atomicAdd(&sb.n, 1);
+                        const uint32_t key = logit_key(cur[u][c], idx, eos_id, eos_key_add);
+                        if (at < NUC_LIST) {
+                            sb.key[at] = key;
+                            sb.id[at] = idx;
+                        }
+                        lo = min(lo, key);
+                        hi = max(hi, key);
+                    }
+                }
+        }
+    }
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, WAVE));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, WAVE));
+    }
+    s = wave_sum_d(s);
+    if (lane == 0) {
+        sb.wave_lo[wave] = lo;
+        sb.wave_hi[wave] = hi;
+    }
+    // ---- the list's cut: the same again over 4096 parts of its key range
+#pragma unroll
+    for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
+    __syncthreads();
+    lo = 0xffffffffu;
+    hi = 0u;
+#pragma unroll
+    for (int w = 0; w < SAMPLE_WAVES; ++w) {
+        lo = min(lo, sb.wave_lo[w]);
+        hi = max(hi, sb.wave_hi[w]);
+    }
+    const int shift = max(0, 32 - 12 - (hi > lo ? __clz((int)(hi - lo)) : 32));
+    auto part_of = [&](uint32_t key) { return NUC_BINS - 1 - (int)((key - lo) >> shift); };
+    for (int e = tid; e < n_list; e += BLOCK)
+        atomicAdd(&sb.bin[part_of(sb.key[e])], (1ull << NUC_COUNT_SHIFT) + fraction(scaled(x[sb.id[e]], sb.id[e]), sel));
+    __syncthreads();
+    nucleus_cross(sb, above, 0.0, want, [&](int) { return scale; }, part_mass);
+    const int part = sb.sel;
+    const double above2 = sb.above;
+    const int n_ties = (int)(sb.bin[part] >> NUC_COUNT_SHIFT);
+    if (n_ties > NUC_TIES) return false;
+    if (tid == 0) sb.n = 0;
+    __syncthreads();
+    for (int e = tid; e < n_list; e += BLOCK)
+        if (part_of(sb.key[e]) == part) {
+            const int at = atomicAdd(&sb.n, 1);
+            if (at < NUC_TIES) {
+                sb.tie_key[at] = sb.key[e];
+                sb.tie_id[at] = sb.id[e];
+                sb.tie_part[at] = fraction(scaled(x[sb.id[e]], sb.id[e]), sel);
+            }
+        }
+    __syncthreads();
+    if (tid < n_ties) {                        // rank by falling key, rising id; the cut is the first that reaches `want`
+        const uint32_t key = sb.tie_key[tid];
+        const int id = sb.tie_id[tid];
+        unsigned long long before = 0ull;
+        int rank = 0;
+        for (int j = 0; j < n_ties; ++j)
+            if (sb.tie_key[j] > key || (sb.tie_key[j] == key && sb.tie_id[j] < id)) {
+                before += sb.tie_part[j];
+                ++rank;
+            }
+        const bool reached_before = rank > 0 && above2 + (double)before * scale >= want;
+        const bool reached = above2 + (double)(before + sb.tie_part[tid]) * scale >= want;
+        if (!reached_before && (reached || rank == n_ties - 1)) {
+            sb.kstar = key;
+            sb.tie_limit = id;
+        }
+    }
+    __syncthreads();
+    nu.kstar = sb.kstar;
+    nu.tie_limit = sb.tie_limit;
+    nu.on = true;
+    // ---- the list's kept tokens join their segments' sums
+    const int b = wave * seg, e1 = b + seg;
+    double t = 0.0;
+    for (int e = lane; e < n_list; e += WAVE) {
+        const int id = sb.id[e];
+        const uint32_t key = sb.key[e];
+        if (id >= b && id < e1 && (key > nu.kstar || (key == nu.kstar && id <= nu.tie_limit)))
+            t += (double)expf(scaled(x[id], id) - M);
+    }
+    t = wave_sum_d(t);
+    if (lane == 0) {
+        s_wm[wave] = M;
+        s_ws[wave] = s + t;
+    }
+    return true;
+}
+
 template <int VEC, bool TOPP>
-__global__ __launch_bounds__(SAMPLE_WAVES *WAVE) void sample_kernel(
+__global__ __launch_bounds__(SAMPLE_WAVES *WAVE, 8) void sample_kernel(
     const float *__restrict__ logits, const int32_t *__restrict__ logit_row, int vocab, float inv_t, float top_p,
     float eos_key_add, uint64_t seed,
     const uint64_t *__restrict__ seq_uid, const int32_t *__restrict__ step, int step_base, int eos_id, float eos_bias,
@@ -104,7 +419,7 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE) void sample_kernel(
     int32_t *__restrict__ hist_tokens, float *__restrict__ hist_logprob, const int32_t *__restrict__ hist_index) {
     __shared__ float s_wm[SAMPLE_WAVES];
     __shared__ double s_ws[SAMPLE_WAVES];
-    __shared__ double s_sub[SAMPLE_WAVES];
+    __shared__ double s_sub[SAMPLE_WAVES], s_seg[SAMPLE_WAVES];
     __shared__ float s_u;
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
     if (finished && finished[row]) {   // block-uniform
@@ -165,13 +480,19 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE) void sample_kernel(
             s_ws[wave] = ws;
         }
     };
-    level1();
+    bool have_sums = false;
+    __shared__ typename std::conditional<TOPP, NucleusBins, int>::type sb;
     if constexpr (TOPP) {
+        have_sums = nucleus_binned<VEC>(x, vocab, seg, inv_t, top_p, eos_id, eos_bias, eos_key_add, sb, s_wm, s_ws, nu);
+    }
+    if (!have_sums) level1();
+    if constexpr (TOPP) {
+      if (!have_sums) {
         // ---- nucleus: the key kstar and the id limit among its ties at which the mass from the top reaches top_p Z
-        __shared__ double s_hist[SAMPLE_WAVES][256];
-        __shared__ int s_cnt[SAMPLE_WAVES][256];
-        __shared__ double s_comb[256];
-        __shared__ int s_ccnt[256];
+        auto &s_hist = sb.radix.hist;
+        auto &s_cnt = sb.radix.cnt;
+        auto &s_comb = sb.radix.comb;
+        auto &s_ccnt = sb.radix.ccnt;
         __shared__ uint32_t s_prefix;
         __shared__ double s_above;
         __shared__ int s_keep_ties, s_tie_limit, s_wcount[SAMPLE_WAVES];
@@ -286,38 +607,41 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE) void sample_kernel(
         nu.on = true;
         __syncthreads();
         level1();   // the same pass over the kept tokens only
+      }
     }
     __syncthreads();
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < SAMPLE_WAVES; ++w) M = fmaxf(M, s_wm[w]);
-    double Z = 0.0, segw[SAMPLE_WAVES];
-#pragma unroll
-    for (int w = 0; w < SAMPLE_WAVES; ++w) {
-        segw[w] = (s_wm[w] == -INFINITY) ? 0.0 : s_ws[w] * (double)expf(s_wm[w] - M);
-        Z += segw[w];
-    }
+    if (tid < SAMPLE_WAVES) s_seg[tid] = (s_wm[tid] == -INFINITY) ? 0.0 : s_ws[tid] * (double)expf(s_wm[tid] - M);
+    __syncthreads();
+    double Z = 0.0;
+#pragma unroll 1
+    for (int w = 0; w < SAMPLE_WAVES; ++w) Z += s_seg[w];
     const double target = (double)s_u * Z;
     int k = -1;
     double before = 0.0, run = 0.0;
-#pragma unroll
+#pragma unroll 1
     for (int w = 0; w < SAMPLE_WAVES; ++w) {
-        if (k < 0 && run + segw[w] > target) {
+        const double sw = s_seg[w];
+        if (k < 0 && run + sw > target) {
             k = w;
             before = run;
         }
-        run += segw[w];
+        run += sw;
     }
     if (k < 0) {   // rounding left no crossing: the last segment with weight
         run = 0.0;
-#pragma unroll
+#pragma unroll 1
         for (int w = 0; w < SAMPLE_WAVES; ++w) {
-            if (segw[w] > 0.0) {
+            const double sw = s_seg[w];
+            if (sw > 0.0) {
                 k = w;
                 before = run;
             }
-            run += segw[w];
+            run += sw;
         }
+        if (k < 0) k = 0;   // no weight anywhere (a row of minus infinities or NaNs): some token of the row
     }
     double rem = target - before;
     const int kb = min(vocab, k * seg), ke = min(vocab, kb + seg);
@@ -342,7 +666,7 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE) void sample_kernel(
     int j = -1;
     before = 0.0;
     run = 0.0;
-#pragma unroll
+#pragma unroll 1
     for (int w = 0; w < SAMPLE_WAVES; ++w) {
         const double sw = s_sub[w];
         if (j < 0 && run + sw > rem) {
@@ -353,7 +677,7 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE) void sample_kernel(
     }
     if (j < 0) {
         run = 0.0;
-#pragma unroll
+#pragma unroll 1
         for (int w = 0; w < SAMPLE_WAVES; ++w) {
             if (s_sub[w] > 0.0) {
                 j = w;

@@ -196,3 +196,68 @@ def test_top_p_tokens_and_logprobs(V, n, T, top_p, scale):
             keep = sampler.nucleus(np.exp(x - x.max()), top_p)
             assert keep[tok[i]]
     assert agree >= math.ceil(0.995 * tot)
+
+
+def _nucleus_form(form, V, rng):
+    x = rng.standard_normal(V).astype(np.float32)
+    if form == "ties":               # an eighth of the row on each of a few values: too many alike for the ranked cut
+        x = np.round(x) + np.float32(0.0)   # (no negative zeros: their order beside zero is the key's)
+    elif form == "some_ties":        # a few dozen alike in one part of the crossing bin
+        x = (np.round(x * 200.0) / 200.0).astype(np.float32) + np.float32(0.0)
+    elif form == "flat":             # a whole row in one or two bins
+        x *= np.float32(0.004)
+    elif form == "hidden_peak":      # a maximum 50 above everything a sample of the row sees
+        x[V // 2 + 1] = 50.0
+    elif form == "masked":           # most of the vocabulary at minus infinity
+        x[rng.random(V) < 0.9] = -np.inf
+    elif form == "lowest":           # masked with the type's lowest value, and all the rest far from zero
+        x = x + np.float32(3000.0)
+        x[rng.random(V) < 0.5] = np.finfo(np.float32).min
+    elif form == "far":              # scaled logits beyond the range of the bins' edges
+        x = x + np.float32(3.0e5)
+    elif form == "one":              # one token holds all the mass
+        x[V // 3] = 200.0
+    if not np.isfinite(x[V // 3]) or x[V // 3] < -1e30:
+        x[V // 3] = 0.5              # some token has weight
+    return x
+
+
+@pytest.mark.parametrize("form", ["normal", "ties", "some_ties", "flat", "hidden_peak", "masked", "lowest", "far", "one"])
+@pytest.mark.parametrize("V", [3, 1023, 5124, 30000])
+def test_top_p_forms(V, form):
+    # rows on either side of every rule that picks the way to the cut.  A token is right if the oracle draws it; where the
+    # mass lands within rounding (1e-6 relative: float32 weights) of top_p Z the cut may move by one token, hence 98 %.
+    rng = np.random.default_rng(V)
+    n, T = 4, 0.8
+    logits = np.stack([_nucleus_form(form, V, rng) for _ in range(n)])
+    uids = np.arange(n, dtype=np.int64) + 11
+    same = tot = 0
+    for top_p in (1e-6, 0.3, 0.9, 0.999999):
+        tok, lp = _run_top_p(logits, T, top_p, 21, uids, 2, V // 2, 0.75)
+        for i in range(n):
+            u = philox.sampling_uniform(21, int(uids[i]), 2)
+            # fp32 scaled logits, as the kernel forms them (far from zero their rounding is the distribution)
+            with np.errstate(over="ignore"):
+                x = logits[i] * np.float32(1.0 / np.float32(T))
+            want, wlp = sampler.sample_token(x, 1.0, u, V // 2, 0.75, top_p=top_p)
+            tot += 1
+            if tok[i] == want:
+                same += 1
+                assert abs(lp[i] - wlp) <= 3e-5 * max(1.0, abs(wlp)) + 1e-6 * np.abs(x[np.isfinite(x) & (x > -1e30)]).max()
+    say("top-p form %s V=%d: %d of %d" % (form, V, same, tot))
+    assert same >= math.floor(0.98 * tot)
+
+
+@pytest.mark.parametrize("top_p", [1.0, 0.9])
+@pytest.mark.parametrize("fill", [-np.inf, np.nan])
+def test_rows_without_weight(fill, top_p):
+    # nothing to draw from: the call still answers with a token of the vocabulary, and the rows beside are untouched
+    V = 2053
+    logits = np.random.default_rng(4).standard_normal((3, V)).astype(np.float32)
+    logits[1] = fill
+    uids = np.arange(3, dtype=np.int64) + 5
+    tok, lp = _run_top_p(logits, 1.0, top_p, 9, uids, 1)
+    assert 0 <= tok[1] < V
+    for i in (0, 2):
+        want, wlp = sampler.sample_token(logits[i], 1.0, philox.sampling_uniform(9, int(uids[i]), 1), top_p=top_p)
+        assert tok[i] == want and abs(lp[i] - wlp) < 3e-5 * max(1.0, abs(wlp))
