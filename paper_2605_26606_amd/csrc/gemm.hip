@@ -1,7 +1,8 @@
 // Projection GEMMs of the decoder (Section 3.1 policy pi_theta):
 //   C[M,N] = A[M,K] * W[N,K]^T, fp32 accumulation, with fused epilogues.
-// Two implementations:
-//   gemm_simt   plain-ALU tiles, any dtype (the fp32 model path)
+// Three implementations:
+//   gemm_f32    fp32 matrix instructions, operands straight from memory (fp32 models)
+//   gemm_simt   plain-ALU tiles, any dtype, any K
 //   gemm_mfma   bf16 / f16 on the matrix cores (32x32x16 or 16x16x32 products),
 //               operands streamed global -> LDS several K tiles ahead, one
 //               barrier per K tile, output rows re-formed through LDS
@@ -112,6 +113,119 @@ static void gemm_simt(const void *A, const void *W, void *C, int M, int N, int K
         case EPI_SWIGLU: gemm_simt_kernel<T, EPI_SWIGLU><<<grid, 256, 0, s>>>(a, w, C, M, N, K, sat); break;
         default: gemm_simt_kernel<T, EPI_STORE_T><<<grid, 256, 0, s>>>(a, w, C, M, N, K, sat); break;
     }
+}
+
+// =====================================================================================
+// fp32 matrix-core GEMM for the sizes at which latency counts (fp32 models, K a multiple of 16)
+// =====================================================================================
+// v_mfma_f32_16x16x4_f32 (full fp32 products and sums): lane l holds A[l%16][k = l/16], B[k = l/16][l%16] and
+// D[4*(l/16) + v][l%16].  A lane loads 16 consecutive bytes of its row, k = 16c + 4g .. + 3 (g = l/16), and the e-th
+// instruction of a chunk takes the e-th of them on both sides: which k meet in one instruction does not matter.
+// A block owns 16 TM x 16 TN outputs over the whole of K, its four waves take every fourth chunk of 16 k and add up
+// through LDS in wave order.  No staging: at these sizes a launch is a few memory latencies long, so what counts is many
+// blocks (TM = TN = 1: one tile each) and all loads of a wave in flight at once; the plain-ALU kernel's 64 x 64 tiles leave
+// two to twelve blocks that walk K 16 at a time behind two barriers (32 rows,
+// N = 128, K = 384: 47.7 -> 3.8 us; N = 2048, K = 1024: 125 -> 6.0 us; 4096 rows: 454 -> 231 us).
+template <int TM, int TN, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W,
+                                                       float *__restrict__ C, int M, int N, int K) {
+    static_assert(EPI != EPI_SWIGLU || TN == 2, "a gate tile and its up tile");
+    constexpr int NT = TM * TN;
+    __shared__ f32x4_t part[4][NT][64];
+    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, i = lane % 16, g = lane / 16;
+    const int m0 = blockIdx.y * 16 * TM;
+    // column tile t of this block starts at weight row col0 + t * cstep; SwiGLU: 16 gate rows of a 64-wide chunk and the
+    // up rows 32 further
+    const int col0 = (EPI == EPI_SWIGLU) ? (blockIdx.x / 2) * 64 + (blockIdx.x % 2) * 16 : blockIdx.x * 16 * TN;
+    constexpr int cstep = (EPI == EPI_SWIGLU) ? 32 : 16;
+    const float *pa[TM], *pw[TN];
+#pragma unroll
+    for (int t = 0; t < TM; ++t) pa[t] = A + (int64_t)min(m0 + 16 * t + i, M - 1) * K + 4 * g;
+#pragma unroll
+    for (int t = 0; t < TN; ++t) pw[t] = W + (int64_t)min(col0 + cstep * t + i, N - 1) * K + 4 * g;
+    f32x4_t acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    constexpr int U = 4;                               // chunks in flight per wave
+    const int chunks = K / 16;
+    for (int c0 = wave; c0 < chunks; c0 += 4 * U) {
+        f32x4_t fa[U][TM], fw[U][TN];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + 4 * u;
+#pragma unroll
+            for (int t = 0; t < TM; ++t) fa[u][t] = c < chunks ? *(const f32x4_t *)(pa[t] + 16 * c) : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < TN; ++t) fw[u][t] = c < chunks ? *(const f32x4_t *)(pw[t] + 16 * c) : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][a][e], fw[u][b][e], acc[a][b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) part[wave][a * TN + b][lane] = acc[a][b];
+    __syncthreads();
+    // thread -> element wave of each lane's four: row 4 g + wave, column i of every tile
+    auto sum = [&](int t) {
+        float v = part[0][t][lane][wave];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += part[w][t][lane][wave];
+        return v;
+    };
+#pragma unroll
+    for (int a = 0; a < TM; ++a) {
+        const int row = m0 + 16 * a + 4 * g + wave;
+        if (EPI == EPI_SWIGLU) {
+            const float gate = sum(a * TN), up = sum(a * TN + 1);
+            const int out = (blockIdx.x / 2) * 32 + (blockIdx.x % 2) * 16 + i;
+            if (row < M && out < N / 2) C[(int64_t)row * (N / 2) + out] = silu_f(gate) * up;
+        } else {
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                const int col = col0 + 16 * b + i;
+                const float v = sum(a * TN + b);
+                if (row < M && col < N) {
+                    if (EPI == EPI_RESID_F32) C[(int64_t)row * N + col] += v;
+                    else C[(int64_t)row * N + col] = v;
+                }
+            }
+        }
+    }
+}
+
+template <int TM, int TN> static void gemm_f32_run(const float *A, const float *W, float *C, int M, int N, int K, int epi, hipStream_t s) {
+    const int rows = (M + 16 * TM - 1) / (16 * TM);
+    const dim3 grid((N + 16 * TN - 1) / (16 * TN), rows);
+    if (epi == EPI_SWIGLU) gemm_f32_kernel<TM, 2, EPI_SWIGLU><<<dim3(N / 32, rows), 256, 0, s>>>(A, W, C, M, N, K);
+    else if (epi == EPI_RESID_F32) gemm_f32_kernel<TM, TN, EPI_RESID_F32><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
+    else gemm_f32_kernel<TM, TN, EPI_STORE_F32><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
+}
+
+// Whole 16-byte pieces of rows on both sides (the caller's lm_head may start anywhere).
+static bool gemm_f32_ok(const void *A, const void *W, int N, int K, int epi) {
+    return K % 16 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0 && (epi != EPI_SWIGLU || N % 64 == 0);
+}
+
+// The largest tile that still gives every CU a block: below that the chip idles (32 rows x 2048 columns x 1024: 6 us with
+// 256 blocks of 16 x 16, 12 us with 64 of 32 x 32, 28 us with 32 of 64 x 64), above it operands are re-read more often than
+// they need be (1024 x 1024 x 4096: 225 / 138 / 100 us).
+static void gemm_f32(const float *A, const float *W, float *C, int M, int N, int K, int epi, hipStream_t s) {
+    auto blocks = [&](int t) {
+        return (int64_t)((M + 16 * t - 1) / (16 * t)) * (epi == EPI_SWIGLU ? N / 32 : (N + 16 * t - 1) / (16 * t));
+    };
+    if (blocks(4) >= 256) gemm_f32_run<4, 4>(A, W, C, M, N, K, epi, s);
+    else if (blocks(2) >= 256) gemm_f32_run<2, 2>(A, W, C, M, N, K, epi, s);
+    else gemm_f32_run<1, 1>(A, W, C, M, N, K, epi, s);
 }
 
 // =====================================================================================
@@ -575,7 +689,8 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
                 float *slices, size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
     if (M <= 0 || N <= 0) return 1;
     if (dtype == KD_F32) {
-        gemm_simt<float>(A, W, C, M, N, K, epi, sat, s);
+        if (gemm_f32_ok(A, W, N, K, epi)) gemm_f32((const float *)A, (const float *)W, (float *)C, M, N, K, epi, s);
+        else gemm_simt<float>(A, W, C, M, N, K, epi, sat, s);
         return 1;
     }
     // (the matrix-core kernel stores whole 16-byte pieces of output rows; the SwiGLU one whole 64-wide chunks)

@@ -173,6 +173,26 @@ def test_fp32_ragged_prompts_partial_blocks_chunks_and_larger_weights():
     _check(m, w, prompts, out, 11, 1e-4, range(0, 24, 2), temperature=0.8)
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,dff,V,lens,G", [
+    (104, 4, 2, 26, 96, 301, [9, 40], 3),              # reductions of 104: not whole 16s, the plain-ALU kernel
+    (112, 4, 2, 32, 352, 1000, [3, 17, 70], 1),        # 7 and 22 chunks of 16 on four waves, 3 decode rows
+    (512, 8, 2, 64, 1376, 5001, [150, 301, 90], 5),    # tiles of 16, 32 and 64 rows and columns
+])
+def test_fp32_gemm_forms(d, hq, hkv, hd, dff, V, lens, G):
+    # the bound of the other fp32 tests: float32 sums of up to 1376 products of order 0.02
+    say("fp32 d=%d d_ff=%d V=%d" % (d, dff, V))
+    m = workloads.scaled(C1, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=dff, vocab=V).model
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 6), 8)
+    toks, cu = workloads.make_ragged_prompts(lens, V, 4)
+    prompts = [toks[cu[i]:cu[i + 1]] for i in range(len(lens))]
+    out = _run_generate(m, w, prompts, G, 6, 11, dict(block_size=32, kv_pool_bytes=64 << 20, max_slots=64, max_ctx=352,
+                                                     max_batch_rows=600))
+    for q in range(len(lens)):
+        want = decoder.forward_full(m, w, prompts[q], rows=[lens[q] - 1])[0]
+        assert np.abs(want - out["last"][q]).max() <= 1e-4 * max(1.0, np.abs(want).max())
+    _check(m, w, prompts, out, 11, 1e-4, range(0, len(lens) * G, 2))
+
+
 def test_bf16_plain_alu_path():
     say("bf16 small model, plain-ALU kernels")
     import paper_2605_26606_amd as pc
