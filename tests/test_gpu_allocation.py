@@ -182,3 +182,23 @@ def test_variance_filter_bit_exact():
             outs.append([t.cpu().numpy() for t in (cls, ev, ci, si, cnt)])
         for a, b in zip(*outs):
             assert np.array_equal(a, b)
+
+
+def test_group_sizes_around_the_lanes():
+    # sizes around the sixteen lanes of a group and the four rewards a lane keeps: statistics and advantages of groups
+    # next to each other, rewards with many levels; both sides round once from double (1 ulp: the order of the sums differs)
+    import paper_2605_26606_amd as pc
+    sizes = [0, 1, 2, 15, 16, 17, 31, 63, 64, 65, 0, 79, 80, 81, 200, 1]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    r = (np.random.default_rng(3).integers(0, 9, off[-1]) / 8.0).astype(np.float32)
+    got, want = _stats(r, off), al.group_stats(r, off)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    for g, w in zip(got[2:], want[2:]):
+        assert np.abs(g - w).max() <= 1.2e-7 * max(1.0, np.abs(w).max())
+    adv = torch.full((len(r),), 5.0, device="cuda")
+    mu, sg = torch.full((len(sizes),), 5.0, device="cuda"), torch.full((len(sizes),), 5.0, device="cuda")
+    pc.pc_advantages(torch.from_numpy(r).cuda(), torch.from_numpy(off).cuda(), 1e-6, adv, mu, sg)
+    torch.cuda.synchronize()
+    wadv, wmu, wsg = al.advantages(r, off, 1e-6)
+    assert np.abs(adv.cpu().numpy() - wadv).max() <= 2.4e-7 * np.abs(wadv).max()
+    assert np.abs(mu.cpu().numpy() - wmu).max() <= 1.2e-7 and np.abs(sg.cpu().numpy() - wsg).max() <= 1.2e-7
