@@ -131,8 +131,10 @@ def _host_i32(a, name: str) -> np.ndarray:
 
 
 def _stream_ptr(stream) -> Optional[int]:
+    """The raw handle of `stream`, or of torch's current stream on the current device.  The latter is asked for directly:
+    building a torch.cuda.Stream object to read it off took a third of a small call (4 us of 11)."""
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream or None
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
     return stream.cuda_stream or None
 
 
