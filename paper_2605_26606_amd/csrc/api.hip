@@ -117,7 +117,7 @@ struct pc_ctx {
     float *rope_cos = nullptr, *rope_sin = nullptr;
     // activations
     float *h = nullptr, *qkv = nullptr, *attn_scratch = nullptr;
-    float *score_logits = nullptr;    // pc_score: logits of score_rows rows at a time (allocated on first use)
+    float *score_logits = nullptr;    // pc_score: logits (or their partial softmax) of score_rows rows at a time (allocated on first use)
     int score_rows = 0;
     void *a = nullptr, *q = nullptr, *attn = nullptr, *act = nullptr;
     void *h_act = nullptr;          // activation-type copy of the residual rows (fused decode path)
@@ -744,10 +744,20 @@ static pc_status forward_chunks(pc_ctx *ctx, const int32_t *prompt_tokens, const
                 // the row metadata is free again once the layers are enqueued (stream order)
                 if ((rc = ctx->stage.push(d_row_slot, local.data(), (size_t)n_sc * 4, st)) != PC_OK) return rc;
                 if ((rc = ctx->stage.push(d_row_pos, global.data(), (size_t)n_sc * 4, st)) != PC_OK) return rc;
-                for (int off = 0; off < n_sc; off += ctx->score_rows) {
-                    const int sr = std::min(ctx->score_rows, n_sc - off);
+                // 16-bit models: as many rows at a time as the (smaller) partial results fit; the logits never exist
+                const int fused = logprob_fused_rows(ctx->kd, ctx->impl(), m.vocab, m.d_model,
+                                                     (size_t)ctx->score_rows * m.vocab * sizeof(float));
+                const int step = fused > 0 ? fused : ctx->score_rows;
+                for (int off = 0; off < n_sc; off += step) {
+                    const int sr = std::min(step, n_sc - off);
                     launch_rmsnorm(ctx->kd, ctx->h, d_row_slot + off, ctx->final_norm, sr, m.d_model, m.rms_eps, ctx->a,
                                    nullptr, 1, ctx->d_sat, st);
+                    if (fused > 0) {
+                        launch_gemm_logprob(ctx->kd, ctx->a, ctx->lm_head, sr, m.vocab, m.d_model, score->temperature,
+                                            prompt_tokens, d_row_pos + off, ctx->score_logits, score->out + score_done + off,
+                                            st);
+                        continue;
+                    }
                     launch_gemm(ctx->kd, ctx->impl(), ctx->a, ctx->lm_head, ctx->score_logits, sr, m.vocab, m.d_model,
                                 EPI_STORE_F32, nullptr, 0, ctx->d_sat, st);
                     launch_logprob(ctx->score_logits, sr, m.vocab, score->temperature, prompt_tokens, d_row_pos + off,

@@ -24,6 +24,14 @@ __device__ inline float silu_mul(float g, float u) {
     return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f)) * u;
 }
 
+// exp(d) for d <= 0 to about one unit in the last place: d log2(e) in two pieces, the small one added to first order
+__device__ inline float exp_neg(float d) {
+    const float p = d * 1.44269502f;
+    const float r = __builtin_amdgcn_exp2f(p);
+    const float e = fmaf(d, 1.92596299e-8f, fmaf(d, 1.44269502f, -p));
+    return p < -126.f ? 0.f : fmaf(r, e * 0.693147181f, r);
+}
+
 // Four values packed into two words.  Values beyond the half range are clamped and counted on a path of their own; one
 // test covers the four (their absolute sum is at most 65504 only if none is beyond it, infinite or not a number).
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -267,7 +275,7 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK, int EP
 __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__restrict__ A, const T *__restrict__ W,
                                                         void *__restrict__ Cv, int M, int N, int K, int mb, int nb,
                                                         int S, int plain, uint32_t *__restrict__ sat,
-                                                        GemmRowScale rsc) {
+                                                        GemmRowScale rsc, GemmLogprob lpa) {
     constexpr bool SWIGLU = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_RS);
     constexpr int CPR = BK / 8;                           // 16-byte chunks per tile row
     constexpr int RPL = 64 / CPR;                         // tile rows one wave-wide load covers
@@ -524,6 +532,56 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     }
     wait_vmcnt_le<0>();   // nothing may still be writing LDS when the block retires
 
+    if constexpr (EPI == EPI_LOGPROB) {
+        // A lane owns row ml of every row tile and 4 TN of the wave's columns, its three partners (16, 32, 48 lanes on) the
+        // others: maximum, then the exponentials summed in double, both folded over the four.  One entry per row and wave
+        // column strip leaves the block instead of the strip's logits (1024 rows x 151936: 15 MB for 622 MB, which the
+        // softmax behind it had to read again).
+        static_assert(M16, "lane layout of the 16x16x32 products");
+        constexpr int WC = BN / WN;
+        const int ml = lane % 16, nq = 4 * (lane / 16), col0 = n0 + wn * WC;
+        const int64_t strip = (int64_t)bn * WN + wn;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = m0 + wm * (BM / WM) + i * 16 + ml;
+            const int want = row < M ? lpa.tokens[lpa.token_index[row] + 1] - col0 - nq : -1;   // (column - nq) of the target
+            float mx = -INFINITY, hit = 0.f;
+            bool found = false;
+#pragma unroll
+            for (int jj = 0; jj < TN; ++jj)
+                if (col0 + jj * 16 < N) {   // N is a multiple of 16: a tile is inside or outside
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        if (want == jj * 16 + v) {
+                            hit = acc[i][jj][v];
+                            found = true;
+                        }
+                        acc[i][jj][v] *= lpa.inv_t;
+                        mx = fmaxf(mx, acc[i][jj][v]);
+                    }
+                }
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float base = (mx == -INFINITY) ? 0.f : mx;
+            double s = 0.0;
+#pragma unroll
+            for (int jj = 0; jj < TN; ++jj)
+                if (col0 + jj * 16 < N) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s += (double)exp_neg(acc[i][jj][v] - base);
+                }
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (row < M) {
+                if (found) lpa.target[row] = hit;
+                if (nq == 0) {
+                    lpa.part_max[strip * M + row] = mx;
+                    lpa.part_sum[strip * M + row] = s;
+                }
+            }
+        }
+        return;
+    } else {
     // ---- epilogue
     // The products take the weights as the row operand, so the accumulators hold the TRANSPOSED tile: a lane owns ONE
     // output row m (m = lane % RT of the tile) and, per tile, runs of four consecutive output columns.  Written out
@@ -610,6 +668,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
         }
         __builtin_amdgcn_wave_barrier();
     }
+    }
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, bool M16 = false> struct MfmaCfg {
@@ -638,18 +697,27 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
         const unsigned grid = plain ? (unsigned)(mb * nb) : (unsigned)((units + N_XCD - 1) / N_XCD * N_XCD * mb);
         const T *a = (const T *)A, *w = (const T *)W;
         switch (epi) {
-            case EPI_STORE_F32: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_STORE_F32, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, split, plain, sat, rsc); break;
-            case EPI_RESID_F32: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_RESID_F32, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc); break;
+            case EPI_STORE_F32: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_STORE_F32, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, split, plain, sat, rsc, GemmLogprob{}); break;
+            case EPI_RESID_F32: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_RESID_F32, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{}); break;
             case EPI_SWIGLU:
                 if constexpr (swiglu_ok)
-                    gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_SWIGLU, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc);
+                    gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_SWIGLU, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{});
                 break;
             case EPI_SWIGLU_RS:
                 if constexpr (swiglu_ok)
-                    gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_SWIGLU_RS, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc);
+                    gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_SWIGLU_RS, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{});
                 break;
-            default: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_STORE_T, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc); break;
+            default: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_STORE_T, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{}); break;
         }
+    }
+    static void init_logprob() { set_attr<EPI_LOGPROB>(); }
+    static int strips(int N) { return (N + BN - 1) / BN * WN; }
+    static void run_logprob(const void *A, const void *W, int M, int N, int K, const GemmLogprob &lpa, hipStream_t s) {
+        const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
+        const int plain = mb > 4 ? ((mb % N_XCD == 0) ? 2 : 1) : 0;
+        const unsigned grid = plain ? (unsigned)(mb * nb) : (unsigned)((nb + N_XCD - 1) / N_XCD * N_XCD * mb);
+        gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_LOGPROB, M16><<<grid, 64 * WM * WN, smem, s>>>(
+            (const T *)A, (const T *)W, nullptr, M, N, K, mb, nb, 1, plain, nullptr, GemmRowScale{nullptr, 0, 1, 0.f}, lpa);
     }
     // K slices so that the launch has about `want_blocks` blocks, each with >= 4 K tiles
     static int pick_split(int M, int N, int K, size_t slice_cap_floats, int want_blocks) {
@@ -675,6 +743,8 @@ template <typename T> static void gemm_init_t() {
     MfmaCfg<T, 128, 128, 2, 2, 3, 32>::init();
     MfmaCfg<T, 256, 64, 4, 2, 3>::init();
     MfmaCfg<T, 64, 64, 2, 2, 4>::init();
+    MfmaCfg<T, 256, 256, 4, 2, 4, 32, true>::init_logprob();
+    MfmaCfg<T, 256, 128, 4, 2, 3, 64, true>::init_logprob();
 }
 void gemm_init() {
     gemm_init_t<bf16_t>();
@@ -701,6 +771,74 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
     }
     if (dtype == KD_BF16) return gemm_mfma_dispatch<bf16_t>(A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
     return gemm_mfma_dispatch<f16_t>(A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
+}
+
+// ---- log-probabilities straight from the vocabulary projection: a scoring pass wrote 622 MB of logits per 1024 rows of the
+// 1.5B shape for a softmax kernel to read once (157 us); now all rows of a chunk go through one launch of the large tiles
+// (scoring 20 sequences of 700 to 1280 tokens on 4 layers: 19.97 -> 17.90 ms)
+static bool logprob_shape_ok(int dtype, int impl, int N, int K) { return dtype != KD_F32 && impl != 0 && K % 64 == 0 && N % 16 == 0; }
+static constexpr int LOGPROB_STRIP = 64;   // the narrowest strip of the configurations below
+
+int logprob_fused_rows(int dtype, int impl, int N, int K, size_t scratch_bytes) {
+    if (!logprob_shape_ok(dtype, impl, N, K)) return 0;
+    const size_t strips = ((size_t)N + 255) / 256 * (256 / LOGPROB_STRIP);
+    return (int)std::min<size_t>(scratch_bytes / (strips * (sizeof(double) + sizeof(float)) + sizeof(float)), 1 << 20);
+}
+
+// 64 rows per block, 16 waves that share the strips
+__global__ __launch_bounds__(1024) void logprob_merge_kernel(GemmLogprob lpa, int M, int N, int strips, float *__restrict__ out) {
+    __shared__ float s_m[16][64];
+    __shared__ double s_s[16][64];
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, row = blockIdx.x * 64 + lane;
+    float m = -INFINITY;
+    double s = 0.0;
+    if (row < M) {
+        for (int t = wave; t < strips; t += 16) {
+            const float pm = lpa.part_max[(int64_t)t * M + row];
+            const double ps = lpa.part_sum[(int64_t)t * M + row];
+            if (pm > m) {
+                s *= (double)expf(m - pm);   // m = -inf -> 0
+                m = pm;
+            }
+            s += (pm == -INFINITY) ? ps : ps * (double)expf(pm - m);
+        }
+    }
+    s_m[wave][lane] = m;
+    s_s[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || row >= M) return;
+    float mx = -INFINITY;
+    for (int w = 0; w < 16; ++w) mx = fmaxf(mx, s_m[w][lane]);
+    double z = 0.0;
+    for (int w = 0; w < 16; ++w) z += (s_m[w][lane] == -INFINITY) ? s_s[w][lane] : s_s[w][lane] * (double)expf(s_m[w][lane] - mx);
+    const int target = lpa.tokens[lpa.token_index[row] + 1];
+    out[row] = (target >= 0 && target < N) ? (float)((double)(lpa.target[row] * lpa.inv_t) - (double)mx - log(z)) : -INFINITY;
+}
+
+template <typename T>
+static void gemm_logprob_t(const void *A, const void *W, int M, int N, int K, GemmLogprob lpa, float *out, hipStream_t s) {
+    typedef MfmaCfg<T, 256, 256, 4, 2, 4, 32, true> CfgWide;
+    typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> CfgPrefill;
+    int strips;
+    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) {   // as for the other wide projections
+        strips = CfgWide::strips(N);
+        CfgWide::run_logprob(A, W, M, N, K, lpa, s);
+    } else {
+        strips = CfgPrefill::strips(N);
+        CfgPrefill::run_logprob(A, W, M, N, K, lpa, s);
+    }
+    logprob_merge_kernel<<<(M + 63) / 64, 1024, 0, s>>>(lpa, M, N, strips, out);
+}
+
+void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, int K, float temperature,
+                         const int32_t *tokens, const int32_t *token_index, void *scratch, float *out, hipStream_t s) {
+    if (M <= 0) return;
+    const size_t strips = ((size_t)N + 255) / 256 * (256 / LOGPROB_STRIP);
+    double *sums = (double *)scratch;
+    float *maxima = (float *)(sums + strips * M);
+    const GemmLogprob lpa{1.0f / temperature, tokens, token_index, maxima, maxima + strips * M, sums};
+    if (dtype == KD_BF16) gemm_logprob_t<bf16_t>(A, W, M, N, K, lpa, out, s);
+    else gemm_logprob_t<f16_t>(A, W, M, N, K, lpa, out, s);
 }
 
 template <typename T>

@@ -165,6 +165,8 @@ enum Epilogue {
     EPI_STORE_T = 3,     // C model dtype [M,N]
     EPI_SWIGLU_RS = 4,   // EPI_SWIGLU on rows that carry the RMSNorm gain but not its scale: gate and up are
                          // multiplied by the row's rsqrt(mean(h^2) + eps) first (statistics in GemmRowScale)
+    EPI_LOGPROB = 5,     // nothing of the product is stored: per row and strip of columns the maximum and the sum of exponentials
+                         // of the scaled product, and the product at the row's target column (GemmLogprob)
 };
 
 // Per-row RMSNorm statistics for EPI_SWIGLU_RS: ssq[t][row], t < tiles, are partial sums of squares of the row (as the fused output projection leaves them); scale = rsqrt(sum_t ssq / d + eps).
@@ -172,6 +174,15 @@ struct GemmRowScale {
     const float *ssq;
     int tiles, d;
     float eps;
+};
+
+// EPI_LOGPROB: part_max / part_sum [strip][M] hold max and sum of exp(x - max) of x = product * inv_t over the strip's columns;
+// target[row] = the product at column tokens[token_index[row] + 1] (written only if that is a column).
+struct GemmLogprob {
+    float inv_t;
+    const int32_t *tokens, *token_index;
+    float *part_max, *target;
+    double *part_sum;
 };
 
 // ---------------------------------------------------------------- kernel launchers
@@ -193,6 +204,12 @@ void gemm_init();   // once per process: raises the dynamic-LDS limit of the mat
 int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int M, int N, int K, int epi,
                 float *slices, size_t slice_cap_floats, uint32_t *sat, hipStream_t s,
                 const GemmRowScale *row_scale = nullptr);
+// out[r] = log softmax(A[r] W^T * inv_t)[tokens[token_index[r] + 1]] without the logits ever reaching memory (16-bit types on
+// the matrix cores).  logprob_fused_rows: how many rows a call may have with `scratch_bytes` of scratch; 0: not a shape the
+// kernels take (the caller then goes through the logits).
+int logprob_fused_rows(int dtype, int impl, int N, int K, size_t scratch_bytes);
+void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, int K, float temperature,
+                         const int32_t *tokens, const int32_t *token_index, void *scratch, float *out, hipStream_t s);
 // Fused decode projections (gemm_skinny.hip); skinny_ok says whether the shape is one they take.
 bool skinny_ok(int M, int N, int K, int head_dim);
 void skinny_init();   // once per process, like gemm_init

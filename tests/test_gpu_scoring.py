@@ -54,6 +54,33 @@ def test_scores_match_the_oracle(name, tol):
         assert err <= tol
 
 
+@pytest.mark.parametrize("vocab,n_seq,length,T,act", [
+    (2000, 5, 40, 1.0, "f16"),       # the last column tile holds 208 of 256 (80 of 128) columns, a strip of it none
+    (4112, 9, 150, 0.7, "f16"),      # row tiles with a remainder, 16 columns in the last tile
+    (33792, 14, 62, 1.3, "f16"),     # four row blocks and 132 column blocks: the large tiles
+    (33792, 14, 62, 1.3, "bf16"),
+    (2001, 3, 30, 1.0, "f16"),       # a vocabulary the matrix-core kernel does not take: through the logits
+])
+def test_scores_at_tile_edges(vocab, n_seq, length, T, act):
+    # targets in every part of the vocabulary, its first and last id among them; the tolerance is the one of the 16-bit
+    # logits (2e-2, and eight times that for bfloat16: three significand bits less) -- a wrong strip, row or target is
+    # off by whole units
+    m = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=256, vocab=vocab,
+                         n_layers=1, rope_theta=1.0e6).model
+    say("scores at tile edges V=%d rows=%d %s" % (vocab, n_seq * length, act))
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 9, std=0.05), 2)
+    rng = np.random.default_rng(vocab)
+    seqs = [rng.integers(0, vocab, length) for _ in range(n_seq)]
+    seqs[0][5], seqs[0][6], seqs[-1][-1] = 0, vocab - 1, vocab - 1
+    plens = [1] + [3] * (n_seq - 1)
+    got = _score(m, w, seqs, plens, T, block_size=32, kv_pool_bytes=64 << 20, max_slots=32, max_ctx=160, max_batch_rows=1400,
+                 act_dtype=act)
+    want = np.concatenate([scoring.score(m, w, s, p, T) for s, p in zip(seqs, plens)])
+    err = np.abs(got - want).max()
+    say("max-abs error %.3g" % err)
+    assert err <= 2e-2 * (8 if act == "bf16" else 1)
+
+
 def test_scores_equal_the_sampler_logprobs_of_generated_rollouts():
     # what the sampler reported while generating is what scoring the finished rollouts gives (same policy)
     import paper_2605_26606_amd as pc
