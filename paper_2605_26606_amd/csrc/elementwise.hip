@@ -271,15 +271,15 @@ void launch_pack_rows(int kd, const void *src, void *dst, int64_t rows, int64_t 
         pack_rows_kernel<bf16_t, f16_t><<<(unsigned)rows, 256, 0, s>>>((const bf16_t *)src, (f16_t *)dst, cols, dst_row0, head_perm);
 }
 
-// dst row 64t + c      = gate row 32t + c   (c < 32)
-// dst row 64t + 32 + c = up   row 32t + c
+// dst row 32t + c      = gate row 16t + c   (c < 16)
+// dst row 32t + 16 + c = up   row 16t + c
 template <typename TS, typename TD>
 __global__ void pack_gate_up_kernel(const TS *__restrict__ gate, const TS *__restrict__ up, TD *__restrict__ dst, int d) {
     int64_t j = blockIdx.x;   // ffn row
-    int64_t t = j / 32, c = j % 32;
+    int64_t t = j / 16, c = j % 16;
     for (int i = threadIdx.x; i < d; i += blockDim.x) {
-        dst[(64 * t + c) * d + i] = conv<TS, TD>(gate[j * d + i]);
-        dst[(64 * t + 32 + c) * d + i] = conv<TS, TD>(up[j * d + i]);
+        dst[(32 * t + c) * d + i] = conv<TS, TD>(gate[j * d + i]);
+        dst[(32 * t + 16 + c) * d + i] = conv<TS, TD>(up[j * d + i]);
     }
 }
 void launch_pack_gate_up(int kd, const void *gate, const void *up, void *dst, int d_ff, int d, hipStream_t s) {

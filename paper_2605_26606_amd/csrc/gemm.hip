@@ -90,13 +90,12 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const T *__restrict__ A,
         int row = m0 + ty + 16 * i;
         if (row >= M) continue;
         if (EPI == EPI_SWIGLU) {
-            // this tile is one gate/up chunk: columns [0,32) gate, [32,64) the matching up
+            // this tile is two gate/up chunks: columns [0,16) gate, [16,32) the matching up, and again
             T *C = (T *)Cv;
-            int ob = (n0 / 64) * 32;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                if (n0 + tx + 16 * j + 32 < N)
-                    store_out(&C[(int64_t)row * (N / 2) + ob + tx + 16 * j], silu_f(acc[i][j]) * acc[i][j + 2], sat);
+                if (n0 + tx + 32 * j + 16 < N)
+                    store_out(&C[(int64_t)row * (N / 2) + n0 / 2 + tx + 16 * j], silu_f(acc[i][2 * j]) * acc[i][2 * j + 1], sat);
             }
         } else {
 #pragma unroll
@@ -142,15 +141,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     __shared__ f32x4_t part[4][NT][64];
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, i = lane % 16, g = lane / 16;
     const int m0 = blockIdx.y * 16 * TM;
-    // column tile t of this block starts at weight row col0 + t * cstep; SwiGLU: 16 gate rows of a 64-wide chunk and the
-    // up rows 32 further
-    const int col0 = (EPI == EPI_SWIGLU) ? (blockIdx.x / 2) * 64 + (blockIdx.x % 2) * 16 : blockIdx.x * 16 * TN;
-    constexpr int cstep = (EPI == EPI_SWIGLU) ? 32 : 16;
+    const int col0 = blockIdx.x * 16 * TN;   // (SwiGLU: a chunk of 16 gate rows and their 16 up rows)
     const float *pa[TM], *pw[TN];
 #pragma unroll
     for (int t = 0; t < TM; ++t) pa[t] = A + (int64_t)min(m0 + 16 * t + i, M - 1) * K + 4 * g;
 #pragma unroll
-    for (int t = 0; t < TN; ++t) pw[t] = W + (int64_t)min(col0 + cstep * t + i, N - 1) * K + 4 * g;
+    for (int t = 0; t < TN; ++t) pw[t] = W + (int64_t)min(col0 + 16 * t + i, N - 1) * K + 4 * g;
     f32x4_t acc[TM][TN];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
@@ -195,7 +191,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
         const int row = m0 + 16 * a + 4 * g + wave;
         if (EPI == EPI_SWIGLU) {
             const float gate = sum(a * TN), up = sum(a * TN + 1);
-            const int out = (blockIdx.x / 2) * 32 + (blockIdx.x % 2) * 16 + i;
+            const int out = blockIdx.x * 16 + i;
             if (row < M && out < N / 2) C[(int64_t)row * (N / 2) + out] = silu_f(gate) * up;
         } else {
 #pragma unroll
@@ -293,7 +289,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     constexpr int STAGE_ELEMS = (BM + BN) * BK;
     static_assert(BK == 64 || BK == 32, "K tile");
     static_assert(BM % (RPL * NW) == 0 && BN % (RPL * NW) == 0, "whole passes");
-    static_assert(!SWIGLU || (BN / WN) % 64 == 0, "SwiGLU needs whole 64-wide gate/up chunks per wave");
+    static_assert(!SWIGLU || (BN / WN) % 32 == 0, "SwiGLU needs whole gate/up chunks per wave");
     static_assert(NSTAGE * LOADS <= 63, "vmcnt is a 6-bit counter");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     T *smem = (T *)smem_raw;                     // [NSTAGE][A tile BM x 64 | W tile BN x 64]
@@ -593,12 +589,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     typedef typename std::conditional<(EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32), float, T>::type OutT;
     constexpr int WCOLS = SWIGLU ? (BN / WN) / 2 : BN / WN;        // output columns of one wave
     constexpr int RB = WCOLS * (int)sizeof(OutT);                 // bytes of one output row of the wave
-    constexpr int LPR = RB / 16;                                  // lanes that store one row
-    constexpr int ROWS_PER = 64 / LPR;                            // rows one store instruction covers
-    constexpr int ITER = RT / ROWS_PER;
+    constexpr int LPR = RB / 16;                                  // 16-byte pieces of one row
+    constexpr int PIECES = RT * LPR, ITER = (PIECES + 63) / 64;   // pieces of the RT rows; store instructions for them
     constexpr int PITCH = RB + 16;                                // bytes; the pad spreads the rows over the banks
     constexpr int EPC = 16 / (int)sizeof(OutT);                   // output elements per 16-byte piece
-    static_assert(LPR >= 1 && LPR <= 64 && (64 % LPR) == 0 && ROWS_PER <= RT && ITER >= 1, "row pieces per wave");
+    static_assert(RB % 16 == 0, "whole pieces");
     static_assert((size_t)NW * RT * PITCH <= (size_t)NSTAGE * STAGE_ELEMS * sizeof(T), "staging fits the ring");
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();   // every wave has consumed its last fragments (they were waited for by the products)
@@ -620,26 +615,24 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     for (int i = 0; i < TM; ++i) {
         const float sc = (EPI == EPI_SWIGLU_RS) ? s_rs[wm * (BM / WM) + i * RT + ml] : 1.f;
         if constexpr (SWIGLU) {
-            // a 64-wide chunk of weight rows = 32 gate rows, then the 32 matching up rows
-            if constexpr (M16) {
+            // a 32-wide chunk of weight rows = 16 gate rows, then the 16 matching up rows
+            if constexpr (M16) {       // two tiles
 #pragma unroll
-                for (int p2 = 0; p2 < TN / 4; ++p2)
+                for (int p2 = 0; p2 < TN / 2; ++p2) {
+                    const acc_t &ga = acc[i][2 * p2], &ua = acc[i][2 * p2 + 1];
+                    put4(16 * p2 + nq, silu_mul(ga[0] * sc, ua[0] * sc), silu_mul(ga[1] * sc, ua[1] * sc),
+                         silu_mul(ga[2] * sc, ua[2] * sc), silu_mul(ga[3] * sc, ua[3] * sc));
+                }
+            } else {                   // the two halves of a tile
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const acc_t &ga = acc[i][4 * p2 + q], &ua = acc[i][4 * p2 + 2 + q];
-                        put4(32 * p2 + 16 * q + nq, silu_mul(ga[0] * sc, ua[0] * sc), silu_mul(ga[1] * sc, ua[1] * sc),
-                             silu_mul(ga[2] * sc, ua[2] * sc), silu_mul(ga[3] * sc, ua[3] * sc));
-                    }
-            } else {
+                for (int jj = 0; jj < TN; ++jj)
 #pragma unroll
-                for (int p2 = 0; p2 < TN / 2; ++p2)
-#pragma unroll
-                    for (int vg = 0; vg < 4; ++vg) {
-                        const acc_t &ga = acc[i][2 * p2], &ua = acc[i][2 * p2 + 1];
-                        put4(32 * p2 + 8 * vg + nq, silu_mul(ga[4 * vg] * sc, ua[4 * vg] * sc),
-                             silu_mul(ga[4 * vg + 1] * sc, ua[4 * vg + 1] * sc),
-                             silu_mul(ga[4 * vg + 2] * sc, ua[4 * vg + 2] * sc),
-                             silu_mul(ga[4 * vg + 3] * sc, ua[4 * vg + 3] * sc));
+                    for (int vg = 0; vg < 2; ++vg) {
+                        const acc_t &ga = acc[i][jj];
+                        put4(16 * jj + 8 * vg + nq, silu_mul(ga[4 * vg] * sc, ga[4 * vg + 8] * sc),
+                             silu_mul(ga[4 * vg + 1] * sc, ga[4 * vg + 9] * sc),
+                             silu_mul(ga[4 * vg + 2] * sc, ga[4 * vg + 10] * sc),
+                             silu_mul(ga[4 * vg + 3] * sc, ga[4 * vg + 11] * sc));
                     }
             }
         } else {
@@ -653,7 +646,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int it = 0; it < ITER; ++it) {
-            const int row = it * ROWS_PER + lane / LPR, piece = lane % LPR;
+            const int e = it * 64 + lane, row = e / LPR, piece = e % LPR;
+            if (PIECES % 64 != 0 && e >= PIECES) break;
             const u32x4 val = *(const u32x4 *)(stg + row * PITCH + piece * 16);
             const int gm = m0 + wm * (BM / WM) + i * RT + row, col = colbase + piece * EPC;
             if (gm < M && col < ldc) {
@@ -673,7 +667,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
 
 template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, bool M16 = false> struct MfmaCfg {
     static constexpr size_t smem = (size_t)NSTAGE * (BM + BN) * BK * sizeof(T);
-    static constexpr bool swiglu_ok = ((BN / WN) % 64 == 0);
+    static constexpr bool swiglu_ok = ((BN / WN) % 32 == 0);
     template <int E> static void set_attr() {
         (void)hipFuncSetAttribute((const void *)gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, E, M16>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -733,22 +727,40 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
     }
 };
 
-template <typename T> static void gemm_init_t() {
-    MfmaCfg<T, 256, 128, 4, 2, 3>::init();
-    MfmaCfg<T, 256, 256, 4, 2, 4, 32, true>::init();
-    MfmaCfg<T, 256, 128, 4, 2, 3, 64, true>::init();
-    MfmaCfg<T, 128, 128, 4, 2, 4>::init();
-    MfmaCfg<T, 128, 64, 2, 2, 4>::init();
-    MfmaCfg<T, 128, 128, 2, 2, 2>::init();
-    MfmaCfg<T, 128, 128, 2, 2, 3, 32>::init();
-    MfmaCfg<T, 256, 64, 4, 2, 3>::init();
-    MfmaCfg<T, 64, 64, 2, 2, 4>::init();
-    MfmaCfg<T, 256, 256, 4, 2, 4, 32, true>::init_logprob();
-    MfmaCfg<T, 256, 128, 4, 2, 3, 64, true>::init_logprob();
-}
+// The tile configurations.  All on 16x16x32 products (0 to 13 % faster than 32x32x16 at every decode shape measured) except
+// the four whose wave tiles are a few 32x32 products only.
+template <typename T> struct Gemm {
+    // 256 x 128, 8 waves of 64 x 64: decode batches of 193 to 256 rows, prefill of narrow outputs
+    typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> T256x128;
+    typedef MfmaCfg<T, 256, 192, 4, 2, 2, 64, true> T256x192;
+    typedef MfmaCfg<T, 256, 256, 4, 2, 4, 32, true> T256x256;   // prefill; wave tile 64 x 128: three fragment reads per four products
+    typedef MfmaCfg<T, 192, 128, 4, 2, 3, 64, true> T192x128;
+    typedef MfmaCfg<T, 192, 192, 4, 2, 3, 64, true> T192x192;
+    typedef MfmaCfg<T, 128, 128, 4, 2, 4, 64, true> T128x128;   // 8 waves of 32 x 64: up to 128 rows what counts is loads in flight
+    typedef MfmaCfg<T, 128, 128, 4, 2, 2, 64, true> T128x128_2; // two stages, 64 KB of LDS: two blocks per CU
+    typedef MfmaCfg<T, 128, 192, 4, 2, 3, 64, true> T128x192;
+    typedef MfmaCfg<T, 64, 128, 2, 4, 3, 64, true> T64x128;     // 72 KB of LDS: two blocks per CU
+    typedef MfmaCfg<T, 64, 192, 4, 2, 4, 64, true> T64x192;
+    typedef MfmaCfg<T, 32, 64, 1, 4, 4, 64, true> T32x64;       // 48 KB of LDS: three blocks per CU
+    typedef MfmaCfg<T, 32, 64, 1, 2, 4, 64, true> T32x64_2;     // the same with whole gate/up chunks per wave
+    typedef MfmaCfg<T, 128, 128, 2, 2, 2> M128x128_2;           // 64 KB of LDS: two blocks per CU
+    typedef MfmaCfg<T, 128, 128, 2, 2, 3, 32> M128x128_3;       // BK 32, 48 KB: three blocks per CU
+    typedef MfmaCfg<T, 128, 64, 2, 2, 4> M128x64;               // wave tile 64 x 32: long-K projections cut into K slices
+    typedef MfmaCfg<T, 256, 64, 4, 2, 3> M256x64;               // the same for more than 256 rows
+    typedef MfmaCfg<T, 64, 64, 2, 2, 4> M64x64;                 // wave tile 32 x 32: many blocks for the small projections
+    static void init() {
+        T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
+        T128x128_2::init(); T128x192::init(); T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init();
+        M128x128_2::init(); M128x128_3::init(); M128x64::init(); M256x64::init(); M64x64::init();
+        T256x256::init_logprob();
+        T256x128::init_logprob();
+        T192x128::init_logprob();
+        T128x128::init_logprob();
+    }
+};
 void gemm_init() {
-    gemm_init_t<bf16_t>();
-    gemm_init_t<f16_t>();
+    Gemm<bf16_t>::init();
+    Gemm<f16_t>::init();
 }
 
 template <typename T>
@@ -763,7 +775,7 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
         else gemm_simt<float>(A, W, C, M, N, K, epi, sat, s);
         return 1;
     }
-    // (the matrix-core kernel stores whole 16-byte pieces of output rows; the SwiGLU one whole 64-wide chunks)
+    // (the matrix-core kernel stores whole 16-byte pieces of output rows; the SwiGLU ones need pairs of chunks)
     if (impl == 0 || (K % 64) != 0 || (N % 16) != 0 || ((epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS) && (N % 64) != 0)) {
         if (dtype == KD_BF16) gemm_simt<bf16_t>(A, W, C, M, N, K, epi, sat, s);
         else gemm_simt<f16_t>(A, W, C, M, N, K, epi, sat, s);
@@ -785,49 +797,52 @@ int logprob_fused_rows(int dtype, int impl, int N, int K, size_t scratch_bytes) 
     return (int)std::min<size_t>(scratch_bytes / (strips * (sizeof(double) + sizeof(float)) + sizeof(float)), 1 << 20);
 }
 
-// 64 rows per block, 16 waves that share the strips
+// 16 rows per block, 64 threads to a row that share its strips (a few rows must not mean a few blocks: the strips are
+// thousands); maxima first, then the sums: no chain through the loads
 __global__ __launch_bounds__(1024) void logprob_merge_kernel(GemmLogprob lpa, int M, int N, int strips, float *__restrict__ out) {
-    __shared__ float s_m[16][64];
-    __shared__ double s_s[16][64];
-    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, row = blockIdx.x * 64 + lane;
+    __shared__ float s_m[64][16];
+    __shared__ double s_s[64][16];
+    const int r = threadIdx.x % 16, part = threadIdx.x / 16, row = blockIdx.x * 16 + r;
     float m = -INFINITY;
+    if (row < M) {
+#pragma unroll 4
+        for (int t = part; t < strips; t += 64) m = fmaxf(m, lpa.part_max[(int64_t)t * M + row]);
+    }
+    s_m[part][r] = m;
+    __syncthreads();
+    float mx = -INFINITY;
+#pragma unroll 8
+    for (int w = 0; w < 64; ++w) mx = fmaxf(mx, s_m[w][r]);
+    const float base = (mx == -INFINITY) ? 0.f : mx;
     double s = 0.0;
     if (row < M) {
-        for (int t = wave; t < strips; t += 16) {
-            const float pm = lpa.part_max[(int64_t)t * M + row];
-            const double ps = lpa.part_sum[(int64_t)t * M + row];
-            if (pm > m) {
-                s *= (double)expf(m - pm);   // m = -inf -> 0
-                m = pm;
-            }
-            s += (pm == -INFINITY) ? ps : ps * (double)expf(pm - m);
-        }
+#pragma unroll 4
+        for (int t = part; t < strips; t += 64)
+            s += lpa.part_sum[(int64_t)t * M + row] * (double)expf(lpa.part_max[(int64_t)t * M + row] - base);
     }
-    s_m[wave][lane] = m;
-    s_s[wave][lane] = s;
+    s_s[part][r] = s;
     __syncthreads();
-    if (wave != 0 || row >= M) return;
-    float mx = -INFINITY;
-    for (int w = 0; w < 16; ++w) mx = fmaxf(mx, s_m[w][lane]);
+    if (part != 0 || row >= M) return;
     double z = 0.0;
-    for (int w = 0; w < 16; ++w) z += (s_m[w][lane] == -INFINITY) ? s_s[w][lane] : s_s[w][lane] * (double)expf(s_m[w][lane] - mx);
+#pragma unroll 8
+    for (int w = 0; w < 64; ++w) z += s_s[w][r];
     const int target = lpa.tokens[lpa.token_index[row] + 1];
     out[row] = (target >= 0 && target < N) ? (float)((double)(lpa.target[row] * lpa.inv_t) - (double)mx - log(z)) : -INFINITY;
 }
 
 template <typename T>
 static void gemm_logprob_t(const void *A, const void *W, int M, int N, int K, GemmLogprob lpa, float *out, hipStream_t s) {
-    typedef MfmaCfg<T, 256, 256, 4, 2, 4, 32, true> CfgWide;
-    typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> CfgPrefill;
-    int strips;
-    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) {   // as for the other wide projections
-        strips = CfgWide::strips(N);
-        CfgWide::run_logprob(A, W, M, N, K, lpa, s);
-    } else {
-        strips = CfgPrefill::strips(N);
-        CfgPrefill::run_logprob(A, W, M, N, K, lpa, s);
-    }
-    logprob_merge_kernel<<<(M + 63) / 64, 1024, 0, s>>>(lpa, M, N, strips, out);
+    typedef Gemm<T> G;
+    int strips = 0;
+    auto run = [&](auto cfg) {
+        strips = decltype(cfg)::strips(N);
+        decltype(cfg)::run_logprob(A, W, M, N, K, lpa, s);
+    };
+    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256 && M > 512) run(typename G::T256x256());   // as for the other wide projections
+    else if (M <= 128) run(typename G::T128x128());
+    else if (M <= 192) run(typename G::T192x128());
+    else run(typename G::T256x128());
+    logprob_merge_kernel<<<(M + 15) / 16, 1024, 0, s>>>(lpa, M, N, strips, out);
 }
 
 void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, int K, float temperature,
@@ -844,102 +859,74 @@ void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, 
 template <typename T>
 static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices,
                               size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
-    // Configurations picked by measurement on MI355X (M = 256 decode rows / 16384 prefill rows, 1.5B shapes).
-    typedef MfmaCfg<T, 256, 128, 4, 2, 3> CfgTall;          // 8 waves, wave tile 64x64, every decode row in one block
-    // prefill: 16x16x32 products (measured +3 to +12 % over 32x32x16 at 16384 rows, nothing at decode sizes;
-    // the results are bit-identical)
-    typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> CfgPrefill;
-    typedef MfmaCfg<T, 256, 256, 4, 2, 4, 32, true> CfgWide;   // wave tile 64x128: three fragment reads per four products
-    typedef MfmaCfg<T, 128, 128, 4, 2, 4> CfgLarge;         // 8 waves of 32x64: up to 128 rows what counts is loads in flight (22 against 25 us for gate/up with 4 waves of 64x64)
-    typedef MfmaCfg<T, 128, 128, 2, 2, 2> CfgLarge2;        // two stages, 64 KB of LDS: two blocks per CU
-    typedef MfmaCfg<T, 128, 128, 2, 2, 3, 32> CfgLarge3;    // BK 32, 48 KB of LDS: three blocks per CU
-    typedef MfmaCfg<T, 128, 64, 2, 2, 4> CfgMid;            // wave tile 64x32: long-K projections cut into K slices
-    typedef MfmaCfg<T, 256, 64, 4, 2, 3> CfgMidTall;        // the same for more than 256 rows
-    typedef MfmaCfg<T, 64, 64, 2, 2, 4> CfgSmall;           // wave tile 32x32: many blocks for the small projections
+    // Rules from sweeps of the configurations over the projection shapes of the 1.5B, 8B and 14B models at 3 to 16384 rows.
+    typedef Gemm<T> G;
+    const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS;
+    const bool can_split = slices && (epi == EPI_STORE_F32 || epi == EPI_RESID_F32);
+    auto whole = [&](auto cfg) {
+        decltype(cfg)::run(A, W, C, M, N, K, epi, 1, sat, s, row_scale);
+        return 1;
+    };
+    auto sliced = [&](auto cfg, int want_blocks) {   // K slices where they bring the launch nearer to want_blocks
+        typedef decltype(cfg) Cfg;
+        const int split = can_split ? Cfg::pick_split(M, N, K, slice_cap_floats, want_blocks) : 1;
+        if (split > 1) Cfg::run(A, W, slices, M, N, K, EPI_STORE_F32, split, sat, s);
+        else Cfg::run(A, W, C, M, N, K, epi, 1, sat, s);
+        return split;
+    };
     if (M > 512) {   // prefill: plenty of tiles
         // 256x256 tiles where they still come in several rounds per CU (the wide projections: +10 % measured);
         // the narrow ones (1536 columns: 1.5 rounds of such tiles) keep 256x128
         const int64_t wide_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-        if (wide_tiles >= 2 * 256) {
-            CfgWide::run(A, W, C, M, N, K, epi, 1, sat, s);
-            return 1;
-        }
+        if (wide_tiles >= 2 * 256) return whole(typename G::T256x256());
         // a large decode batch (a thousand rows) against a narrow projection leaves most CUs without a tile
-        // (1024 rows x 1536 columns: 48 tiles of 256x128): cut K into slices, as the small batches do
+        // (1024 rows x 1536 columns: 48 tiles of 256x128): cut K into slices, as the small batches do.  A short reduction
+        // wants small tiles and few slices (1024 x 2048 x 1536: 14.0 us with two slices of 128x128 tiles, 20.3 with four of
+        // 256x128), a long one the larger tile (1024 x 1536 x 8960: 42.3 against 48.7 us)
         const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 127) / 128);
-        if (tiles < 160 && slices && (epi == EPI_STORE_F32 || epi == EPI_RESID_F32)) {
-            const int split = CfgPrefill::pick_split(M, N, K, slice_cap_floats, 240);
-            if (split > 1) {
-                CfgPrefill::run(A, W, slices, M, N, K, EPI_STORE_F32, split, sat, s);
-                return split;
-            }
-        }
-        CfgPrefill::run(A, W, C, M, N, K, epi, 1, sat, s);
-        return 1;
+        if (tiles < 160 && can_split) return K < 3072 ? sliced(typename G::T128x128_2(), 240) : sliced(typename G::T256x128(), 240);
+        return whole(typename G::T256x128());
     }
-    // decode: the weights are streamed once; fill the chip with blocks, by K slices where N is small.
-    // (Rules from sweeps of every configuration over the projection shapes of the 1.5B, 8B and 14B models at
-    // 128, 256 and 400 rows.)
-    const bool can_split = slices && (epi == EPI_STORE_F32 || epi == EPI_RESID_F32);
-    const int nb128 = (N + 127) / 128;
+    // decode: the weights are streamed once; fill the chip with blocks, by K slices where N is small
+    const int nb128 = (N + 127) / 128, nb192 = (N + 191) / 192;
     // a long reduction amortises a block's fill and drain, and the tile with the most fragment reuse wins at
     // every row count; a short one (the 1.5B model: 24 K tiles) prefers several smaller blocks per CU
     const bool deep = K >= 3072;
-    if (epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS || nb128 >= 96) {   // wide outputs: no K slices needed
+    if (swiglu || nb128 >= 96) {   // wide outputs: no K slices needed
+        // 128-column tiles that need a second, nearly empty round of blocks (one per CU) where 192-column ones fit the first
+        // (14B gate/up, 34816 columns: 272 blocks against 182; 112 / 119 / 162 / 159 us against 74 / 84 / 90 / 132 us at
+        // 60 / 116 / 168 / 256 rows)
+        const bool second_round = nb128 > 256 && nb192 <= 256;
+        if (M <= 32 && !second_round) return swiglu ? whole(typename G::T32x64_2()) : whole(typename G::T32x64());
+        if (M <= 64) return second_round ? whole(typename G::T64x192()) : whole(typename G::T64x128());
+        if (M <= 128) return second_round ? whole(typename G::T128x192()) : whole(typename G::T128x128());
+        if (M <= 192) return second_round ? whole(typename G::T192x192()) : whole(typename G::T192x128());
+        if (M <= 256) return second_round ? whole(typename G::T256x192()) : whole(typename G::T256x128());   // a weight tile is fetched by exactly one block
         // (the vocabulary projection: several rounds of blocks per CU at any tile size, the big tile wins --
         // 240 us against 311 us at 400 rows of the 1.5B shape)
-        if (M > 256 && nb128 >= 512 && epi != EPI_SWIGLU && epi != EPI_SWIGLU_RS) CfgPrefill::run(A, W, C, M, N, K, epi, 1, sat, s);
-        else if (M > 384 && !deep) CfgLarge3::run(A, W, C, M, N, K, epi, 1, sat, s, row_scale);       // four 128-row blocks, three per CU at a time
-        else if (M > 256 && !deep) CfgLarge2::run(A, W, C, M, N, K, epi, 1, sat, s, row_scale);  // three 128-row blocks, not two of 256
-        else if (M > 128) CfgTall::run(A, W, C, M, N, K, epi, 1, sat, s, row_scale);    // a weight tile is fetched by exactly one block
-        else CfgLarge::run(A, W, C, M, N, K, epi, 1, sat, s, row_scale);
-        return 1;
+        if (deep || (nb128 >= 512 && !swiglu)) return whole(typename G::T256x128());
+        if (M > 384) return whole(typename G::M128x128_3());   // four 128-row blocks, three per CU at a time
+        return whole(typename G::M128x128_2());                // three 128-row blocks, not two of 256
     }
+    // The smallest batches stream the weights and little else: rows loaded for nothing (a tile of 128 for 3) cost as much of
+    // the load path as the weights (4096 x 12288 at 3 rows: 20 us against 27 us, 1536 x 8960: 6.6 against 9.5 us)
+    if (M <= 32) return sliced(typename G::T32x64(), 480);
     if ((int64_t)N * K >= (int64_t)8 << 20 && nb128 >= 24) {
         // mid-width outputs with large weights (q/k/v, o and down projections of the 8B / 14B models): 128-column
-        // tiles cut into about 240 blocks by K slices (8B down at 256 rows: 33 us against 48 us for 128x64 tiles)
-        if (M > 128) {
-            const int split = can_split ? CfgTall::pick_split(M, N, K, slice_cap_floats, 240) : 1;
-            if (split > 1) {
-                CfgTall::run(A, W, slices, M, N, K, EPI_STORE_F32, split, sat, s);
-                return split;
-            }
-            CfgTall::run(A, W, C, M, N, K, epi, 1, sat, s);
-            return 1;
-        }
-        const int split = can_split ? CfgLarge::pick_split(M, N, K, slice_cap_floats, 240) : 1;
-        if (split > 1) {
-            CfgLarge::run(A, W, slices, M, N, K, EPI_STORE_F32, split, sat, s);
-            return split;
-        }
-        CfgLarge::run(A, W, C, M, N, K, epi, 1, sat, s);
-        return 1;
+        // tiles cut into about 240 blocks by K slices (8B down at 256 rows: 38 us against 48 us with 128x64 tiles); the tile is
+        // as tall as the batch needs (8B down at 60 rows: 22 us, 29 us with 128-row tiles; 14B q/k/v at 168: 25 us, 30 us
+        // with 256-row ones)
+        if (M <= 64) return sliced(typename G::T64x128(), 240);
+        if (M <= 128) return sliced(typename G::T128x128(), 240);
+        if (M <= 192) return sliced(typename G::T192x128(), 240);
+        return sliced(typename G::T256x128(), 240);
     }
     if ((int64_t)N * K >= (int64_t)8 << 20) {   // narrow output, long K (the 1.5B model's down projection)
-        if (M > 256) {
-            const int split = can_split ? CfgMidTall::pick_split(M, N, K, slice_cap_floats, 240) : 1;
-            if (split > 1) {
-                CfgMidTall::run(A, W, slices, M, N, K, EPI_STORE_F32, split, sat, s);
-                return split;
-            }
-            CfgMidTall::run(A, W, C, M, N, K, epi, 1, sat, s);
-            return 1;
-        }
-        const int split = can_split ? CfgMid::pick_split(M, N, K, slice_cap_floats, 240) : 1;
-        if (split > 1) {
-            CfgMid::run(A, W, slices, M, N, K, EPI_STORE_F32, split, sat, s);
-            return split;
-        }
-        CfgMid::run(A, W, C, M, N, K, epi, 1, sat, s);
-        return 1;
+        if (M <= 64) return sliced(typename G::M64x64(), 240);   // 8.2 us against 10.4 us with 128-row tiles at 60 rows
+        if (M <= 256) return sliced(typename G::M128x64(), 240);
+        return sliced(typename G::M256x64(), 240);
     }
-    const int split = can_split ? CfgSmall::pick_split(M, N, K, slice_cap_floats, 192) : 1;
-    if (split > 1) {
-        CfgSmall::run(A, W, slices, M, N, K, EPI_STORE_F32, split, sat, s);
-        return split;
-    }
-    CfgSmall::run(A, W, C, M, N, K, epi, 1, sat, s);
-    return 1;
+    return sliced(typename G::M64x64(), 192);
 }
 
 }  // namespace pc

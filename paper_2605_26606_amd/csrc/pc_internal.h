@@ -160,7 +160,7 @@ __host__ __device__ inline int qkv_packed_dim(int j, int hd) {
 enum Epilogue {
     EPI_STORE_F32 = 0,   // C fp32 [M,N]
     EPI_RESID_F32 = 1,   // C fp32 [M,N] += product (residual stream update)
-    EPI_SWIGLU = 2,      // rows of W come in chunks of 64: 32 gate rows then the 32 matching up rows;
+    EPI_SWIGLU = 2,      // rows of W come in chunks of 32: 16 gate rows then the 16 matching up rows;
                          // C (model dtype) [M, N/2] = silu(gate) * up
     EPI_STORE_T = 3,     // C model dtype [M,N]
     EPI_SWIGLU_RS = 4,   // EPI_SWIGLU on rows that carry the RMSNorm gain but not its scale: gate and up are

@@ -241,6 +241,32 @@ def test_bf16_matrix_core_path(model, lens, G, T, bs, std, act):
     _check(model, w, prompts, out, 21, 2e-2, range(0, len(lens) * G, max(2, len(lens) * G // 12)))
 
 
+# outputs wide enough for unsplit tiles: 8192 and 12992 columns of 128-wide tiles, and 34816 and 33024 columns, for which
+# 128-wide tiles would need a second round of blocks and 192-wide ones do not
+WIDE1 = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=6400, vocab=12992,
+                         n_layers=1, rope_theta=1.0e6).model
+WIDE2 = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=17408, vocab=33024,
+                         n_layers=1, rope_theta=1.0e6).model
+
+
+@pytest.mark.parametrize("model,P,G,act", [(WIDE1, 3, 1, "f16"), (WIDE1, 11, 3, "f16"), (WIDE1, 13, 5, "f16"),
+                                           (WIDE1, 43, 3, "f16"), (WIDE1, 49, 4, "f16"), (WIDE1, 64, 4, "bf16"),
+                                           (WIDE2, 1, 1, "f16"), (WIDE2, 8, 4, "f16"), (WIDE2, 16, 4, "bf16"),
+                                           (WIDE2, 32, 4, "f16"), (WIDE2, 64, 3, "f16"), (WIDE2, 65, 3, "f16")])
+def test_wide_tiles_by_row_count(model, P, G, act):
+    # decode batches of 3, 33, 65, 129, 196, 256 and of 1, 32, 64, 128, 192, 195 rows: each side of the tiles' heights
+    say("wide tiles, d_ff %d, %d rows" % (model.d_ff, P * G))
+    w = workloads.perturb_norm_gains(workloads.make_weights(model, 3), 10)
+    rng = np.random.default_rng(P)
+    lens = rng.integers(1, 9, P).tolist()
+    toks, cu = workloads.make_ragged_prompts(lens, model.vocab, 8)
+    prompts = [toks[cu[i]:cu[i + 1]] for i in range(P)]
+    out = _run_generate(model, w, prompts, G, 3, 21, dict(block_size=32, kv_pool_bytes=256 << 20,
+                                                         max_slots=P * (G + 1) + 8, max_ctx=64, max_batch_rows=600,
+                                                         act_dtype=act))
+    _check(model, w, prompts, out, 21, 2e-2, range(0, P * G, max(1, P * G // 6)))
+
+
 def test_graph_replay_equals_eager_and_is_deterministic():
     say("graph vs eager, bf16")
     import paper_2605_26606_amd as pc
