@@ -181,8 +181,9 @@ pc_status pc_fork_need(const pc_ctx *ctx, const int32_t *prompt_handle, int32_t 
  *   seq        host int32 [n], distinct sequence ids
  *   tokens_in  device int32 [n]
  *   logits     device fp32 [n, vocab]
- * With PC_OPT_USE_GRAPH the step is captured once per (sequence list,
- * pointers, stream) and replayed; keep the pointers stable across steps.
+ * With PC_OPT_USE_GRAPH the step is captured once per (number of sequences,
+ * sequences per prompt, pointers, stream) and replayed; keep the pointers
+ * stable across steps.
  * A sequence that already holds prompt length + max_new_tokens tokens (the
  * reservation of its pc_fork) is PC_ERR_INVALID_ARG. */
 pc_status pc_decode_step(pc_ctx *ctx, const int32_t *seq, const int32_t *tokens_in, int32_t n,

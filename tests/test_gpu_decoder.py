@@ -177,6 +177,8 @@ def test_fp32_ragged_prompts_partial_blocks_chunks_and_larger_weights():
     (104, 4, 2, 26, 96, 301, [9, 40], 3),              # reductions of 104: not whole 16s, the plain-ALU kernel
     (112, 4, 2, 32, 352, 1000, [3, 17, 70], 1),        # 7 and 22 chunks of 16 on four waves, 3 decode rows
     (512, 8, 2, 64, 1376, 5001, [150, 301, 90], 5),    # tiles of 16, 32 and 64 rows and columns
+    (192, 2, 1, 96, 128, 500, [33, 64, 130], 2),       # attention over heads of 96 and of 160, caches in fragment order
+    (320, 4, 2, 160, 160, 500, [1, 63, 97], 2),
 ])
 def test_fp32_gemm_forms(d, hq, hkv, hd, dff, V, lens, G):
     # the bound of the other fp32 tests: float32 sums of up to 1376 products of order 0.02
