@@ -302,14 +302,21 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
             }
             continue;
         }
-        int s_qkv;
+        int s_qkv = 0;
+        bool appended;   // (the large batches' projection rotates and appends by itself)
         {
             Timed t(ctx, PC_KERNEL_GEMM_QKV, st);
-            s_qkv = launch_gemm(dt, impl, ctx->a, ctx->wqkv[l], ctx->qkv, rows, qd + 2 * kvd, m.d_model, EPI_STORE_F32,
-                                ctx->cur_slices, ctx->cur_slice_cap, sat, st);
+            appended = ctx->qkv_perm &&
+                       launch_gemm_qkv(dt, impl, ctx->a, ctx->wqkv[l], rows, m.d_model,
+                                       GemmQkv{row_slot, row_pos, ctx->d_slot_len, ctx->rope_cos, ctx->rope_sin, kv, l,
+                                               m.n_q_heads, ctx->q}, sat, st);
+            if (!appended)
+                s_qkv = launch_gemm(dt, impl, ctx->a, ctx->wqkv[l], ctx->qkv, rows, qd + 2 * kvd, m.d_model, EPI_STORE_F32,
+                                    ctx->cur_slices, ctx->cur_slice_cap, sat, st);
         }
-        launch_rope_append(dt, s_qkv > 1 ? ctx->cur_slices : ctx->qkv, s_qkv, row_slot, row_pos, ctx->d_slot_len,
-                           ctx->rope_cos, ctx->rope_sin, rows, m.n_q_heads, kv, l, ctx->q, sat, ctx->qkv_perm ? 1 : 0, st);
+        if (!appended)
+            launch_rope_append(dt, s_qkv > 1 ? ctx->cur_slices : ctx->qkv, s_qkv, row_slot, row_pos, ctx->d_slot_len,
+                               ctx->rope_cos, ctx->rope_sin, rows, m.n_q_heads, kv, l, ctx->q, sat, ctx->qkv_perm ? 1 : 0, st);
         if (ctx->mfma_attention()) {
             if (row_pos)
                 launch_attention_prefill_mfma(dt, ctx->q, cu_rows, prompt_slot, n_prompts, max_len, m.n_q_heads, kv, l,

@@ -264,6 +264,13 @@ template <int N> __device__ inline void wait_vmcnt_le() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+// What an epilogue needs besides the common arguments.
+struct NoExtra {};
+template <int EPI> struct GemmExtra { typedef NoExtra type; };
+template <> struct GemmExtra<EPI_SWIGLU_RS> { typedef GemmRowScale type; };
+template <> struct GemmExtra<EPI_LOGPROB> { typedef GemmLogprob type; };
+template <> struct GemmExtra<EPI_QKV> { typedef GemmQkv type; };
+
 // M16: the products are 16x16x32 instructions (a: A[row l%16][k = 8*(l/16) .. +7], b likewise,
 // d[v]: D[row 4*(l/16) + v][col l%16]) instead of 32x32x16: the same fragment bytes per product volume, four
 // times as many accumulator tiles per wave.
@@ -271,7 +278,7 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK, int EP
 __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__restrict__ A, const T *__restrict__ W,
                                                         void *__restrict__ Cv, int M, int N, int K, int mb, int nb,
                                                         int S, int plain, uint32_t *__restrict__ sat,
-                                                        GemmRowScale rsc, GemmLogprob lpa) {
+                                                        typename GemmExtra<EPI>::type extra) {
     constexpr bool SWIGLU = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_RS);
     constexpr int CPR = BK / 8;                           // 16-byte chunks per tile row
     constexpr int RPL = 64 / CPR;                         // tile rows one wave-wide load covers
@@ -480,10 +487,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
         float ss = 0.f;
         if (part < PARTS) {
             const int row = min(m0 + r, M - 1);
-            for (int t0 = part * RS_MAXT; t0 < rsc.tiles; t0 += PARTS * RS_MAXT) {
+            for (int t0 = part * RS_MAXT; t0 < extra.tiles; t0 += PARTS * RS_MAXT) {
                 float v[RS_MAXT];
 #pragma unroll
-                for (int u = 0; u < RS_MAXT; ++u) v[u] = (t0 + u < rsc.tiles) ? rsc.ssq[(int64_t)(t0 + u) * M + row] : 0.f;
+                for (int u = 0; u < RS_MAXT; ++u) v[u] = (t0 + u < extra.tiles) ? extra.ssq[(int64_t)(t0 + u) * M + row] : 0.f;
 #pragma unroll
                 for (int u = 0; u < RS_MAXT; ++u) ss += v[u];
             }
@@ -493,7 +500,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
             __syncthreads();
             if (part == 0) ss += s_rs_part[r];
         }
-        if (part == 0) s_rs[r] = 1.0f / sqrtf(ss / (float)rsc.d + rsc.eps);
+        if (part == 0) s_rs[r] = 1.0f / sqrtf(ss / (float)extra.d + extra.eps);
         __syncthreads();
     }
     frag_t fa[2][TM], fb[2][TN];
@@ -540,7 +547,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int row = m0 + wm * (BM / WM) + i * 16 + ml;
-            const int want = row < M ? lpa.tokens[lpa.token_index[row] + 1] - col0 - nq : -1;   // (column - nq) of the target
+            const int want = row < M ? extra.tokens[extra.token_index[row] + 1] - col0 - nq : -1;   // (column - nq) of the target
             float mx = -INFINITY, hit = 0.f;
             bool found = false;
 #pragma unroll
@@ -552,7 +559,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
                             hit = acc[i][jj][v];
                             found = true;
                         }
-                        acc[i][jj][v] *= lpa.inv_t;
+                        acc[i][jj][v] *= extra.inv_t;
                         mx = fmaxf(mx, acc[i][jj][v]);
                     }
                 }
@@ -569,12 +576,86 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
             s += __shfl_xor(s, 16, 64);
             s += __shfl_xor(s, 32, 64);
             if (row < M) {
-                if (found) lpa.target[row] = hit;
+                if (found) extra.target[row] = hit;
                 if (nq == 0) {
-                    lpa.part_max[strip * M + row] = mx;
-                    lpa.part_sum[strip * M + row] = s;
+                    extra.part_max[strip * M + row] = mx;
+                    extra.part_sum[strip * M + row] = s;
                 }
             }
+        }
+        return;
+    } else if constexpr (EPI == EPI_QKV) {
+        // A wave's columns lie within one head.  q and k: columns come in blocks of 32, 16 dims and their 16 rotary partners
+        // (dim + 64): two accumulator tiles that hold the same lanes' pairs.  The rotated 16-row tiles go through the wave's
+        // piece of the idle LDS ring and leave as 16-byte pieces (eight dims: contiguous in q and in a key's cache fragment).
+        // v: a lane's four dims of one token are four places of the cache; 16 lanes hold 16 rows, so a prompt's consecutive
+        // tokens leave as runs of eight.  The fp32 q | k | v rows (134 MB per layer at 16384 rows of the 1.5B shape, written
+        // and read again by a kernel of its own) never exist.
+        static_assert(M16, "lane layout of the 16x16x32 products");
+        constexpr int WC = BN / WN, HALF = WC / 2;
+        constexpr int PITCH = WC * 2 + 16, LPR = WC / 8, PIECES = 16 * LPR;
+        static_assert(WC % 32 == 0 && 128 % WC == 0, "whole 32-column blocks of one head");
+        static_assert((size_t)NW * 16 * PITCH <= (size_t)NSTAGE * STAGE_ELEMS * sizeof(T), "staging fits the ring");
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // every wave has consumed its last fragments
+        asm volatile("" ::: "memory");
+        unsigned char *stg = smem_raw + (size_t)wave * 16 * PITCH;
+        const int ml = lane % 16, nq = 4 * (lane / 16), col0 = n0 + wn * WC;
+        if (col0 >= N) return;
+        const int hkv = extra.kv.n_kv_heads, bs = extra.kv.block_size;
+        const int qd = extra.hq * 128, kvd = hkv * 128;
+        const int part = col0 < qd ? 0 : (col0 < qd + kvd ? 1 : 2);   // q, k, v (wave-uniform)
+        const int pc0 = col0 - (part == 0 ? 0 : (part == 1 ? qd : qd + kvd));
+        const int head = pc0 / 128, in = pc0 % 128;                   // first column inside the head
+        T *pool = (T *)extra.kv.pool + (int64_t)extra.layer * extra.kv.layer_stride + (int64_t)head * extra.kv.head_elems();
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int mt = m0 + wm * (BM / WM) + i * 16, row = mt + ml;
+            int pos = 0, blk = 0;
+            if (row < M) {
+                const int slot = extra.row_slot[row];
+                pos = extra.row_pos ? extra.row_pos[row] : extra.slot_len[slot];
+                if (part) blk = extra.kv.block_table[(int64_t)slot * extra.kv.max_blocks_per_slot + pos / bs];
+            }
+            const int tin = pos % bs;
+            if (part == 2) {
+                if (row < M) {
+                    T *vd = pool + (int64_t)blk * extra.kv.block_elems();
+#pragma unroll
+                    for (int jj = 0; jj < TN; ++jj)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            vd[extra.kv.v_index(tin, in + 16 * jj + nq + v)] = from_f32_sat<T>(acc[i][jj][v], sat);
+                }
+                continue;
+            }
+#pragma unroll
+            for (int p2 = 0; p2 < TN / 2; ++p2) {
+                const int j = in / 2 + 16 * p2 + nq;                  // first of the lane's four pair indices
+                const f32x4_t c = *(const f32x4_t *)(extra.rope_cos + (int64_t)pos * 64 + j);
+                const f32x4_t sn = *(const f32x4_t *)(extra.rope_sin + (int64_t)pos * 64 + j);
+                const acc_t &x1 = acc[i][2 * p2], &x2 = acc[i][2 * p2 + 1];
+                unsigned char *dst = stg + ml * PITCH + (16 * p2 + nq) * 2;
+                *(u32x2 *)dst = pack4_sat<T>(x1[0] * c[0] - x2[0] * sn[0], x1[1] * c[1] - x2[1] * sn[1],
+                                             x1[2] * c[2] - x2[2] * sn[2], x1[3] * c[3] - x2[3] * sn[3], sat);
+                *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(x2[0] * c[0] + x1[0] * sn[0], x2[1] * c[1] + x1[1] * sn[1],
+                                                          x2[2] * c[2] + x1[2] * sn[2], x2[3] * c[3] + x1[3] * sn[3], sat);
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int it = 0; it < (PIECES + 63) / 64; ++it) {
+                const int e = it * 64 + lane, r = (e / LPR) % 16, piece = e % LPR;
+                const u32x4 val = *(const u32x4 *)(stg + r * PITCH + piece * 16);
+                const int dim = in / 2 + (8 * piece) % HALF + 64 * ((8 * piece) / HALF);
+                const int rblk = __shfl(blk, r, 64), rtin = __shfl(tin, r, 64);
+                if (mt + r < M && (PIECES % 64 == 0 || e < PIECES)) {
+                    if (part == 0)
+                        *(u32x4 *)((T *)extra.q_out + ((int64_t)(mt + r) * extra.hq + head) * 128 + dim) = val;
+                    else
+                        *(u32x4 *)(pool + (int64_t)rblk * extra.kv.block_elems() + extra.kv.k_index(rtin, dim)) = val;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
         }
         return;
     } else {
@@ -681,38 +762,34 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
             set_attr<EPI_SWIGLU_RS>();
         }
     }
-    // split > 1 only with EPI_STORE_F32, C then being the slice buffer [split][M][N]
-    static void run(const void *A, const void *W, void *C, int M, int N, int K, int epi, int split, uint32_t *sat, hipStream_t s,
-                    const GemmRowScale *row_scale = nullptr) {
-        const GemmRowScale rsc = row_scale ? *row_scale : GemmRowScale{nullptr, 0, 1, 0.f};
+    template <int E>
+    static void launch(const void *A, const void *W, void *C, int M, int N, int K, int split, uint32_t *sat, hipStream_t s,
+                       const typename GemmExtra<E>::type &extra) {
         const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
         const int units = nb * split;
         const int plain = (split == 1 && mb > 4) ? ((mb % N_XCD == 0) ? 2 : 1) : 0;
         const unsigned grid = plain ? (unsigned)(mb * nb) : (unsigned)((units + N_XCD - 1) / N_XCD * N_XCD * mb);
-        const T *a = (const T *)A, *w = (const T *)W;
+        gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, E, M16><<<grid, 64 * WM * WN, smem, s>>>(
+            (const T *)A, (const T *)W, C, M, N, K, mb, nb, split, plain, sat, extra);
+    }
+    // split > 1 only with EPI_STORE_F32, C then being the slice buffer [split][M][N]
+    static void run(const void *A, const void *W, void *C, int M, int N, int K, int epi, int split, uint32_t *sat, hipStream_t s,
+                    const GemmRowScale *row_scale = nullptr) {
         switch (epi) {
-            case EPI_STORE_F32: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_STORE_F32, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, split, plain, sat, rsc, GemmLogprob{}); break;
-            case EPI_RESID_F32: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_RESID_F32, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{}); break;
+            case EPI_STORE_F32: launch<EPI_STORE_F32>(A, W, C, M, N, K, split, sat, s, {}); break;
+            case EPI_RESID_F32: launch<EPI_RESID_F32>(A, W, C, M, N, K, 1, sat, s, {}); break;
             case EPI_SWIGLU:
-                if constexpr (swiglu_ok)
-                    gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_SWIGLU, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{});
+                if constexpr (swiglu_ok) launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
                 break;
             case EPI_SWIGLU_RS:
-                if constexpr (swiglu_ok)
-                    gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_SWIGLU_RS, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{});
+                if constexpr (swiglu_ok) launch<EPI_SWIGLU_RS>(A, W, C, M, N, K, 1, sat, s, *row_scale);
                 break;
-            default: gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_STORE_T, M16><<<grid, 64 * WM * WN, smem, s>>>(a, w, C, M, N, K, mb, nb, 1, plain, sat, rsc, GemmLogprob{}); break;
+            default: launch<EPI_STORE_T>(A, W, C, M, N, K, 1, sat, s, {}); break;
         }
     }
     static void init_logprob() { set_attr<EPI_LOGPROB>(); }
     static int strips(int N) { return (N + BN - 1) / BN * WN; }
-    static void run_logprob(const void *A, const void *W, int M, int N, int K, const GemmLogprob &lpa, hipStream_t s) {
-        const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
-        const int plain = mb > 4 ? ((mb % N_XCD == 0) ? 2 : 1) : 0;
-        const unsigned grid = plain ? (unsigned)(mb * nb) : (unsigned)((nb + N_XCD - 1) / N_XCD * N_XCD * mb);
-        gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, EPI_LOGPROB, M16><<<grid, 64 * WM * WN, smem, s>>>(
-            (const T *)A, (const T *)W, nullptr, M, N, K, mb, nb, 1, plain, nullptr, GemmRowScale{nullptr, 0, 1, 0.f}, lpa);
-    }
+    static void init_qkv() { set_attr<EPI_QKV>(); }
     // K slices so that the launch has about `want_blocks` blocks, each with >= 4 K tiles
     static int pick_split(int M, int N, int K, size_t slice_cap_floats, int want_blocks) {
         const int64_t tiles = (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM);
@@ -756,6 +833,9 @@ template <typename T> struct Gemm {
         T256x128::init_logprob();
         T192x128::init_logprob();
         T128x128::init_logprob();
+        T256x256::init_qkv();
+        T256x128::init_qkv();
+        T128x128_2::init_qkv();
     }
 };
 void gemm_init() {
@@ -783,6 +863,25 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
     }
     if (dtype == KD_BF16) return gemm_mfma_dispatch<bf16_t>(A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
     return gemm_mfma_dispatch<f16_t>(A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
+}
+
+// ---- q | k | v projection with rotary positions and cache append
+template <typename T> static void gemm_qkv_t(const void *A, const void *W, int M, int N, int K, const GemmQkv &qkv, uint32_t *sat, hipStream_t s) {
+    typedef Gemm<T> G;
+    // the tile of the plain projection of this size (gemm_mfma_dispatch), where that is not cut into K slices; where it is
+    // (1024 rows x 2048 columns), smaller tiles without slices
+    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) G::T256x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else if ((int64_t)((M + 255) / 256) * ((N + 127) / 128) >= 160) G::T256x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else G::T128x128_2::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+}
+
+bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
+                     hipStream_t s) {
+    const int N = (qkv.hq + 2 * qkv.kv.n_kv_heads) * qkv.kv.head_dim;
+    if (dtype == KD_F32 || impl == 0 || qkv.kv.head_dim != 128 || K % 64 != 0 || M <= 512) return false;
+    if (dtype == KD_BF16) gemm_qkv_t<bf16_t>(A, W, M, N, K, qkv, sat, s);
+    else gemm_qkv_t<f16_t>(A, W, M, N, K, qkv, sat, s);
+    return true;
 }
 
 // ---- log-probabilities straight from the vocabulary projection: a scoring pass wrote 622 MB of logits per 1024 rows of the
@@ -836,7 +935,7 @@ static void gemm_logprob_t(const void *A, const void *W, int M, int N, int K, Ge
     int strips = 0;
     auto run = [&](auto cfg) {
         strips = decltype(cfg)::strips(N);
-        decltype(cfg)::run_logprob(A, W, M, N, K, lpa, s);
+        decltype(cfg)::template launch<EPI_LOGPROB>(A, W, nullptr, M, N, K, 1, nullptr, s, lpa);
     };
     if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256 && M > 512) run(typename G::T256x256());   // as for the other wide projections
     else if (M <= 128) run(typename G::T128x128());

@@ -167,6 +167,8 @@ enum Epilogue {
                          // multiplied by the row's rsqrt(mean(h^2) + eps) first (statistics in GemmRowScale)
     EPI_LOGPROB = 5,     // nothing of the product is stored: per row and strip of columns the maximum and the sum of exponentials
                          // of the scaled product, and the product at the row's target column (GemmLogprob)
+    EPI_QKV = 6,         // the fused q | k | v projection: rotary positions applied to q and k, q written in the model dtype,
+                         // k and v appended to the cache (GemmQkv; heads of 128, rows of W in the order of qkv_packed_dim)
 };
 
 // Per-row RMSNorm statistics for EPI_SWIGLU_RS: ssq[t][row], t < tiles, are partial sums of squares of the row (as the fused output projection leaves them); scale = rsqrt(sum_t ssq / d + eps).
@@ -183,6 +185,15 @@ struct GemmLogprob {
     const int32_t *tokens, *token_index;
     float *part_max, *target;
     double *part_sum;
+};
+
+// EPI_QKV: row r belongs to slot row_slot[r] at position row_pos[r] (NULL: slot_len[slot]).
+struct GemmQkv {
+    const int32_t *row_slot, *row_pos, *slot_len;
+    const float *rope_cos, *rope_sin;
+    KvGeom kv;
+    int layer, hq;
+    void *q_out;
 };
 
 // ---------------------------------------------------------------- kernel launchers
@@ -210,6 +221,10 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
 int logprob_fused_rows(int dtype, int impl, int N, int K, size_t scratch_bytes);
 void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, int K, float temperature,
                          const int32_t *tokens, const int32_t *token_index, void *scratch, float *out, hipStream_t s);
+// C = A W^T as EPI_QKV leaves it, for batches whose projection needs no K slices (more than 512 rows); false: not a shape it
+// takes, nothing launched.
+bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
+                     hipStream_t s);
 // Fused decode projections (gemm_skinny.hip); skinny_ok says whether the shape is one they take.
 bool skinny_ok(int M, int N, int K, int head_dim);
 void skinny_init();   // once per process, like gemm_init

@@ -269,6 +269,29 @@ def test_wide_tiles_by_row_count(model, P, G, act):
     _check(model, w, prompts, out, 21, 2e-2, range(0, P * G, max(1, P * G // 6)))
 
 
+@pytest.mark.parametrize("hq,hkv,lens,bs,act", [
+    (8, 2, [201, 3, 190, 128, 90], 32, "f16"),             # 612 rows x 1536 columns: the 128 x 128 tiles
+    (48, 8, [333, 1, 300, 65, 301], 64, "f16"),           # 1000 x 8192: 256 x 128
+    (48, 8, [700, 9, 650, 800, 777, 640, 555], 64, "f16"),    # 4131 x 8192: 256 x 256, a row tile with 35 rows
+    (48, 8, [700, 9, 650, 800, 777, 640, 555], 128, "bf16"),
+])
+def test_projection_that_rotates_and_appends(hq, hkv, lens, bs, act):
+    # prefill chunks of more than 512 rows: q, k and v leave the projection rotated and filed; sequences start anywhere in a
+    # tile and in a KV block, and two decode steps read the cache back
+    say("q/k/v projection with rotary positions, %d rows x %d columns" % (sum(lens), (hq + 2 * hkv) * 128))
+    m = workloads.scaled(C1, dtype="bf16", d_model=128, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ff=128, vocab=512,
+                         n_layers=2, rope_theta=1.0e6).model
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 3, std=0.05), 10)
+    toks, cu = workloads.make_ragged_prompts(lens, m.vocab, 8)
+    prompts = [toks[cu[i]:cu[i + 1]] for i in range(len(lens))]
+    out = _run_generate(m, w, prompts, 2, 3, 21, dict(block_size=bs, kv_pool_bytes=256 << 20, max_slots=40, max_ctx=900,
+                                                     max_batch_rows=4200, act_dtype=act))
+    for q in range(len(lens)):
+        want = decoder.forward_full(m, w, prompts[q], rows=[lens[q] - 1])[0]
+        assert np.abs(want - out["last"][q]).max() <= 2e-2 * max(1.0, np.abs(want).max())
+    _check(m, w, prompts, out, 21, 2e-2, range(0, len(lens) * 2, 3))
+
+
 def test_graph_replay_equals_eager_and_is_deterministic():
     say("graph vs eager, bf16")
     import paper_2605_26606_amd as pc
