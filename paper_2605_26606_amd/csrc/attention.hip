@@ -212,20 +212,31 @@ __device__ inline void load_kv_tile(const T *__restrict__ head_base, int64_t blo
     for (int nn = 0; nn < 8; ++nn) kt.vf[nn] = ld_frag(vb + ((tile * 8 + nn) << 9));
 }
 
+// Two probabilities (0 .. 2^RESCALE) to the operand type, rounded to nearest even
+template <typename T> __device__ inline uint32_t pack_prob(float a, float b);
+template <> __device__ inline uint32_t pack_prob<f16_t>(float a, float b) {
+    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+    return __builtin_bit_cast(uint32_t, (f16x2){(_Float16)a, (_Float16)b});
+}
+template <> __device__ inline uint32_t pack_prob<bf16_t>(float a, float b) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 b16x2;
+    return __builtin_bit_cast(uint32_t, (b16x2){(__bf16)a, (__bf16)b});
+}
+
 // One tile's update of the running softmax state of NH query-head groups that share the kv head.
-// Tokens > col_limit (this lane's column) or >= tok_end are masked.
-template <typename T, int NH>
+// MASKED: tokens > col_limit (this lane's column) or >= tok_end are left out; otherwise all 32 take part.
+//
+// The vector ALU, not the matrix cores, bounds this loop (8 scores per lane against 16 products of 16 clocks), so a tile does
+// as little as possible beside its exponentials: the state's reference m is raised -- and the outputs rescaled, the maxima
+// exchanged between the lanes of a column -- only when some column's score exceeds it by more than RESCALE powers of two, which
+// after a column's first tile is rare; until then the probabilities may reach 2^RESCALE, which neither their rounding
+// (relative) nor the fp32 sums notice.  Any reference gives the same quotient at the end.
+static constexpr float RESCALE = 8.0f;
+
+template <typename T, int NH, bool MASKED>
 __device__ inline void attend_tile(const KvTile<T> &kt, const typename Mma<T>::frag (&qf)[NH][4], int t0, int tok_end,
                                    int col_limit, float scale_log2, AttnState (&st)[NH]) {
     const int lane = threadIdx.x % WAVE, g = lane / 16;
-    bool ok[2][4];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int tok = t0 + 8 * g + 4 * u + v;
-            ok[u][v] = (tok <= col_limit) && (tok < tok_end);
-        }
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
         f32x4 s[2];
@@ -236,39 +247,46 @@ __device__ inline void attend_tile(const KvTile<T> &kt, const typename Mma<T>::f
             for (int kk = 0; kk < 4; ++kk) s[u] = Mma<T>::m16(kt.ka[u][kk], qf[h][kk], s[u]);
         }
         // lane (column i, g) holds the scores of tokens t0 + 8g + 4u + v
-        float mx = -INFINITY;
+        if (MASKED) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (ok[u][v]) mx = fmaxf(mx, s[u][v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-        const float m_new = fmaxf(st[h].m, mx);
-        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        const float corr = exp2f((st[h].m - m_use) * scale_log2);   // st.m = -inf -> 0
+                for (int v = 0; v < 4; ++v) {
+                    const int tok = t0 + 8 * g + 4 * u + v;
+                    if (tok > col_limit || tok >= tok_end) s[u][v] = -INFINITY;
+                }
+        }
+        float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                         fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+        if (__any((mx - st[h].m) * scale_log2 > RESCALE)) {   // (m = -inf: any finite score exceeds it; both: NaN, does not)
+            mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+            const float m_new = fmaxf(st[h].m, mx);
+            const float corr = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((st[h].m - m_new) * scale_log2);
+            st[h].l *= corr;
+            st[h].m = m_new;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float c = __shfl(corr, 4 * g + v, WAVE);
+#pragma unroll
+                for (int nn = 0; nn < 8; ++nn) st[h].o[nn][v] *= c;
+            }
+        }
+        const float off = (st[h].m == -INFINITY) ? 0.f : st[h].m * scale_log2;
         float p[2][4], psum = 0.f;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                p[u][v] = ok[u][v] ? exp2f((s[u][v] - m_use) * scale_log2) : 0.f;
+                p[u][v] = __builtin_amdgcn_exp2f(fmaf(s[u][v], scale_log2, -off));
                 psum += p[u][v];
             }
-        st[h].l = st[h].l * corr + psum;
-        st[h].m = m_new;
-        float c4[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) c4[v] = __shfl(corr, 4 * g + v, WAVE);
-        u32x4 pw = {pack2<T>(p[0][0], p[0][1]), pack2<T>(p[0][2], p[0][3]), pack2<T>(p[1][0], p[1][1]),
-                    pack2<T>(p[1][2], p[1][3])};
+        st[h].l += psum;
+        u32x4 pw = {pack_prob<T>(p[0][0], p[0][1]), pack_prob<T>(p[0][2], p[0][3]), pack_prob<T>(p[1][0], p[1][1]),
+                    pack_prob<T>(p[1][2], p[1][3])};
         const typename Mma<T>::frag pa = __builtin_bit_cast(typename Mma<T>::frag, pw);
 #pragma unroll
-        for (int nn = 0; nn < 8; ++nn) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) st[h].o[nn][v] *= c4[v];
-            st[h].o[nn] = Mma<T>::m16(pa, kt.vf[nn], st[h].o[nn]);
-        }
+        for (int nn = 0; nn < 8; ++nn) st[h].o[nn] = Mma<T>::m16(pa, kt.vf[nn], st[h].o[nn]);
     }
 }
 
@@ -281,6 +299,14 @@ __device__ inline void attend_tiles(const T *__restrict__ head_base, int64_t blo
                                     const int32_t *__restrict__ table, int bs,
                                     const typename Mma<T>::frag (&qf)[NH][4], int tile_begin, int tile_step, int tok_end,
                                     int col_limit, float scale_log2, AttnState (&st)[NH]) {
+    // a tile needs the masks only where it reaches past a column's limit or the end (col_limit < 0: an unused column, whose
+    // results nobody reads, but whose state must not see a token: its lanes keep every tile masked)
+    auto attend = [&](const KvTile<T> &kt, int t0) {
+        if (__all(t0 + 31 <= col_limit) && t0 + 32 <= tok_end)
+            attend_tile<T, NH, false>(kt, qf, t0, tok_end, col_limit, scale_log2, st);
+        else
+            attend_tile<T, NH, true>(kt, qf, t0, tok_end, col_limit, scale_log2, st);
+    };
     if (AHEAD) {
         KvTile<T> a, b;
         int ta = tile_begin;
@@ -289,11 +315,11 @@ __device__ inline void attend_tiles(const T *__restrict__ head_base, int64_t blo
         for (;;) {
             const int tb = ta + tile_step;
             if (tb < tok_end) load_kv_tile<T>(head_base, block_elems, table, bs, tb, b);
-            attend_tile<T, NH>(a, qf, ta, tok_end, col_limit, scale_log2, st);
+            attend(a, ta);
             if (tb >= tok_end) break;
             ta = tb + tile_step;
             if (ta < tok_end) load_kv_tile<T>(head_base, block_elems, table, bs, ta, a);
-            attend_tile<T, NH>(b, qf, tb, tok_end, col_limit, scale_log2, st);
+            attend(b, tb);
             if (ta >= tok_end) break;
         }
         return;
@@ -301,7 +327,7 @@ __device__ inline void attend_tiles(const T *__restrict__ head_base, int64_t blo
     for (int t0 = tile_begin; t0 < tok_end; t0 += tile_step) {
         KvTile<T> kt;
         load_kv_tile<T>(head_base, block_elems, table, bs, t0, kt);
-        attend_tile<T, NH>(kt, qf, t0, tok_end, col_limit, scale_log2, st);
+        attend(kt, t0);
     }
 }
 
