@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -386,6 +387,15 @@ pc_status static_scratch_base(int device, unsigned char **out) {
     return PC_OK;
 }
 
+// The kernels' dynamic-LDS limits, once per device (a few hundred runtime calls, 1 ms: not for every context).
+void kernel_init(int device) {
+    static std::atomic<bool> done[64];   // (two threads at once: both set the same limits)
+    if (device >= 0 && device < 64 && done[device].load(std::memory_order_acquire)) return;
+    gemm_init();
+    skinny_init();
+    if (device >= 0 && device < 64) done[device].store(true, std::memory_order_release);
+}
+
 pc_status check_launch() {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) PC_FAIL(PC_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -451,8 +461,7 @@ pc_status pc_create(const pc_model_config *model, const pc_weights *w, const pc_
     } while (0)
     TRY_HIP(hipGetDevice(&ctx->device));
     TRY(static_scratch_base(ctx->device, &ctx->static_scratch));
-    gemm_init();
-    skinny_init();
+    kernel_init(ctx->device);
     const size_t esz = ctx->esz;
     const int qd = m.n_q_heads * m.head_dim, kvd = m.n_kv_heads * m.head_dim;
     hipStream_t st = nullptr;

@@ -14,7 +14,7 @@ __device__ inline float wave_sum(float v) {
 }
 
 // ------------------------------------------------------------------ embed
-template <typename T>
+template <typename T, bool VEC>
 __global__ void embed_kernel(const T *__restrict__ table, const int32_t *__restrict__ tokens, int d, int vocab,
                              float *__restrict__ h) {
     int r = blockIdx.x;
@@ -22,16 +22,29 @@ __global__ void embed_kernel(const T *__restrict__ table, const int32_t *__restr
     if (tok < 0 || tok >= vocab) tok = 0;
     const T *src = table + (int64_t)tok * d;
     float *dst = h + (int64_t)r * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) dst[i] = to_f32(src[i]);
+    if (VEC) {   // four elements per access (16384 rows of 1536: 48 us one by one, 28 us)
+        for (int i = 4 * threadIdx.x; i < d; i += 4 * blockDim.x) {
+            struct alignas(4 * sizeof(T)) Four { T e[4]; };
+            const Four f = *(const Four *)(src + i);
+            *(float4 *)(dst + i) = make_float4(to_f32(f.e[0]), to_f32(f.e[1]), to_f32(f.e[2]), to_f32(f.e[3]));
+        }
+    } else {
+        for (int i = threadIdx.x; i < d; i += blockDim.x) dst[i] = to_f32(src[i]);
+    }
 }
 
 void launch_embed(int dtype, const void *table, const int32_t *tokens, int rows, int d, int vocab, float *h,
                   hipStream_t s) {
     if (rows <= 0) return;
-    if (dtype == KD_F32)   // the table is the caller's: fp32, or bf16 for both 16-bit kernel dtypes
-        embed_kernel<float><<<rows, 256, 0, s>>>((const float *)table, tokens, d, vocab, h);
-    else
-        embed_kernel<bf16_t><<<rows, 256, 0, s>>>((const bf16_t *)table, tokens, d, vocab, h);
+    // the table is the caller's (fp32, or bf16 for both 16-bit kernel dtypes) and may start anywhere
+    const bool vec = d % 4 == 0 && ((uintptr_t)table) % 16 == 0;
+    if (dtype == KD_F32) {
+        if (vec) embed_kernel<float, true><<<rows, 256, 0, s>>>((const float *)table, tokens, d, vocab, h);
+        else embed_kernel<float, false><<<rows, 256, 0, s>>>((const float *)table, tokens, d, vocab, h);
+    } else {
+        if (vec) embed_kernel<bf16_t, true><<<rows, 256, 0, s>>>((const bf16_t *)table, tokens, d, vocab, h);
+        else embed_kernel<bf16_t, false><<<rows, 256, 0, s>>>((const bf16_t *)table, tokens, d, vocab, h);
+    }
 }
 
 // ------------------------------------------------------------------ RMSNorm

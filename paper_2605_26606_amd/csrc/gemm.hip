@@ -548,17 +548,19 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
         for (int i = 0; i < TM; ++i) {
             const int row = m0 + wm * (BM / WM) + i * 16 + ml;
             const int want = row < M ? extra.tokens[extra.token_index[row] + 1] - col0 - nq : -1;   // (column - nq) of the target
-            float mx = -INFINITY, hit = 0.f;
-            bool found = false;
+            if (__any(want >= 0 && want < WC)) {   // (rare: a row's target is in one of a thousand strips)
+#pragma unroll
+                for (int jj = 0; jj < TN; ++jj)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (want == jj * 16 + v && col0 + jj * 16 < N) extra.target[row] = acc[i][jj][v];
+            }
+            float mx = -INFINITY;
 #pragma unroll
             for (int jj = 0; jj < TN; ++jj)
                 if (col0 + jj * 16 < N) {   // N is a multiple of 16: a tile is inside or outside
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        if (want == jj * 16 + v) {
-                            hit = acc[i][jj][v];
-                            found = true;
-                        }
                         acc[i][jj][v] *= extra.inv_t;
                         mx = fmaxf(mx, acc[i][jj][v]);
                     }
@@ -575,12 +577,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
                 }
             s += __shfl_xor(s, 16, 64);
             s += __shfl_xor(s, 32, 64);
-            if (row < M) {
-                if (found) extra.target[row] = hit;
-                if (nq == 0) {
-                    extra.part_max[strip * M + row] = mx;
-                    extra.part_sum[strip * M + row] = s;
-                }
+            if (row < M && nq == 0) {
+                extra.part_max[strip * M + row] = mx;
+                extra.part_sum[strip * M + row] = s;
             }
         }
         return;

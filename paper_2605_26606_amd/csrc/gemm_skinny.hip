@@ -20,12 +20,20 @@
 
 namespace pc {
 
-static constexpr int SK_BM = 64, SK_BN = 32, SK_WAVES = 4;
-static constexpr int SK_BK = 64, SK_NS = 3;                            // K step, steps in flight per wave
-static constexpr int SK_STEP_ELEMS = (SK_BM + SK_BN) * SK_BK;          // one step of one wave: A rows, then W rows
-static constexpr int SK_LOADS = (SK_BM + SK_BN) / 8;                   // wave-wide 1 KB loads per step (8 rows each)
-static constexpr size_t SK_SMEM = (size_t)SK_WAVES * SK_NS * SK_STEP_ELEMS * 2;   // 144 KB of 16-bit elements
+static constexpr int SK_BN = 32, SK_WAVES = 4;
+static constexpr int SK_BK = 64;                                       // K step
 static constexpr int SK_STRIDE = 36;                                   // LDS row stride of the wave partials (floats)
+// Rows of the block's tile (64, or 16 / 32 for batches that small: the rows a taller tile loads for nothing cost load path and
+// LDS) and steps in flight per wave, as many as the LDS holds: at 3 rows of the 1.5B shape all of a wave's six steps, 8.0 -> 6.8
+// (q/k/v) and 7.8 -> 6.6 us (o) per launch under the profiler.
+template <int BM> struct SkinnyTile {
+    static constexpr int NS = BM == 64 ? 3 : (BM == 32 ? 4 : 6);
+    static constexpr int STEP_ELEMS = (BM + SK_BN) * SK_BK;            // one step of one wave: A rows, then W rows
+    static constexpr int LOADS = (BM + SK_BN) / 8;                     // wave-wide 1 KB loads per step (8 rows each)
+    static constexpr size_t SMEM = (size_t)SK_WAVES * NS * STEP_ELEMS * 2;   // 144 / 128 / 144 KB of 16-bit elements
+    static_assert((NS - 1) * LOADS <= 63, "vmcnt is a 6-bit counter");
+    static_assert(SMEM >= (size_t)SK_WAVES * BM * SK_STRIDE * 4, "the partial sums fit");
+};
 
 typedef __attribute__((ext_vector_type(4))) uint32_t sk_u32x4;
 
@@ -50,10 +58,12 @@ template <typename T> __device__ inline typename Mma<T>::frag sk_ld(const T *p) 
 // MODE 0: q/k/v + RoPE + append (weights rows of every q and k head permuted so that a 32-column block holds
 //         16 dims of the first half of the head and their 16 rotation partners, see pack_qkv_rows)
 // MODE 1: residual update + activation copy + sums of squares
-template <typename T, int MODE>
+template <typename T, int MODE, int BM>
 __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__restrict__ A, const T *__restrict__ W,
                                                                   int M, int N, int K, int mb, int nb, SkinnyQkv qa,
                                                                   SkinnyO oa, uint32_t *__restrict__ sat) {
+    constexpr int SK_BM = BM, SK_NS = SkinnyTile<BM>::NS, SK_STEP_ELEMS = SkinnyTile<BM>::STEP_ELEMS,
+                  SK_LOADS = SkinnyTile<BM>::LOADS, MT = BM / 16;
     extern __shared__ __attribute__((aligned(1024))) unsigned char sk_smem[];
     const int id = blockIdx.x, die = id % 8, j = id / 8;
     const int bn = (j / mb) * 8 + die;
@@ -71,7 +81,7 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__r
     const T *src[SK_LOADS];
 #pragma unroll
     for (int l = 0; l < SK_LOADS; ++l) {
-        const int row = 8 * l + lr;                    // rows 0..63: A, 64..95: W
+        const int row = 8 * l + lr;                    // rows 0..BM-1: A, then 32 of W
         const int chunk = lslot ^ ((row / 2) & 7);
         src[l] = (row < SK_BM ? A + (int64_t)min(m0 + row, M - 1) * K : W + (int64_t)(n0 + row - SK_BM) * K) + kwave +
                  chunk * 8;
@@ -86,16 +96,16 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__r
     };
 
     typedef typename Mma<T>::frag frag_t;
-    f32x4_t acc[4][2];
+    f32x4_t acc[MT][2];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
     // fragment addressing: lane (i, g) reads chunk 4 kk + g of row 16 t + i, stored at slot chunk ^ swz(row)
-    int foff[6][2];
+    int foff[MT + 2][2];
 #pragma unroll
-    for (int t = 0; t < 6; ++t) {
+    for (int t = 0; t < MT + 2; ++t) {
         const int row = 16 * t + i;
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) foff[t][kk] = row * SK_BK + (((4 * kk + g) ^ ((row / 2) & 7)) * 8);
@@ -114,13 +124,13 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__r
         const T *base = ring + stage * SK_STEP_ELEMS;
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-            frag_t fa[4], fb[2];
+            frag_t fa[MT], fb[2];
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) fa[mt] = *(const frag_t *)(base + foff[mt][kk]);
+            for (int mt = 0; mt < MT; ++mt) fa[mt] = *(const frag_t *)(base + foff[mt][kk]);
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) fb[nt] = *(const frag_t *)(base + foff[4 + nt][kk]);
+            for (int nt = 0; nt < 2; ++nt) fb[nt] = *(const frag_t *)(base + foff[MT + nt][kk]);
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = Mma<T>::m16(fa[mt], fb[nt], acc[mt][nt]);
         }
@@ -133,7 +143,7 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__r
 
     // ---- the four K quarters meet in LDS: acc[mt][nt][v] is C[16 mt + 4 g + v][16 nt + i] of the tile
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
@@ -141,6 +151,7 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__r
     __syncthreads();
     // thread -> row r of the tile, columns 8 cg .. 8 cg + 7
     const int r = tid / 4, cg = tid % 4, row = m0 + r;
+    if (r >= SK_BM) return;            // (whole waves; no barrier follows)
     float v8[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -227,19 +238,28 @@ bool skinny_ok(int M, int N, int K, int head_dim) {
     return M > 0 && M <= 512 && N % SK_BN == 0 && K % (SK_BK * SK_WAVES) == 0 && head_dim == 128;
 }
 
-void skinny_init() {   // once per process: the kernels use more dynamic LDS than the default limit
-    (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<bf16_t, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SK_SMEM);
-    (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<bf16_t, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SK_SMEM);
-    (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<f16_t, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SK_SMEM);
-    (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<f16_t, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SK_SMEM);
+template <typename T, int BM> static void skinny_init_t() {
+    (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<T, 0, BM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SkinnyTile<BM>::SMEM);
+    (void)hipFuncSetAttribute((const void *)gemm_skinny_kernel<T, 1, BM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SkinnyTile<BM>::SMEM);
+}
+void skinny_init() {   // once per device: the kernels use more dynamic LDS than the default limit
+    skinny_init_t<bf16_t, 64>(); skinny_init_t<bf16_t, 32>(); skinny_init_t<bf16_t, 16>();
+    skinny_init_t<f16_t, 64>(); skinny_init_t<f16_t, 32>(); skinny_init_t<f16_t, 16>();
 }
 
+template <typename T, int MODE, int BM>
+static void skinny_launch_bm(const void *A, const void *W, int M, int N, int K, const SkinnyQkv &qa, const SkinnyO &oa,
+                             uint32_t *sat, hipStream_t s) {
+    const int mb = (M + BM - 1) / BM, nb = N / SK_BN;
+    const unsigned grid = (unsigned)((nb + 7) / 8 * 8 * mb);
+    gemm_skinny_kernel<T, MODE, BM><<<grid, 64 * SK_WAVES, SkinnyTile<BM>::SMEM, s>>>((const T *)A, (const T *)W, M, N, K, mb, nb, qa, oa, sat);
+}
 template <typename T, int MODE>
 static void skinny_launch(const void *A, const void *W, int M, int N, int K, const SkinnyQkv &qa, const SkinnyO &oa,
                           uint32_t *sat, hipStream_t s) {
-    const int mb = (M + SK_BM - 1) / SK_BM, nb = N / SK_BN;
-    const unsigned grid = (unsigned)((nb + 7) / 8 * 8 * mb);
-    gemm_skinny_kernel<T, MODE><<<grid, 64 * SK_WAVES, SK_SMEM, s>>>((const T *)A, (const T *)W, M, N, K, mb, nb, qa, oa, sat);
+    if (M <= 16) skinny_launch_bm<T, MODE, 16>(A, W, M, N, K, qa, oa, sat, s);
+    else if (M <= 32) skinny_launch_bm<T, MODE, 32>(A, W, M, N, K, qa, oa, sat, s);
+    else skinny_launch_bm<T, MODE, 64>(A, W, M, N, K, qa, oa, sat, s);
 }
 
 void launch_skinny_qkv(int dtype, const void *A, const void *W, int M, int K, const int32_t *row_slot,

@@ -206,7 +206,7 @@ void launch_embed(int dtype, const void *table, const int32_t *tokens, int rows,
 void launch_rmsnorm(int dtype, float *h, const int32_t *src_row, const float *gain, int rows, int d, float eps,
                     void *out, const float *slices, int S, uint32_t *sat, hipStream_t s);
 // C = A[M,K] * W[N,K]^T with the given epilogue.  impl 0: plain ALU, 1: matrix cores (bf16 only)
-void gemm_init();   // once per process: raises the dynamic-LDS limit of the matrix-core kernels
+void gemm_init();   // once per device: raises the dynamic-LDS limit of the matrix-core kernels
 // Returns the number of K slices S the product was cut into.  S == 1: C holds the finished result.
 // S > 1 (only when `slices` is given, for EPI_STORE_F32 / EPI_RESID_F32 at decode sizes): C is untouched
 // and `slices` holds S fp32 partial products [S][M][N]; the consumer adds them in slice order (and, for
@@ -227,7 +227,7 @@ bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, i
                      hipStream_t s);
 // Fused decode projections (gemm_skinny.hip); skinny_ok says whether the shape is one they take.
 bool skinny_ok(int M, int N, int K, int head_dim);
-void skinny_init();   // once per process, like gemm_init
+void skinny_init();   // once per device, like gemm_init
 void launch_skinny_qkv(int dtype, const void *A, const void *W, int M, int K, const int32_t *row_slot,
                        const int32_t *slot_len, const float *rope_cos, const float *rope_sin, int hq, KvGeom kv, int layer,
                        void *q_out, uint32_t *sat, hipStream_t s);
