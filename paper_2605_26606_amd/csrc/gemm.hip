@@ -804,7 +804,7 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
 };
 
 // The tile configurations.  All on 16x16x32 products (0 to 13 % faster than 32x32x16 at every decode shape measured) except
-// the four whose wave tiles are a few 32x32 products only.
+// two whose wave tiles are a few 32x32 products only.
 template <typename T> struct Gemm {
     // 256 x 128, 8 waves of 64 x 64: decode batches of 193 to 256 rows, prefill of narrow outputs
     typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> T256x128;
@@ -819,15 +819,13 @@ template <typename T> struct Gemm {
     typedef MfmaCfg<T, 64, 192, 4, 2, 4, 64, true> T64x192;
     typedef MfmaCfg<T, 32, 64, 1, 4, 4, 64, true> T32x64;       // 48 KB of LDS: three blocks per CU
     typedef MfmaCfg<T, 32, 64, 1, 2, 4, 64, true> T32x64_2;     // the same with whole gate/up chunks per wave
-    typedef MfmaCfg<T, 128, 128, 2, 2, 2> M128x128_2;           // 64 KB of LDS: two blocks per CU
     typedef MfmaCfg<T, 128, 128, 2, 2, 3, 32> M128x128_3;       // BK 32, 48 KB: three blocks per CU
-    typedef MfmaCfg<T, 128, 64, 2, 2, 4> M128x64;               // wave tile 64 x 32: long-K projections cut into K slices
-    typedef MfmaCfg<T, 256, 64, 4, 2, 3> M256x64;               // the same for more than 256 rows
+    typedef MfmaCfg<T, 128, 64, 4, 2, 4, 64, true> T128x64;     // 8 waves of 32 x 32: long-K projections cut into K slices
     typedef MfmaCfg<T, 64, 64, 2, 2, 4> M64x64;                 // wave tile 32 x 32: many blocks for the small projections
     static void init() {
         T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
         T128x128_2::init(); T128x192::init(); T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init();
-        M128x128_2::init(); M128x128_3::init(); M128x64::init(); M256x64::init(); M64x64::init();
+        M128x128_3::init(); T128x64::init(); M64x64::init();
         T256x256::init_logprob();
         T256x128::init_logprob();
         T192x128::init_logprob();
@@ -996,15 +994,18 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         // 60 / 116 / 168 / 256 rows)
         const bool second_round = nb128 > 256 && nb192 <= 256;
         if (M <= 32 && !second_round) return swiglu ? whole(typename G::T32x64_2()) : whole(typename G::T32x64());
-        if (M <= 64) return second_round ? whole(typename G::T64x192()) : whole(typename G::T64x128());
+        // (a 64-row tile buys the vocabulary projection 5 %, gate/up nothing: at 60 rows 22.7 us for 21.7 with the norm scale)
+        if (M <= 64 && (second_round || !swiglu)) return second_round ? whole(typename G::T64x192()) : whole(typename G::T64x128());
         if (M <= 128) return second_round ? whole(typename G::T128x192()) : whole(typename G::T128x128());
         if (M <= 192) return second_round ? whole(typename G::T192x192()) : whole(typename G::T192x128());
         if (M <= 256) return second_round ? whole(typename G::T256x192()) : whole(typename G::T256x128());   // a weight tile is fetched by exactly one block
+        // two 192-row blocks instead of two of 256 (380 rows: 24576 x 4096 70 us against 119 us, 17920 x 1536 27 us against 33
+        // us with three 128-row blocks)
+        if (M <= 384) return whole(typename G::T192x192());
         // (the vocabulary projection: several rounds of blocks per CU at any tile size, the big tile wins --
         // 240 us against 311 us at 400 rows of the 1.5B shape)
         if (deep || (nb128 >= 512 && !swiglu)) return whole(typename G::T256x128());
-        if (M > 384) return whole(typename G::M128x128_3());   // four 128-row blocks, three per CU at a time
-        return whole(typename G::M128x128_2());                // three 128-row blocks, not two of 256
+        return whole(typename G::M128x128_3());   // four 128-row blocks, three per CU at a time
     }
     // The smallest batches stream the weights and little else: rows loaded for nothing (a tile of 128 for 3) cost as much of
     // the load path as the weights (4096 x 12288 at 3 rows: 20 us against 27 us, 1536 x 8960: 6.6 against 9.5 us)
@@ -1017,12 +1018,13 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         if (M <= 64) return sliced(typename G::T64x128(), 240);
         if (M <= 128) return sliced(typename G::T128x128(), 240);
         if (M <= 192) return sliced(typename G::T192x128(), 240);
+        if (M > 256 && M <= 384) return sliced(typename G::T192x192(), 240);   // 8B down at 380 rows: 44 us against 49 us
         return sliced(typename G::T256x128(), 240);
     }
     if ((int64_t)N * K >= (int64_t)8 << 20) {   // narrow output, long K (the 1.5B model's down projection)
         if (M <= 64) return sliced(typename G::M64x64(), 240);   // 8.2 us against 10.4 us with 128-row tiles at 60 rows
-        if (M <= 256) return sliced(typename G::M128x64(), 240);
-        return sliced(typename G::M256x64(), 240);
+        // (4 waves of 64x32 took 19.7 us for 17.0 at 256 rows and 11.6 for 10.7 at 116; 256-row tiles 21.2 for 19.9 at 380)
+        return sliced(typename G::T128x64(), 240);
     }
     return sliced(typename G::M64x64(), 192);
 }

@@ -182,7 +182,7 @@ static int bench_gemm() {
     CK(hipDeviceSynchronize());
     int rc = 0;
     rc |= run_gemm<Gemm<T>::T256x128>("decode gate/up (SwiGLU)", 256, 17920, 1536, EPI_SWIGLU, 1, Ws, A, C, slices);
-    rc |= run_gemm<Gemm<T>::M128x64>("decode down", 256, 1536, 8960, EPI_STORE_F32, 5, Ws, A, C, slices);
+    rc |= run_gemm<Gemm<T>::T128x64>("decode down", 256, 1536, 8960, EPI_STORE_F32, 5, Ws, A, C, slices);
     rc |= run_gemm<Gemm<T>::M64x64>("decode o-proj", 256, 1536, 1536, EPI_STORE_F32, 2, Ws, A, C, slices);
     rc |= run_gemm<Gemm<T>::M64x64>("decode qkv", 256, 2048, 1536, EPI_STORE_F32, 2, Ws, A, C, slices);
     rc |= run_gemm<Gemm<T>::T256x256>("prefill gate/up (SwiGLU)", 16384, 17920, 1536, EPI_SWIGLU, 1, Ws, A, C, slices);

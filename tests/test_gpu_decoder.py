@@ -215,7 +215,7 @@ def test_bf16_plain_alu_path():
     (BF, [40] * 64 + [7], 4, 6, 64, 0.02, "f16"),         # 260 sequences: one split per sequence, direct output
     (BF8, [100, 31], 3, 10, 64, 0.02, "f16"),             # split-K in the large-tile GEMM
     (BF8, [100, 31], 3, 10, 64, 0.02, "bf16"),
-    (BF8, [12] * 75, 4, 5, 64, 0.02, "f16"),              # 300 decode rows: 128-row GEMM blocks in threes, tall K slices
+    (BF8, [12] * 75, 4, 5, 64, 0.02, "f16"),              # 300 decode rows: two 192-row GEMM blocks, tall K slices
     (BF8, [12] * 105, 4, 4, 64, 0.02, "f16"),             # 420 decode rows: four 128-row blocks, BK 32
     (BF8, [12] * 130, 4, 3, 64, 0.02, "f16"),             # 520 decode rows: the large-batch tiles, narrow outputs in K slices
     (BF, [70, 33, 300, 5, 256], 3, 10, 128, 0.02, "f16"), # larger KV blocks
@@ -254,9 +254,10 @@ WIDE2 = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=
 @pytest.mark.parametrize("model,P,G,act", [(WIDE1, 3, 1, "f16"), (WIDE1, 11, 3, "f16"), (WIDE1, 13, 5, "f16"),
                                            (WIDE1, 43, 3, "f16"), (WIDE1, 49, 4, "f16"), (WIDE1, 64, 4, "bf16"),
                                            (WIDE2, 1, 1, "f16"), (WIDE2, 8, 4, "f16"), (WIDE2, 16, 4, "bf16"),
-                                           (WIDE2, 32, 4, "f16"), (WIDE2, 64, 3, "f16"), (WIDE2, 65, 3, "f16")])
+                                           (WIDE2, 32, 4, "f16"), (WIDE2, 64, 3, "f16"), (WIDE2, 65, 3, "f16"),
+                                           (WIDE1, 65, 4, "f16"), (WIDE2, 77, 5, "bf16")])
 def test_wide_tiles_by_row_count(model, P, G, act):
-    # decode batches of 3, 33, 65, 129, 196, 256 and of 1, 32, 64, 128, 192, 195 rows: each side of the tiles' heights
+    # decode batches of 3, 33, 65, 129, 196, 256, 260 and of 1, 32, 64, 128, 192, 195, 385 rows: each side of the tiles' heights
     say("wide tiles, d_ff %d, %d rows" % (model.d_ff, P * G))
     w = workloads.perturb_norm_gains(workloads.make_weights(model, 3), 10)
     rng = np.random.default_rng(P)
