@@ -9,7 +9,7 @@
 //                                                                 (one launch instead of GEMM + RMSNorm)
 //
 // C[M,N] = A[M,K] W[N,K]^T with N of a few thousand and K of a few thousand: 5-40 MB of weights, a handful of
-// microseconds.  A block owns a 64 x 32 output tile over the WHOLE of K, so no partial sums ever leave the
+// microseconds.  A block owns a tile of 64, 32 or 16 rows x 32 columns over the WHOLE of K, so no partial sums ever leave the
 // block; its four waves each take a quarter of K and add up through LDS at the end.  Every wave runs its own
 // pipeline without any block barrier: 64-deep K steps of its quarter go global memory -> LDS directly
 // (global_load_lds, 16 bytes per lane, whole 128-byte rows per eight lanes: fragment loads straight from
