@@ -288,8 +288,7 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
     const int sel = sb.sel;
     const double above = sb.above, want = (double)top_p * Z0;
     const double scale = unit * exp((double)top - (double)sel / (double)NUC_PER_UNIT - (double)M);
-    const int n_list = (int)(sb.bin[sel] >> NUC_COUNT_SHIFT);
-    if (n_list > NUC_LIST) return false;
+    if ((int)(sb.bin[sel] >> NUC_COUNT_SHIFT) > NUC_LIST) return false;
     // ---- pass 2: this wave's segment: sum of the tokens above the crossing bin, the bin's own tokens into the list
     double s = 0.0;
     uint32_t lo = 0xffffffffu, hi = 0u;
@@ -340,6 +339,11 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
         sb.wave_hi[wave] = hi;
     }
     // ---- the list's cut: the same again over 4096 parts of its key range
+    // (Waves without tokens of their own come here at once: behind the barrier every wave has read the first bins and filed
+    // its tokens, so the bins may be cleared and the list is as long as its own counter says, whatever the first pass counted.)
+    __syncthreads();
+    const int n_list = sb.n;
+    if (n_list > NUC_LIST || n_list == 0) return false;
 #pragma unroll
     for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
     __syncthreads();
