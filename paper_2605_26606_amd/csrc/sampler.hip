@@ -222,10 +222,12 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
             for (int c = 0; c < VEC; ++c) v[c] = (idx + c) < end ? x[idx + c] : -INFINITY;
         }
     };
-    // ---- the top edge of the bins: 32 above the largest of 1024 tokens
+    // ---- the top edge of the bins: 32 above the largest of 1024 tokens, the EOS id with its bias (a bias may have pushed the
+    // row's largest logit below all others)
     {
-        const float v = x[(int)((int64_t)tid * vocab / BLOCK)] * inv_t;
-        const float wm = wave_max_f32(v);
+        const int idx = (int)((int64_t)tid * vocab / BLOCK);
+        const float raw = x[idx];
+        const float wm = wave_max_f32((idx == eos_id ? raw + eos_key_add : raw) * inv_t);
         if (lane == 0) sb.wave_max[wave] = wm;
     }
 #pragma unroll
@@ -279,7 +281,9 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < SAMPLE_WAVES; ++w) M = fmaxf(M, sb.wave_max[w]);
-    if (!(fabsf(M) < 1e5f)) return false;
+    // (the largest sampled token is at least 33 below the edge, so M is: below 34 the edge does not fit the row and the bins
+    // may have cut off tokens that count)
+    if (!(fabsf(M) < 1e5f && M >= top - 34.0f)) return false;
     const double unit = 1.0 / 33554432.0;
     double Z0, part_mass;
     nucleus_cross(sb, 0.0, (double)top_p, -1.0, [&](int b) {

@@ -248,6 +248,27 @@ def test_top_p_forms(V, form):
     assert same >= math.floor(0.98 * tot)
 
 
+@pytest.mark.parametrize("V", [512, 5000])
+@pytest.mark.parametrize("gap", [40.0, 94.0, 96.0, 97.0, 110.0, 280.0])
+def test_top_p_with_the_largest_logit_suppressed(V, gap):
+    # the EOS id is far above every other token and its bias takes it far below them: nucleus and log-probabilities are
+    # those of the others.  A token may differ where the mass lands within rounding of top_p Z or of u Z (1e-6 relative).
+    rng = np.random.default_rng(V + int(gap))
+    n, T, eos = 16, 1.0, V // 2          # (an id that the sampled tokens include, at both sizes)
+    logits = (2.0 * rng.standard_normal((n, V))).astype(np.float32)
+    logits[:, eos] = logits.max(axis=1) + np.float32(gap)
+    uids = np.arange(n, dtype=np.int64) + 31
+    for bias in (-300.0, -np.inf):
+        tok, lp = _run_top_p(logits, T, 0.97, 8, uids, 4, eos, bias)
+        same = 0
+        for i in range(n):
+            want, wlp = sampler.sample_token(logits[i], T, philox.sampling_uniform(8, int(uids[i]), 4), eos, bias, top_p=0.97)
+            if tok[i] == want:
+                same += 1
+                assert abs(lp[i] - wlp) <= 3e-5 * max(1.0, abs(wlp))
+        assert same >= n - 1
+
+
 @pytest.mark.parametrize("top_p", [1.0, 0.9])
 @pytest.mark.parametrize("fill", [-np.inf, np.nan])
 def test_rows_without_weight(fill, top_p):
