@@ -10,20 +10,21 @@
 //
 // Nucleus truncation (top_p < 1): the tokens in order of decreasing probability (ties: lower id first) until their
 // cumulative mass reaches top_p keep their weight, the rest get none; the passes above then run on the kept tokens.
-// Two ways to the cut:
-//   binned (nucleus_binned): one pass over the row files every token in one of 4096 bins of 1/32 of a scaled logit, with
-//     its count and its mass relative to the bin's upper edge as a 25-bit fraction in ONE 64-bit LDS integer add (exact in
-//     any order), so neither the maximum nor Z is needed beforehand; the bin in which the mass from the top crosses
-//     top_p Z is known then, a second pass sums the tokens above it per wave segment (the sums the sampler needs anyway)
-//     and lists the bin's own tokens in LDS, and the exact cut is found in that list.  The row is read twice.
+// The first pass of the scheme above gives the maximum and Z of the whole row; there are two ways from there to the cut:
+//   binned (nucleus_binned): one pass over the row files the tokens that can matter in bins of 1/32 of a scaled logit, with
+//     a count and a sum of 25-bit fractions in ONE 64-bit LDS integer add; the bin in which the mass from the top crosses
+//     top_p Z is known then.  A second pass sums the float weights in front of that bin and lists the bin's own tokens in
+//     LDS, where the exact cut is found.  The row is read twice.
 //   radix (any row): a select over an order-preserving 32-bit key of the logit, four passes of 8 bits with a histogram of
-//     the mass per bucket (double, one histogram per wave, added up in wave order), between two summing passes.  The row
-//     is read six times and the few buckets in use make the LDS adds collide.  Taken when the binned way cannot be:
-//     a maximum more than 32 above that of 1024 sampled tokens, more than 5120 tokens in the crossing bin, or more than
-//     256 of them in one of its 4096 parts (logits almost all alike), scaled logits beyond 1e5.
-//   1024 rows of 151936 logits: 1470 us by the radix way, 271 us binned (read once at the copy rate: 121 us).
-#include <type_traits>
-
+//     the mass per bucket (double, one histogram per wave, added up in wave order).  The row is read four times and the few
+//     buckets in use make the LDS adds collide.  Taken when the binned way cannot be: more than 5120 tokens in the
+//     crossing bin (logits almost all alike), scaled logits beyond 1e5.
+//   Both decide on the same float weights and the same Z, so they keep the same tokens.
+// The kept tokens then go through the first pass again: tokens and log-probabilities are those of plain sampling with all
+// other tokens masked, to the last bit.
+//   1024 rows of 151936 logits, T = 0.7, top_p = 0.95: 1509 us by the radix way, 615 us binned (a read of the rows at the
+//   copy rate: 121 us).  Rows that fall back have paid for a first pass over their bins, which the collisions in the radix
+//   buckets hide: all logits within 0.06 of each other 1549 us without it and 1496 with it, all alike 6034 and 6038.
 #include "pc_internal.h"
 
 namespace pc {
@@ -109,8 +110,7 @@ __device__ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 static constexpr int NUC_BINS = 4096;          // four per thread
 static constexpr float NUC_PER_UNIT = 32.0f;   // bins per unit of scaled logit
 static constexpr int NUC_LIST = 5120;          // tokens of the crossing bin that fit the list (72 KB in all: two blocks per CU)
-static constexpr int NUC_TIES = 256;           // tokens of one part of it that are ranked one against the other
-static constexpr int NUC_COUNT_SHIFT = 44;     // a bin: count above, sum of 25-bit fractions below (2^18 tokens fit either)
+static constexpr int NUC_COUNT_SHIFT = 44;     // a bin: count above, sum of weights as integers below (2^18 tokens fit either)
 
 struct NucleusBins {
     union {
@@ -127,32 +127,22 @@ struct NucleusBins {
         } radix;
     };
     double wave_sum[SAMPLE_WAVES];
-    float wave_max[SAMPLE_WAVES];
     uint32_t wave_lo[SAMPLE_WAVES], wave_hi[SAMPLE_WAVES];
     double above;
-    int sel, last, n, bad;
-    uint32_t tie_key[NUC_TIES], tie_part[NUC_TIES];
-    int32_t tie_id[NUC_TIES];
-    uint32_t kstar;
-    int tie_limit;
+    int sel, n;
 };
 
 // From the bins (each thread owns four, in order of falling logit): the first one at which above + the running mass reaches
-// `want`, and the mass in front of it.  scale(bin) turns a bin's fraction sum into mass.  Leaves sb.sel (the last bin in
-// use if rounding leaves the total short) and sb.above; every thread must call it.  `total` (out): the mass of all bins.
+// `want` (NUC_BINS if none does) into sb.sel, and the mass in front of it into sb.above.  scale(bin) turns a bin's integer sum
+// into mass.  Every thread must call it; the bins are read before its first barrier only.
 template <typename Scale>
-__device__ inline void nucleus_cross(NucleusBins &sb, double above, double top_p, double want, Scale scale, double &total) {
+__device__ inline void nucleus_cross(NucleusBins &sb, double above, double want, Scale scale) {
     const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
     double m[4], own = 0.0;
-    int used = -1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const unsigned long long b = sb.bin[4 * tid + i];
-        m[i] = 0.0;
-        if (b >> NUC_COUNT_SHIFT) {
-            m[i] = (double)(b & ((1ull << NUC_COUNT_SHIFT) - 1)) * scale(4 * tid + i);
-            used = 4 * tid + i;
-        }
+        m[i] = (b >> NUC_COUNT_SHIFT) ? (double)(b & ((1ull << NUC_COUNT_SHIFT) - 1)) * scale(4 * tid + i) : 0.0;
         own += m[i];
     }
     double incl = own;
@@ -161,23 +151,14 @@ __device__ inline void nucleus_cross(NucleusBins &sb, double above, double top_p
         const double t = __shfl_up(incl, o, WAVE);
         if (lane >= o) incl += t;
     }
-    if (tid == 0) {
-        sb.sel = NUC_BINS;
-        sb.last = -1;
-    }
+    if (tid == 0) sb.sel = NUC_BINS;
     if (lane == WAVE - 1) sb.wave_sum[wave] = incl;
     __syncthreads();
-    double before = above, all = 0.0;
-#pragma unroll
-    for (int w = 0; w < SAMPLE_WAVES; ++w) {
-        if (w < wave) before += sb.wave_sum[w];
-        all += sb.wave_sum[w];
-    }
-    total = all;
-    if (want < 0.0) want = top_p * all;
-    before += incl - own;
+    double run = above;
+    for (int w = 0; w < wave; ++w) run += sb.wave_sum[w];
+    run += incl - own;
     int mine = -1;
-    double run = before, at = 0.0;
+    double at = 0.0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (mine < 0 && m[i] > 0.0 && run + m[i] >= want) {
@@ -187,149 +168,108 @@ __device__ inline void nucleus_cross(NucleusBins &sb, double above, double top_p
         run += m[i];
     }
     if (mine >= 0) atomicMin(&sb.sel, mine);
-    if (used >= 0) atomicMax(&sb.last, used);
     __syncthreads();
-    if (sb.sel == NUC_BINS) {                  // (block-uniform)
-        if (used >= 0 && used == sb.last) {
-            double r = before;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (4 * tid + i < used) r += m[i];
-            sb.above = r;
-        }
-        __syncthreads();
-        if (tid == 0) sb.sel = sb.last;
-    } else if (mine == sb.sel) {
-        sb.above = at;
-    }
+    if (mine >= 0 && mine == sb.sel) sb.above = at;
     __syncthreads();
 }
 
+// How many of the c tied tokens at the cut it takes, whose masses sum to `comb` and in front of which lies `run`; -1: all.
+__device__ inline int ties_to_keep(double want, double run, double comb, int c) {
+    const double wt = comb / (double)c;
+    int r = (int)ceil((want - run) / wt);
+    r = max(1, min(r, c));
+    while (r > 1 && run + (double)(r - 1) * wt >= want) --r;
+    while (r < c && run + (double)r * wt < want) ++r;
+    return r >= c ? -1 : r;
+}
+
+// The cut at mass `want` = top_p Z of a row with maximum M and sum Z: kstar and the number of its ties to keep (-1: all).
+// False: not found this way, nothing is left behind (the caller's arithmetic decides either way, see the end of pass 2).
 template <int VEC>
-__device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, int seg, float inv_t, float top_p, int eos_id,
-                                      float eos_bias, float eos_key_add, NucleusBins &sb, float *s_wm, double *s_ws,
-                                      Nucleus &nu) {
-    constexpr int STRIDE = WAVE * VEC, BLOCK = SAMPLE_WAVES * WAVE;
-    constexpr float LOG2E = 1.4426950408889634f;
+__device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, float inv_t, float top_p, int eos_id,
+                                      float eos_bias, float eos_key_add, float M, double Z, double want, NucleusBins &sb,
+                                      uint32_t &kstar, int &keep_ties) {
+    constexpr int BLOCK = SAMPLE_WAVES * WAVE, STEP = BLOCK * VEC;
     const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    if (vocab > (1 << 18)) return false;
-    auto raw_load = [&](int idx, int end, float (&v)[VEC]) {
-        if (VEC == 4 && idx + 3 < end) {
+    // (beyond these sizes the bins' edges are no longer exact, or an EOS logit and its bias may cancel)
+    if (vocab > (1 << 18) || !(fabsf(M) < 1e5f) || !(Z >= 0.5 && Z < 1e9)) return false;
+    if (eos_id >= 0 && !(fabsf(eos_bias) < 1e5f) && eos_bias != -INFINITY) return false;
+    auto raw_load = [&](int idx, float (&v)[VEC]) {
+        if (VEC == 4 && idx + 3 < vocab) {
             const float4 t = *(const float4 *)(x + idx);
             v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
         } else {
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) v[c] = (idx + c) < end ? x[idx + c] : -INFINITY;
+            for (int c = 0; c < VEC; ++c) v[c] = (idx + c) < vocab ? x[idx + c] : -INFINITY;
         }
     };
-    // ---- the top edge of the bins: 32 above the largest of 1024 tokens, the EOS id with its bias (a bias may have pushed the
-    // row's largest logit below all others)
-    {
-        const int idx = (int)((int64_t)tid * vocab / BLOCK);
-        const float raw = x[idx];
-        const float wm = wave_max_f32((idx == eos_id ? raw + eos_key_add : raw) * inv_t);
-        if (lane == 0) sb.wave_max[wave] = wm;
-    }
+    auto scaled = [&](float raw, int idx) {   // as load_scaled forms it
+        float v = raw * inv_t;
+        if (idx == eos_id) v += eos_bias;
+        return v;
+    };
+    // place of a logit: (top - scaled logit) * 32, one explicit fma so that both passes round alike; the EOS id's bias counts
+    // like in its key, so tokens with the same key have the same place.  The edge lies 1 to 2 above the maximum: whatever the
+    // rounding of its scaled value, no place is negative
+    const float top = ceilf(M) + 1.0f, place_a = -NUC_PER_UNIT * inv_t, place_b = NUC_PER_UNIT * top;
+    auto place = [&](float raw, int idx) { return fmaf(idx == eos_id ? raw + eos_key_add : raw, place_a, place_b); };
+    // Tokens of a weight below half of (1 - top_p) Z / vocab lie behind the cut, all of them together: they need no bin.
+    const float reach = (float)(NUC_PER_UNIT * ((double)top - (double)M - log(0.5 * (1.0 - (double)top_p) * Z / vocab))) + 1.0f;
+    const float end = fminf(reach, (float)(NUC_BINS - 1));
+    const double edge0 = (double)top - (double)M;
 #pragma unroll
     for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
-    if (tid == 0) sb.bad = sb.n = 0;
+    if (tid == 0) sb.n = 0;
     __syncthreads();
-    float top = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < SAMPLE_WAVES; ++w) top = fmaxf(top, sb.wave_max[w]);
-    if (!(fabsf(top) < 1e5f)) return false;
-    top = ceilf(top) + 32.0f;                  // every bin edge is then a multiple of 1/32 that fp32 holds exactly
-    __syncthreads();                           // (wave_max is written again below)
-    // place of a logit: (top - scaled logit) * 32; the EOS id's bias counts like in its key
-    auto place = [&](float raw, int idx) { return (top - (idx == eos_id ? raw + eos_key_add : raw) * inv_t) * NUC_PER_UNIT; };
-    auto scaled = [&](float raw, int idx) { return raw * inv_t + (idx == eos_id ? eos_bias : 0.f); };
-    auto fraction = [&](float v, int bin) {    // weight relative to the bin's upper edge, 25 bits
-        const float edge = top - (float)bin * (1.0f / NUC_PER_UNIT);
-        return (unsigned int)(__builtin_amdgcn_exp2f((v - edge) * LOG2E) * 33554432.0f + 0.5f);
-    };
-    // ---- pass 1: bins and maximum
-    float m = -INFINITY;
-    bool bad = false;
+    // ---- pass 1: count and weight per bin, weights relative to the bin's upper edge in 25 bits: which bin the cut is in
     {
         float cur[VEC], nxt[VEC];
-        raw_load(tid * VEC, vocab, nxt);
-        for (int base = tid * VEC; base < vocab; base += BLOCK * VEC) {
+        raw_load(tid * VEC, nxt);
+        for (int base = tid * VEC; base < vocab; base += STEP) {
 #pragma unroll
             for (int c = 0; c < VEC; ++c) cur[c] = nxt[c];
-            if (base + BLOCK * VEC < vocab) raw_load(base + BLOCK * VEC, vocab, nxt);
+            if (base + STEP < vocab) raw_load(base + STEP, nxt);
 #pragma unroll
             for (int c = 0; c < VEC; ++c) {
                 const float p = place(cur[c], base + c);
-                if (p < (float)(NUC_BINS - 1)) {   // (96 below the top token's neighbourhood: no mass a double would notice)
-                    const float v = scaled(cur[c], base + c);
-                    m = fmaxf(m, v);
-                    if (p < 0.f) {
-                        bad = true;
-                    } else {
-                        const int b = (int)p;
-                        atomicAdd(&sb.bin[b], (1ull << NUC_COUNT_SHIFT) + fraction(v, b));
-                    }
+                if (p < end) {
+                    const int b = max((int)p, 0);
+                    const float rel = __builtin_amdgcn_exp2f(((float)b - p) * (1.4426950408889634f / NUC_PER_UNIT));
+                    atomicAdd(&sb.bin[b], (1ull << NUC_COUNT_SHIFT) + (unsigned int)(rel * 33554432.0f + 0.5f));
                 }
             }
         }
     }
-    const float wm = wave_max_f32(m);
-    if (lane == 0) sb.wave_max[wave] = wm;
-    if (bad) sb.bad = 1;
     __syncthreads();
-    if (sb.bad) return false;
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < SAMPLE_WAVES; ++w) M = fmaxf(M, sb.wave_max[w]);
-    // (the largest sampled token is at least 33 below the edge, so M is: below 34 the edge does not fit the row and the bins
-    // may have cut off tokens that count)
-    if (!(fabsf(M) < 1e5f && M >= top - 34.0f)) return false;
-    const double unit = 1.0 / 33554432.0;
-    double Z0, part_mass;
-    nucleus_cross(sb, 0.0, (double)top_p, -1.0, [&](int b) {
-        return unit * exp((double)top - (double)b / (double)NUC_PER_UNIT - (double)M);
-    }, Z0);
+    nucleus_cross(sb, 0.0, want, [&](int b) { return (1.0 / 33554432.0) * exp(edge0 - (double)b / (double)NUC_PER_UNIT); });
     const int sel = sb.sel;
-    const double above = sb.above, want = (double)top_p * Z0;
-    const double scale = unit * exp((double)top - (double)sel / (double)NUC_PER_UNIT - (double)M);
-    if ((int)(sb.bin[sel] >> NUC_COUNT_SHIFT) > NUC_LIST) return false;
-    // ---- pass 2: this wave's segment: sum of the tokens above the crossing bin, the bin's own tokens into the list
+    if (sel == NUC_BINS || (int)(sb.bin[sel] >> NUC_COUNT_SHIFT) > NUC_LIST) return false;
+    // ---- pass 2: the mass in front of that bin, its tokens into the list
     double s = 0.0;
     uint32_t lo = 0xffffffffu, hi = 0u;
     {
-        const int b = min(vocab, wave * seg), e = min(vocab, b + seg);
-        constexpr int AHEAD = 2;
-        float cur[AHEAD][VEC], nxt[AHEAD][VEC];
+        float raw[VEC], nxt[VEC];
+        raw_load(tid * VEC, nxt);
+        for (int base = tid * VEC; base < vocab; base += STEP) {
 #pragma unroll
-        for (int u = 0; u < AHEAD; ++u) raw_load(b + u * STRIDE + lane * VEC, e, nxt[u]);
-        for (int base = b; base < e; base += AHEAD * STRIDE) {
+            for (int c = 0; c < VEC; ++c) raw[c] = nxt[c];
+            if (base + STEP < vocab) raw_load(base + STEP, nxt);
 #pragma unroll
-            for (int u = 0; u < AHEAD; ++u)
-#pragma unroll
-                for (int c = 0; c < VEC; ++c) cur[u][c] = nxt[u][c];
-            if (base + AHEAD * STRIDE < e) {
-#pragma unroll
-                for (int u = 0; u < AHEAD; ++u) raw_load(base + (AHEAD + u) * STRIDE + lane * VEC, e, nxt[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < AHEAD; ++u)
-#pragma unroll
-                for (int c = 0; c < VEC; ++c) {
-                    const int idx = base + u * STRIDE + lane * VEC + c;
-                    const float p = place(cur[u][c], idx);
-                    if (p < (float)sel) {
-                        s += (double)expf(scaled(cur[u][c], idx) - M);
-                    } else if (p < (float)(sel + 1)) {
-                        const int at = atomicAdd(&sb.n, 1);
-                        const uint32_t key = logit_key(cur[u][c], idx, eos_id, eos_key_add);
-                        if (at < NUC_LIST) {
-                            sb.key[at] = key;
-                            sb.id[at] = idx;
-                        }
-                        lo = min(lo, key);
-                        hi = max(hi, key);
+            for (int c = 0; c < VEC; ++c) {
+                const float p = place(raw[c], base + c);
+                if (p < (float)sel) {
+                    s += (double)expf(scaled(raw[c], base + c) - M);
+                } else if (p < (float)(sel + 1)) {
+                    const int at = atomicAdd(&sb.n, 1);
+                    const uint32_t key = logit_key(raw[c], base + c, eos_id, eos_key_add);
+                    if (at < NUC_LIST) {
+                        sb.key[at] = key;
+                        sb.id[at] = base + c;
                     }
+                    lo = min(lo, key);
+                    hi = max(hi, key);
                 }
+            }
         }
     }
 #pragma unroll
@@ -341,81 +281,55 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
     if (lane == 0) {
         sb.wave_lo[wave] = lo;
         sb.wave_hi[wave] = hi;
+        sb.wave_sum[wave] = s;
     }
-    // ---- the list's cut: the same again over 4096 parts of its key range
-    // (Waves without tokens of their own come here at once: behind the barrier every wave has read the first bins and filed
-    // its tokens, so the bins may be cleared and the list is as long as its own counter says, whatever the first pass counted.)
+    // Behind this barrier every wave has read the first bins and filed its tokens.
     __syncthreads();
     const int n_list = sb.n;
     if (n_list > NUC_LIST || n_list == 0) return false;
-#pragma unroll
-    for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
-    __syncthreads();
+    double above = 0.0;
     lo = 0xffffffffu;
     hi = 0u;
-#pragma unroll
+#pragma unroll 4
     for (int w = 0; w < SAMPLE_WAVES; ++w) {
         lo = min(lo, sb.wave_lo[w]);
         hi = max(hi, sb.wave_hi[w]);
+        above += sb.wave_sum[w];
     }
-    const int shift = max(0, 32 - 12 - (hi > lo ? __clz((int)(hi - lo)) : 32));
-    auto part_of = [&](uint32_t key) { return NUC_BINS - 1 - (int)((key - lo) >> shift); };
-    for (int e = tid; e < n_list; e += BLOCK)
-        atomicAdd(&sb.bin[part_of(sb.key[e])], (1ull << NUC_COUNT_SHIFT) + fraction(scaled(x[sb.id[e]], sb.id[e]), sel));
-    __syncthreads();
-    nucleus_cross(sb, above, 0.0, want, [&](int) { return scale; }, part_mass);
-    const int part = sb.sel;
-    const double above2 = sb.above;
-    const int n_ties = (int)(sb.bin[part] >> NUC_COUNT_SHIFT);
-    if (n_ties > NUC_TIES) return false;
-    if (tid == 0) sb.n = 0;
-    __syncthreads();
-    for (int e = tid; e < n_list; e += BLOCK)
-        if (part_of(sb.key[e]) == part) {
-            const int at = atomicAdd(&sb.n, 1);
-            if (at < NUC_TIES) {
-                sb.tie_key[at] = sb.key[e];
-                sb.tie_id[at] = sb.id[e];
-                sb.tie_part[at] = fraction(scaled(x[sb.id[e]], sb.id[e]), sel);
-            }
+    // From here on the weights are the ones that every other way to the cut takes, expf(v - M), and their sums are exact: the
+    // list's, all within 3 % of the bin's edge, as integers of at most 2^28.  The cut is the list's if it is reached within it.
+    if (!(above < want)) return false;
+    const float unit = ldexpf(1.0f, 26 - ilogbf(expf(top - (float)sel * (1.0f / NUC_PER_UNIT) - M)));
+    auto weight = [&](uint32_t key, int id) {
+        const float raw = id == eos_id ? x[id] : __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
+        return (unsigned int)(expf(scaled(raw, id) - M) * unit);
+    };
+    // ---- the list's cut: 4096 parts of its key range, then of that part's, until a part is one key
+    for (;;) {
+        const int shift = max(0, 32 - 12 - (hi > lo ? __clz((int)(hi - lo)) : 32));
+#pragma unroll
+        for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
+        __syncthreads();
+        for (int e = tid; e < n_list; e += BLOCK) {
+            const uint32_t key = sb.key[e];
+            if (key >= lo && key <= hi)
+                atomicAdd(&sb.bin[NUC_BINS - 1 - (int)((key - lo) >> shift)], (1ull << NUC_COUNT_SHIFT) + weight(key, sb.id[e]));
         }
-    __syncthreads();
-    if (tid < n_ties) {                        // rank by falling key, rising id; the cut is the first that reaches `want`
-        const uint32_t key = sb.tie_key[tid];
-        const int id = sb.tie_id[tid];
-        unsigned long long before = 0ull;
-        int rank = 0;
-        for (int j = 0; j < n_ties; ++j)
-            if (sb.tie_key[j] > key || (sb.tie_key[j] == key && sb.tie_id[j] < id)) {
-                before += sb.tie_part[j];
-                ++rank;
-            }
-        const bool reached_before = rank > 0 && above2 + (double)before * scale >= want;
-        const bool reached = above2 + (double)(before + sb.tie_part[tid]) * scale >= want;
-        if (!reached_before && (reached || rank == n_ties - 1)) {
-            sb.kstar = key;
-            sb.tie_limit = id;
+        __syncthreads();
+        nucleus_cross(sb, above, want, [&](int) { return 1.0 / (double)unit; });
+        const int part = sb.sel;
+        if (part == NUC_BINS) return false;
+        above = sb.above;
+        lo += (uint32_t)(NUC_BINS - 1 - part) << shift;
+        if (shift == 0) {
+            const unsigned long long b = sb.bin[part];
+            kstar = lo;
+            keep_ties = ties_to_keep(want, above, (double)(b & ((1ull << NUC_COUNT_SHIFT) - 1)) / (double)unit,
+                                     (int)(b >> NUC_COUNT_SHIFT));
+            return true;
         }
+        hi = min(hi, lo + ((1u << shift) - 1u));
     }
-    __syncthreads();
-    nu.kstar = sb.kstar;
-    nu.tie_limit = sb.tie_limit;
-    nu.on = true;
-    // ---- the list's kept tokens join their segments' sums
-    const int b = wave * seg, e1 = b + seg;
-    double t = 0.0;
-    for (int e = lane; e < n_list; e += WAVE) {
-        const int id = sb.id[e];
-        const uint32_t key = sb.key[e];
-        if (id >= b && id < e1 && (key > nu.kstar || (key == nu.kstar && id <= nu.tie_limit)))
-            t += (double)expf(scaled(x[id], id) - M);
-    }
-    t = wave_sum_d(t);
-    if (lane == 0) {
-        s_wm[wave] = M;
-        s_ws[wave] = s + t;
-    }
-    return true;
 }
 
 // ROOMY: a launch of at most half a block per CU keeps the segment sums in registers (107 rows back to back: 17.7 us, 19.3 us
@@ -479,9 +393,10 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
                     s *= (double)expf(m - lm);   // m = -inf -> 0
                     m = lm;
                 }
+                const float base_m = (m == -INFINITY) ? 0.f : m;   // (so far masked tokens only: no weight)
 #pragma unroll
                 for (int c = 0; c < VEC; ++c)
-                    if (ok[u][c]) s += (double)expf(v[u][c] - m);
+                    if (ok[u][c]) s += (double)expf(v[u][c] - base_m);
             }
         }
         const float wm = wave_max_f32(m);
@@ -491,19 +406,10 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
             s_ws[wave] = ws;
         }
     };
-    bool have_sums = false;
-    __shared__ typename std::conditional<TOPP, NucleusBins, int>::type sb;
+    level1();
     if constexpr (TOPP) {
-        have_sums = nucleus_binned<VEC>(x, vocab, seg, inv_t, top_p, eos_id, eos_bias, eos_key_add, sb, s_wm, s_ws, nu);
-    }
-    if (!have_sums) level1();
-    if constexpr (TOPP) {
-      if (!have_sums) {
+        __shared__ NucleusBins sb;
         // ---- nucleus: the key kstar and the id limit among its ties at which the mass from the top reaches top_p Z
-        auto &s_hist = sb.radix.hist;
-        auto &s_cnt = sb.radix.cnt;
-        auto &s_comb = sb.radix.comb;
-        auto &s_ccnt = sb.radix.ccnt;
         __shared__ uint32_t s_prefix;
         __shared__ double s_above;
         __shared__ int s_keep_ties, s_tie_limit, s_wcount[SAMPLE_WAVES];
@@ -512,9 +418,16 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
 #pragma unroll
         for (int w = 0; w < SAMPLE_WAVES; ++w) M0 = fmaxf(M0, s_wm[w]);
         double Z0 = 0.0;
-#pragma unroll
+#pragma unroll 4
         for (int w = 0; w < SAMPLE_WAVES; ++w) Z0 += (s_wm[w] == -INFINITY) ? 0.0 : s_ws[w] * (double)expf(s_wm[w] - M0);
         const double want = (double)top_p * Z0;
+        int keep_ties;
+        if (!nucleus_binned<VEC>(x, vocab, inv_t, top_p, eos_id, eos_bias, eos_key_add, M0, Z0, want, sb, nu.kstar, keep_ties)) {
+        auto &s_hist = sb.radix.hist;
+        auto &s_cnt = sb.radix.cnt;
+        auto &s_comb = sb.radix.comb;
+        auto &s_ccnt = sb.radix.ccnt;
+        __syncthreads();
         if (tid == 0) {
             s_prefix = 0u;
             s_above = 0.0;
@@ -576,20 +489,15 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
                 s_above = run;
                 s_prefix = (prefix << 8) | (uint32_t)sel;
                 if (pass == 3) {   // ties at the cut: as many as it takes, lowest ids first
-                    const int c = s_ccnt[sel];
-                    const double wt = s_comb[sel] / (double)c;
-                    int r = (int)ceil((want - run) / wt);
-                    r = max(1, min(r, c));
-                    while (r > 1 && run + (double)(r - 1) * wt >= want) --r;
-                    while (r < c && run + (double)r * wt < want) ++r;
-                    s_keep_ties = (r >= c) ? -1 : r;
+                    s_keep_ties = ties_to_keep(want, run, s_comb[sel], s_ccnt[sel]);
                 }
             }
             __syncthreads();
         }
         nu.kstar = s_prefix;
+        keep_ties = s_keep_ties;
+        }
         nu.tie_limit = 0x7fffffff;
-        const int keep_ties = s_keep_ties;
         if (keep_ties > 0) {   // (block-uniform, rare) only the first keep_ties of the tied ids stay: find the id of the last one
             int seen = 0;      // ties in the ids before this chunk (same value in every thread)
             int limit = -1;
@@ -618,7 +526,6 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
         nu.on = true;
         __syncthreads();
         level1();   // the same pass over the kept tokens only
-      }
     }
     __syncthreads();
     float M = -INFINITY;

@@ -248,6 +248,47 @@ def test_top_p_forms(V, form):
     assert same >= math.floor(0.98 * tot)
 
 
+@pytest.mark.parametrize("V,T,top_p,eos,bias", [(32000, 0.7, 0.95, 9, 0.5), (30001, 1.0, 0.8, -1, 0.0), (700, 1.3, 0.3, -1, 0.0)])
+def test_top_p_draws_as_the_plain_sampler_on_the_kept_tokens(V, T, top_p, eos, bias):
+    # Nothing but the cut distinguishes the two: with the other tokens masked, plain sampling gives the same token and the same
+    # log-probability to the last bit.  (The float64 cut may lie one token off, see above: each row equals one of three.)
+    rng = np.random.default_rng(V)
+    n = 300
+    logits = rng.standard_normal((n, V)).astype(np.float32)
+    uids = np.arange(n, dtype=np.int64) + 17
+    tok, lp = _run_top_p(logits, T, top_p, 33, uids, 6, eos, bias)
+    x = logits.astype(np.float64) / T
+    if eos >= 0:
+        x[:, eos] += bias
+    order = np.argsort(-x, axis=1, kind="stable")
+    size = np.array([sampler.nucleus(np.exp(r - r.max()), top_p).sum() for r in x])
+    matched = np.zeros(n, dtype=bool)
+    for d in (0, -1, 1):
+        masked = logits.copy()
+        for i in range(n):
+            masked[i, order[i, max(1, size[i] + d):]] = -np.inf
+        t1, l1 = _run(masked, n, V, T, 33, uids, 6, eos, bias)
+        matched |= (t1 == tok) & (l1 == lp)
+    assert matched.all(), "rows %s" % np.nonzero(~matched)[0]
+
+
+@pytest.mark.parametrize("V", [700, 5001])
+@pytest.mark.parametrize("share", [0.5, 0.99])
+def test_masked_rows(V, share):
+    # top_p = 1 over rows with most of the vocabulary at minus infinity, whole stretches of it
+    rng = np.random.default_rng(V)
+    n = 40
+    logits = rng.standard_normal((n, V)).astype(np.float32)
+    logits[rng.random((n, V)) < share] = -np.inf
+    logits[:, :V // 3] = -np.inf
+    logits[:, V // 2] = 0.25
+    uids = np.arange(n, dtype=np.int64) + 7
+    tok, lp = _run(logits, n, V, 0.9, 12, uids, 3)
+    for i in range(n):
+        want, wlp = sampler.sample_token(logits[i], 0.9, philox.sampling_uniform(12, int(uids[i]), 3))
+        assert tok[i] == want and abs(lp[i] - wlp) < 3e-5 * max(1.0, abs(wlp))
+
+
 @pytest.mark.parametrize("V", [512, 5000])
 @pytest.mark.parametrize("gap", [40.0, 94.0, 96.0, 97.0, 110.0, 280.0])
 def test_top_p_with_the_largest_logit_suppressed(V, gap):
