@@ -293,6 +293,55 @@ def test_projection_that_rotates_and_appends(hq, hkv, lens, bs, act):
     _check(m, w, prompts, out, 21, 2e-2, range(0, len(lens) * 2, 3))
 
 
+def test_attention_keeps_the_largest_probability_exact():
+    # One key holds nearly all of a head's weight, in a later tile than the largest score before it.  Its probability is 1 and
+    # must not round: weighted values and weights are then summed alike and the output is the value itself.  (Taken relative to
+    # the earlier score it would be 2^2 .. 2^7.3 here, picked so that half rounds it by 2e-4 to 4e-4 of itself, up in every
+    # other head.)  Scores are sums of +-1 times the query weights, exact in half, and the dims in use have rotary angles of
+    # zero.  Logit h is the sum of head h's outputs over 128 dims: their own rounding averages to 2^-12 / sqrt(3 * 128) =
+    # 1.2e-5, twice (attention output, normalised row); three standard deviations of both and an equal share for the weights
+    # below the largest: 6e-5.
+    m = workloads.scaled(C1, dtype="bf16", d_model=1024, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=64, vocab=512,
+                         n_layers=1, rope_theta=1.0e30).model
+    say("largest probability exact")
+    w = workloads.make_weights(m, 1)
+    for k in ("wq", "wk", "wv", "wo", "w_down"):
+        w[k][0].zero_()
+    sign = torch.randint(0, 2, (m.vocab, m.d_model), generator=torch.Generator().manual_seed(2)) * 2.0 - 1.0
+    sign[:, 0] = 1.0                                      # query and value source
+    sign[:, 1:3] = -1.0                                   # token 1: the largest score of the first tile, token 2: the peak
+    sign[1, 1] = sign[2, 1] = sign[2, 2] = 1.0
+    w["tok_embed"].copy_(sign)
+    dims = torch.arange(32, 64), torch.arange(96, 128)
+    for h, second in enumerate((192, 158, 164, 227, 223, 220, 95, 161)):
+        w["wq"][0][128 * h + dims[0], 0] = 2.5
+        w["wq"][0][128 * h + dims[1], 0] = second / 256.0
+        w["wo"][0][128 * h + torch.arange(128), 128 * h + torch.arange(128)] = 1.0
+    for g in range(2):
+        w["wk"][0][128 * g + dims[0], 1] = 1.0
+        w["wk"][0][128 * g + dims[1], 2] = 1.0
+        w["wv"][0][128 * g + torch.arange(128), 0] = (1.0 + torch.arange(128) / 128.0).to(torch.bfloat16)
+    w["lm_head"].zero_()
+    for h in range(8):
+        w["lm_head"][h, 128 * h:128 * (h + 1)] = 1.0
+    prompt = np.zeros(300, dtype=np.int64)
+    prompt[5], prompt[260] = 1, 2                         # (decode: eight waves take every eighth tile of 32)
+    want = decoder.forward_full(m, w, np.append(prompt, 0), rows=[299, 300])[:, :8]
+    import paper_2605_26606_amd as pc
+    ctx = make_ctx(m, w, block_size=32, kv_pool_bytes=64 << 20, max_slots=130, max_ctx=320, max_batch_rows=512, act_dtype="f16")
+    last = torch.empty(1, m.vocab, device="cuda")
+    handle = pc.pc_prefill_shared(ctx, torch.from_numpy(prompt.astype(np.int32)).cuda(), np.array([0, 300], np.int32), last)
+    seqs = pc.pc_fork(ctx, np.repeat(handle, 100), 4)     # 200 (row, kv head) pairs: contexts are not split
+    logits = torch.empty(100, m.vocab, device="cuda")
+    pc.pc_decode_step(ctx, seqs, torch.zeros(100, dtype=torch.int32, device="cuda"), logits)
+    torch.cuda.synchronize()
+    for name, got, ref in (("prefill", last[0, :8], want[0]), ("decode", logits[99, :8], want[1])):
+        err = np.abs(got.cpu().numpy() / ref - 1.0)
+        say("%s: relative errors %s" % (name, " ".join("%.1e" % e for e in err)))
+        assert err.max() <= 6e-5
+    ctx.close()
+
+
 def test_graph_replay_equals_eager_and_is_deterministic():
     say("graph vs eager, bf16")
     import paper_2605_26606_amd as pc
