@@ -617,6 +617,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
                 if (part) blk = extra.kv.block_table[(int64_t)slot * extra.kv.max_blocks_per_slot + pos / bs];
             }
             const int tin = pos % bs;
+            uint32_t *const count = row < M ? sat : nullptr;          // (rows past the end are copies of the last one)
             if (part == 2) {
                 if (row < M) {
                     T *vd = pool + (int64_t)blk * extra.kv.block_elems();
@@ -636,9 +637,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
                 const acc_t &x1 = acc[i][2 * p2], &x2 = acc[i][2 * p2 + 1];
                 unsigned char *dst = stg + ml * PITCH + (16 * p2 + nq) * 2;
                 *(u32x2 *)dst = pack4_sat<T>(x1[0] * c[0] - x2[0] * sn[0], x1[1] * c[1] - x2[1] * sn[1],
-                                             x1[2] * c[2] - x2[2] * sn[2], x1[3] * c[3] - x2[3] * sn[3], sat);
+                                             x1[2] * c[2] - x2[2] * sn[2], x1[3] * c[3] - x2[3] * sn[3], count);
                 *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(x2[0] * c[0] + x1[0] * sn[0], x2[1] * c[1] + x1[1] * sn[1],
-                                                          x2[2] * c[2] + x1[2] * sn[2], x2[3] * c[3] + x1[3] * sn[3], sat);
+                                                          x2[2] * c[2] + x1[2] * sn[2], x2[3] * c[3] + x1[3] * sn[3], count);
             }
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -683,16 +684,18 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     const int ldc = SWIGLU ? N / 2 : N;
     const int colbase = SWIGLU ? (n0 + wn * (BN / WN)) / 2 : n0 + wn * (BN / WN);
     OutT *Cbase = (OutT *)Cv + ((EPI == EPI_STORE_F32) ? (int64_t)z * M * N : 0);
+    uint32_t *count = nullptr;                                    // clamped values are counted only where they are stored
     auto put4 = [&](int col, float v0, float v1, float v2, float v3) {   // four consecutive columns of row ml
         unsigned char *dst = stg + ml * PITCH + col * (int)sizeof(OutT);
         if constexpr (sizeof(OutT) == 4) {
             *(f32x4_t *)dst = (f32x4_t){v0, v1, v2, v3};
         } else {
-            *(u32x2 *)dst = pack4_sat<T>(v0, v1, v2, v3, sat);
+            *(u32x2 *)dst = pack4_sat<T>(v0, v1, v2, v3, colbase + col < ldc ? count : nullptr);
         }
     };
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+        count = m0 + wm * (BM / WM) + i * RT + ml < M ? sat : nullptr;
         const float sc = (EPI == EPI_SWIGLU_RS) ? s_rs[wm * (BM / WM) + i * RT + ml] : 1.f;
         if constexpr (SWIGLU) {
             // a 32-wide chunk of weight rows = 16 gate rows, then the 16 matching up rows

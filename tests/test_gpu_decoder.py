@@ -519,6 +519,46 @@ def test_peaked_distributions_token_agreement(act, floor):
     assert own >= math.ceil(floor * tot)
 
 
+def test_saturation_count_is_that_of_the_stored_values():
+    # Normalised rows are +-1 (+1 in the first 16 places), so a weight row of 8192 in those places gives 131072, beyond half,
+    # and all other values stay far inside: three key dims and ten gate/up outputs saturate in every row, and three query dims
+    # in the second run (dims 40 and 104 are rotary partners, with an angle of zero at this theta).  Row tiles of 128 and more end in rows that do not exist; the copies standing in for them must not be counted.
+    m = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=224, vocab=512,
+                         n_layers=1, rope_theta=1.0e30).model
+    w = workloads.make_weights(m, 1)
+    w["tok_embed"].copy_(torch.randint(0, 2, (m.vocab, m.d_model), generator=torch.Generator().manual_seed(2)) * 2.0 - 1.0)
+    w["tok_embed"][:, :16] = 1.0
+    w["wo"][0].zero_()
+    w["w_down"][0].zero_()
+    for name, rows in (("wk", (40, 104, 128 + 41)), ("w_gate", range(0, 220, 22)), ("w_up", range(0, 220, 22))):
+        w[name][0][list(rows), :16] = 8192.0
+    per_row = 3 + 10
+    import paper_2605_26606_amd as pc
+    lens = [201, 3, 190, 128, 90]                         # 612 rows: 128-row tiles end in 28 that do not exist
+    rng = np.random.default_rng(1)
+    prompts = [rng.integers(0, m.vocab, n) for n in lens]
+    toks = torch.from_numpy(np.concatenate(prompts).astype(np.int32)).cuda()
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    for query in (False, True):
+        if query:
+            w["wq"][0][[40, 104, 128 * 7 + 41], :16] = 8192.0
+        want = per_row + (3 if query else 0)
+        for max_rows in (700, 256):                       # one chunk, and several
+            ctx = make_ctx(m, w, block_size=32, kv_pool_bytes=64 << 20, max_slots=40, max_ctx=256, max_batch_rows=max_rows,
+                           act_dtype="f16")
+            last = torch.empty(len(lens), m.vocab, device="cuda")
+            handles = pc.pc_prefill_shared(ctx, toks, cu, last)
+            count = pc.pc_saturation_count(ctx, True)
+            say("saturated: %d (max rows %d)" % (count, max_rows))
+            assert count == want * sum(lens)
+            for n in (3, 20):                             # decode tiles of 16, 32 and 128 rows
+                seqs = pc.pc_fork(ctx, np.repeat(handles[:1], n), 2)
+                pc.pc_decode_step(ctx, seqs, torch.zeros(n, dtype=torch.int32, device="cuda"), torch.empty(n, m.vocab, device="cuda"))
+                assert pc.pc_saturation_count(ctx, True) == want * n
+                pc.pc_release(ctx, seqs, 0)
+            ctx.close()
+
+
 def test_half_range_saturation_is_clamped_and_counted():
     # A model whose feed-forward product leaves the IEEE-half range (gate and up projections inflated): the
     # stores clamp to +-65504 instead of producing inf/NaN, every clamp is counted, and the logits stay finite.
