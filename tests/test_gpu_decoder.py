@@ -355,6 +355,49 @@ def test_graph_replay_equals_eager_and_is_deterministic():
     assert np.array_equal(a["tokens"], c["tokens"]) and np.array_equal(a["logits"], c["logits"])
 
 
+def test_captured_step_replays_for_other_lists():
+    # one context, stream and pair of buffers; lists of the same length and grouping over other slots and lengths, a list over
+    # released and reused slots, a permuted one, and one of another grouping in between: every step equals the eager one
+    import paper_2605_26606_amd as pc
+    say("captured step with other lists")
+    w = workloads.make_weights(BF, 4, std=0.05)
+    toks, cu = workloads.make_ragged_prompts([100, 7, 260, 33, 64, 190], BF.vocab, 8)
+    feed = torch.from_numpy(np.random.default_rng(5).integers(0, BF.vocab, (14, 6)).astype(np.int32)).cuda()
+    runs = []
+    for graph in (1, 0):
+        ctx = make_ctx(BF, w, block_size=64, kv_pool_bytes=128 << 20, max_slots=64, max_ctx=512, max_batch_rows=800)
+        pc.pc_set_option(ctx, pc.PC_OPT_USE_GRAPH, graph)
+        out = []
+        with torch.cuda.stream(side_stream()):
+            last = torch.empty(6, BF.vocab, device="cuda")
+            h = pc.pc_prefill_shared(ctx, torch.from_numpy(toks.astype(np.int32)).cuda(), cu.astype(np.int32), last)
+            tokens, logits = torch.empty(6, dtype=torch.int32, device="cuda"), torch.empty(6, BF.vocab, device="cuda")
+
+            def steps(seqs, n):
+                for _ in range(n):
+                    tokens.copy_(feed[len(out)])
+                    pc.pc_decode_step(ctx, seqs, tokens, logits)
+                    out.append(logits.clone())
+
+            a = pc.pc_fork(ctx, np.repeat(h[:3], 2), 16)
+            b = pc.pc_fork(ctx, np.repeat(h[3:], 2), 16)
+            steps(a, 2)
+            steps(b, 2)
+            steps(a[[4, 5, 0, 1, 2, 3]], 2)              # the same sequences, prompts in another order
+            pc.pc_release(ctx, b[:4], 0)
+            c = pc.pc_fork(ctx, np.repeat(h[[0, 5]], 2), 16)
+            steps(np.concatenate([c, a[2:4]]), 2)         # reused slots beside sequences that have decoded
+            steps(np.concatenate([a[::2], b[4:5], c[::2]]), 2)   # single sequences: another grouping
+            steps(a, 2)
+            steps(np.concatenate([b[4:], c]), 2)
+        torch.cuda.synchronize()
+        runs.append(out)
+        ctx.close()
+    assert len(runs[0]) == 14
+    for t, (x, y) in enumerate(zip(*runs)):
+        assert torch.equal(x, y), "step %d" % t
+
+
 def test_eos_stops_sequences_fp32():
     say("fp32 C1 with a biased EOS id")
     m = C1.model
