@@ -103,7 +103,7 @@ typedef struct {
 
 /* Options for pc_set_option. */
 #define PC_OPT_USE_GRAPH 1   /* 1: replay the decode step as a HIP graph (default 1) */
-#define PC_OPT_FORCE_SIMT 2  /* 1: plain-ALU kernels also for bf16 (debugging aid; default 0) */
+#define PC_OPT_FORCE_SIMT 2  /* 1: plain-ALU kernels, whatever the model's type (debugging aid; default 0) */
 #define PC_OPT_FUSE_DECODE 4   /* 1: decode batches of up to 512 rows of a 16-bit model with head_dim 128 whose q/k/v
                                   projection has at most 8 M weights run the fused layer (q/k/v projection with rotary
                                   positions and cache append in its epilogue; output projection that also leaves the next

@@ -171,8 +171,8 @@ struct pc_ctx {
         g.block_table = d_block_table;
         return g;
     }
-    int impl() const { return (kd != KD_F32 && !force_simt) ? 1 : 0; }
-    bool mfma_attention() const { return impl() == 1 && m.head_dim == 128 && (m.n_q_heads / m.n_kv_heads) <= 16; }
+    int impl() const { return force_simt ? 0 : 1; }
+    bool mfma_attention() const { return kd != KD_F32 && impl() == 1 && m.head_dim == 128 && (m.n_q_heads / m.n_kv_heads) <= 16; }
 };
 
 namespace {

@@ -851,7 +851,7 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
                 float *slices, size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
     if (M <= 0 || N <= 0) return 1;
     if (dtype == KD_F32) {
-        if (gemm_f32_ok(A, W, N, K, epi)) gemm_f32((const float *)A, (const float *)W, (float *)C, M, N, K, epi, s);
+        if (impl != 0 && gemm_f32_ok(A, W, N, K, epi)) gemm_f32((const float *)A, (const float *)W, (float *)C, M, N, K, epi, s);
         else gemm_simt<float>(A, W, C, M, N, K, epi, sat, s);
         return 1;
     }

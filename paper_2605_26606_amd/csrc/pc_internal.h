@@ -205,7 +205,7 @@ void launch_embed(int dtype, const void *table, const int32_t *tokens, int rows,
 // (written back); src_row must be NULL then.
 void launch_rmsnorm(int dtype, float *h, const int32_t *src_row, const float *gain, int rows, int d, float eps,
                     void *out, const float *slices, int S, uint32_t *sat, hipStream_t s);
-// C = A[M,K] * W[N,K]^T with the given epilogue.  impl 0: plain ALU, 1: matrix cores (bf16 only)
+// C = A[M,K] * W[N,K]^T with the given epilogue.  impl 0: plain ALU, 1: matrix cores
 void gemm_init();   // once per device: raises the dynamic-LDS limit of the matrix-core kernels
 // Returns the number of K slices S the product was cut into.  S == 1: C holds the finished result.
 // S > 1 (only when `slices` is given, for EPI_STORE_F32 / EPI_RESID_F32 at decode sizes): C is untouched

@@ -206,6 +206,20 @@ def test_bf16_plain_alu_path():
     _check(BF, w, prompts, out, 5, 2e-2, range(6))
 
 
+def test_fp32_plain_alu_option():
+    # the option holds for fp32 models too: within the bound of the matrix instructions, but not their sums to the last bit
+    say("fp32 small model, plain-ALU kernels by option")
+    import paper_2605_26606_amd as pc
+    m = C1.model
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 2), 9)
+    prompts = list(workloads.make_prompts(3, 40, m.vocab, 6))
+    kw = dict(block_size=32, kv_pool_bytes=64 << 20, max_slots=32, max_ctx=128, max_batch_rows=256)
+    a = _run_generate(m, w, prompts, 2, 6, 5, kw, opts=[(pc.PC_OPT_FORCE_SIMT, 1)])
+    b = _run_generate(m, w, prompts, 2, 6, 5, kw)
+    _check(m, w, prompts, a, 5, 1e-4, range(6))
+    assert not np.array_equal(a["last"], b["last"])
+
+
 @pytest.mark.parametrize("model,lens,G,T,bs,std,act", [
     (BF, [70, 33, 128, 5, 64], 4, 24, 64, 0.02, "f16"),   # the workloads' init: absolute 2e-2 bound
     (BF, [70, 33, 128, 5, 64], 4, 24, 64, 0.02, "bf16"),  # same with bfloat16 activations
