@@ -826,11 +826,12 @@ template <typename T> struct Gemm {
     typedef MfmaCfg<T, 32, 64, 1, 2, 4, 64, true> T32x64_2;     // the same with whole gate/up chunks per wave
     typedef MfmaCfg<T, 128, 128, 2, 2, 3, 32> M128x128_3;       // BK 32, 48 KB: three blocks per CU
     typedef MfmaCfg<T, 128, 64, 4, 2, 4, 64, true> T128x64;     // 8 waves of 32 x 32: long-K projections cut into K slices
+    typedef MfmaCfg<T, 192, 64, 4, 2, 4, 64, true> T192x64;     // the same in wave tiles of 48 x 32
     typedef MfmaCfg<T, 64, 64, 2, 2, 4> M64x64;                 // wave tile 32 x 32: many blocks for the small projections
     static void init() {
         T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
         T128x128_2::init(); T128x192::init(); T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init();
-        M128x128_3::init(); T128x64::init(); M64x64::init();
+        M128x128_3::init(); T128x64::init(); T192x64::init(); M64x64::init();
         T256x256::init_logprob();
         T256x128::init_logprob();
         T192x128::init_logprob();
@@ -1028,8 +1029,14 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
     }
     if ((int64_t)N * K >= (int64_t)8 << 20) {   // narrow output, long K (the 1.5B model's down projection)
         if (M <= 64) return sliced(typename G::M64x64(), 240);   // 8.2 us against 10.4 us with 128-row tiles at 60 rows
-        // (4 waves of 64x32 took 19.7 us for 17.0 at 256 rows and 11.6 for 10.7 at 116; 256-row tiles 21.2 for 19.9 at 380)
-        return sliced(typename G::T128x64(), 240);
+        // (4 waves of 64x32 took 16.1 us for 15.8 at 256 rows and 12.0 for 11.8 at 116)
+        if (M <= 256) return sliced(typename G::T128x64(), 240);
+        // One block per CU and 32 CUs to a die: with three and four row blocks of 128 x 64 the slices no longer come out even
+        // over the dies (1536 x 8960 at 420 rows: 72 slices, 9 to a die, 36 blocks on its CUs).  Two row blocks up to 384
+        // (17.2 us at 300 rows, 18.8 with three of 128), then four of twice the width (420 rows: 20.2 us against 35.5 us with
+        // 128 x 64, 22.2 us with 256 x 64; the same order for 2048 x 6144 and 2560 x 4096)
+        if (M <= 384) return sliced(typename G::T192x64(), 240);
+        return sliced(typename G::T128x128(), 240);
     }
     return sliced(typename G::M64x64(), 192);
 }
