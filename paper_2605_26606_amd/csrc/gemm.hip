@@ -836,6 +836,8 @@ template <typename T> struct Gemm {
         T256x128::init_logprob();
         T192x128::init_logprob();
         T128x128::init_logprob();
+        T64x128::init_qkv();
+        T128x128::init_qkv();
         T256x256::init_qkv();
         T256x128::init_qkv();
         T128x128_2::init_qkv();
@@ -871,9 +873,14 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
 // ---- q | k | v projection with rotary positions and cache append
 template <typename T> static void gemm_qkv_t(const void *A, const void *W, int M, int N, int K, const GemmQkv &qkv, uint32_t *sat, hipStream_t s) {
     typedef Gemm<T> G;
-    // the tile of the plain projection of this size (gemm_mfma_dispatch), where that is not cut into K slices; where it is
-    // (1024 rows x 2048 columns), smaller tiles without slices
-    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) G::T256x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    // The tallest grid that one round of blocks takes, one per CU, in the smallest tile for which it does: 1024 rows x 2048
+    // columns x 1536 in 64 x 128 tiles 17.3 us, in 128 x 128 22.1 us, in 128 x 128 two per CU 27.7 us, K slices and a rotating
+    // kernel behind them 22.3 us; 2048 rows 26.0 / 24.8 / 29.0 / 32.7 us; 640 rows x 6144 x 4096 54.8 / 47.8 / 64.7 / 68.4 us.
+    // Beyond one round the tile of the plain projection (gemm_mfma_dispatch).
+    const int nb128 = (N + 127) / 128;
+    if ((M + 63) / 64 * nb128 <= 256) G::T64x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else if ((M + 127) / 128 * nb128 <= 256) G::T128x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) G::T256x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
     else if ((int64_t)((M + 255) / 256) * ((N + 127) / 128) >= 160) G::T256x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
     else G::T128x128_2::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
 }
@@ -882,6 +889,11 @@ bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, i
                      hipStream_t s) {
     const int N = (qkv.hq + 2 * qkv.kv.n_kv_heads) * qkv.kv.head_dim;
     if (dtype == KD_F32 || impl == 0 || qkv.kv.head_dim != 128 || K % 64 != 0 || M <= 512) return false;
+    // (three row blocks of 256 that fill the chip once: with few rows to rotate a kernel of its own costs less than the
+    // epilogue of one block per CU, 69.9 us against 76.0 us at 513 rows x 7168 x 5120, 82.9 against 84.1 at 768; 91.9 against
+    // 87.4 at 896)
+    const int nb128 = (N + 127) / 128;
+    if (M <= 768 && 3 * nb128 >= 160 && (M + 127) / 128 * nb128 > 256) return false;
     if (dtype == KD_BF16) gemm_qkv_t<bf16_t>(A, W, M, N, K, qkv, sat, s);
     else gemm_qkv_t<f16_t>(A, W, M, N, K, qkv, sat, s);
     return true;

@@ -288,7 +288,10 @@ def test_wide_tiles_by_row_count(model, P, G, act):
 
 
 @pytest.mark.parametrize("hq,hkv,lens,bs,act", [
-    (8, 2, [201, 3, 190, 128, 90], 32, "f16"),             # 612 rows x 1536 columns: the 128 x 128 tiles
+    (8, 2, [201, 3, 190, 128, 90], 32, "f16"),             # 612 rows x 1536 columns: the 64 x 128 tiles
+    (8, 2, [333, 201, 3, 300, 66, 400, 201], 32, "f16"),   # 1504 x 1536: 128 x 128, one per CU
+    (32, 8, [201, 3, 190, 128, 178], 64, "bf16"),          # 700 x 6144: 128 x 128, two per CU
+    (48, 8, [201, 3, 190, 128, 78], 32, "f16"),            # 600 x 8192: rotation in a kernel of its own
     (48, 8, [333, 1, 300, 65, 301], 64, "f16"),           # 1000 x 8192: 256 x 128
     (48, 8, [700, 9, 650, 800, 777, 640, 555], 64, "f16"),    # 4131 x 8192: 256 x 256, a row tile with 35 rows
     (48, 8, [700, 9, 650, 800, 777, 640, 555], 128, "bf16"),
