@@ -371,7 +371,7 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
     const int seg = round_up((vocab + SAMPLE_WAVES - 1) / SAMPLE_WAVES, STRIDE);
     auto level1 = [&]() {
         const int b = min(vocab, wave * seg), e = min(vocab, b + seg);
-        float m = -INFINITY;
+        float m = -INFINITY, ref = 0.f;   // (ref is m, or 0 while all tokens so far are masked: no weight)
         double s = 0.0;
         // four strides are fetched before the first is folded in (the fold is a serial chain, and a load
         // per link would leave the memory latency exposed at every step); the order of the arithmetic is
@@ -391,12 +391,11 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
                     if (ok[u][c]) lm = fmaxf(lm, v[u][c]);
                 if (lm > m) {
                     s *= (double)expf(m - lm);   // m = -inf -> 0
-                    m = lm;
+                    m = ref = lm;
                 }
-                const float base_m = (m == -INFINITY) ? 0.f : m;   // (so far masked tokens only: no weight)
 #pragma unroll
                 for (int c = 0; c < VEC; ++c)
-                    if (ok[u][c]) s += (double)expf(v[u][c] - base_m);
+                    if (ok[u][c]) s += (double)expf(v[u][c] - ref);
             }
         }
         const float wm = wave_max_f32(m);
