@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__r
     for (int st = 0; st < steps; ++st) {
         const int refill = (stage == 0) ? SK_NS - 1 : stage - 1;   // consumed in the previous iteration
         issue(st + SK_NS - 1, refill);
-        // at most the loads of the two younger steps are still in flight: this step has landed in LDS
+        // at most the loads of the SK_NS - 1 younger steps are still in flight: this step has landed in LDS
         __builtin_amdgcn_s_waitcnt((((SK_NS - 1) * SK_LOADS) & 0xF) | ((((SK_NS - 1) * SK_LOADS) >> 4) << 14) | (0x7 << 4) |
                                    (0xF << 8));
         asm volatile("" ::: "memory");
