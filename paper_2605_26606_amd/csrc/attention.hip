@@ -227,9 +227,12 @@ template <> __device__ inline uint32_t pack_prob<bf16_t>(float a, float b) {
 // MASKED: tokens > col_limit (this lane's column) or >= tok_end are left out; otherwise all 32 take part.
 //
 // The vector ALU, not the matrix cores, bounds this loop (8 scores per lane against 16 products of 16 clocks), so a tile does
-// as little as possible beside its exponentials: the maxima are exchanged between the lanes of a column, and the outputs
-// rescaled, only when some lane's score exceeds its column's maximum so far.  The reference m is that maximum exactly: a
-// column's largest probability is 1 and does not round, and a peaked column's result carries no rounding of its weights.
+// as little as possible beside its exponentials: with one head group the maxima are exchanged between the lanes of a column,
+// and the outputs rescaled, only when some lane's score exceeds its column's maximum so far (14B prefill, prompts of 900 to
+// 1100 tokens: 512 -> 460 us; decode, 256 sequences of the 8B shape: 144 -> 140 us).  With several it is done always, without
+// a branch: the groups' exchanges then overlap (3 groups, 64 x 256 tokens: 98 us with the branch, 92 without).  The reference
+// m is the maximum exactly: a column's largest probability is 1 and does not round, and a peaked column's result carries no
+// rounding of its weights.
 // (A reference allowed to lag by a factor of 2^8 took another 1 % off a 1.5B prefill of 64 x 256 tokens and added 1 to 3 % to
 // the logits' error against 64-bit values.)
 template <typename T, int NH, bool MASKED>
@@ -257,7 +260,7 @@ __device__ inline void attend_tile(const KvTile<T> &kt, const typename Mma<T>::f
         }
         float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
                          fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-        if (__any(mx > st[h].m)) {
+        if (NH > 1 || __any(mx > st[h].m)) {
             mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
             mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
             const float m_new = fmaxf(st[h].m, mx);
@@ -301,7 +304,9 @@ __device__ inline void attend_tiles(const T *__restrict__ head_base, int64_t blo
     // a tile needs the masks only where it reaches past a column's limit or the end (col_limit < 0: an unused column, whose
     // results nobody reads, but whose state must not see a token: its lanes keep every tile masked)
     auto attend = [&](const KvTile<T> &kt, int t0) {
-        if (__all(t0 + 31 <= col_limit) && t0 + 32 <= tok_end)
+        // (two head groups: one copy of the body, always masked, 141 us for 11 prompts of 37 to 1100 tokens of the 8B shape
+        // against 174 us with two; three groups 96 against 92 us)
+        if (NH != 2 && __all(t0 + 31 <= col_limit) && t0 + 32 <= tok_end)
             attend_tile<T, NH, false>(kt, qf, t0, tok_end, col_limit, scale_log2, st);
         else
             attend_tile<T, NH, true>(kt, qf, t0, tok_end, col_limit, scale_log2, st);
