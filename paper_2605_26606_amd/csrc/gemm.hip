@@ -17,7 +17,8 @@ namespace pc {
 __device__ inline float silu_f(float x) { return x / (1.0f + expf(-x)); }
 
 // silu(g) * u of the matrix-core epilogues, whose results are rounded to 16 bits: exp2 and reciprocal are the hardware's
-// (errors of 1e-7 against a rounding of 5e-4; the logits' error against 64-bit values did not change).  The epilogue is
+// (the fp32 value is off by 5.3e-8 of its size instead of 4.7e-8; rounded to half or bfloat16 both forms are equally far from
+// 64-bit values in all of seven digits, gates and ups of deviation 0.3 to 40).  The epilogue is
 // vector-ALU work that nothing overlaps, one block per CU: with expf, an IEEE division and a range test per value it took
 // a tenth of the kernel (gate/up of the 1.5B shape: 1020 -> 935 us at 16384 rows, 28.3 -> 25.7 us at 256 rows).
 __device__ inline float silu_mul(float g, float u) {

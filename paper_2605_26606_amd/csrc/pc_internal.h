@@ -221,8 +221,8 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
 int logprob_fused_rows(int dtype, int impl, int N, int K, size_t scratch_bytes);
 void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, int K, float temperature,
                          const int32_t *tokens, const int32_t *token_index, void *scratch, float *out, hipStream_t s);
-// C = A W^T as EPI_QKV leaves it, for batches whose projection needs no K slices (more than 512 rows); false: not a shape it
-// takes, nothing launched.
+// C = A W^T as EPI_QKV leaves it, for batches of more than 512 rows; false: not a shape it takes, or one that a kernel of its
+// own for the rotation serves better; nothing launched.
 bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
                      hipStream_t s);
 // Fused decode projections (gemm_skinny.hip); skinny_ok says whether the shape is one they take.
