@@ -265,7 +265,10 @@ __device__ inline void attend_tile(const KvTile<T> &kt, const typename Mma<T>::f
             mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
             const float m_new = fmaxf(st[h].m, mx);
             const float corr = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((st[h].m - m_new) * scale_log2);
-            st[h].l *= corr;
+            {
+#pragma clang fp contract(off)   // (not fused into the sum below: the same bits with and without the branch)
+                st[h].l *= corr;
+            }
             st[h].m = m_new;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
