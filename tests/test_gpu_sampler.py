@@ -200,13 +200,13 @@ def test_top_p_tokens_and_logprobs(V, n, T, top_p, scale):
 
 def _nucleus_form(form, V, rng):
     x = rng.standard_normal(V).astype(np.float32)
-    if form == "ties":               # an eighth of the row on each of a few values: too many alike for the ranked cut
+    if form == "ties":               # a row on a few values: at 30000 tokens more alike than the list of the cut's bin holds
         x = np.round(x) + np.float32(0.0)   # (no negative zeros: their order beside zero is the key's)
-    elif form == "some_ties":        # a few dozen alike in one part of the crossing bin
+    elif form == "some_ties":        # a few dozen alike at the cut: the lowest ids of them stay
         x = (np.round(x * 200.0) / 200.0).astype(np.float32) + np.float32(0.0)
-    elif form == "flat":             # a whole row in one or two bins
+    elif form == "flat":             # a whole row in one or two bins, more than the list holds at 30000
         x *= np.float32(0.004)
-    elif form == "hidden_peak":      # a maximum 50 above everything a sample of the row sees
+    elif form == "hidden_peak":      # one token 50 above all others
         x[V // 2 + 1] = 50.0
     elif form == "masked":           # most of the vocabulary at minus infinity
         x[rng.random(V) < 0.9] = -np.inf
