@@ -1,50 +1,21 @@
 // Projection GEMMs of the decoder (Section 3.1 policy pi_theta):
 //   C[M,N] = A[M,K] * W[N,K]^T, fp32 accumulation, with fused epilogues.
-// Three implementations:
+// Three implementations here:
 //   gemm_f32    fp32 matrix instructions, operands straight from memory (fp32 models)
 //   gemm_simt   plain-ALU tiles, any dtype, any K
 //   gemm_mfma   bf16 / f16 on the matrix cores (32x32x16 or 16x16x32 products),
 //               operands streamed global -> LDS several K tiles ahead, one
-//               barrier per K tile, output rows re-formed through LDS
+//               barrier per K tile, output rows re-formed through LDS: up to 512
+//               rows (gemm_large.hip takes the larger batches)
 #include <algorithm>
 
 #include <type_traits>
 
-#include "pc_internal.h"
+#include "gemm_common.h"
 
 namespace pc {
 
 __device__ inline float silu_f(float x) { return x / (1.0f + expf(-x)); }
-
-// silu(g) * u of the matrix-core epilogues, whose results are rounded to 16 bits: exp2 and reciprocal are the hardware's
-// (the fp32 value is off by 5.3e-8 of its size instead of 4.7e-8; rounded to half or bfloat16 both forms are equally far from
-// 64-bit values in all of seven digits, gates and ups of deviation 0.3 to 40).  The epilogue is
-// vector-ALU work that nothing overlaps, one block per CU: with expf, an IEEE division and a range test per value it took
-// a tenth of the kernel (gate/up of the 1.5B shape: 1020 -> 935 us at 16384 rows, 28.3 -> 25.7 us at 256 rows).
-__device__ inline float silu_mul(float g, float u) {
-    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f)) * u;
-}
-
-// exp(d) for d <= 0 to about one unit in the last place: d log2(e) in two pieces, the small one added to first order
-__device__ inline float exp_neg(float d) {
-    const float p = d * 1.44269502f;
-    const float r = __builtin_amdgcn_exp2f(p);
-    const float e = fmaf(d, 1.92596299e-8f, fmaf(d, 1.44269502f, -p));
-    return p < -126.f ? 0.f : fmaf(r, e * 0.693147181f, r);
-}
-
-// Four values packed into two words.  Values beyond the half range are clamped and counted on a path of their own; one
-// test covers the four (their absolute sum is at most 65504 only if none is beyond it, infinite or not a number).
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-template <typename T> __device__ inline u32x2 pack4_sat(float a, float b, float c, float d, uint32_t *sat) {
-    return (u32x2){pack2_sat<T>(a, b, sat), pack2_sat<T>(c, d, sat)};
-}
-template <> __device__ inline u32x2 pack4_sat<f16_t>(float a, float b, float c, float d, uint32_t *sat) {
-    typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-    if (fabsf(a) + fabsf(b) + fabsf(c) + fabsf(d) <= 65504.f)
-        return __builtin_bit_cast(u32x2, (f16x4){(_Float16)a, (_Float16)b, (_Float16)c, (_Float16)d});
-    return (u32x2){pack2_sat<f16_t>(a, b, sat), pack2_sat<f16_t>(c, d, sat)};
-}
 
 template <typename T> __device__ inline void store_out(T *p, float v, uint32_t *sat) { *p = from_f32_sat<T>(v, sat); }
 
@@ -238,8 +209,6 @@ static void gemm_f32(const float *A, const float *W, float *C, int M, int N, int
 // =====================================================================================
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-
 static constexpr int N_XCD = 8;   // MI355X: 8 accelerator dies, each with its own L2; workgroup i runs on die i % 8
 
 // One 32x32x16 product per instruction.  Operand layout (wave of 64 lanes):
@@ -260,18 +229,6 @@ static constexpr int N_XCD = 8;   // MI355X: 8 accelerator dies, each with its o
 // 64 k); to keep the 128-bit fragment reads conflict free without padding, the 16-byte chunk c of
 // row r is stored at chunk slot c ^ swz(r) (the lane fetches the chunk its slot must hold), where swz
 // makes any 16 consecutive rows hit 16 different 16-byte bank groups.  K must be a multiple of 64 here.
-template <int N> __device__ inline void wait_vmcnt_le() {
-    // s_waitcnt with only the vector-memory counter set (gfx9 encoding: vmcnt = bits 15:14 | 3:0)
-    __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
-// What an epilogue needs besides the common arguments.
-struct NoExtra {};
-template <int EPI> struct GemmExtra { typedef NoExtra type; };
-template <> struct GemmExtra<EPI_SWIGLU_RS> { typedef GemmRowScale type; };
-template <> struct GemmExtra<EPI_LOGPROB> { typedef GemmLogprob type; };
-template <> struct GemmExtra<EPI_QKV> { typedef GemmQkv type; };
-
 // M16: the products are 16x16x32 instructions (a: A[row l%16][k = 8*(l/16) .. +7], b likewise,
 // d[v]: D[row 4*(l/16) + v][col l%16]) instead of 32x32x16: the same fragment bytes per product volume, four
 // times as many accumulator tiles per wave.
@@ -586,81 +543,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
             }
         }
         return;
-    } else if constexpr (EPI == EPI_QKV) {
-        // A wave's columns lie within one head.  q and k: columns come in blocks of 32, 16 dims and their 16 rotary partners
-        // (dim + 64): two accumulator tiles that hold the same lanes' pairs.  The rotated 16-row tiles go through the wave's
-        // piece of the idle LDS ring and leave as 16-byte pieces (eight dims: contiguous in q and in a key's cache fragment).
-        // v: a lane's four dims of one token are four places of the cache; 16 lanes hold 16 rows, so a prompt's consecutive
-        // tokens leave as runs of eight.  The fp32 q | k | v rows (134 MB per layer at 16384 rows of the 1.5B shape, written
-        // and read again by a kernel of its own) never exist.
-        static_assert(M16, "lane layout of the 16x16x32 products");
-        constexpr int WC = BN / WN, HALF = WC / 2;
-        constexpr int PITCH = WC * 2 + 16, LPR = WC / 8, PIECES = 16 * LPR;
-        static_assert(WC % 32 == 0 && 128 % WC == 0, "whole 32-column blocks of one head");
-        static_assert((size_t)NW * 16 * PITCH <= (size_t)NSTAGE * STAGE_ELEMS * sizeof(T), "staging fits the ring");
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();   // every wave has consumed its last fragments
-        asm volatile("" ::: "memory");
-        unsigned char *stg = smem_raw + (size_t)wave * 16 * PITCH;
-        const int ml = lane % 16, nq = 4 * (lane / 16), col0 = n0 + wn * WC;
-        if (col0 >= N) return;
-        const int hkv = extra.kv.n_kv_heads, bs = extra.kv.block_size;
-        const int qd = extra.hq * 128, kvd = hkv * 128;
-        const int part = col0 < qd ? 0 : (col0 < qd + kvd ? 1 : 2);   // q, k, v (wave-uniform)
-        const int pc0 = col0 - (part == 0 ? 0 : (part == 1 ? qd : qd + kvd));
-        const int head = pc0 / 128, in = pc0 % 128;                   // first column inside the head
-        T *pool = (T *)extra.kv.pool + (int64_t)extra.layer * extra.kv.layer_stride + (int64_t)head * extra.kv.head_elems();
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int mt = m0 + wm * (BM / WM) + i * 16, row = mt + ml;
-            int pos = 0, blk = 0;
-            if (row < M) {
-                const int slot = extra.row_slot[row];
-                pos = extra.row_pos ? extra.row_pos[row] : extra.slot_len[slot];
-                if (part) blk = extra.kv.block_table[(int64_t)slot * extra.kv.max_blocks_per_slot + pos / bs];
-            }
-            const int tin = pos % bs;
-            uint32_t *const count = row < M ? sat : nullptr;          // (rows past the end are copies of the last one)
-            if (part == 2) {
-                if (row < M) {
-                    T *vd = pool + (int64_t)blk * extra.kv.block_elems();
-#pragma unroll
-                    for (int jj = 0; jj < TN; ++jj)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            vd[extra.kv.v_index(tin, in + 16 * jj + nq + v)] = from_f32_sat<T>(acc[i][jj][v], sat);
-                }
-                continue;
-            }
-#pragma unroll
-            for (int p2 = 0; p2 < TN / 2; ++p2) {
-                const int j = in / 2 + 16 * p2 + nq;                  // first of the lane's four pair indices
-                const f32x4_t c = *(const f32x4_t *)(extra.rope_cos + (int64_t)pos * 64 + j);
-                const f32x4_t sn = *(const f32x4_t *)(extra.rope_sin + (int64_t)pos * 64 + j);
-                const acc_t &x1 = acc[i][2 * p2], &x2 = acc[i][2 * p2 + 1];
-                unsigned char *dst = stg + ml * PITCH + (16 * p2 + nq) * 2;
-                *(u32x2 *)dst = pack4_sat<T>(x1[0] * c[0] - x2[0] * sn[0], x1[1] * c[1] - x2[1] * sn[1],
-                                             x1[2] * c[2] - x2[2] * sn[2], x1[3] * c[3] - x2[3] * sn[3], count);
-                *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(x2[0] * c[0] + x1[0] * sn[0], x2[1] * c[1] + x1[1] * sn[1],
-                                                          x2[2] * c[2] + x1[2] * sn[2], x2[3] * c[3] + x1[3] * sn[3], count);
-            }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int it = 0; it < (PIECES + 63) / 64; ++it) {
-                const int e = it * 64 + lane, r = (e / LPR) % 16, piece = e % LPR;
-                const u32x4 val = *(const u32x4 *)(stg + r * PITCH + piece * 16);
-                const int dim = in / 2 + (8 * piece) % HALF + 64 * ((8 * piece) / HALF);
-                const int rblk = __shfl(blk, r, 64), rtin = __shfl(tin, r, 64);
-                if (mt + r < M && (PIECES % 64 == 0 || e < PIECES)) {
-                    if (part == 0)
-                        *(u32x4 *)((T *)extra.q_out + ((int64_t)(mt + r) * extra.hq + head) * 128 + dim) = val;
-                    else
-                        *(u32x4 *)(pool + (int64_t)rblk * extra.kv.block_elems() + extra.kv.k_index(rtin, dim)) = val;
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-        return;
     } else {
     // ---- epilogue
     // The products take the weights as the row operand, so the accumulators hold the TRANSPOSED tile: a lane owns ONE
@@ -772,9 +654,7 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
                        const typename GemmExtra<E>::type &extra) {
         const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
         const int units = nb * split;
-        // (log-probabilities: the vocabulary is so wide that a die keeps to one weight slab for all its row blocks where no
-        // patches fit; in plain order every die streams all of the weights, 1640 rows x 151936 x 5120: 3001 against 2499 us)
-        const int plain = (split == 1 && mb > 4) ? ((mb % N_XCD == 0) ? 2 : (E == EPI_LOGPROB ? 0 : 1)) : 0;
+        const int plain = (split == 1 && mb > 4) ? ((mb % N_XCD == 0) ? 2 : 1) : 0;
         const unsigned grid = plain ? (unsigned)(mb * nb) : (unsigned)((units + N_XCD - 1) / N_XCD * N_XCD * mb);
         gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, E, M16><<<grid, 64 * WM * WN, smem, s>>>(
             (const T *)A, (const T *)W, C, M, N, K, mb, nb, split, plain, sat, extra);
@@ -796,7 +676,6 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
     }
     static void init_logprob() { set_attr<EPI_LOGPROB>(); }
     static int strips(int N) { return (N + BN - 1) / BN * WN; }
-    static void init_qkv() { set_attr<EPI_QKV>(); }
     // K slices so that the launch has about `want_blocks` blocks, each with >= 4 K tiles
     static int pick_split(int M, int N, int K, size_t slice_cap_floats, int want_blocks) {
         const int64_t tiles = (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM);
@@ -814,14 +693,12 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
 // The tile configurations.  All on 16x16x32 products (0 to 13 % faster than 32x32x16 at every decode shape measured) except
 // two whose wave tiles are a few 32x32 products only.
 template <typename T> struct Gemm {
-    // 256 x 128, 8 waves of 64 x 64: decode batches of 193 to 256 rows, prefill of narrow outputs
+    // 256 x 128, 8 waves of 64 x 64: decode batches of 193 to 256 rows
     typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> T256x128;
     typedef MfmaCfg<T, 256, 192, 4, 2, 2, 64, true> T256x192;
-    typedef MfmaCfg<T, 256, 256, 4, 2, 4, 32, true> T256x256;   // prefill; wave tile 64 x 128: three fragment reads per four products
     typedef MfmaCfg<T, 192, 128, 4, 2, 3, 64, true> T192x128;
     typedef MfmaCfg<T, 192, 192, 4, 2, 3, 64, true> T192x192;
     typedef MfmaCfg<T, 128, 128, 4, 2, 4, 64, true> T128x128;   // 8 waves of 32 x 64: up to 128 rows what counts is loads in flight
-    typedef MfmaCfg<T, 128, 128, 4, 2, 2, 64, true> T128x128_2; // two stages, 64 KB of LDS: two blocks per CU
     typedef MfmaCfg<T, 128, 192, 4, 2, 3, 64, true> T128x192;
     typedef MfmaCfg<T, 64, 128, 2, 4, 3, 64, true> T64x128;     // 72 KB of LDS: two blocks per CU
     typedef MfmaCfg<T, 64, 192, 4, 2, 4, 64, true> T64x192;
@@ -832,23 +709,18 @@ template <typename T> struct Gemm {
     typedef MfmaCfg<T, 192, 64, 4, 2, 4, 64, true> T192x64;     // the same in wave tiles of 48 x 32
     typedef MfmaCfg<T, 64, 64, 2, 2, 4> M64x64;                 // wave tile 32 x 32: many blocks for the small projections
     static void init() {
-        T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
-        T128x128_2::init(); T128x192::init(); T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init();
-        M128x128_3::init(); T128x64::init(); T192x64::init(); M64x64::init();
-        T256x256::init_logprob();
+        T256x128::init(); T256x192::init(); T192x128::init(); T192x192::init(); T128x128::init(); T128x192::init();
+        T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init(); M128x128_3::init(); T128x64::init();
+        T192x64::init(); M64x64::init();
         T256x128::init_logprob();
         T192x128::init_logprob();
         T128x128::init_logprob();
-        T64x128::init_qkv();
-        T128x128::init_qkv();
-        T256x256::init_qkv();
-        T256x128::init_qkv();
-        T128x128_2::init_qkv();
     }
 };
 void gemm_init() {
     Gemm<bf16_t>::init();
     Gemm<f16_t>::init();
+    gemm_large_init();
 }
 
 template <typename T>
@@ -869,37 +741,20 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
         else gemm_simt<f16_t>(A, W, C, M, N, K, epi, sat, s);
         return 1;
     }
+    if (M > 512) {
+        const int S = launch_gemm_large(dtype, A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s);
+        if (S) return S;
+    }
     if (dtype == KD_BF16) return gemm_mfma_dispatch<bf16_t>(A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
     return gemm_mfma_dispatch<f16_t>(A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
 }
 
 // ---- q | k | v projection with rotary positions and cache append
-template <typename T> static void gemm_qkv_t(const void *A, const void *W, int M, int N, int K, const GemmQkv &qkv, uint32_t *sat, hipStream_t s) {
-    typedef Gemm<T> G;
-    // The tallest grid that one round of blocks takes, one per CU, in the smallest tile for which it does: 1024 rows x 2048
-    // columns x 1536 in 64 x 128 tiles 17.3 us, in 128 x 128 22.1 us, in 128 x 128 two per CU 27.7 us, K slices and a rotating
-    // kernel behind them 22.3 us; 2048 rows 26.0 / 24.8 / 29.0 / 32.7 us; 640 rows x 6144 x 4096 54.8 / 47.8 / 64.7 / 68.4 us.
-    // Beyond one round the tile of the plain projection (gemm_mfma_dispatch).
-    const int nb128 = (N + 127) / 128;
-    if ((M + 63) / 64 * nb128 <= 256) G::T64x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
-    else if ((M + 127) / 128 * nb128 <= 256) G::T128x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
-    else if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) G::T256x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
-    else if ((int64_t)((M + 255) / 256) * ((N + 127) / 128) >= 160) G::T256x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
-    else G::T128x128_2::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
-}
-
 bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
                      hipStream_t s) {
     const int N = (qkv.hq + 2 * qkv.kv.n_kv_heads) * qkv.kv.head_dim;
     if (dtype == KD_F32 || impl == 0 || qkv.kv.head_dim != 128 || K % 64 != 0 || M <= 512) return false;
-    // (three row blocks of 256 that fill the chip once: with few rows to rotate a kernel of its own costs less than the
-    // epilogue of one block per CU, 69.9 us against 76.0 us at 513 rows x 7168 x 5120, 82.9 against 84.1 at 768; 91.9 against
-    // 87.4 at 896)
-    const int nb128 = (N + 127) / 128;
-    if (M <= 768 && 3 * nb128 >= 160 && (M + 127) / 128 * nb128 > 256) return false;
-    if (dtype == KD_BF16) gemm_qkv_t<bf16_t>(A, W, M, N, K, qkv, sat, s);
-    else gemm_qkv_t<f16_t>(A, W, M, N, K, qkv, sat, s);
-    return true;
+    return launch_gemm_large_qkv(dtype, A, W, M, N, K, qkv, sat, s);
 }
 
 // ---- log-probabilities straight from the vocabulary projection: a scoring pass wrote 622 MB of logits per 1024 rows of the
@@ -955,10 +810,12 @@ static void gemm_logprob_t(const void *A, const void *W, int M, int N, int K, Ge
         strips = decltype(cfg)::strips(N);
         decltype(cfg)::template launch<EPI_LOGPROB>(A, W, nullptr, M, N, K, 1, nullptr, s, lpa);
     };
-    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256 && M > 512) run(typename G::T256x256());   // as for the other wide projections
-    else if (M <= 128) run(typename G::T128x128());
-    else if (M <= 192) run(typename G::T192x128());
-    else run(typename G::T256x128());
+    if (M > 512) strips = launch_gemm_large_logprob(std::is_same<T, bf16_t>::value ? KD_BF16 : KD_F16, A, W, M, N, K, lpa, s);
+    if (strips == 0) {
+        if (M <= 128) run(typename G::T128x128());
+        else if (M <= 192) run(typename G::T192x128());
+        else run(typename G::T256x128());
+    }
     logprob_merge_kernel<<<(M + 15) / 16, 1024, 0, s>>>(lpa, M, N, strips, out);
 }
 
@@ -991,19 +848,7 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         else Cfg::run(A, W, C, M, N, K, epi, 1, sat, s);
         return split;
     };
-    if (M > 512) {   // prefill: plenty of tiles
-        // 256x256 tiles where they still come in several rounds per CU (the wide projections: +10 % measured);
-        // the narrow ones (1536 columns: 1.5 rounds of such tiles) keep 256x128
-        const int64_t wide_tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-        if (wide_tiles >= 2 * 256) return whole(typename G::T256x256());
-        // a large decode batch (a thousand rows) against a narrow projection leaves most CUs without a tile
-        // (1024 rows x 1536 columns: 48 tiles of 256x128): cut K into slices, as the small batches do.  A short reduction
-        // wants small tiles and few slices (1024 x 2048 x 1536: 14.0 us with two slices of 128x128 tiles, 20.3 with four of
-        // 256x128), a long one the larger tile (1024 x 1536 x 8960: 42.3 against 48.7 us)
-        const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 127) / 128);
-        if (tiles < 160 && can_split) return K < 3072 ? sliced(typename G::T128x128_2(), 240) : sliced(typename G::T256x128(), 240);
-        return whole(typename G::T256x128());
-    }
+    if (M > 512) return whole(typename G::T256x128());   // (what gemm_large.hip does not take: operands off 16-byte boundaries, K = 64)
     // decode: the weights are streamed once; fill the chip with blocks, by K slices where N is small
     const int nb128 = (N + 127) / 128, nb192 = (N + 191) / 192;
     // a long reduction amortises a block's fill and drain, and the tile with the most fragment reuse wins at

@@ -1,0 +1,627 @@
+// Projection GEMMs with many rows (prefill, scoring, decode batches of more than 512 sequences; Section 3.1 policy pi_theta):
+//   C[M,N] = A[M,K] * W[N,K]^T, fp32 accumulation, the epilogues of gemm.hip.
+#include <algorithm>
+
+#include "gemm_common.h"
+
+namespace pc {
+
+// 16x16x32 products whose accumulator lives in the accumulation registers (256 of a wave's 512 registers at one wave per
+// SIMD).  Written out because the compiler, left to itself, keeps such accumulators in the other half and moves them back and
+// forth (900 TFLOP/s at 8192^3 where this form reaches 1450).  `volatile` also keeps the order of the products and of the memory
+// operations between them as they stand in the source.  The results must not be read before the pipeline has drained
+// (mma_drain).
+template <typename T> struct AccMma;
+template <> struct AccMma<f16_t> {
+    __device__ static inline void first(f16x8_t a, f16x8_t b, f32x4_t &c) {   // c = a b
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+    }
+    __device__ static inline void add(f16x8_t a, f16x8_t b, f32x4_t &c) {     // c += a b
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    }
+};
+template <> struct AccMma<bf16_t> {
+    __device__ static inline void first(bf16x8_t a, bf16x8_t b, f32x4_t &c) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+    }
+    __device__ static inline void add(bf16x8_t a, bf16x8_t b, f32x4_t &c) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    }
+};
+__device__ inline f32x4_t acc_read(const f32x4_t &c) {
+    f32x4_t v;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[0]) : "a"(c[0]));
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[1]) : "a"(c[1]));
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[2]) : "a"(c[2]));
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[3]) : "a"(c[3]));
+    return v;
+}
+__device__ inline void mma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+__device__ inline void code_fence() { asm volatile("" ::: "memory"); }
+
+// Eight values to 16 bits, rounded to nearest even; what lies beyond the half range becomes infinite.
+template <typename T> constexpr bool range_limited() { return false; }   // whether there is such a range
+template <> constexpr bool range_limited<f16_t>() { return true; }
+template <typename T> __device__ inline u32x4 pack8(const float (&x)[8]);
+template <> __device__ inline u32x4 pack8<f16_t>(const float (&x)[8]) {
+    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+    u32x4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = __builtin_bit_cast(uint32_t, (f16x2){(_Float16)x[2 * e], (_Float16)x[2 * e + 1]});
+    return r;
+}
+template <> __device__ inline u32x4 pack8<bf16_t>(const float (&x)[8]) {
+    u32x4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = pack2<bf16_t>(x[2 * e], x[2 * e + 1]);
+    return r;
+}
+
+// How the weight rows of a wave's strip are dealt to its column tiles, i.e. which output columns a lane ends up with.  Lane
+// group g (lane / 16) of tile j holds, in element v, the product with weight row large_row(order, j, 4 g + v) of the strip.
+enum LargeOrder {
+    LO_PLAIN = 0,   // 16 j + r: four consecutive columns (fp32 stores of 16 bytes, row statistics)
+    LO_PAIRED = 1,  // weight rows come in chunks of 32 = 16 + their 16 partners (gate and up; a head's dims and their rotary
+                    // partners); four tiles (first, partner, first, partner) cover two chunks such that the lane's 2 x 4 values of
+                    // either kind are eight consecutive ones: 16-byte stores of 16-bit results without a trip through LDS
+};
+PC_HD inline int large_row(int order, int j, int r) {
+    if (order == LO_PLAIN) return 16 * j + r;
+    const int o = 8 * (r / 4) + 4 * ((j / 2) % 2) + r % 4;           // place among the 32 firsts (partners) of the two chunks
+    return 64 * (j / 4) + 32 * (o / 16) + 16 * (j % 2) + o % 16;
+}
+
+// Work decomposition: 256 threads, four waves in a square, one block per CU; a block computes a tile of 128 TMH/2 .. rows x
+// columns after another (`run` of them), a wave a quarter of it, (32 TMH) x (32 TNH) outputs.
+//
+// Why this shape.  The products need 256 x 256 x 64 x 2 flop per 64 k, 2048 clocks of the matrix cores at best; the same tile on
+// eight waves of 64 x 128 asks LDS for 192 KB of fragments per 64 k and 64 KB of fills, which takes about as long as the
+// products and does not overlap with them entirely.  Four waves of 128 x 128 need 128 KB.  (8192^3 in half: eight waves 1190
+// TFLOP/s, four 1450; the vendor's library 1476.)
+//
+// Data path: an operand tile of 64 k is cut into two units, the halves h = 0, 1 of every wave's rows (columns); A0, A1, W0, W1.
+// A wave multiplies quadrant by quadrant, (A0 W0) (A0 W1) (A1 W1) (A1 W0), and while one quadrant's products run it reads the
+// one unit that the next quadrant needs anew: W1, A1, then A0 and W0 of the next 64 k.  Units are fetched in that order too,
+// two to a pair, into a ring of NP pairs in LDS (buffer loads that write LDS directly; the 16-byte chunk c of row r is stored at
+// c ^ (r / 2) % 8, which makes fragment reads conflict free).  One barrier per pair: behind it the pair is there and the slot
+// of the pair before it is free and takes the pair NP places on.  The ring runs on across output tiles: the last products of one
+// run over the first loads of the next, so only a block's first tile waits for memory; a tile after that costs its products and
+// its epilogue.  (Rows past the end read as zero through the buffer's bounds, stores past the end are dropped by them.)
+template <typename T, int TMH, int TNH, int NP, int EPI>
+__global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict__ A, const T *__restrict__ W,
+                                                            void *__restrict__ Cv, int M, int N, int K, int mb, int nb,
+                                                            int S, int bh, int run, uint32_t *__restrict__ sat,
+                                                            typename GemmExtra<EPI>::type extra) {
+#if defined(__HIP_DEVICE_COMPILE__)   // (the buffer descriptor's type does not exist in the host pass)
+    constexpr int BM = 64 * TMH, BN = 64 * TNH, BK = 64, SM = BM / 2, SN = BN / 2;   // tile, K step, a wave's part
+    constexpr int LA = BM / 64, LW = BN / 64, L = LA + LW;    // wave-wide 1 KB loads per wave for a unit of A, of W, for a pair
+    constexpr int UA = SM * BK, PAIR = (SM + SN) * BK;        // elements
+    constexpr int ORDER = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? LO_PAIRED : LO_PLAIN;
+    static_assert(ORDER == LO_PLAIN || TNH % 2 == 0, "whole pairs of chunks per wave");
+    static_assert(EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_SWIGLU || EPI == EPI_QKV || EPI == EPI_LOGPROB, "epilogue");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+    T *smem = (T *)smem_raw;
+
+    const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wm = wave / 2, wn = wave % 2;
+
+    struct Tile {   // (wave-uniform)
+        int m0, n0, z, kt;
+        const T *a, *w;
+        uint32_t a_bytes, w_bytes;
+    };
+    const int KT = K / BK, per = (KT + S - 1) / S;
+    auto locate = [&](int i, Tile &t) {
+        int bm, bn;
+        if (!gemm_band_tile(blockIdx.x, i, run, mb, nb, S, bh, &bm, &bn, &t.z)) return false;
+        t.m0 = bm * BM;
+        t.n0 = bn * BN;
+        const int k0 = t.z * per;
+        t.kt = min(KT, k0 + per) - k0;
+        t.a = A + (int64_t)t.m0 * K + (int64_t)k0 * BK;
+        t.w = W + (int64_t)t.n0 * K + (int64_t)k0 * BK;
+        t.a_bytes = ((uint32_t)min(M - t.m0, BM) * (uint32_t)K - (uint32_t)(k0 * BK)) * 2u;   // up to the end of the last row
+        t.w_bytes = ((uint32_t)min(N - t.n0, BN) * (uint32_t)K - (uint32_t)(k0 * BK)) * 2u;
+        return true;
+    };
+
+    // ---- global -> LDS: a wave-wide load fills 8 rows of 64 k; load i of wave w the unit's rows 32 i + 8 w .. + 7.
+    // Row u of a unit of half h: rows (columns) of wave row (column) u / (S / 2), half h.
+    const int lr = lane / 8, slot8 = lane % 8;
+    uint32_t va[2][LA], vw[2][LW];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const int u = 32 * i + 8 * wave + lr;
+            const int row = (u / (SM / 2)) * SM + h * (SM / 2) + u % (SM / 2);
+            va[h][i] = (uint32_t)row * (uint32_t)K * 2u + (uint32_t)(slot8 ^ ((u / 2) & 7)) * 16u;
+        }
+#pragma unroll
+        for (int i = 0; i < LW; ++i) {
+            const int u = 32 * i + 8 * wave + lr;
+            const int in = h * (SN / 2) + u % (SN / 2);
+            const int row = (u / (SN / 2)) * SN + large_row(ORDER, in / 16, in % 16);
+            vw[h][i] = (uint32_t)row * (uint32_t)K * 2u + (uint32_t)(slot8 ^ ((u / 2) & 7)) * 16u;
+        }
+    }
+    Tile cur, nxt;
+    bool more = false;
+    // load q of the unit of half h of K step t, counted from the current tile's first: steps past its end are the next tile's,
+    // or nothing (a buffer of no bytes: the counter of loads in flight goes on, no memory is touched)
+    auto load_a = [&](int t, int slot, int h, int q) {
+        const bool in = t < cur.kt;
+        const T *base = in ? cur.a : nxt.a;
+        const uint32_t bytes = in ? cur.a_bytes : (more ? nxt.a_bytes : 0u);
+        const int off = in ? t : (more ? t - cur.kt : 0);
+        __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            r, (__attribute__((address_space(3))) void *)(smem + slot * PAIR + (32 * q + 8 * wave) * BK), 16, va[h][q], off * (BK * 2), 0, 0);
+    };
+    auto load_w = [&](int t, int slot, int h, int q) {
+        const bool in = t < cur.kt;
+        const T *base = in ? cur.w : nxt.w;
+        const uint32_t bytes = in ? cur.w_bytes : (more ? nxt.w_bytes : 0u);
+        const int off = in ? t : (more ? t - cur.kt : 0);
+        __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            r, (__attribute__((address_space(3))) void *)(smem + slot * PAIR + UA + (32 * q + 8 * wave) * BK), 16, vw[h][q], off * (BK * 2), 0, 0);
+    };
+
+    // ---- LDS -> registers
+    typedef typename Mma<T>::frag frag_t;
+    const int fr = lane % 16, fg = lane / 16;
+    int offa[2], offw[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        const int o = fr * BK + (((4 * kk + fg) ^ ((fr / 2) & 7)) * 8);
+        offa[kk] = o + wm * (SM / 2) * BK;
+        offw[kk] = o + UA + wn * (SN / 2) * BK;
+    }
+    auto read_a = [&](int slot, frag_t (&f)[2][TMH], int q) {
+        f[q / TMH][q % TMH] = *(const frag_t *)(smem + slot * PAIR + offa[q / TMH] + (q % TMH) * 16 * BK);
+    };
+    auto read_w = [&](int slot, frag_t (&f)[2][TNH], int q) {
+        f[q / TNH][q % TNH] = *(const frag_t *)(smem + slot * PAIR + offw[q / TNH] + (q % TNH) * 16 * BK);
+    };
+
+    // ---- products
+    f32x4_t acc[2 * TMH][2 * TNH];
+    frag_t fa0[2][TMH], fa1[2][TMH], fbx[2][TNH], fby[2][TNH];
+    constexpr int MM = 2 * TMH * TNH;   // products of a quadrant
+    // one quadrant; NR fragment reads spread over its first half, NL loads over all of it
+#define PC_QUADRANT(FIRST, FA, FB, HA, HB, NR, READ, NL, LOAD)                                              \
+    do {                                                                                                    \
+        constexpr int RS = (MM / 2) / (NR) > 1 ? (MM / 2) / (NR) : 1, LS = MM / (NL);               \
+        _Pragma("unroll") for (int e = 0; e < MM; ++e) {                                                    \
+            const int kk = e / (TMH * TNH), ti = (e / TNH) % TMH, tj = e % TNH;                             \
+            f32x4_t &c = acc[HA * TMH + ti][HB * TNH + tj];                                                 \
+            if (FIRST && kk == 0) AccMma<T>::first(FB[kk][tj], FA[kk][ti], c);                              \
+            else AccMma<T>::add(FB[kk][tj], FA[kk][ti], c);                                                 \
+            if (e % RS == RS - 1 && e / RS < (NR)) { const int q = e / RS; READ; }                          \
+            if (e % LS == LS / 2 && e / LS < (NL)) { const int q = e / LS; LOAD; }                          \
+        }                                                                                                   \
+    } while (0)
+    // The pair about to be read has landed when at most the loads of the NP - 2 pairs behind it are in flight.  (An epilogue's
+    // stores count too; leaving them in flight over the first syncs of the next tile, or writing its results over the next
+    // tile's first steps, gained nothing: what stores there are slow the loads wherever they stand.)
+    auto sync = [&]() {
+        wait_vmcnt_le<(NP - 2) * L>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's fragments are in registers
+        code_fence();
+        __builtin_amdgcn_s_barrier();         // (a bare one: __syncthreads() would drain the loads in flight)
+        code_fence();
+    };
+    auto next = [&](int s) { return s + 1 == NP ? 0 : s + 1; };
+    // Pairs in reading order: p = 2t: (W1, A1) of K step t; 2t + 1: (A0, W0) of step t + 1.  Behind the sync of pair p the slot of
+    // pair p - 1 takes pair p - 1 + NP.
+    constexpr int H0 = (NP % 2 == 0) ? 0 : 1, H1 = 1 - H0;   // the halves in pairs 2t - 1 + NP and 2t + NP
+    auto step = [&](auto first, int t, int free, int s0, int s1, frag_t (&fb0)[2][TNH], frag_t (&fb1)[2][TNH]) {
+        constexpr bool FIRST = decltype(first)::value;
+        const int t0 = t + NP / 2, t1 = t + (NP + 1) / 2;
+        sync();
+        PC_QUADRANT(FIRST, fa0, fb0, 0, 0, 2 * TNH, read_w(s0, fb1, q), LA, load_a(t0, free, H0, q));
+        PC_QUADRANT(FIRST, fa0, fb1, 0, 1, 2 * TMH, read_a(s0, fa1, q), LW, load_w(t0, free, H0, q));
+        sync();
+        PC_QUADRANT(FIRST, fa1, fb1, 1, 1, 2 * TMH, read_a(s1, fa0, q), LW, load_w(t1, s0, H1, q));
+        PC_QUADRANT(FIRST, fa1, fb0, 1, 0, 2 * TNH, read_w(s1, fb1, q), LA, load_a(t1, s0, H1, q));
+    };
+#undef PC_QUADRANT
+    if (!locate(0, cur)) return;
+    nxt = cur;
+#pragma unroll
+    for (int p = -1; p < NP - 1; ++p) {
+        const int t = (p + 1) >> 1, h = (p & 1) ? 0 : 1;
+#pragma unroll
+        for (int q = 0; q < LA; ++q) load_a(t, p + 1, h, q);
+#pragma unroll
+        for (int q = 0; q < LW; ++q) load_w(t, p + 1, h, q);
+    }
+    wait_vmcnt_le<(NP - 1) * L>();
+    code_fence();
+    __builtin_amdgcn_s_barrier();
+    code_fence();
+#pragma unroll
+    for (int q = 0; q < 2 * TMH; ++q) read_a(0, fa0, q);
+#pragma unroll
+    for (int q = 0; q < 2 * TNH; ++q) read_w(0, fbx, q);
+
+    int slot = 0;   // of the pair read last
+    for (int i = 0;; ++i) {
+        more = i + 1 < run && locate(i + 1, nxt);
+        auto advance = [&](auto first, int t, frag_t (&fb0)[2][TNH], frag_t (&fb1)[2][TNH]) {
+            const int s0 = next(slot), s1 = next(s0);
+            step(first, t, slot, s0, s1, fb0, fb1);
+            slot = s1;
+        };
+        advance(std::true_type{}, 0, fbx, fby);
+        int t = 1;
+        for (; t + 1 < cur.kt; t += 2) {
+            advance(std::false_type{}, t, fby, fbx);
+            advance(std::false_type{}, t + 1, fbx, fby);
+        }
+        if (t < cur.kt) {
+            advance(std::false_type{}, t, fby, fbx);
+        } else {   // an odd number of steps: the next tile's first W fragments are in the other set
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int j = 0; j < TNH; ++j) fbx[kk][j] = fby[kk][j];
+        }
+        mma_drain();
+#pragma unroll
+        for (int i2 = 0; i2 < 2 * TMH; ++i2)
+#pragma unroll
+            for (int j = 0; j < 2 * TNH; ++j) asm volatile("" : "+a"(acc[i2][j]));
+        if (!more) wait_vmcnt_le<0>();   // nothing may still be writing LDS when the block retires
+        code_fence();
+
+        // ---- epilogue: lane (ml, g) owns row ml of every row tile; of column tile j the four columns of large_row(j, 4g ..)
+        // (rolled up by row tiles, their values taken out of the accumulation registers by a branch each: written out, an epilogue
+        // is 10 to 20 KB of code that runs once per tile, and fetching it took longer than executing it)
+        const int ml = lane % 16, g = lane / 16;
+        auto take = [&](int i2, f32x4_t (&v)[2 * TNH]) {
+#pragma unroll
+            for (int k = 0; k < 2 * TMH; ++k)
+                if (i2 == k) {
+#pragma unroll
+                    for (int j = 0; j < 2 * TNH; ++j) v[j] = acc_read(acc[k][j]);
+                }
+        };
+        const int m0 = cur.m0 + wm * SM, n0 = cur.n0 + wn * SN;   // the wave's first row and column
+        if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) {
+            float *C = (float *)Cv + ((EPI == EPI_STORE_F32) ? (int64_t)cur.z * M * N : 0) + (int64_t)cur.m0 * N;
+            __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)C, 0, (int)((uint32_t)min(M - cur.m0, BM) * (uint32_t)N * 4u), 0x00020000);
+            auto place = [&](uint32_t row_off, int j) {   // of the lane's four columns of tile j
+                const int col = n0 + 16 * j + 4 * g;
+                return (int)(col < N ? row_off + (uint32_t)col * 4u : 0xFFFFFFF0u);
+            };
+            uint32_t row_off = (uint32_t)(wm * SM + ml) * (uint32_t)N * 4u;
+            if constexpr (EPI == EPI_STORE_F32) {
+#pragma unroll
+                for (int i2 = 0; i2 < 2 * TMH; ++i2) {
+#pragma unroll
+                    for (int j = 0; j < 2 * TNH; ++j)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i2][j]), rc, place(row_off, j), 0, 0);
+                    row_off += 16u * (uint32_t)N * 4u;
+                }
+            } else {
+                constexpr int D = TMH;   // row tiles whose old values are under way
+                u32x4 old[D][2 * TNH];
+                const uint32_t tile_off = 16u * (uint32_t)N * 4u;
+#pragma unroll
+                for (int d = 0; d < D; ++d)
+#pragma unroll
+                    for (int j = 0; j < 2 * TNH; ++j)
+                        old[d][j] = __builtin_amdgcn_raw_buffer_load_b128(rc, place(row_off + d * tile_off, j), 0, 0);
+#pragma unroll
+                for (int i2 = 0; i2 < 2 * TMH; ++i2) {
+#pragma unroll
+                    for (int j = 0; j < 2 * TNH; ++j) {
+                        const f32x4_t sum = __builtin_bit_cast(f32x4_t, old[i2 % D][j]) + acc_read(acc[i2][j]);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, sum), rc, place(row_off, j), 0, 0);
+                        if (i2 + D < 2 * TMH)
+                            old[i2 % D][j] = __builtin_amdgcn_raw_buffer_load_b128(rc, place(row_off + D * tile_off, j), 0, 0);
+                    }
+                    row_off += tile_off;
+                }
+            }
+        } else if constexpr (EPI == EPI_SWIGLU) {
+            const int ldc = N / 2;
+            T *C = (T *)Cv + (int64_t)cur.m0 * ldc;
+            __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)C, 0, (int)((uint32_t)min(M - cur.m0, BM) * (uint32_t)ldc * 2u), 0x00020000);
+            uint32_t row_off = (uint32_t)(wm * SM + ml) * (uint32_t)ldc * 2u;
+#pragma unroll 1
+            for (int i2 = 0; i2 < 2 * TMH; ++i2) {
+                f32x4_t x[2 * TNH];
+                take(i2, x);
+                // converted unchecked, and again with clamps and their count if anything of the row tile may be beyond the half range
+                u32x4 out[TNH / 2];
+                float sum = 0.f;
+#pragma unroll
+                for (int c = 0; c < TNH / 2; ++c) {
+                    float y[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        y[e] = silu_mul(x[4 * c + 2 * (e / 4)][e % 4], x[4 * c + 2 * (e / 4) + 1][e % 4]);
+                        sum += fabsf(y[e]);
+                    }
+                    out[c] = pack8<T>(y);
+                }
+                if (range_limited<T>() && !__all(sum <= 65504.f)) {
+#pragma unroll
+                    for (int c = 0; c < TNH / 2; ++c) {
+                        // clamps are counted where stored
+                        uint32_t *const count = n0 / 2 + 32 * c + 8 * g < ldc && m0 + 16 * i2 + ml < M ? sat : nullptr;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const f32x4_t &ga = x[4 * c + 2 * (e / 2)], &ua = x[4 * c + 2 * (e / 2) + 1];
+                            out[c][e] = pack2_sat<T>(silu_mul(ga[2 * (e % 2)], ua[2 * (e % 2)]),
+                                                     silu_mul(ga[2 * (e % 2) + 1], ua[2 * (e % 2) + 1]), count);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < TNH / 2; ++c) {
+                    const int col = n0 / 2 + 32 * c + 8 * g;
+                    __builtin_amdgcn_raw_buffer_store_b128(out[c], rc, (int)(col < ldc ? row_off + (uint32_t)col * 2u : 0xFFFFFFF0u), 0, 0);
+                }
+                row_off += 16u * (uint32_t)ldc * 2u;
+            }
+        } else if constexpr (EPI == EPI_QKV) {
+            // a wave's columns lie within one head (128 of them, or its first or second 64)
+            static_assert(128 % SN == 0, "a strip lies within one head");
+            if (n0 < N) {
+                const int hkv = extra.kv.n_kv_heads, bs = extra.kv.block_size;
+                const int qd = extra.hq * 128, kvd = hkv * 128;
+                const int part = n0 < qd ? 0 : (n0 < qd + kvd ? 1 : 2);   // q, k, v (wave-uniform)
+                const int pc0 = n0 - (part == 0 ? 0 : (part == 1 ? qd : qd + kvd));
+                const int head = pc0 / 128, in = pc0 % 128;               // first column inside the head
+                T *pool = (T *)extra.kv.pool + (int64_t)extra.layer * extra.kv.layer_stride + (int64_t)head * extra.kv.head_elems();
+#pragma unroll 1
+                for (int i2 = 0; i2 < 2 * TMH; ++i2) {
+                    f32x4_t x[2 * TNH];
+                    take(i2, x);
+                    const int row = m0 + 16 * i2 + ml;
+                    if (row >= M) continue;
+                    const int sl = extra.row_slot[row];
+                    const int pos = extra.row_pos ? extra.row_pos[row] : extra.slot_len[sl];
+                    const int blk = part ? extra.kv.block_table[(int64_t)sl * extra.kv.max_blocks_per_slot + pos / bs] : 0;
+                    const int tin = pos % bs;
+                    T *block = pool + (int64_t)blk * extra.kv.block_elems();
+                    if (part == 2) {
+#pragma unroll
+                        for (int j = 0; j < 2 * TNH; ++j)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                block[extra.kv.v_index(tin, in + large_row(ORDER, j, 4 * g + v))] = from_f32_sat<T>(x[j][v], sat);
+                        continue;
+                    }
+#pragma unroll
+                    for (int c = 0; c < TNH / 2; ++c) {
+                        const int j0 = in / 2 + 32 * c + 8 * g;           // the lane's eight pair indices
+                        u32x2 lo[2], hi[2];
+#pragma unroll
+                        for (int s = 0; s < 2; ++s) {
+                            const f32x4_t cs = *(const f32x4_t *)(extra.rope_cos + (int64_t)pos * 64 + j0 + 4 * s);
+                            const f32x4_t sn = *(const f32x4_t *)(extra.rope_sin + (int64_t)pos * 64 + j0 + 4 * s);
+                            const f32x4_t &x1 = x[4 * c + 2 * s], &x2 = x[4 * c + 2 * s + 1];
+                            lo[s] = pack4_sat<T>(x1[0] * cs[0] - x2[0] * sn[0], x1[1] * cs[1] - x2[1] * sn[1],
+                                                 x1[2] * cs[2] - x2[2] * sn[2], x1[3] * cs[3] - x2[3] * sn[3], sat);
+                            hi[s] = pack4_sat<T>(x2[0] * cs[0] + x1[0] * sn[0], x2[1] * cs[1] + x1[1] * sn[1],
+                                                 x2[2] * cs[2] + x1[2] * sn[2], x2[3] * cs[3] + x1[3] * sn[3], sat);
+                        }
+                        const u32x4 a = {lo[0][0], lo[0][1], lo[1][0], lo[1][1]}, b = {hi[0][0], hi[0][1], hi[1][0], hi[1][1]};
+                        T *dst = part == 0 ? (T *)extra.q_out + ((int64_t)row * extra.hq + head) * 128 : block;
+                        *(u32x4 *)(dst + (part == 0 ? j0 : extra.kv.k_index(tin, j0))) = a;   // (eight dims are contiguous in both)
+                        *(u32x4 *)(dst + (part == 0 ? j0 + 64 : extra.kv.k_index(tin, j0 + 64))) = b;
+                    }
+                }
+            }
+        } else {
+            // EPI_LOGPROB: maximum and, in double, sum of the exponentials of a row over the wave's strip of columns; the lane's
+            // three partners (16, 32, 48 lanes on) hold the rest of the row's strip
+            const int64_t strip = (int64_t)(n0 / SN);
+            const int nq = 4 * g;
+#pragma unroll 1
+            for (int i2 = 0; i2 < 2 * TMH; ++i2) {
+                f32x4_t x[2 * TNH];
+                take(i2, x);
+                const int row = m0 + 16 * i2 + ml;
+                const int want = row < M ? extra.tokens[extra.token_index[row] + 1] - n0 - nq : -1;   // (column - nq) of the target
+                if (__any(want >= 0 && want < SN)) {   // (rare: a row's target is in one of a thousand strips)
+#pragma unroll
+                    for (int j = 0; j < 2 * TNH; ++j)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (want == j * 16 + v && n0 + j * 16 < N) extra.target[row] = x[j][v];
+                }
+                float mx = -INFINITY;
+#pragma unroll
+                for (int j = 0; j < 2 * TNH; ++j) {
+                    x[j] *= extra.inv_t;
+                    if (n0 + j * 16 < N) mx = fmaxf(mx, fmaxf(fmaxf(x[j][0], x[j][1]), fmaxf(x[j][2], x[j][3])));   // N is a multiple of 16
+                }
+                mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                const float base = (mx == -INFINITY) ? 0.f : mx;
+                double s = 0.0;
+#pragma unroll
+                for (int j = 0; j < 2 * TNH; ++j)
+                    if (n0 + j * 16 < N) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) s += (double)exp_neg(x[j][v] - base);
+                    }
+                s += __shfl_xor(s, 16, 64);
+                s += __shfl_xor(s, 32, 64);
+                if (row < M && nq == 0) {
+                    extra.part_max[strip * M + row] = mx;
+                    extra.part_sum[strip * M + row] = s;
+                }
+            }
+        }
+        code_fence();
+        if (!more) break;
+        cur = nxt;
+    }
+#endif
+}
+
+template <typename T, int TMH, int TNH> struct LargeCfg {
+    static constexpr int BM = 64 * TMH, BN = 64 * TNH, NP = 4;
+    static constexpr size_t smem = (size_t)NP * (BM + BN) * 64;   // a pair holds half of the rows, 2 bytes an element
+    template <int E> static void set_attr() {
+        (void)hipFuncSetAttribute((const void *)gemm_large_kernel<T, TMH, TNH, NP, E>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    }
+    template <int E>
+    static void launch(const void *A, const void *W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s,
+                       const typename GemmExtra<E>::type &extra) {
+        const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
+        int bh, run;
+        const unsigned grid = gemm_band_grid(mb, nb, S, &bh, &run);
+        gemm_large_kernel<T, TMH, TNH, NP, E><<<grid, 256, smem, s>>>((const T *)A, (const T *)W, C, M, N, K, mb, nb, S, bh, run, sat, extra);
+    }
+};
+
+// ---- which tile, how many K slices
+// Estimated microseconds of a launch: rounds of blocks (one per CU) times K steps times the time of a step, plus what the first
+// and each further tile of a block cost beside their steps.  A step takes longer the more CUs are busy (`load`: the clock falls under
+// the matrix cores' power, 2.0 PFLOP/s on operands of zeros and 1.45 on random ones); K slices are written and read once more.
+// The constants are a least-regret fit to 96 shapes of 520 to 16384 rows x 1536 to 151936 columns x 1536 to 17408 in every tile
+// and up to 8 slices: what it chooses takes 0.5 % longer on average than the best of them, 8 % at worst but for one (640 x 5120 x
+// 5120 where it may not slice: 22 %).
+struct LargeTile {
+    int id, bm, bn;
+    double step, load, fixed;
+};
+enum { LT_256x256, LT_256x192, LT_192x256, LT_256x128, LT_192x128, LT_128x128 };
+static const LargeTile LARGE_TILES[] = {
+    {LT_256x256, 256, 256, 1.11, 0.37, 15.6}, {LT_256x192, 256, 192, 0.78, 0.57, 12.4}, {LT_192x256, 192, 256, 0.88, 0.55, 9.7},
+    {LT_256x128, 256, 128, 0.54, 0.76, 11.4}, {LT_192x128, 192, 128, 0.505, 0.355, 12.5}, {LT_128x128, 128, 128, 0.36, 0.73, 6.2},
+};
+static double large_cost(const LargeTile &t, int S, int M, int N, int K, int epi) {
+    const int KT = K / 64, per = (KT + S - 1) / S;
+    const int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * S, rounds = (tiles + 255) / 256;
+    const double busy = (double)tiles / (256.0 * (double)rounds);
+    const double fixed = epi == EPI_RESID_F32 ? t.fixed : 0.75 * t.fixed;
+    return (double)rounds * per * t.step * (1.0 + t.load * busy * busy) + fixed + (double)(rounds - 1) * std::max(0.0, fixed - 6.0) +
+           (S > 1 ? (double)S * M * N * 4.0 / 4.5e6 : 0.0);
+}
+static int large_pick(std::initializer_list<int> among, int max_slices, int M, int N, int K, int epi, int *S) {
+    const int KT = K / 64;
+    int best = -1;
+    double best_cost = 0.0;
+    for (int id : among)
+        for (int n = 1; n <= max_slices; ++n) {
+            const int per = (KT + n - 1) / n;
+            if (n > 1 && (per < 4 || KT - (n - 1) * per < 2)) continue;   // (two steps at least: the ring reaches that far ahead)
+            const double c = large_cost(LARGE_TILES[id], n, M, N, K, epi);
+            if (best < 0 || c < best_cost) {
+                best = id;
+                best_cost = c;
+                *S = n;
+            }
+        }
+    return best;
+}
+
+static bool large_ok(const void *A, const void *W, const void *C, int M, int N, int K) {
+    // (rows of operands and results in whole 16-byte pieces; a tile's bytes within a buffer descriptor's 32 bits)
+    return M > 512 && K % 64 == 0 && K >= 128 && N % 16 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)C) & 15) == 0 &&
+           K <= (1 << 21) && N <= (1 << 21);
+}
+
+template <typename T> struct Large {
+    typedef LargeCfg<T, 4, 4> T256x256;
+    typedef LargeCfg<T, 4, 3> T256x192;
+    typedef LargeCfg<T, 3, 4> T192x256;
+    typedef LargeCfg<T, 4, 2> T256x128;
+    typedef LargeCfg<T, 3, 2> T192x128;
+    typedef LargeCfg<T, 2, 2> T128x128;
+    template <int E> static void init_plain() {
+        T256x256::template set_attr<E>(); T256x192::template set_attr<E>(); T192x256::template set_attr<E>();
+        T256x128::template set_attr<E>(); T192x128::template set_attr<E>(); T128x128::template set_attr<E>();
+    }
+    static void init() {
+        init_plain<EPI_STORE_F32>();
+        init_plain<EPI_RESID_F32>();
+        T256x256::template set_attr<EPI_SWIGLU>(); T192x256::template set_attr<EPI_SWIGLU>(); T192x128::template set_attr<EPI_SWIGLU>();
+        T256x256::template set_attr<EPI_QKV>(); T192x256::template set_attr<EPI_QKV>(); T192x128::template set_attr<EPI_QKV>();
+        T128x128::template set_attr<EPI_QKV>();
+        T256x256::template set_attr<EPI_LOGPROB>(); T192x256::template set_attr<EPI_LOGPROB>();
+    }
+    template <int E>
+    static void plain(int id, const void *A, const void *W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s) {
+        switch (id) {
+            case LT_256x256: T256x256::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
+            case LT_256x192: T256x192::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
+            case LT_192x256: T192x256::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
+            case LT_256x128: T256x128::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
+            case LT_192x128: T192x128::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
+            default: T128x128::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
+        }
+    }
+    static int gemm(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap, uint32_t *sat,
+                    hipStream_t s) {
+        int S = 1;
+        if (epi == EPI_SWIGLU) {
+            const int id = large_pick({LT_256x256, LT_192x256, LT_192x128}, 1, M, N, K, epi, &S);
+            if (id == LT_256x256) T256x256::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
+            else if (id == LT_192x256) T192x256::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
+            else T192x128::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
+            return 1;
+        }
+        const int max_slices = slices ? (int)std::min<size_t>(8, slice_cap / ((size_t)M * N)) : 1;
+        const int id = large_pick({LT_256x256, LT_256x192, LT_192x256, LT_256x128, LT_192x128, LT_128x128}, std::max(1, max_slices), M, N, K,
+                                  epi, &S);
+        if (S > 1) plain<EPI_STORE_F32>(id, A, W, slices, M, N, K, S, sat, s);
+        else if (epi == EPI_RESID_F32) plain<EPI_RESID_F32>(id, A, W, C, M, N, K, 1, sat, s);
+        else plain<EPI_STORE_F32>(id, A, W, C, M, N, K, 1, sat, s);
+        return S;
+    }
+    static void qkv(const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
+        int S = 1;
+        switch (large_pick({LT_256x256, LT_192x256, LT_192x128, LT_128x128}, 1, M, N, K, EPI_QKV, &S)) {
+            case LT_256x256: T256x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
+            case LT_192x256: T192x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
+            case LT_192x128: T192x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
+            default: T128x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
+        }
+    }
+    static int logprob(const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
+        int S = 1;
+        if (large_pick({LT_256x256, LT_192x256}, 1, M, N, K, EPI_LOGPROB, &S) == LT_256x256)
+            T256x256::template launch<EPI_LOGPROB>(A, W, nullptr, M, N, K, 1, nullptr, s, lp);
+        else
+            T192x256::template launch<EPI_LOGPROB>(A, W, nullptr, M, N, K, 1, nullptr, s, lp);
+        return (N + 255) / 256 * 2;   // strips of 128 columns
+    }
+};
+
+void gemm_large_init() {
+    Large<bf16_t>::init();
+    Large<f16_t>::init();
+}
+
+int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap,
+                      uint32_t *sat, hipStream_t s) {
+    if ((epi != EPI_STORE_F32 && epi != EPI_RESID_F32 && epi != EPI_SWIGLU) || !large_ok(A, W, C, M, N, K) ||
+        ((uintptr_t)slices & 15) != 0 || (epi == EPI_SWIGLU && N % 64 != 0))
+        return 0;
+    if (dtype == KD_BF16) return Large<bf16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s);
+    return Large<f16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s);
+}
+
+bool launch_gemm_large_qkv(int dtype, const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
+    if (!large_ok(A, W, nullptr, M, N, K)) return false;
+    if (dtype == KD_BF16) Large<bf16_t>::qkv(A, W, M, N, K, q, sat, s);
+    else Large<f16_t>::qkv(A, W, M, N, K, q, sat, s);
+    return true;
+}
+
+int launch_gemm_large_logprob(int dtype, const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
+    if (!large_ok(A, W, nullptr, M, N, K)) return 0;
+    return dtype == KD_BF16 ? Large<bf16_t>::logprob(A, W, M, N, K, lp, s) : Large<f16_t>::logprob(A, W, M, N, K, lp, s);
+}
+
+}   // namespace pc

@@ -2,6 +2,8 @@
 // build of the tests checks them exhaustively on the CPU).
 #pragma once
 
+#include <stdint.h>
+
 #if defined(__HIPCC__) || defined(__CUDACC__)
 #define PC_HD __host__ __device__
 #else
@@ -44,6 +46,35 @@ PC_HD inline bool gemm_patch_tile(int id, int mb, int nb, int *bm, int *bn) {
     *bm = die * rows_per + sg * ph + r % ph;
     *bn = 8 * cg + r / ph;
     return true;
+}
+
+// ---- GEMM in runs of tiles: workgroup -> its i-th output tile (of `run`), K slice included.  The mb x nb x S tiles are walked
+// in bands of `bh` row blocks (the last one may be lower), a band column by column; every die takes one eighth of that walk
+// and its workgroups, 32 at a time (one per CU), neighbouring places of it: they share bh activation and 32 / bh weight slabs
+// through the die's L2.  False: no such tile.
+PC_HD inline bool gemm_band_tile(int block, int i, int run, int mb, int nb, int S, int bh, int *bm, int *bn, int *z) {
+    const int die = block % 8, j = block / 8;
+    const int64_t total = (int64_t)mb * nb * S, share = (total + 7) / 8;
+    const int64_t pos = (int64_t)(j / 32) * 32 * run + 32 * i + j % 32, p = die * share + pos;
+    if (pos >= share || p >= total) return false;
+    const int nu = nb * S, band = (int)(p / ((int64_t)bh * nu));
+    const int h = (mb - band * bh < bh) ? mb - band * bh : bh;
+    const int r = (int)(p - (int64_t)band * bh * nu);
+    *bm = band * bh + r % h;
+    *bn = (r / h) % nb;
+    *z = (r / h) / nb;
+    return true;
+}
+// Grid, band height and run length for it.  A run costs its first tile's wait for memory once; up to six tiles, so that a
+// workgroup which comes late (another stream's kernel on its CU) does not hold the rest up for long.
+inline unsigned gemm_band_grid(int mb, int nb, int S, int *bh, int *run) {
+    const int64_t share = ((int64_t)mb * nb * S + 7) / 8;         // tiles per die
+    const int64_t rounds = (share + 31) / 32, parts = (rounds + 5) / 6;
+    *run = (int)((rounds + parts - 1) / parts);
+    const int bands = (mb + 7) / 8;
+    *bh = (mb + bands - 1) / bands;
+    const int64_t groups = (share + 32 * *run - 1) / (32 * *run);    // groups of 32 workgroups per die
+    return (unsigned)(groups > 1 ? groups * 256 : 8 * (share < 32 ? share : 32));
 }
 
 }   // namespace pc

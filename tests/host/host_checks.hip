@@ -195,7 +195,7 @@ static int run_book(int n_ops) {
 // (token, dim) pairs onto its elements in which every operand fragment is 512 consecutive elements with lane
 // (i, g) at element (16 g + i) * 8 holding what the matrix-core kernels expect there; the GEMM's patch order
 // visits every tile exactly once, gives every die the same number of tiles, and any 32 consecutive tiles of a die
-// touch at most 4 row blocks and 8 column blocks (ragged last column group aside).
+// touch at most 4 row blocks and 8 column blocks (ragged last column group aside); its runs of tiles cover everything once.
 static int run_maps() {
     using namespace pc;
     for (int hd : {32, 64, 128, 256})
@@ -258,6 +258,30 @@ static int run_maps() {
             }
             ++checked;
         }
+    // runs of tiles: the launcher's grid visits every (tile, slice) exactly once, a workgroup's tiles come without a gap, and
+    // the 32 workgroups a die runs at a time stay within one or two bands
+    for (int mb : {1, 2, 3, 4, 5, 7, 8, 9, 17, 25, 63, 64})
+        for (int nb : {1, 2, 6, 7, 33, 70, 594})
+            for (int S : {1, 2, 3, 8}) {
+                int bh = 0, run = 0;
+                const unsigned grid = gemm_band_grid(mb, nb, S, &bh, &run);
+                REQUIRE(bh >= 1 && bh <= 8 && run >= 1 && run <= 6 && grid >= 1);
+                std::vector<int> seen((size_t)mb * nb * S, 0);
+                for (unsigned b = 0; b < grid; ++b) {
+                    bool there = true;
+                    for (int i = 0; i < run; ++i) {
+                        int bm = -1, bn = -1, z = -1;
+                        const bool got = gemm_band_tile((int)b, i, run, mb, nb, S, bh, &bm, &bn, &z);
+                        REQUIRE(!got || there);
+                        there = got;
+                        if (!got) continue;
+                        REQUIRE(bm >= 0 && bm < mb && bn >= 0 && bn < nb && z >= 0 && z < S);
+                        seen[((size_t)z * mb + bm) * nb + bn]++;
+                    }
+                }
+                for (int x : seen) REQUIRE(x == 1);
+                ++checked;
+            }
     printf("maps ok: cache layouts for 16 geometries, %d tile grids\n", checked);
     return 0;
 }

@@ -288,11 +288,11 @@ def test_wide_tiles_by_row_count(model, P, G, act):
 
 
 @pytest.mark.parametrize("hq,hkv,lens,bs,act", [
-    (8, 2, [201, 3, 190, 128, 90], 32, "f16"),             # 612 rows x 1536 columns: the 64 x 128 tiles
-    (8, 2, [333, 201, 3, 300, 66, 400, 201], 32, "f16"),   # 1504 x 1536: 128 x 128, one per CU
-    (32, 8, [201, 3, 190, 128, 178], 64, "bf16"),          # 700 x 6144: 128 x 128, two per CU
-    (48, 8, [201, 3, 190, 128, 78], 32, "f16"),            # 600 x 8192: rotation in a kernel of its own
-    (48, 8, [333, 1, 300, 65, 301], 64, "f16"),           # 1000 x 8192: 256 x 128
+    (8, 2, [201, 3, 190, 128, 90], 32, "f16"),             # 612 rows x 1536 columns: one round of 128 x 128 tiles
+    (8, 2, [333, 201, 3, 300, 66, 400, 201], 32, "f16"),   # 1504 x 1536
+    (32, 8, [201, 3, 190, 128, 178], 64, "bf16"),          # 700 x 6144
+    (48, 8, [201, 3, 190, 128, 78], 32, "f16"),            # 600 x 8192
+    (48, 8, [333, 1, 300, 65, 301], 64, "f16"),           # 1000 x 8192
     (48, 8, [700, 9, 650, 800, 777, 640, 555], 64, "f16"),    # 4131 x 8192: 256 x 256, a row tile with 35 rows
     (48, 8, [700, 9, 650, 800, 777, 640, 555], 128, "bf16"),
 ])
@@ -311,6 +311,29 @@ def test_projection_that_rotates_and_appends(hq, hkv, lens, bs, act):
         want = decoder.forward_full(m, w, prompts[q], rows=[lens[q] - 1])[0]
         assert np.abs(want - out["last"][q]).max() <= 2e-2 * max(1.0, np.abs(want).max())
     _check(m, w, prompts, out, 21, 2e-2, range(0, len(lens) * 2, 3))
+
+
+@pytest.mark.parametrize("d,dff,vocab,lens,act", [
+    (192, 6400, 528, [700, 9, 650, 800, 777, 640, 555], "f16"),   # 4131 rows: several tiles per block, 3 steps of 64 to a tile
+    (192, 6400, 528, [700, 9, 650, 800, 777, 640, 555], "bf16"),
+    (320, 320, 8208, [513], "f16"),                               # one row beyond the small batches, 5 steps
+    (128, 1184, 8208, [190] * 70 + [257], "f16"),                 # two steps to a tile; 13557 rows in chunks; 80 last rows
+    (2048, 384, 528, [333, 201, 300], "f16"),                     # 834 rows of a wide model: K slices in the large tiles
+])
+def test_many_rows(d, dff, vocab, lens, act):
+    # batches of more than 512 rows: runs of tiles, remainders in rows and columns, odd numbers of steps between two tiles
+    say("%d rows, d_model %d, d_ff %d, %s" % (sum(lens), d, dff, act))
+    m = workloads.scaled(C1, dtype="bf16", d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=dff, vocab=vocab,
+                         n_layers=2, rope_theta=1.0e6).model
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 3), 10)
+    toks, cu = workloads.make_ragged_prompts(lens, m.vocab, 8)
+    prompts = [toks[cu[i]:cu[i + 1]] for i in range(len(lens))]
+    out = _run_generate(m, w, prompts, 1, 2, 21, dict(block_size=64, kv_pool_bytes=512 << 20, max_slots=160, max_ctx=900,
+                                                     max_batch_rows=4200, act_dtype=act))
+    for q in range(0, len(lens), max(1, len(lens) // 9)):
+        want = decoder.forward_full(m, w, prompts[q], rows=[lens[q] - 1])[0]
+        assert np.abs(want - out["last"][q]).max() <= 2e-2 * max(1.0, np.abs(want).max())
+    _check(m, w, prompts, out, 21, 2e-2, range(0, len(lens), max(1, len(lens) // 9)))
 
 
 def test_attention_keeps_the_largest_probability_exact():
