@@ -101,6 +101,8 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
     static_assert(EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_SWIGLU || EPI == EPI_QKV || EPI == EPI_LOGPROB, "epilogue");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     T *smem = (T *)smem_raw;
+    constexpr size_t RING_BYTES = (size_t)NP * PAIR * sizeof(T);
+    constexpr int V_PITCH = SN + 8;                           // (q/k/v: elements of a row of V under way to the cache)
 
     const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int wm = wave / 2, wn = wave % 2;
@@ -229,9 +231,25 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
 #undef PC_QUADRANT
     if (!locate(0, cur)) return;
     nxt = cur;
+    // q/k/v: sequence, position and cache block of the wave's rows, one or two to a lane.  Each is the address of the next; the
+    // first tile's are fetched between its operand loads.
+    constexpr int RL = EPI == EPI_QKV ? (SM + 63) / 64 : 1;
+    int row_slot[RL], row_pos[RL], row_blk[RL];
+    auto find_rows = [&](int stage) {
+        if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+            for (int r = 0; r < RL; ++r) {
+                const int row = min(cur.m0 + wm * SM + 64 * r + lane, M - 1);
+                if (stage == 0) row_slot[r] = extra.row_slot[row];
+                if (stage == 1) row_pos[r] = extra.row_pos ? extra.row_pos[row] : extra.slot_len[row_slot[r]];
+                if (stage == 2) row_blk[r] = extra.kv.block_table[(int64_t)row_slot[r] * extra.kv.max_blocks_per_slot + row_pos[r] / extra.kv.block_size];
+            }
+        }
+    };
 #pragma unroll
     for (int p = -1; p < NP - 1; ++p) {
         const int t = (p + 1) >> 1, h = (p & 1) ? 0 : 1;
+        find_rows(p + 1);
 #pragma unroll
         for (int q = 0; q < LA; ++q) load_a(t, p + 1, h, q);
 #pragma unroll
@@ -378,43 +396,93 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
                 const int pc0 = n0 - (part == 0 ? 0 : (part == 1 ? qd : qd + kvd));
                 const int head = pc0 / 128, in = pc0 % 128;               // first column inside the head
                 T *pool = (T *)extra.kv.pool + (int64_t)extra.layer * extra.kv.layer_stride + (int64_t)head * extra.kv.head_elems();
-#pragma unroll 1
-                for (int i2 = 0; i2 < 2 * TMH; ++i2) {
-                    f32x4_t x[2 * TNH];
-                    take(i2, x);
-                    const int row = m0 + 16 * i2 + ml;
-                    if (row >= M) continue;
-                    const int sl = extra.row_slot[row];
-                    const int pos = extra.row_pos ? extra.row_pos[row] : extra.slot_len[sl];
-                    const int blk = part ? extra.kv.block_table[(int64_t)sl * extra.kv.max_blocks_per_slot + pos / bs] : 0;
-                    const int tin = pos % bs;
-                    T *block = pool + (int64_t)blk * extra.kv.block_elems();
-                    if (part == 2) {
-#pragma unroll
-                        for (int j = 0; j < 2 * TNH; ++j)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                block[extra.kv.v_index(tin, in + large_row(ORDER, j, 4 * g + v))] = from_f32_sat<T>(x[j][v], sat);
-                        continue;
+                auto of_row = [&](const int (&v)[RL], int r) {            // what lane r % 64 holds for row r of the wave's
+                    int x = __shfl(v[0], r % 64, 64);
+                    if constexpr (RL == 2) {
+                        const int y = __shfl(v[1], r % 64, 64);
+                        x = r < 64 ? x : y;
                     }
+                    return x;
+                };
+                if (part == 2) {
+                    // A token's 128 dims lie 16 bytes apart in the cache: whole rows are re-formed in LDS, so that one store covers 64
+                    // dims of one token (8 cache lines) and not one dim of 16 tokens and 4 groups (64 lines)
+                    T *stg = (T *)(smem_raw + RING_BYTES) + wave * 16 * V_PITCH;
+#pragma unroll 1
+                    for (int i2 = 0; i2 < 2 * TMH; ++i2) {
+                        f32x4_t x[2 * TNH];
+                        take(i2, x);
+                        uint32_t *const count = m0 + 16 * i2 + ml < M ? sat : nullptr;   // clamps are counted where stored
+                        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int c = 0; c < TNH / 2; ++c) {
-                        const int j0 = in / 2 + 32 * c + 8 * g;           // the lane's eight pair indices
-                        u32x2 lo[2], hi[2];
+                        for (int c = 0; c < TNH / 2; ++c)
 #pragma unroll
-                        for (int s = 0; s < 2; ++s) {
-                            const f32x4_t cs = *(const f32x4_t *)(extra.rope_cos + (int64_t)pos * 64 + j0 + 4 * s);
-                            const f32x4_t sn = *(const f32x4_t *)(extra.rope_sin + (int64_t)pos * 64 + j0 + 4 * s);
-                            const f32x4_t &x1 = x[4 * c + 2 * s], &x2 = x[4 * c + 2 * s + 1];
-                            lo[s] = pack4_sat<T>(x1[0] * cs[0] - x2[0] * sn[0], x1[1] * cs[1] - x2[1] * sn[1],
-                                                 x1[2] * cs[2] - x2[2] * sn[2], x1[3] * cs[3] - x2[3] * sn[3], sat);
-                            hi[s] = pack4_sat<T>(x2[0] * cs[0] + x1[0] * sn[0], x2[1] * cs[1] + x1[1] * sn[1],
-                                                 x2[2] * cs[2] + x1[2] * sn[2], x2[3] * cs[3] + x1[3] * sn[3], sat);
+                            for (int h = 0; h < 2; ++h) {
+                                const f32x4_t &x1 = x[4 * c + h], &x2 = x[4 * c + 2 + h];
+                                const u32x2 lo = pack4_sat<T>(x1[0], x1[1], x1[2], x1[3], count);
+                                const u32x2 hi = pack4_sat<T>(x2[0], x2[1], x2[2], x2[3], count);
+                                *(u32x4 *)(stg + ml * V_PITCH + large_row(ORDER, 4 * c + h, 4 * g)) = (u32x4){lo[0], lo[1], hi[0], hi[1]};
+                            }
+                        __builtin_amdgcn_wave_barrier();
+                        const int pos16 = of_row(row_pos, 16 * i2 + ml), blk16 = of_row(row_blk, 16 * i2 + ml);
+                        const int left = min(16, M - m0 - 16 * i2);
+#pragma unroll 1
+                        for (int r4 = 0; r4 < left; r4 += 4)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const int r = min(r4 + k, left - 1);   // (past the end: the last row once more)
+                            const int tin = __builtin_amdgcn_readlane(pos16, r) % bs;
+                            T *block = pool + (int64_t)__builtin_amdgcn_readlane(blk16, r) * extra.kv.block_elems();
+#pragma unroll
+                            for (int d = 0; d < SN / 64; ++d)
+                                block[extra.kv.v_index(tin, in + 64 * d + lane)] = stg[r * V_PITCH + 64 * d + lane];
                         }
-                        const u32x4 a = {lo[0][0], lo[0][1], lo[1][0], lo[1][1]}, b = {hi[0][0], hi[0][1], hi[1][0], hi[1][1]};
-                        T *dst = part == 0 ? (T *)extra.q_out + ((int64_t)row * extra.hq + head) * 128 : block;
-                        *(u32x4 *)(dst + (part == 0 ? j0 : extra.kv.k_index(tin, j0))) = a;   // (eight dims are contiguous in both)
-                        *(u32x4 *)(dst + (part == 0 ? j0 + 64 : extra.kv.k_index(tin, j0 + 64))) = b;
+                    }
+                } else {
+                    f32x4_t cs[TNH / 2][2], sn[TNH / 2][2];               // of the lane's eight pair indices per chunk, for the row tile to come
+                    auto rotation = [&](int pos) {
+#pragma unroll
+                        for (int c = 0; c < TNH / 2; ++c)
+#pragma unroll
+                            for (int s = 0; s < 2; ++s) {
+                                const int64_t at = (int64_t)pos * 64 + in / 2 + 32 * c + 8 * g + 4 * s;
+                                cs[c][s] = *(const f32x4_t *)(extra.rope_cos + at);
+                                sn[c][s] = *(const f32x4_t *)(extra.rope_sin + at);
+                            }
+                    };
+                    int pos = of_row(row_pos, ml);
+                    rotation(pos);
+#pragma unroll 1
+                    for (int i2 = 0; i2 < 2 * TMH; ++i2) {
+                        f32x4_t x[2 * TNH];
+                        take(i2, x);
+                        const int row = m0 + 16 * i2 + ml;
+                        const int blk = of_row(row_blk, 16 * i2 + ml), tin = pos % bs;
+                        uint32_t *const count = row < M ? sat : nullptr;
+                        u32x2 lo[TNH / 2][2], hi[TNH / 2][2];
+#pragma unroll
+                        for (int c = 0; c < TNH / 2; ++c)
+#pragma unroll
+                            for (int s = 0; s < 2; ++s) {
+                                const f32x4_t &x1 = x[4 * c + 2 * s], &x2 = x[4 * c + 2 * s + 1], &k = cs[c][s], &n = sn[c][s];
+                                lo[c][s] = pack4_sat<T>(x1[0] * k[0] - x2[0] * n[0], x1[1] * k[1] - x2[1] * n[1],
+                                                        x1[2] * k[2] - x2[2] * n[2], x1[3] * k[3] - x2[3] * n[3], count);
+                                hi[c][s] = pack4_sat<T>(x2[0] * k[0] + x1[0] * n[0], x2[1] * k[1] + x1[1] * n[1],
+                                                        x2[2] * k[2] + x1[2] * n[2], x2[3] * k[3] + x1[3] * n[3], count);
+                            }
+                        pos = of_row(row_pos, min(16 * i2 + 16, SM - 16) + ml);
+                        rotation(pos);
+                        if (row >= M) continue;
+                        T *block = pool + (int64_t)blk * extra.kv.block_elems();
+#pragma unroll
+                        for (int c = 0; c < TNH / 2; ++c) {
+                            const int j0 = in / 2 + 32 * c + 8 * g;
+                            T *dst = part == 0 ? (T *)extra.q_out + ((int64_t)row * extra.hq + head) * 128 : block;
+                            *(u32x4 *)(dst + (part == 0 ? j0 : extra.kv.k_index(tin, j0))) =   // (eight dims are contiguous in both)
+                                (u32x4){lo[c][0][0], lo[c][0][1], lo[c][1][0], lo[c][1][1]};
+                            *(u32x4 *)(dst + (part == 0 ? j0 + 64 : extra.kv.k_index(tin, j0 + 64))) =
+                                (u32x4){hi[c][0][0], hi[c][0][1], hi[c][1][0], hi[c][1][1]};
+                        }
                     }
                 }
             }
@@ -463,15 +531,19 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
         code_fence();
         if (!more) break;
         cur = nxt;
+#pragma unroll
+        for (int stage = 0; stage < 3; ++stage) find_rows(stage);
     }
 #endif
 }
 
 template <typename T, int TMH, int TNH> struct LargeCfg {
     static constexpr int BM = 64 * TMH, BN = 64 * TNH, NP = 4;
-    static constexpr size_t smem = (size_t)NP * (BM + BN) * 64;   // a pair holds half of the rows, 2 bytes an element
+    template <int E> static constexpr size_t smem() {   // a pair of units holds half of the rows, 2 bytes an element
+        return (size_t)NP * (BM + BN) * 64 + (E == EPI_QKV ? (size_t)4 * 16 * (BN / 2 + 8) * 2 : 0);
+    }
     template <int E> static void set_attr() {
-        (void)hipFuncSetAttribute((const void *)gemm_large_kernel<T, TMH, TNH, NP, E>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        (void)hipFuncSetAttribute((const void *)gemm_large_kernel<T, TMH, TNH, NP, E>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem<E>());
     }
     template <int E>
     static void launch(const void *A, const void *W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s,
@@ -479,7 +551,7 @@ template <typename T, int TMH, int TNH> struct LargeCfg {
         const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
         int bh, run;
         const unsigned grid = gemm_band_grid(mb, nb, S, &bh, &run);
-        gemm_large_kernel<T, TMH, TNH, NP, E><<<grid, 256, smem, s>>>((const T *)A, (const T *)W, C, M, N, K, mb, nb, S, bh, run, sat, extra);
+        gemm_large_kernel<T, TMH, TNH, NP, E><<<grid, 256, smem<E>(), s>>>((const T *)A, (const T *)W, C, M, N, K, mb, nb, S, bh, run, sat, extra);
     }
 };
 
