@@ -681,6 +681,8 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
         const int64_t tiles = (int64_t)((N + BN - 1) / BN) * ((M + BM - 1) / BM);
         const int KT = K / BK;
         int64_t split = (want_blocks + tiles / 2) / tiles;
+        // (never a second round for a few blocks: 6144 x 4096 at 400 rows 41.3 us with 288 blocks, 30.2 with 192)
+        if (want_blocks <= 256) split = std::min<int64_t>(split, std::max<int64_t>(1, 256 / tiles));
         split = std::min<int64_t>(split, KT / 4);
         split = std::min<int64_t>(split, 8);
         split = std::min<int64_t>(split, (int64_t)(slice_cap_floats / ((size_t)M * N)));
@@ -704,13 +706,13 @@ template <typename T> struct Gemm {
     typedef MfmaCfg<T, 64, 192, 4, 2, 4, 64, true> T64x192;
     typedef MfmaCfg<T, 32, 64, 1, 4, 4, 64, true> T32x64;       // 48 KB of LDS: three blocks per CU
     typedef MfmaCfg<T, 32, 64, 1, 2, 4, 64, true> T32x64_2;     // the same with whole gate/up chunks per wave
-    typedef MfmaCfg<T, 128, 128, 2, 2, 3, 32> M128x128_3;       // BK 32, 48 KB: three blocks per CU
+    typedef MfmaCfg<T, 256, 160, 4, 1, 3, 64, true> T256x160;   // 4 waves of 64 x 160
     typedef MfmaCfg<T, 128, 64, 4, 2, 4, 64, true> T128x64;     // 8 waves of 32 x 32: long-K projections cut into K slices
     typedef MfmaCfg<T, 192, 64, 4, 2, 4, 64, true> T192x64;     // the same in wave tiles of 48 x 32
     typedef MfmaCfg<T, 64, 64, 2, 2, 4> M64x64;                 // wave tile 32 x 32: many blocks for the small projections
     static void init() {
         T256x128::init(); T256x192::init(); T192x128::init(); T192x192::init(); T128x128::init(); T128x192::init();
-        T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init(); M128x128_3::init(); T128x64::init();
+        T256x160::init(); T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init(); T128x64::init();
         T192x64::init(); M64x64::init();
         T256x128::init_logprob();
         T192x128::init_logprob();
@@ -741,8 +743,14 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
         else gemm_simt<f16_t>(A, W, C, M, N, K, epi, sat, s);
         return 1;
     }
-    if (M > 512) {
-        const int S = launch_gemm_large(dtype, A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s);
+    // Four waves with a quarter of a large tile each (gemm_large.hip) win above 512 rows, on gate/up above 384 (1.5B shape at 512
+    // rows 51.9 -> 31.8 us against three 128-row blocks per CU, 8B 111 -> 91 us) and on the vocabulary projection above 192 (1.5B /
+    // 8B shape: 161 / 361 -> 158 / 346 us at 256 rows, 218 / 480 -> 209 / 431 at 380, 284 / 612 -> 233 / 522 at 500); gate/up at
+    // 256 rows takes as long either way (27.9 and 27.1 us).
+    const int nb128 = (N + 127) / 128;
+    if (M > 512 || (M > 384 && (epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS || nb128 >= 96)) ||
+        (M > 192 && nb128 >= 512 && epi == EPI_STORE_F32)) {
+        const int S = launch_gemm_large(dtype, A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
         if (S) return S;
     }
     if (dtype == KD_BF16) return gemm_mfma_dispatch<bf16_t>(A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
@@ -849,11 +857,10 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         return split;
     };
     if (M > 512) return whole(typename G::T256x128());   // (what gemm_large.hip does not take: operands off 16-byte boundaries, K = 64)
+    // blocks of one round of the chip, one per CU
+    auto one_round = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) <= 256; };
     // decode: the weights are streamed once; fill the chip with blocks, by K slices where N is small
     const int nb128 = (N + 127) / 128, nb192 = (N + 191) / 192;
-    // a long reduction amortises a block's fill and drain, and the tile with the most fragment reuse wins at
-    // every row count; a short one (the 1.5B model: 24 K tiles) prefers several smaller blocks per CU
-    const bool deep = K >= 3072;
     if (swiglu || nb128 >= 96) {   // wide outputs: no K slices needed
         // 128-column tiles that need a second, nearly empty round of blocks (one per CU) where 192-column ones fit the first
         // (14B gate/up, 34816 columns: 272 blocks against 182; 112 / 119 / 162 / 159 us against 74 / 84 / 90 / 132 us at
@@ -864,14 +871,17 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         if (M <= 64 && (second_round || !swiglu)) return second_round ? whole(typename G::T64x192()) : whole(typename G::T64x128());
         if (M <= 128) return second_round ? whole(typename G::T128x192()) : whole(typename G::T128x128());
         if (M <= 192) return second_round ? whole(typename G::T192x192()) : whole(typename G::T192x128());
-        if (M <= 256) return second_round ? whole(typename G::T256x192()) : whole(typename G::T256x128());   // a weight tile is fetched by exactly one block
+        if (M <= 256) {
+            // Where one row block of 128 columns is more than a round, the narrowest tile that is not (34816 x 5120: 256 x 192 127 us,
+            // 256 x 160 106.5; 17920 x 1536 in two row blocks of 128 x 160, 224 CUs instead of 140, is 25.8 us for 28.3 alone, but
+            // decode steps on several streams, which fill the idle CUs, take 3 % longer: the same work costs more CU time)
+            if (swiglu && second_round && one_round(256, 160)) return whole(typename G::T256x160());
+            return second_round ? whole(typename G::T256x192()) : whole(typename G::T256x128());   // a weight tile is fetched by exactly one block
+        }
         // two 192-row blocks instead of two of 256 (380 rows: 24576 x 4096 70 us against 119 us, 17920 x 1536 27 us against 33
         // us with three 128-row blocks)
         if (M <= 384) return whole(typename G::T192x192());
-        // (the vocabulary projection: several rounds of blocks per CU at any tile size, the big tile wins --
-        // 240 us against 311 us at 400 rows of the 1.5B shape)
-        if (deep || (nb128 >= 512 && !swiglu)) return whole(typename G::T256x128());
-        return whole(typename G::M128x128_3());   // four 128-row blocks, three per CU at a time
+        return whole(typename G::T256x128());   // (what gemm_large.hip does not take)
     }
     // The smallest batches stream the weights and little else: rows loaded for nothing (a tile of 128 for 3) cost as much of
     // the load path as the weights (4096 x 12288 at 3 rows: 20 us against 27 us, 1536 x 8960: 6.6 against 9.5 us)
@@ -882,6 +892,11 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         // as tall as the batch needs (8B down at 60 rows: 22 us, 29 us with 128-row tiles; 14B q/k/v at 168: 25 us, 30 us
         // with 256-row ones)
         if (M <= 64) return sliced(typename G::T64x128(), 240);
+        // A shorter reduction is cheaper in few slices of smaller tiles, also for whoever adds them up (4096 x 4096 with the reading
+        // of the slices: 128 x 128 in 4 19.9 us at 256 rows, 256 x 128 in 8 28.7; 17.9 against 20.8 at 168; 27.6 against 32.3 at
+        // 512.  5120 x 5120: 27.9 against 28.9 at 256, 22.4 against 23.1 at 168); wider outputs or longer reductions want the
+        // taller tile (6144 x 4096 at 168: 22.3 for 22.2; 4096 x 12288 at 256: 41.4 for 40.8)
+        if (K <= 5120 && ((M > 128 && M <= 256 && nb128 <= 40) || (M > 384 && nb128 <= 32))) return sliced(typename G::T128x128(), 240);
         if (M <= 128) return sliced(typename G::T128x128(), 240);
         if (M <= 192) return sliced(typename G::T192x128(), 240);
         if (M > 256 && M <= 384) return sliced(typename G::T192x192(), 240);   // 8B down at 380 rows: 44 us against 49 us

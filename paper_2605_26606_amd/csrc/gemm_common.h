@@ -49,10 +49,10 @@ template <> struct GemmExtra<EPI_SWIGLU_RS> { typedef GemmRowScale type; };
 template <> struct GemmExtra<EPI_LOGPROB> { typedef GemmLogprob type; };
 template <> struct GemmExtra<EPI_QKV> { typedef GemmQkv type; };
 
-// gemm_large.hip: batches of more than 512 rows.  Each launches nothing and says so (0, false) if it does not take the call.
+// gemm_large.hip: large batches.  Each launches nothing and says so (0, false) if it does not take the call.
 void gemm_large_init();   // once per device, like gemm_init
 int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap,
-                      uint32_t *sat, hipStream_t s);   // the number of K slices, as launch_gemm
+                      uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale);   // the number of K slices, as launch_gemm
 bool launch_gemm_large_qkv(int dtype, const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s);
 int launch_gemm_large_logprob(int dtype, const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp,
                               hipStream_t s);          // the number of column strips

@@ -1,4 +1,4 @@
-// Projection GEMMs with many rows (prefill, scoring, decode batches of more than 512 sequences; Section 3.1 policy pi_theta):
+// Projection GEMMs with many rows (prefill, scoring, large decode batches; Section 3.1 policy pi_theta):
 //   C[M,N] = A[M,K] * W[N,K]^T, fp32 accumulation, the epilogues of gemm.hip.
 #include <algorithm>
 
@@ -96,9 +96,10 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
     constexpr int BM = 64 * TMH, BN = 64 * TNH, BK = 64, SM = BM / 2, SN = BN / 2;   // tile, K step, a wave's part
     constexpr int LA = BM / 64, LW = BN / 64, L = LA + LW;    // wave-wide 1 KB loads per wave for a unit of A, of W, for a pair
     constexpr int UA = SM * BK, PAIR = (SM + SN) * BK;        // elements
-    constexpr int ORDER = (EPI == EPI_SWIGLU || EPI == EPI_QKV) ? LO_PAIRED : LO_PLAIN;
+    constexpr bool SWIGLU = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_RS;
+    constexpr int ORDER = (SWIGLU || EPI == EPI_QKV) ? LO_PAIRED : LO_PLAIN;
     static_assert(ORDER == LO_PLAIN || TNH % 2 == 0, "whole pairs of chunks per wave");
-    static_assert(EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || EPI == EPI_SWIGLU || EPI == EPI_QKV || EPI == EPI_LOGPROB, "epilogue");
+    static_assert(EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || SWIGLU || EPI == EPI_QKV || EPI == EPI_LOGPROB, "epilogue");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     T *smem = (T *)smem_raw;
     constexpr size_t RING_BYTES = (size_t)NP * PAIR * sizeof(T);
@@ -246,6 +247,32 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
             }
         }
     };
+    // gate/up behind a norm: 1 / rms of the tile's rows, a thread to a row, from the row's sums of squares over 32 columns each.
+    // Two tiles' worth in LDS: a wave may still be at the epilogue of one while the next one's are written.
+    float *row_scale = (float *)(smem_raw + RING_BYTES);
+    constexpr int RS_AHEAD = EPI == EPI_SWIGLU_RS ? 48 : 1;   // sums fetched at a time
+    float sums[RS_AHEAD];
+    auto fetch_sums = [&](int from) {   // (past the end: clamped, not left out; a branch around each load would make them wait for one another)
+        if constexpr (EPI == EPI_SWIGLU_RS) {
+            const int row = min(cur.m0 + tid, M - 1);
+#pragma unroll
+            for (int u = 0; u < RS_AHEAD; ++u) sums[u] = extra.ssq[(int64_t)min(from + u, extra.tiles - 1) * M + row];
+        }
+    };
+    auto write_scale = [&](int which) {
+        if constexpr (EPI == EPI_SWIGLU_RS) {
+            float ss = 0.f;
+            for (int from = 0;;) {
+#pragma unroll
+                for (int u = 0; u < RS_AHEAD; ++u) ss += from + u < extra.tiles ? sums[u] : 0.f;
+                from += RS_AHEAD;
+                if (from >= extra.tiles) break;
+                fetch_sums(from);
+            }
+            if (tid < BM) row_scale[which * BM + tid] = 1.0f / sqrtf(ss / (float)extra.d + extra.eps);
+        }
+    };
+    fetch_sums(0);
 #pragma unroll
     for (int p = -1; p < NP - 1; ++p) {
         const int t = (p + 1) >> 1, h = (p & 1) ? 0 : 1;
@@ -255,6 +282,7 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
 #pragma unroll
         for (int q = 0; q < LW; ++q) load_w(t, p + 1, h, q);
     }
+    write_scale(0);
     wait_vmcnt_le<(NP - 1) * L>();
     code_fence();
     __builtin_amdgcn_s_barrier();
@@ -344,7 +372,7 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
                     row_off += tile_off;
                 }
             }
-        } else if constexpr (EPI == EPI_SWIGLU) {
+        } else if constexpr (SWIGLU) {
             const int ldc = N / 2;
             T *C = (T *)Cv + (int64_t)cur.m0 * ldc;
             __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)C, 0, (int)((uint32_t)min(M - cur.m0, BM) * (uint32_t)ldc * 2u), 0x00020000);
@@ -353,6 +381,11 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
             for (int i2 = 0; i2 < 2 * TMH; ++i2) {
                 f32x4_t x[2 * TNH];
                 take(i2, x);
+                if constexpr (EPI == EPI_SWIGLU_RS) {
+                    const float scale = row_scale[(i % 2) * BM + wm * SM + 16 * i2 + ml];
+#pragma unroll
+                    for (int j = 0; j < 2 * TNH; ++j) x[j] *= scale;
+                }
                 // converted unchecked, and again with clamps and their count if anything of the row tile may be beyond the half range
                 u32x4 out[TNH / 2];
                 float sum = 0.f;
@@ -533,6 +566,8 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
         cur = nxt;
 #pragma unroll
         for (int stage = 0; stage < 3; ++stage) find_rows(stage);
+        fetch_sums(0);
+        write_scale((i + 1) % 2);
     }
 #endif
 }
@@ -540,7 +575,8 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
 template <typename T, int TMH, int TNH> struct LargeCfg {
     static constexpr int BM = 64 * TMH, BN = 64 * TNH, NP = 4;
     template <int E> static constexpr size_t smem() {   // a pair of units holds half of the rows, 2 bytes an element
-        return (size_t)NP * (BM + BN) * 64 + (E == EPI_QKV ? (size_t)4 * 16 * (BN / 2 + 8) * 2 : 0);
+        return (size_t)NP * (BM + BN) * 64 + (E == EPI_QKV ? (size_t)4 * 16 * (BN / 2 + 8) * 2 : 0) +
+               (E == EPI_SWIGLU_RS ? (size_t)2 * BM * sizeof(float) : 0);
     }
     template <int E> static void set_attr() {
         (void)hipFuncSetAttribute((const void *)gemm_large_kernel<T, TMH, TNH, NP, E>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem<E>());
@@ -599,7 +635,7 @@ static int large_pick(std::initializer_list<int> among, int max_slices, int M, i
 
 static bool large_ok(const void *A, const void *W, const void *C, int M, int N, int K) {
     // (rows of operands and results in whole 16-byte pieces; a tile's bytes within a buffer descriptor's 32 bits)
-    return M > 512 && K % 64 == 0 && K >= 128 && N % 16 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)C) & 15) == 0 &&
+    return K % 64 == 0 && K >= 128 && N % 16 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)C) & 15) == 0 &&
            K <= (1 << 21) && N <= (1 << 21);
 }
 
@@ -618,6 +654,7 @@ template <typename T> struct Large {
         init_plain<EPI_STORE_F32>();
         init_plain<EPI_RESID_F32>();
         T256x256::template set_attr<EPI_SWIGLU>(); T192x256::template set_attr<EPI_SWIGLU>(); T192x128::template set_attr<EPI_SWIGLU>();
+        T256x256::template set_attr<EPI_SWIGLU_RS>(); T192x256::template set_attr<EPI_SWIGLU_RS>();
         T256x256::template set_attr<EPI_QKV>(); T192x256::template set_attr<EPI_QKV>(); T192x128::template set_attr<EPI_QKV>();
         T128x128::template set_attr<EPI_QKV>();
         T256x256::template set_attr<EPI_LOGPROB>(); T192x256::template set_attr<EPI_LOGPROB>();
@@ -634,13 +671,26 @@ template <typename T> struct Large {
         }
     }
     static int gemm(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap, uint32_t *sat,
-                    hipStream_t s) {
+                    hipStream_t s, const GemmRowScale *row_scale) {
         int S = 1;
+        if (epi == EPI_SWIGLU_RS) {   // (up to 512 rows: never many tiles)
+            if (large_pick({LT_256x256, LT_192x256}, 1, M, N, K, EPI_SWIGLU, &S) == LT_256x256)
+                T256x256::template launch<EPI_SWIGLU_RS>(A, W, C, M, N, K, 1, sat, s, *row_scale);
+            else
+                T192x256::template launch<EPI_SWIGLU_RS>(A, W, C, M, N, K, 1, sat, s, *row_scale);
+            return 1;
+        }
         if (epi == EPI_SWIGLU) {
             const int id = large_pick({LT_256x256, LT_192x256, LT_192x128}, 1, M, N, K, epi, &S);
             if (id == LT_256x256) T256x256::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
             else if (id == LT_192x256) T192x256::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
             else T192x128::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
+            return 1;
+        }
+        // (the vocabulary projection of a decode step, whose time is half the weights' way from memory, which the estimate leaves out:
+        // the shortest tile that holds the rows in one or two blocks, its figures stand at the rule that leads here)
+        if (M <= 512 && epi == EPI_STORE_F32 && !slices) {
+            plain<EPI_STORE_F32>(M <= 256 ? LT_256x128 : (M <= 384 ? LT_192x256 : LT_256x256), A, W, C, M, N, K, 1, sat, s);
             return 1;
         }
         const int max_slices = slices ? (int)std::min<size_t>(8, slice_cap / ((size_t)M * N)) : 1;
@@ -676,12 +726,13 @@ void gemm_large_init() {
 }
 
 int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap,
-                      uint32_t *sat, hipStream_t s) {
-    if ((epi != EPI_STORE_F32 && epi != EPI_RESID_F32 && epi != EPI_SWIGLU) || !large_ok(A, W, C, M, N, K) ||
-        ((uintptr_t)slices & 15) != 0 || (epi == EPI_SWIGLU && N % 64 != 0))
+                      uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
+    const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS;
+    if ((epi != EPI_STORE_F32 && epi != EPI_RESID_F32 && !swiglu) || !large_ok(A, W, C, M, N, K) || ((uintptr_t)slices & 15) != 0 ||
+        (swiglu && N % 64 != 0) || (epi == EPI_SWIGLU_RS && !row_scale))
         return 0;
-    if (dtype == KD_BF16) return Large<bf16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s);
-    return Large<f16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s);
+    if (dtype == KD_BF16) return Large<bf16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s, row_scale);
+    return Large<f16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s, row_scale);
 }
 
 bool launch_gemm_large_qkv(int dtype, const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {

@@ -287,6 +287,31 @@ def test_wide_tiles_by_row_count(model, P, G, act):
     _check(model, w, prompts, out, 21, 2e-2, range(0, P * G, max(1, P * G // 6)))
 
 
+# a vocabulary of 513 column blocks: the head of a decode step on the large tiles; its gate/up, without and with the norm scale
+VOC1 = workloads.scaled(C1, dtype="bf16", d_model=128, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=6400, vocab=65552,
+                        n_layers=1, rope_theta=1.0e6).model
+VOC2 = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=20512, vocab=512,
+                        n_layers=2, rope_theta=1.0e6).model
+
+
+@pytest.mark.parametrize("model,P,G,act", [(VOC1, 48, 4, "f16"), (VOC1, 193, 1, "f16"), (VOC1, 64, 4, "bf16"), (VOC1, 257, 1, "f16"),
+                                           (VOC1, 96, 4, "f16"), (VOC1, 77, 5, "f16"), (VOC1, 128, 4, "bf16"), (VOC1, 171, 3, "f16"),
+                                           (VOC2, 64, 3, "f16"), (VOC2, 193, 1, "f16"), (VOC2, 64, 4, "f16"), (VOC2, 77, 5, "f16"),
+                                           (VOC2, 128, 4, "bf16"), (VOC2, 128, 4, "f16"), (WIDE1, 128, 4, "f16"), (WIDE1, 96, 4, "f16")])
+def test_large_tiles_of_decode_batches(model, P, G, act):
+    # 192, 193, 256, 257, 384, 385, 512 and 513 rows: each side of the rules that send a step's projections to the large tiles;
+    # gate/up of 41024 columns runs several tiles per block, each with row scales of its own
+    say("large tiles in decode, d_ff %d, vocabulary %d, %d rows" % (model.d_ff, model.vocab, P * G))
+    w = workloads.perturb_norm_gains(workloads.make_weights(model, 3), 10)
+    lens = np.random.default_rng(P).integers(1, 9, P).tolist()
+    toks, cu = workloads.make_ragged_prompts(lens, model.vocab, 8)
+    prompts = [toks[cu[i]:cu[i + 1]] for i in range(P)]
+    out = _run_generate(model, w, prompts, G, 2, 21, dict(block_size=32, kv_pool_bytes=256 << 20,
+                                                         max_slots=P * (G + 1) + 8, max_ctx=64, max_batch_rows=1400,
+                                                         act_dtype=act))
+    _check(model, w, prompts, out, 21, 2e-2, list(range(0, P * G, max(1, P * G // 6))) + [P * G - 1])
+
+
 @pytest.mark.parametrize("hq,hkv,lens,bs,act", [
     (8, 2, [201, 3, 190, 128, 90], 32, "f16"),             # 612 rows x 1536 columns: one round of 128 x 128 tiles
     (8, 2, [333, 201, 3, 300, 66, 400, 201], 32, "f16"),   # 1504 x 1536
