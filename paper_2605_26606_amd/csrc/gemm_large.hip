@@ -9,8 +9,11 @@ namespace pc {
 // 16x16x32 products whose accumulator lives in the accumulation registers (256 of a wave's 512 registers at one wave per
 // SIMD).  Written out because the compiler, left to itself, keeps such accumulators in the other half and moves them back and
 // forth (900 TFLOP/s at 8192^3 where this form reaches 1450).  `volatile` also keeps the order of the products and of the memory
-// operations between them as they stand in the source.  The results must not be read before the pipeline has drained
-// (mma_drain).
+// operations between them as they stand in the source.
+// What the compiler does not see it does not keep apart either.  A product must not read a register less than two wait states
+// after a vector-ALU instruction wrote it: its fragments come from LDS reads only, and where they are copied the copy is pinned
+// to its place.  The results must not be read before the pipeline has drained (mma_drain).  tests/test_wait_states.py checks
+// both on the generated code.
 template <typename T> struct AccMma;
 template <> struct AccMma<f16_t> {
     __device__ static inline void first(f16x8_t a, f16x8_t b, f32x4_t &c) {   // c = a b
@@ -312,7 +315,10 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-                for (int j = 0; j < TNH; ++j) fbx[kk][j] = fby[kk][j];
+                for (int j = 0; j < TNH; ++j) {
+                    fbx[kk][j] = fby[kk][j];
+                    asm volatile("" : "+v"(fbx[kk][j]));   // (made here, not between the products that read it)
+                }
         }
         mma_drain();
 #pragma unroll
