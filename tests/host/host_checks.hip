@@ -9,6 +9,7 @@
 #include <string.h>
 
 #include <set>
+#include <utility>
 #include <vector>
 
 #include "../../paper_2605_26606_amd/csrc/index_maps.h"
@@ -259,7 +260,7 @@ static int run_maps() {
             ++checked;
         }
     // runs of tiles: the launcher's grid visits every (tile, slice) exactly once, a workgroup's tiles come without a gap, and
-    // the 32 workgroups a die runs at a time stay within one or two bands
+    // the 32 workgroups a die runs at a time stay within one or two bands and share few slabs of weights
     for (int mb : {1, 2, 3, 4, 5, 7, 8, 9, 17, 25, 63, 64})
         for (int nb : {1, 2, 6, 7, 33, 70, 594})
             for (int S : {1, 2, 3, 8}) {
@@ -280,6 +281,23 @@ static int run_maps() {
                     }
                 }
                 for (int x : seen) REQUIRE(x == 1);
+                // (h: the lowest band; 32 neighbouring places of a walk in columns of h reach 31 / h + 2 columns at most, one more
+                // where they pass from one band into the next)
+                const int bands = (mb + bh - 1) / bh, h = mb - (bands - 1) * bh;
+                for (unsigned die = 0; die < 8 && die < grid; ++die)
+                    for (unsigned first = 0; first * 8 + die < grid; first += 32)
+                        for (int i = 0; i < run; ++i) {
+                            std::set<int> in_bands;
+                            std::set<std::pair<int, int>> slabs;
+                            for (unsigned j = first; j < first + 32 && j * 8 + die < grid; ++j) {
+                                int bm, bn, z;
+                                if (!gemm_band_tile((int)(j * 8 + die), i, run, mb, nb, S, bh, &bm, &bn, &z)) continue;
+                                in_bands.insert(bm / bh);
+                                slabs.insert({bn, z});
+                            }
+                            if (h * nb * S >= 31) REQUIRE(in_bands.size() <= 2);   // (a band of fewer tiles lies within the 32)
+                            REQUIRE((int)slabs.size() <= 31 / h + 2 + (in_bands.size() > 1 ? 1 : 0));
+                        }
                 ++checked;
             }
     printf("maps ok: cache layouts for 16 geometries, %d tile grids\n", checked);
