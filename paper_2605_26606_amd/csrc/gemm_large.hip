@@ -578,6 +578,17 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
 #endif
 }
 
+// The tiles, and in which of them an epilogue exists (one bit each).
+enum { LT_256x256, LT_256x192, LT_192x256, LT_256x128, LT_192x128, LT_128x128, LT_COUNT };
+constexpr int LARGE_SHAPES[LT_COUNT][2] = {{256, 256}, {256, 192}, {192, 256}, {256, 128}, {192, 128}, {128, 128}};
+constexpr unsigned large_tiles(int epi) {
+    return epi == EPI_STORE_F32 || epi == EPI_RESID_F32 ? (1u << LT_COUNT) - 1
+           : epi == EPI_SWIGLU                          ? 1u << LT_256x256 | 1u << LT_192x256 | 1u << LT_192x128
+           : epi == EPI_QKV                             ? 1u << LT_256x256 | 1u << LT_192x256 | 1u << LT_192x128 | 1u << LT_128x128
+           : epi == EPI_SWIGLU_RS || epi == EPI_LOGPROB ? 1u << LT_256x256 | 1u << LT_192x256
+                                                        : 0u;
+}
+
 template <typename T, int TMH, int TNH> struct LargeCfg {
     static constexpr int BM = 64 * TMH, BN = 64 * TNH, NP = 4;
     template <int E> static constexpr size_t smem() {   // a pair of units holds half of the rows, 2 bytes an element
@@ -604,32 +615,33 @@ template <typename T, int TMH, int TNH> struct LargeCfg {
 // The constants are a least-regret fit to 96 shapes of 520 to 16384 rows x 1536 to 151936 columns x 1536 to 17408 in every tile
 // and up to 8 slices: what it chooses takes 0.5 % longer on average than the best of them, 8 % at worst but for one (640 x 5120 x
 // 5120 where it may not slice: 22 %).
-struct LargeTile {
-    int id, bm, bn;
+struct LargeTime {
     double step, load, fixed;
 };
-enum { LT_256x256, LT_256x192, LT_192x256, LT_256x128, LT_192x128, LT_128x128 };
-static const LargeTile LARGE_TILES[] = {
-    {LT_256x256, 256, 256, 1.11, 0.37, 15.6}, {LT_256x192, 256, 192, 0.78, 0.57, 12.4}, {LT_192x256, 192, 256, 0.88, 0.55, 9.7},
-    {LT_256x128, 256, 128, 0.54, 0.76, 11.4}, {LT_192x128, 192, 128, 0.505, 0.355, 12.5}, {LT_128x128, 128, 128, 0.36, 0.73, 6.2},
-};
-static double large_cost(const LargeTile &t, int S, int M, int N, int K, int epi) {
+static const LargeTime LARGE_TIMES[LT_COUNT] = {{1.11, 0.37, 15.6}, {0.78, 0.57, 12.4}, {0.88, 0.55, 9.7},
+                                                {0.54, 0.76, 11.4}, {0.505, 0.355, 12.5}, {0.36, 0.73, 6.2}};
+static double large_cost(int id, int S, int M, int N, int K, int epi) {
+    const LargeTime &t = LARGE_TIMES[id];
+    const int bm = LARGE_SHAPES[id][0], bn = LARGE_SHAPES[id][1];
     const int KT = K / 64, per = (KT + S - 1) / S;
-    const int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * S, rounds = (tiles + 255) / 256;
+    const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * S, rounds = (tiles + 255) / 256;
     const double busy = (double)tiles / (256.0 * (double)rounds);
     const double fixed = epi == EPI_RESID_F32 ? t.fixed : 0.75 * t.fixed;
     return (double)rounds * per * t.step * (1.0 + t.load * busy * busy) + fixed + (double)(rounds - 1) * std::max(0.0, fixed - 6.0) +
            (S > 1 ? (double)S * M * N * 4.0 / 4.5e6 : 0.0);
 }
-static int large_pick(std::initializer_list<int> among, int max_slices, int M, int N, int K, int epi, int *S) {
-    const int KT = K / 64;
+// (two steps at least to a slice: the ring reaches that far ahead)
+static bool large_slices_ok(int S, int K) {
+    const int KT = K / 64, per = (KT + S - 1) / S;
+    return S == 1 || (per >= 4 && KT - (S - 1) * per >= 2);
+}
+static int large_pick(int max_slices, int M, int N, int K, int epi, int *S) {
     int best = -1;
     double best_cost = 0.0;
-    for (int id : among)
-        for (int n = 1; n <= max_slices; ++n) {
-            const int per = (KT + n - 1) / n;
-            if (n > 1 && (per < 4 || KT - (n - 1) * per < 2)) continue;   // (two steps at least: the ring reaches that far ahead)
-            const double c = large_cost(LARGE_TILES[id], n, M, N, K, epi);
+    for (int id = 0; id < LT_COUNT; ++id)
+        for (int n = 1; n <= max_slices && (large_tiles(epi) >> id & 1); ++n) {
+            if (!large_slices_ok(n, K)) continue;
+            const double c = large_cost(id, n, M, N, K, epi);
             if (best < 0 || c < best_cost) {
                 best = id;
                 best_cost = c;
@@ -646,83 +658,80 @@ static bool large_ok(const void *A, const void *W, const void *C, int M, int N, 
 }
 
 template <typename T> struct Large {
-    typedef LargeCfg<T, 4, 4> T256x256;
-    typedef LargeCfg<T, 4, 3> T256x192;
-    typedef LargeCfg<T, 3, 4> T192x256;
-    typedef LargeCfg<T, 4, 2> T256x128;
-    typedef LargeCfg<T, 3, 2> T192x128;
-    typedef LargeCfg<T, 2, 2> T128x128;
-    template <int E> static void init_plain() {
-        T256x256::template set_attr<E>(); T256x192::template set_attr<E>(); T192x256::template set_attr<E>();
-        T256x128::template set_attr<E>(); T192x128::template set_attr<E>(); T128x128::template set_attr<E>();
+    template <typename F> static void with_tile(int id, F f) {
+        switch (id) {
+            case LT_256x256: f(LargeCfg<T, 4, 4>()); break;
+            case LT_256x192: f(LargeCfg<T, 4, 3>()); break;
+            case LT_192x256: f(LargeCfg<T, 3, 4>()); break;
+            case LT_256x128: f(LargeCfg<T, 4, 2>()); break;
+            case LT_192x128: f(LargeCfg<T, 3, 2>()); break;
+            case LT_128x128: f(LargeCfg<T, 2, 2>()); break;
+        }
+    }
+    template <int E, typename Cfg> static constexpr bool built() {
+        for (int id = 0; id < LT_COUNT; ++id)
+            if (LARGE_SHAPES[id][0] == Cfg::BM && LARGE_SHAPES[id][1] == Cfg::BN) return large_tiles(E) >> id & 1;
+        return false;
+    }
+    template <int E> static void init_epilogue() {
+        for (int id = 0; id < LT_COUNT; ++id)
+            with_tile(id, [](auto cfg) {
+                if constexpr (built<E, decltype(cfg)>()) decltype(cfg)::template set_attr<E>();
+            });
     }
     static void init() {
-        init_plain<EPI_STORE_F32>();
-        init_plain<EPI_RESID_F32>();
-        T256x256::template set_attr<EPI_SWIGLU>(); T192x256::template set_attr<EPI_SWIGLU>(); T192x128::template set_attr<EPI_SWIGLU>();
-        T256x256::template set_attr<EPI_SWIGLU_RS>(); T192x256::template set_attr<EPI_SWIGLU_RS>();
-        T256x256::template set_attr<EPI_QKV>(); T192x256::template set_attr<EPI_QKV>(); T192x128::template set_attr<EPI_QKV>();
-        T128x128::template set_attr<EPI_QKV>();
-        T256x256::template set_attr<EPI_LOGPROB>(); T192x256::template set_attr<EPI_LOGPROB>();
+        init_epilogue<EPI_STORE_F32>(); init_epilogue<EPI_RESID_F32>(); init_epilogue<EPI_SWIGLU>();
+        init_epilogue<EPI_SWIGLU_RS>(); init_epilogue<EPI_QKV>(); init_epilogue<EPI_LOGPROB>();
     }
     template <int E>
-    static void plain(int id, const void *A, const void *W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s) {
-        switch (id) {
-            case LT_256x256: T256x256::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
-            case LT_256x192: T256x192::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
-            case LT_192x256: T192x256::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
-            case LT_256x128: T256x128::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
-            case LT_192x128: T192x128::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
-            default: T128x128::template launch<E>(A, W, C, M, N, K, S, sat, s, {}); break;
-        }
+    static void launch(int id, const void *A, const void *W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s,
+                       const typename GemmExtra<E>::type &extra) {
+        with_tile(id, [&](auto cfg) {
+            if constexpr (built<E, decltype(cfg)>()) decltype(cfg)::template launch<E>(A, W, C, M, N, K, S, sat, s, extra);
+        });
     }
     static int gemm(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap, uint32_t *sat,
                     hipStream_t s, const GemmRowScale *row_scale) {
         int S = 1;
-        if (epi == EPI_SWIGLU_RS) {   // (up to 512 rows: never many tiles)
-            if (large_pick({LT_256x256, LT_192x256}, 1, M, N, K, EPI_SWIGLU, &S) == LT_256x256)
-                T256x256::template launch<EPI_SWIGLU_RS>(A, W, C, M, N, K, 1, sat, s, *row_scale);
-            else
-                T192x256::template launch<EPI_SWIGLU_RS>(A, W, C, M, N, K, 1, sat, s, *row_scale);
-            return 1;
-        }
-        if (epi == EPI_SWIGLU) {
-            const int id = large_pick({LT_256x256, LT_192x256, LT_192x128}, 1, M, N, K, epi, &S);
-            if (id == LT_256x256) T256x256::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
-            else if (id == LT_192x256) T192x256::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
-            else T192x128::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
+        if (epi == EPI_SWIGLU_RS || epi == EPI_SWIGLU) {
+            const int id = large_pick(1, M, N, K, epi, &S);
+            if (epi == EPI_SWIGLU) launch<EPI_SWIGLU>(id, A, W, C, M, N, K, 1, sat, s, {});
+            else launch<EPI_SWIGLU_RS>(id, A, W, C, M, N, K, 1, sat, s, *row_scale);
             return 1;
         }
         // (the vocabulary projection of a decode step, whose time is half the weights' way from memory, which the estimate leaves out:
         // the shortest tile that holds the rows in one or two blocks, its figures stand at the rule that leads here)
         if (M <= 512 && epi == EPI_STORE_F32 && !slices) {
-            plain<EPI_STORE_F32>(M <= 256 ? LT_256x128 : (M <= 384 ? LT_192x256 : LT_256x256), A, W, C, M, N, K, 1, sat, s);
+            launch<EPI_STORE_F32>(M <= 256 ? LT_256x128 : (M <= 384 ? LT_192x256 : LT_256x256), A, W, C, M, N, K, 1, sat, s, {});
             return 1;
         }
         const int max_slices = slices ? (int)std::min<size_t>(8, slice_cap / ((size_t)M * N)) : 1;
-        const int id = large_pick({LT_256x256, LT_256x192, LT_192x256, LT_256x128, LT_192x128, LT_128x128}, std::max(1, max_slices), M, N, K,
-                                  epi, &S);
-        if (S > 1) plain<EPI_STORE_F32>(id, A, W, slices, M, N, K, S, sat, s);
-        else if (epi == EPI_RESID_F32) plain<EPI_RESID_F32>(id, A, W, C, M, N, K, 1, sat, s);
-        else plain<EPI_STORE_F32>(id, A, W, C, M, N, K, 1, sat, s);
+        const int id = large_pick(std::max(1, max_slices), M, N, K, epi, &S);
+        if (S > 1) launch<EPI_STORE_F32>(id, A, W, slices, M, N, K, S, sat, s, {});
+        else if (epi == EPI_RESID_F32) launch<EPI_RESID_F32>(id, A, W, C, M, N, K, 1, sat, s, {});
+        else launch<EPI_STORE_F32>(id, A, W, C, M, N, K, 1, sat, s, {});
         return S;
     }
     static void qkv(const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
         int S = 1;
-        switch (large_pick({LT_256x256, LT_192x256, LT_192x128, LT_128x128}, 1, M, N, K, EPI_QKV, &S)) {
-            case LT_256x256: T256x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
-            case LT_192x256: T192x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
-            case LT_192x128: T192x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
-            default: T128x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, q); break;
-        }
+        launch<EPI_QKV>(large_pick(1, M, N, K, EPI_QKV, &S), A, W, nullptr, M, N, K, 1, sat, s, q);
     }
     static int logprob(const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
         int S = 1;
-        if (large_pick({LT_256x256, LT_192x256}, 1, M, N, K, EPI_LOGPROB, &S) == LT_256x256)
-            T256x256::template launch<EPI_LOGPROB>(A, W, nullptr, M, N, K, 1, nullptr, s, lp);
-        else
-            T192x256::template launch<EPI_LOGPROB>(A, W, nullptr, M, N, K, 1, nullptr, s, lp);
+        launch<EPI_LOGPROB>(large_pick(1, M, N, K, EPI_LOGPROB, &S), A, W, nullptr, M, N, K, 1, nullptr, s, lp);
         return (N + 255) / 256 * 2;   // strips of 128 columns
+    }
+    // `extra`: the epilogue's own arguments, if it has any
+    static void named(int id, int epi, const void *A, const void *W, void *C, int M, int N, int K, int S, const void *extra, uint32_t *sat,
+                      hipStream_t s) {
+        switch (epi) {
+            case EPI_STORE_F32: launch<EPI_STORE_F32>(id, A, W, C, M, N, K, S, sat, s, {}); break;
+            case EPI_RESID_F32: launch<EPI_RESID_F32>(id, A, W, C, M, N, K, 1, sat, s, {}); break;
+            case EPI_SWIGLU: launch<EPI_SWIGLU>(id, A, W, C, M, N, K, 1, sat, s, {}); break;
+            case EPI_SWIGLU_RS: launch<EPI_SWIGLU_RS>(id, A, W, C, M, N, K, 1, sat, s, *(const GemmRowScale *)extra); break;
+            case EPI_QKV: launch<EPI_QKV>(id, A, W, nullptr, M, N, K, 1, sat, s, *(const GemmQkv *)extra); break;
+            case EPI_LOGPROB: launch<EPI_LOGPROB>(id, A, W, nullptr, M, N, K, 1, nullptr, s, *(const GemmLogprob *)extra); break;
+        }
     }
 };
 
@@ -754,3 +763,23 @@ int launch_gemm_large_logprob(int dtype, const void *A, const void *W, int M, in
 }
 
 }   // namespace pc
+
+// For tests and tuning, not part of the C ABI: one launch in the tile of bm rows x bn columns (`extra`: the GemmRowScale, GemmQkv
+// or GemmLogprob of such an epilogue).  1: launched; 0: no such tile with this epilogue, or not a call that the kernels take.
+extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int slices, const void *A, const void *W, void *C, int M, int N,
+                                      int K, const void *extra, uint32_t *sat, void *stream) {
+    using namespace pc;
+    const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS, own = epi == EPI_SWIGLU_RS || epi == EPI_QKV || epi == EPI_LOGPROB;
+    for (int id = 0; id < LT_COUNT; ++id) {
+        if (LARGE_SHAPES[id][0] != bm || LARGE_SHAPES[id][1] != bn || epi < 0 || !(large_tiles(epi) >> id & 1)) continue;
+        if ((dtype != KD_BF16 && dtype != KD_F16) || !A || !W || (!C && epi != EPI_QKV && epi != EPI_LOGPROB) || (own && !extra) || M <= 0 ||
+            N <= 0 || !large_ok(A, W, C, M, N, K) || (swiglu && N % 64 != 0) || (epi == EPI_QKV && N % 128 != 0) || slices < 1 ||
+            (slices > 1 && epi != EPI_STORE_F32) || !large_slices_ok(slices, K))
+            return 0;
+        gemm_large_init();
+        if (dtype == KD_BF16) Large<bf16_t>::named(id, epi, A, W, C, M, N, K, slices, extra, sat, (hipStream_t)stream);
+        else Large<f16_t>::named(id, epi, A, W, C, M, N, K, slices, extra, sat, (hipStream_t)stream);
+        return 1;
+    }
+    return 0;
+}
