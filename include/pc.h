@@ -70,9 +70,10 @@ typedef struct {
 /* Device pointers to the weights.  The per-layer members are HOST arrays of
  * n_layers DEVICE pointers.  Norm gains are fp32 [d_model]; everything else
  * has the model dtype.  lm_head may alias tok_embed (tied embeddings).
- * pc_create copies the per-layer matrices into its own fused layout (and, with
- * PC_ACT_F16, lm_head too), so only tok_embed, lm_head and final_norm must
- * outlive the context. */
+ * pc_create copies the per-layer matrices into its own fused layout (and lm_head
+ * too with PC_ACT_F16, or where a 16-bit lm_head does not start at a multiple of
+ * 16 bytes), so only tok_embed, lm_head and final_norm must outlive the
+ * context. */
 typedef struct {
     const void *tok_embed;  /* [vocab, d_model] */
     const void *lm_head;    /* [vocab, d_model] */

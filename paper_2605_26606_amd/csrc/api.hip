@@ -102,7 +102,7 @@ struct pc_ctx {
     pc_cache_config c;
     int device = 0;
     int kd = KD_F32;      // kernel dtype of activations, KV cache and weight copies
-    void *lm_head_copy = nullptr;   // half copy of lm_head (KD_F16)
+    void *lm_head_copy = nullptr;   // copy of lm_head: half (KD_F16), or aligned (KD_BF16)
     size_t esz = 2;
     // weights (library-owned fused copies, except embed / lm_head / final_norm)
     const void *tok_embed = nullptr, *lm_head = nullptr;
@@ -495,7 +495,9 @@ pc_status pc_create(const pc_model_config *model, const pc_weights *w, const pc_
         TRY_HIP(hipMemcpyAsync(g, w->ffn_norm[l], (size_t)m.d_model * 4, hipMemcpyDeviceToDevice, st));
     }
 
-    if (ctx->kd == KD_F16) {   // the output projection is read through a half copy
+    // the output projection is read through a half copy; a bfloat16 one in place, unless it starts off a 16-byte boundary, which
+    // the matrix-core kernels' wide loads want
+    if (ctx->kd == KD_F16 || (ctx->kd == KD_BF16 && ((uintptr_t)w->lm_head & 15) != 0)) {
         TRY(dev_alloc((char **)&ctx->lm_head_copy, (size_t)m.vocab * m.d_model * esz));
         launch_pack_rows(ctx->kd, w->lm_head, ctx->lm_head_copy, m.vocab, m.d_model, 0, 0, st);
         ctx->lm_head = ctx->lm_head_copy;

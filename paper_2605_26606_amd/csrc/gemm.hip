@@ -856,7 +856,7 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         else Cfg::run(A, W, C, M, N, K, epi, 1, sat, s);
         return split;
     };
-    if (M > 512) return whole(typename G::T256x128());   // (what gemm_large.hip does not take: operands off 16-byte boundaries, K = 64)
+    if (M > 512) return whole(typename G::T256x128());   // (what gemm_large.hip does not take: K = 64, widths beyond its limit)
     // blocks of one round of the chip, one per CU
     auto one_round = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) <= 256; };
     // decode: the weights are streamed once; fill the chip with blocks, by K slices where N is small

@@ -651,9 +651,10 @@ static int large_pick(int max_slices, int M, int N, int K, int epi, int *S) {
     return best;
 }
 
-static bool large_ok(const void *A, const void *W, const void *C, int M, int N, int K) {
-    // (rows of operands and results in whole 16-byte pieces; a tile's bytes within a buffer descriptor's 32 bits)
-    return K % 64 == 0 && K >= 128 && N % 16 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)C) & 15) == 0 &&
+static bool large_ok(const void *A, const void *W, const void *C, int M, int N, int K, int epi) {
+    // (two steps of K at least, the ring reaches that far ahead; rows of operands and results in whole 16-byte pieces, but fp32
+    // results may start at any float: the logits are the caller's; a tile's bytes within a buffer descriptor's 32 bits)
+    return K % 64 == 0 && K >= 128 && N % 16 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0 && ((uintptr_t)C & (epi == EPI_STORE_F32 ? 3 : 15)) == 0 &&
            K <= (1 << 21) && N <= (1 << 21);
 }
 
@@ -743,7 +744,7 @@ void gemm_large_init() {
 int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap,
                       uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
     const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS;
-    if ((epi != EPI_STORE_F32 && epi != EPI_RESID_F32 && !swiglu) || !large_ok(A, W, C, M, N, K) || ((uintptr_t)slices & 15) != 0 ||
+    if ((epi != EPI_STORE_F32 && epi != EPI_RESID_F32 && !swiglu) || !large_ok(A, W, C, M, N, K, epi) || ((uintptr_t)slices & 15) != 0 ||
         (swiglu && N % 64 != 0) || (epi == EPI_SWIGLU_RS && !row_scale))
         return 0;
     if (dtype == KD_BF16) return Large<bf16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s, row_scale);
@@ -751,14 +752,14 @@ int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, i
 }
 
 bool launch_gemm_large_qkv(int dtype, const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
-    if (!large_ok(A, W, nullptr, M, N, K)) return false;
+    if (!large_ok(A, W, nullptr, M, N, K, EPI_QKV)) return false;
     if (dtype == KD_BF16) Large<bf16_t>::qkv(A, W, M, N, K, q, sat, s);
     else Large<f16_t>::qkv(A, W, M, N, K, q, sat, s);
     return true;
 }
 
 int launch_gemm_large_logprob(int dtype, const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
-    if (!large_ok(A, W, nullptr, M, N, K)) return 0;
+    if (!large_ok(A, W, nullptr, M, N, K, EPI_LOGPROB)) return 0;
     return dtype == KD_BF16 ? Large<bf16_t>::logprob(A, W, M, N, K, lp, s) : Large<f16_t>::logprob(A, W, M, N, K, lp, s);
 }
 
@@ -773,7 +774,7 @@ extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int sl
     for (int id = 0; id < LT_COUNT; ++id) {
         if (LARGE_SHAPES[id][0] != bm || LARGE_SHAPES[id][1] != bn || epi < 0 || !(large_tiles(epi) >> id & 1)) continue;
         if ((dtype != KD_BF16 && dtype != KD_F16) || !A || !W || (!C && epi != EPI_QKV && epi != EPI_LOGPROB) || (own && !extra) || M <= 0 ||
-            N <= 0 || !large_ok(A, W, C, M, N, K) || (swiglu && N % 64 != 0) || (epi == EPI_QKV && N % 128 != 0) || slices < 1 ||
+            N <= 0 || !large_ok(A, W, C, M, N, K, epi) || (swiglu && N % 64 != 0) || (epi == EPI_QKV && N % 128 != 0) || slices < 1 ||
             (slices > 1 && epi != EPI_STORE_F32) || !large_slices_ok(slices, K))
             return 0;
         gemm_large_init();

@@ -361,6 +361,47 @@ def test_many_rows(d, dff, vocab, lens, act):
     _check(m, w, prompts, out, 21, 2e-2, range(0, len(lens), max(1, len(lens) // 9)))
 
 
+def test_output_projection_and_logits_off_16_byte_boundaries():
+    # an lm_head two bytes into an allocation (a view into a flat buffer of parameters), logits one float into theirs: the same
+    # bits as from aligned ones, for prefill, decode and scoring of few and of many rows; the misaligned head is copied by
+    # pc_create, its memory may change afterwards
+    import paper_2605_26606_amd as pc
+    say("lm_head and logits off 16-byte boundaries")
+    m = workloads.scaled(C1, dtype="bf16", d_model=128, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=256, vocab=65552,
+                         n_layers=1, rope_theta=1.0e6).model
+    w = workloads.weights_to(workloads.perturb_norm_gains(workloads.make_weights(m, 3), 10), "cuda")
+    rng = np.random.default_rng(5)
+    results = []
+    for off in (0, 1):
+        wd = dict(w)
+        flat = torch.empty(m.vocab * m.d_model + 8, dtype=torch.bfloat16, device="cuda")
+        wd["lm_head"] = flat[off:off + m.vocab * m.d_model].view(m.vocab, m.d_model)
+        wd["lm_head"].copy_(w["lm_head"])
+        ctx = pc.Context(m, wd, block_size=32, kv_pool_bytes=256 << 20, max_slots=1400, max_ctx=64, max_batch_rows=1400, act_dtype="bf16")
+        if off:
+            flat.zero_()
+        got = []
+        for P in (3, 200, 600):
+            toks = torch.from_numpy(np.random.default_rng(P).integers(0, m.vocab, 2 * P).astype(np.int32)).cuda()
+            cu = (np.arange(P + 1) * 2).astype(np.int32)
+            last = torch.empty(P * m.vocab + 4, device="cuda")[off:off + P * m.vocab].view(P, m.vocab)
+            logits = torch.empty(P * m.vocab + 4, device="cuda")[off:off + P * m.vocab].view(P, m.vocab)
+            handles = pc.pc_prefill_shared(ctx, toks, cu, last)
+            seqs = pc.pc_fork(ctx, handles, 4)
+            pc.pc_decode_step(ctx, seqs, toks[:P], logits)
+            pc.pc_release(ctx, seqs, 0)
+            pc.pc_release(ctx, handles, 1)
+            score = torch.empty(P, device="cuda")
+            pc.pc_score(ctx, toks, cu, np.ones(P, np.int32), 1.0, score)
+            got += [last.clone(), logits.clone(), score]
+        torch.cuda.synchronize()
+        ctx.close()
+        results.append(got)
+    assert float(results[0][0].abs().max()) > 0.05
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 def test_attention_keeps_the_largest_probability_exact():
     # One key holds nearly all of a head's weight, in a later tile than the largest score before it.  Its probability is 1 and
     # must not round: weighted values and weights are then summed alike and the output is the value itself.  (Taken relative to

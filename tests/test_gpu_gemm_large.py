@@ -1,5 +1,5 @@
 """Every tile of the large projection kernel by name, in every epilogue it is built for and both 16-bit types, against 64-bit
-sums: row and column remainders, one to five steps of K to a tile, several output tiles per block, an uneven last K slice.
+sums: row and column remainders, two, three and five steps of K to a tile, several output tiles per block, an uneven last K slice.
 (The library chooses a tile by an estimate of its time, so the sizes of a model test say little about which one runs.)
 
 Tolerances.  The operands are exact in 16 bits; a product is summed in float32, K of them with at most K roundings of 2^-24 each:
@@ -106,6 +106,13 @@ def test_plain_tiles(epi, tile, act):
         want = exact + old.double()
         assert bool(((c.double() - want).abs() <= d + 2.0 ** -23 * want.abs()).all())
         assert bool((whole[m:] == GUARD).all())
+    if epi == STORE:   # results that start at any float
+        m, n, k = tile[0] + 3, tile[1] + 48, 128
+        a, w, exact, d = _operands(act, m, n, k, 6)
+        flat = torch.full((m * n + 8,), GUARD, device="cuda")
+        assert _launch(act, tile, epi, a, w, flat[1:])
+        assert bool(((flat[1:1 + m * n].double().reshape(m, n) - exact).abs() <= d).all())
+        assert bool((flat[1 + m * n:] == GUARD).all()) and float(flat[0]) == GUARD
     if epi == STORE:   # K slices: 4 + 4 + 3 steps; the sum of the slices is the product
         m, n, k, s = tile[0] + 5, tile[1] + 16, 704, 3
         a, w, exact, d = _operands(act, m, n, k, 5)
