@@ -654,7 +654,9 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
                        const typename GemmExtra<E>::type &extra) {
         const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
         const int units = nb * split;
-        const int plain = (split == 1 && mb > 4) ? ((mb % N_XCD == 0) ? 2 : 1) : 0;
+        // (log-probabilities: the vocabulary is so wide that a die keeps to one weight slab for all its row blocks where no
+        // patches fit; in plain order every die streams all of the weights, 1640 rows x 151936 x 5120: 3001 against 2499 us)
+        const int plain = (split == 1 && mb > 4) ? ((mb % N_XCD == 0) ? 2 : (E == EPI_LOGPROB ? 0 : 1)) : 0;
         const unsigned grid = plain ? (unsigned)(mb * nb) : (unsigned)((units + N_XCD - 1) / N_XCD * N_XCD * mb);
         gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, E, M16><<<grid, 64 * WM * WN, smem, s>>>(
             (const T *)A, (const T *)W, C, M, N, K, mb, nb, split, plain, sat, extra);
@@ -698,9 +700,11 @@ template <typename T> struct Gemm {
     // 256 x 128, 8 waves of 64 x 64: decode batches of 193 to 256 rows
     typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> T256x128;
     typedef MfmaCfg<T, 256, 192, 4, 2, 2, 64, true> T256x192;
+    typedef MfmaCfg<T, 256, 256, 4, 2, 4, 32, true> T256x256;   // short reductions of many rows; 64 x 128 per wave: three fragment reads per four products
     typedef MfmaCfg<T, 192, 128, 4, 2, 3, 64, true> T192x128;
     typedef MfmaCfg<T, 192, 192, 4, 2, 3, 64, true> T192x192;
     typedef MfmaCfg<T, 128, 128, 4, 2, 4, 64, true> T128x128;   // 8 waves of 32 x 64: up to 128 rows what counts is loads in flight
+    typedef MfmaCfg<T, 128, 128, 4, 2, 2, 64, true> T128x128_2; // two stages, 64 KB of LDS: two blocks per CU
     typedef MfmaCfg<T, 128, 192, 4, 2, 3, 64, true> T128x192;
     typedef MfmaCfg<T, 64, 128, 2, 4, 3, 64, true> T64x128;     // 72 KB of LDS: two blocks per CU
     typedef MfmaCfg<T, 64, 192, 4, 2, 4, 64, true> T64x192;
@@ -711,9 +715,10 @@ template <typename T> struct Gemm {
     typedef MfmaCfg<T, 192, 64, 4, 2, 4, 64, true> T192x64;     // the same in wave tiles of 48 x 32
     typedef MfmaCfg<T, 64, 64, 2, 2, 4> M64x64;                 // wave tile 32 x 32: many blocks for the small projections
     static void init() {
-        T256x128::init(); T256x192::init(); T192x128::init(); T192x192::init(); T128x128::init(); T128x192::init();
-        T256x160::init(); T64x128::init(); T64x192::init(); T32x64::init(); T32x64_2::init(); T128x64::init();
-        T192x64::init(); M64x64::init();
+        T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
+        T128x128_2::init(); T128x192::init(); T256x160::init(); T64x128::init(); T64x192::init(); T32x64::init();
+        T32x64_2::init(); T128x64::init(); T192x64::init(); M64x64::init();
+        T256x256::init_logprob();
         T256x128::init_logprob();
         T192x128::init_logprob();
         T128x128::init_logprob();
@@ -728,6 +733,7 @@ void gemm_init() {
 template <typename T>
 static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices,
                               size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale);
+static int large_min_k(bool swiglu) { return swiglu ? 128 : 256; }   // the shortest reduction that gemm_large.hip gets above 512 rows
 
 int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int M, int N, int K, int epi,
                 float *slices, size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
@@ -743,13 +749,21 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
         else gemm_simt<f16_t>(A, W, C, M, N, K, epi, sat, s);
         return 1;
     }
-    // Four waves with a quarter of a large tile each (gemm_large.hip) win above 512 rows, on gate/up above 384 (1.5B shape at 512
-    // rows 51.9 -> 31.8 us against three 128-row blocks per CU, 8B 111 -> 91 us) and on the vocabulary projection above 192 (1.5B /
-    // 8B shape: 161 / 361 -> 158 / 346 us at 256 rows, 218 / 480 -> 209 / 431 at 380, 284 / 612 -> 233 / 522 at 500); gate/up at
-    // 256 rows takes as long either way (27.9 and 27.1 us).
+    // Four waves with a quarter of a large tile each (gemm_large.hip) win above 512 rows, on gate/up above 384 (512 rows x 17920 x
+    // 1536 with the norm scale 51.2 -> 37.2 us against three 128-row blocks per CU, 24576 x 4096 108 -> 89) and on the vocabulary
+    // projection above 192 (151936 x 1536 / 4096: 160 / 360 -> 157 / 336 us at 256 rows, 218 / 481 -> 206 / 425 at 384, 288 / 601 ->
+    // 237 / 512 at 512; not yet at 256 rows of 5120: 444 -> 455, 580 -> 553 at 384); gate/up at 256 rows takes as long either way (27.9 and 27.1 us).
+    // Not where the reduction is so short that the epilogue is most of it, which eight waves with half the values each get through
+    // faster: gate/up 1024 rows x 6400, K = 64 6.8 against 7.7 us (7000 x 16384: 48.7, 49.5; K = 128: 58.1, 47.5); 600 x 512 / 1024 x 2048
+    // with residual, K = 128 9.7 / 14.4 against 10.4 / 14.6, K = 256 11.2 / 16.0 against 11.3 / 15.5; 400 rows of gate/up x 6400, K = 256 6.1
+    // against 10.3, K = 384 8.9 against 8.4; 384 x 65552 fp32, K = 128 28.2 against 31.8, K = 256 37.5 against 34.5.
     const int nb128 = (N + 127) / 128;
-    if (M > 512 || (M > 384 && (epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS || nb128 >= 96)) ||
-        (M > 192 && nb128 >= 512 && epi == EPI_STORE_F32)) {
+    const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS;
+    const bool large = M > 512   ? K >= large_min_k(swiglu)
+                       : swiglu  ? M > 384 && K >= 384
+                                 : (M > 384 && nb128 >= 96) ||
+                                       (M > 192 && nb128 >= 512 && epi == EPI_STORE_F32 && K >= 256 && (M > 256 || K <= 4096));
+    if (large) {
         const int S = launch_gemm_large(dtype, A, W, C, M, N, K, epi, slices, slice_cap_floats, sat, s, row_scale);
         if (S) return S;
     }
@@ -818,9 +832,12 @@ static void gemm_logprob_t(const void *A, const void *W, int M, int N, int K, Ge
         strips = decltype(cfg)::strips(N);
         decltype(cfg)::template launch<EPI_LOGPROB>(A, W, nullptr, M, N, K, 1, nullptr, s, lpa);
     };
-    if (M > 512) strips = launch_gemm_large_logprob(std::is_same<T, bf16_t>::value ? KD_BF16 : KD_F16, A, W, M, N, K, lpa, s);
+    // (short reductions: the epilogue is most of it and eight waves get through it faster: 4500 rows x 151936 x 256 616 us against
+    // 820, 3072 x 151936 x 512 586 against 688, 1400 and 2048 x 151936 x 768 418 and 586 against 429 and 566)
+    if (M > 512 && K >= 1024) strips = launch_gemm_large_logprob(std::is_same<T, bf16_t>::value ? KD_BF16 : KD_F16, A, W, M, N, K, lpa, s);
     if (strips == 0) {
-        if (M <= 128) run(typename G::T128x128());
+        if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256 && M > 512) run(typename G::T256x256());
+        else if (M <= 128) run(typename G::T128x128());
         else if (M <= 192) run(typename G::T192x128());
         else run(typename G::T256x128());
     }
@@ -856,7 +873,14 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         else Cfg::run(A, W, C, M, N, K, epi, 1, sat, s);
         return split;
     };
-    if (M > 512) return whole(typename G::T256x128());   // (what gemm_large.hip does not take: K = 64, widths beyond its limit)
+    if (M > 512) {
+        if (K >= large_min_k(swiglu)) return whole(typename G::T256x128());   // (widths beyond gemm_large.hip's limit)
+        // 256 x 256 tiles where they still come in several rounds per CU, 256 x 128 below that
+        if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) return whole(typename G::T256x256());
+        // (a few row blocks against a narrow projection leave most CUs without a tile: smaller ones, and K slices)
+        if ((int64_t)((M + 255) / 256) * ((N + 127) / 128) < 160 && can_split) return sliced(typename G::T128x128_2(), 240);
+        return whole(typename G::T256x128());
+    }
     // blocks of one round of the chip, one per CU
     auto one_round = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) <= 256; };
     // decode: the weights are streamed once; fill the chip with blocks, by K slices where N is small
@@ -881,7 +905,10 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         // two 192-row blocks instead of two of 256 (380 rows: 24576 x 4096 70 us against 119 us, 17920 x 1536 27 us against 33
         // us with three 128-row blocks)
         if (M <= 384) return whole(typename G::T192x192());
-        return whole(typename G::T256x128());   // (what gemm_large.hip does not take)
+        // (up to 512 rows, gate/up of a short reduction: 400 rows x 6400 x 256 6.1 us, 8.2 in 256 x 128, 7.5 with three 128-row blocks per
+        // CU; beyond one round 256 x 128, 400 x 16384 x 256 9.8, 11.6 and 10.4)
+        if (swiglu && K < 384 && one_round(128, 128)) return whole(typename G::T128x128());
+        return whole(typename G::T256x128());
     }
     // The smallest batches stream the weights and little else: rows loaded for nothing (a tile of 128 for 3) cost as much of
     // the load path as the weights (4096 x 12288 at 3 rows: 20 us against 27 us, 1536 x 8960: 6.6 against 9.5 us)

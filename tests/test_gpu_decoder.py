@@ -361,6 +361,21 @@ def test_many_rows(d, dff, vocab, lens, act):
     _check(m, w, prompts, out, 21, 2e-2, range(0, len(lens), max(1, len(lens) // 9)))
 
 
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_many_rows_of_a_64_wide_model(act):
+    # every reduction but the down projection's is a single step of 64: prefill and decode of more than 512 rows
+    say("64-wide model, %s" % act)
+    m = workloads.scaled(C1, dtype="bf16", d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=1184, vocab=65552,
+                         n_layers=2, rope_theta=1.0e6).model
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 3, std=0.05), 10)
+    lens = np.random.default_rng(4).integers(1, 9, 173).tolist()
+    toks, cu = workloads.make_ragged_prompts(lens, m.vocab, 8)
+    prompts = [toks[cu[i]:cu[i + 1]] for i in range(len(lens))]
+    out = _run_generate(m, w, prompts, 3, 2, 21, dict(block_size=32, kv_pool_bytes=256 << 20, max_slots=720, max_ctx=64,
+                                                     max_batch_rows=1400, act_dtype=act))
+    _check(m, w, prompts, out, 21, 2e-2, [0, 100, 259, 400, 518])
+
+
 def test_output_projection_and_logits_off_16_byte_boundaries():
     # an lm_head two bytes into an allocation (a view into a flat buffer of parameters), logits one float into theirs: the same
     # bits as from aligned ones, for prefill, decode and scoring of few and of many rows; the misaligned head is copied by
