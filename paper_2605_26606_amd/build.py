@@ -37,14 +37,16 @@ def build(verbose: bool = False) -> str:
     cc = _hipcc()
     objs = [os.path.join(OBJ, s.replace(".hip", ".o")) for s in SOURCES]
 
-    def one(i):
-        return _run([cc, *FLAGS, "-c", os.path.join(CSRC, SOURCES[i]), "-o", objs[i]])
+    bench = os.path.join(OBJ, "kernel_bench.o")
+
+    def one(job):
+        quiet = ["-Wno-unused-value"] if job[1] == bench else []
+        return _run([cc, *FLAGS, *quiet, "-c", os.path.join(CSRC, job[0]), "-o", job[1]])
 
     with ThreadPoolExecutor(max_workers=min(6, os.cpu_count() or 1)) as ex:
-        outs = list(ex.map(one, range(len(SOURCES))))
+        outs = list(ex.map(one, [("kernel_bench.hip", bench), *zip(SOURCES, objs)]))
     outs.append(_run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]))
-    outs.append(_run([cc, *[f for f in FLAGS if f != "-fPIC"], "-Wno-unused-value", os.path.join(CSRC, "kernel_bench.hip"),
-                      "-o", KERNEL_BENCH]))
+    outs.append(_run([cc, "--offload-arch=gfx950", "-o", KERNEL_BENCH, bench, objs[SOURCES.index("elementwise.hip")]]))
     if verbose:
         sys.stdout.write("\n".join(o for o in outs if o.strip()) + "\n")
     return LIB

@@ -874,7 +874,7 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         return split;
     };
     if (M > 512) {
-        if (K >= large_min_k(swiglu)) return whole(typename G::T256x128());   // (widths beyond gemm_large.hip's limit)
+        if (K >= large_min_k(swiglu)) return whole(typename G::T256x128());   // (gate/up that gemm_large.hip left to this tile; widths beyond its limit)
         // 256 x 256 tiles where they still come in several rounds per CU, 256 x 128 below that
         if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) return whole(typename G::T256x256());
         // (a few row blocks against a narrow projection leave most CUs without a tile: smaller ones, and K slices)

@@ -578,9 +578,10 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
 #endif
 }
 
-// The tiles, and in which of them an epilogue exists (one bit each).
-enum { LT_256x256, LT_256x192, LT_192x256, LT_256x128, LT_192x128, LT_128x128, LT_COUNT };
-constexpr int LARGE_SHAPES[LT_COUNT][2] = {{256, 256}, {256, 192}, {192, 256}, {256, 128}, {192, 128}, {128, 128}};
+// The tiles, and in which of them an epilogue exists (one bit each).  LT_EIGHT: not here, but the 256 x 128 tile on eight waves of
+// gemm_mfma, whose epilogues take fewer values per lane.
+enum { LT_256x256, LT_256x192, LT_192x256, LT_256x128, LT_192x128, LT_128x128, LT_COUNT, LT_EIGHT = LT_COUNT };
+constexpr int LARGE_SHAPES[LT_COUNT + 1][2] = {{256, 256}, {256, 192}, {192, 256}, {256, 128}, {192, 128}, {128, 128}, {256, 128}};
 constexpr unsigned large_tiles(int epi) {
     return epi == EPI_STORE_F32 || epi == EPI_RESID_F32 ? (1u << LT_COUNT) - 1
            : epi == EPI_SWIGLU                          ? 1u << LT_256x256 | 1u << LT_192x256 | 1u << LT_192x128
@@ -609,45 +610,76 @@ template <typename T, int TMH, int TNH> struct LargeCfg {
 };
 
 // ---- which tile, how many K slices
-// Estimated microseconds of a launch: rounds of blocks (one per CU) times K steps times the time of a step, plus what the first
-// and each further tile of a block cost beside their steps.  A step takes longer the more CUs are busy (`load`: the clock falls under
-// the matrix cores' power, 2.0 PFLOP/s on operands of zeros and 1.45 on random ones); K slices are written and read once more.
-// The constants are a least-regret fit to 96 shapes of 520 to 16384 rows x 1536 to 151936 columns x 1536 to 17408 in every tile
-// and up to 8 slices: what it chooses takes 0.5 % longer on average than the best of them, 8 % at worst but for one (640 x 5120 x
-// 5120 where it may not slice: 22 %).
+// Estimated microseconds of a launch: rounds of blocks (one per CU) times K steps times the time of a step, plus what the first and
+// each further tile of a block cost beside their steps, plus the fp32 results' way to the kernel that reads them.  A step takes
+// longer the more CUs are busy (`load`: the clock falls under the matrix cores' power, 2.0 PFLOP/s on operands of zeros and 1.45 on
+// random ones).  The constants are a least-squares fit, then moved a little for least regret, to the times of 720 launches of 513 to
+// 16384 rows x 512 to 151936 columns x 128 to 17408, each in every tile and up to 8 slices (profiles/large_tile_times.txt, taken by
+// kernel_bench tiles; tests/test_tile_choice.py holds the choice against them): what it chooses takes 0.9 % longer on average than
+// the fastest form, 13 % at worst from K = 1024 up (576 x 32000 x 2048) and 39 % below (16384 x 2368 x 256, 32 us for 23).  (One set of
+// constants for all epilogues, fitted without the norm that reads the slices and to K of 1536 and more, was up to 28 % off there and
+// 60 % below: 640 rows x 2560 x 9728 58.2 us for 44.5.)
 struct LargeTime {
-    double step, load, fixed;
+    double step, load, first, next;
 };
-static const LargeTime LARGE_TIMES[LT_COUNT] = {{1.11, 0.37, 15.6}, {0.78, 0.57, 12.4}, {0.88, 0.55, 9.7},
-                                                {0.54, 0.76, 11.4}, {0.505, 0.355, 12.5}, {0.36, 0.73, 6.2}};
-static double large_cost(int id, int S, int M, int N, int K, int epi) {
+static const LargeTime LARGE_TIMES[LT_COUNT + 1] = {{0.96, 0.274, 12.1, 2.98}, {0.78, 0.269, 11.1, 1.99}, {0.794, 0.235, 10.8, 2.03},
+                                                    {0.591, 0.171, 8.87, 1.65}, {0.54, 0.150, 8.01, 1.03}, {0.478, 0.173, 7.85, 0.902},
+                                                    {0.619, 0.248, 5.61, 4.05}};
+struct LargeEpilogue {
+    double first, next;   // times those of the tile
+};
+static LargeEpilogue large_epilogue(int id, int epi) {
+    if (id == LT_EIGHT) return epi == EPI_QKV ? LargeEpilogue{2.34, 2.13} : LargeEpilogue{1.0, 1.0};
+    switch (epi) {
+        case EPI_RESID_F32: return {1.32, 2.97};
+        case EPI_SWIGLU: case EPI_SWIGLU_RS: return {0.694, 1.61};
+        case EPI_QKV: return {2.46, 2.88};
+        case EPI_LOGPROB: return {1.24, 3.72};
+        default: return {1.35, 2.79};
+    }
+}
+// `decode`: q/k/v of rows that all belong to different sequences, whose keys and values go all over the cache.  `read_back`: fp32
+// results of which a kernel behind this one reads all slices.
+static double large_cost(int id, int S, int M, int N, int K, int epi, bool decode, bool read_back) {
     const LargeTime &t = LARGE_TIMES[id];
+    const LargeEpilogue e = large_epilogue(id, S > 1 ? (int)EPI_STORE_F32 : epi);
     const int bm = LARGE_SHAPES[id][0], bn = LARGE_SHAPES[id][1];
     const int KT = K / 64, per = (KT + S - 1) / S;
     const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * S, rounds = (tiles + 255) / 256;
-    const double busy = (double)tiles / (256.0 * (double)rounds);
-    const double fixed = epi == EPI_RESID_F32 ? t.fixed : 0.75 * t.fixed;
-    return (double)rounds * per * t.step * (1.0 + t.load * busy * busy) + fixed + (double)(rounds - 1) * std::max(0.0, fixed - 6.0) +
-           (S > 1 ? (double)S * M * N * 4.0 / 4.5e6 : 0.0);
+    const double busy = (double)tiles / (256.0 * (double)rounds), mb = (double)M * N * 4e-6;
+    return (double)rounds * per * t.step * (1.0 + t.load * busy * busy) + t.first * e.first + (double)(rounds - 1) * t.next * e.next +
+           (read_back ? 0.39 * S * mb : 0.0) + (decode ? (id == LT_EIGHT ? 10.5 : 2.1) : 0.0);
+}
+// The tiles that a launch of this epilogue chooses from.  (The eight waves win where the epilogue is much of the launch:
+// gate/up of short reductions, 1280 rows x 6400 x 128 7.9 us against 9.6, x 768 15.5 against 18.5.)
+static unsigned large_choice(int epi) {
+    return large_tiles(epi) | (epi == EPI_SWIGLU ? 1u << LT_EIGHT : 0u);
 }
 // (two steps at least to a slice: the ring reaches that far ahead)
 static bool large_slices_ok(int S, int K) {
     const int KT = K / 64, per = (KT + S - 1) / S;
     return S == 1 || (per >= 4 && KT - (S - 1) * per >= 2);
 }
-static int large_pick(int max_slices, int M, int N, int K, int epi, int *S) {
+static int large_pick(int max_slices, int M, int N, int K, int epi, int *S, bool decode = false, bool read_back = false) {
     int best = -1;
     double best_cost = 0.0;
-    for (int id = 0; id < LT_COUNT; ++id)
-        for (int n = 1; n <= max_slices && (large_tiles(epi) >> id & 1); ++n) {
+    for (int id = 0; id <= LT_EIGHT; ++id)
+        for (int n = 1; n <= max_slices && (large_choice(epi) >> id & 1); ++n) {
             if (!large_slices_ok(n, K)) continue;
-            const double c = large_cost(id, n, M, N, K, epi);
+            const double c = large_cost(id, n, M, N, K, epi, decode, read_back);
             if (best < 0 || c < best_cost) {
                 best = id;
                 best_cost = c;
                 *S = n;
             }
         }
+    // (gate/up in three whole rounds of the eight-wave tile where the larger one half-fills its second: 1024 x 24576 x 4096 168.5 us
+    // against 176.8, 1280 x 19456 x 2560 112.8 and 117.1; on another card 153.0, 153.7 and 101.3, 104.4)
+    auto fill = [&](int bm, int bn) {
+        const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+        return (double)tiles / (256.0 * (double)((tiles + 255) / 256));
+    };
+    if (epi == EPI_SWIGLU && best == LT_256x256 && K >= 2048 && fill(256, 128) > 0.98 && fill(256, 256) < 0.77) best = LT_EIGHT;
     return best;
 }
 
@@ -696,6 +728,7 @@ template <typename T> struct Large {
         int S = 1;
         if (epi == EPI_SWIGLU_RS || epi == EPI_SWIGLU) {
             const int id = large_pick(1, M, N, K, epi, &S);
+            if (id == LT_EIGHT) return 0;
             if (epi == EPI_SWIGLU) launch<EPI_SWIGLU>(id, A, W, C, M, N, K, 1, sat, s, {});
             else launch<EPI_SWIGLU_RS>(id, A, W, C, M, N, K, 1, sat, s, *row_scale);
             return 1;
@@ -707,15 +740,18 @@ template <typename T> struct Large {
             return 1;
         }
         const int max_slices = slices ? (int)std::min<size_t>(8, slice_cap / ((size_t)M * N)) : 1;
-        const int id = large_pick(std::max(1, max_slices), M, N, K, epi, &S);
+        const int id = large_pick(std::max(1, max_slices), M, N, K, epi, &S, false, epi == EPI_RESID_F32 || slices);
         if (S > 1) launch<EPI_STORE_F32>(id, A, W, slices, M, N, K, S, sat, s, {});
         else if (epi == EPI_RESID_F32) launch<EPI_RESID_F32>(id, A, W, C, M, N, K, 1, sat, s, {});
         else launch<EPI_STORE_F32>(id, A, W, C, M, N, K, 1, sat, s, {});
         return S;
     }
-    static void qkv(const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
+    static bool qkv(const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
         int S = 1;
-        launch<EPI_QKV>(large_pick(1, M, N, K, EPI_QKV, &S), A, W, nullptr, M, N, K, 1, sat, s, q);
+        const int id = large_pick(1, M, N, K, EPI_QKV, &S, !q.row_pos);
+        if (id == LT_EIGHT) return false;
+        launch<EPI_QKV>(id, A, W, nullptr, M, N, K, 1, sat, s, q);
+        return true;
     }
     static int logprob(const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
         int S = 1;
@@ -753,9 +789,7 @@ int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, i
 
 bool launch_gemm_large_qkv(int dtype, const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
     if (!large_ok(A, W, nullptr, M, N, K, EPI_QKV)) return false;
-    if (dtype == KD_BF16) Large<bf16_t>::qkv(A, W, M, N, K, q, sat, s);
-    else Large<f16_t>::qkv(A, W, M, N, K, q, sat, s);
-    return true;
+    return dtype == KD_BF16 ? Large<bf16_t>::qkv(A, W, M, N, K, q, sat, s) : Large<f16_t>::qkv(A, W, M, N, K, q, sat, s);
 }
 
 int launch_gemm_large_logprob(int dtype, const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
@@ -783,4 +817,10 @@ extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int sl
         return 1;
     }
     return 0;
+}
+// The tile (its place in the list above; LT_EIGHT: gemm_mfma's) and the number of K slices that the estimate chooses, up to
+// max_slices where there is room for slices (0: there is none).
+extern "C" int pc_internal_gemm_large_pick(int epi, int decode, int max_slices, int M, int N, int K, int *slices) {
+    *slices = 1;
+    return pc::large_pick(max_slices > 1 ? max_slices : 1, M, N, K, epi, slices, decode != 0, max_slices > 0 || epi == pc::EPI_RESID_F32);
 }

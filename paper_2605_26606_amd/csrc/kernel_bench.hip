@@ -7,13 +7,17 @@
 //       event_study: also brackets single launches with an event pair, as the library's per-launch timing does,
 //       next to pairs around nothing / one / two empty kernels and around two launches
 //   kernel_bench gemm
+//   kernel_bench tiles [launch ...]                         (projections of more than 512 rows in every tile and K slicing:
+//       what the choice of gemm_large.hip is fitted to; launches as listed in bench_tiles, all by default)
 //   kernel_bench copy                                       (a plain 1 GiB copy: the counters' known-size reference)
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
+#include <string>
 #include <vector>
 
-#include "attention.hip"
+#include "attention.hip"   // (elementwise.hip is linked)
 #include "gemm.hip"
 #include "gemm_large.hip"
 
@@ -199,6 +203,137 @@ static int bench_gemm() {
     return rc;
 }
 
+// One line per launch: name, rows, columns, K, "dec" (every row a sequence of its own, as in a decode step) or "pre" (prompts), then
+// the best of five times in us of every form that computes it: tile[/K slices], m...: a tile of gemm_mfma.  A projection onto the
+// residual stream includes the norm behind it, which reads the slices.  Weights come from memory, activations are hot.
+static int bench_tiles(int n_only, char **only) {
+    typedef f16_t T;
+    typedef Gemm<T> G;
+    typedef Large<T> L;
+    const int RMAX = 16384, SLOTS = 1024, PER_SLOT = 32, BS = 64, HKV = 8;
+    const size_t W_BYTES = (size_t)3 << 30, SLICE_CAP = (size_t)8 << 20;
+    char *A, *W, *C, *out;
+    float *slices, *table_f, *gain;
+    void *pool;
+    CK(hipMalloc(&A, (size_t)RMAX * 17408 * 2));
+    CK(hipMalloc(&W, W_BYTES));
+    CK(hipMalloc(&C, (size_t)RMAX * 17920 * 4));
+    CK(hipMalloc(&out, (size_t)RMAX * 17920 * 2));
+    CK(hipMalloc(&slices, SLICE_CAP * 4));
+    CK(hipMalloc(&table_f, 4096 * 64 * 4));   // rotary cosines and sines
+    CK(hipMalloc(&gain, RMAX * 4));
+    CK(hipMalloc(&pool, (size_t)SLOTS * PER_SLOT * BS * HKV * 128 * 2 * 2));
+    fill_half_kernel<<<(unsigned)((size_t)RMAX * 17408 / 256), 256>>>((uint16_t *)A, (size_t)RMAX * 17408, 1);
+    fill_half_kernel<<<(unsigned)(W_BYTES / 2 / 256), 256>>>((uint16_t *)W, W_BYTES / 2, 77);
+    CK(hipMemset(C, 0, (size_t)RMAX * 17920 * 4));
+    CK(hipMemset(table_f, 0, 4096 * 64 * 4));
+    CK(hipMemset(gain, 0, RMAX * 4));
+    std::vector<int32_t> blocks((size_t)SLOTS * PER_SLOT), id(RMAX + 8), prompt(RMAX), in_prompt(RMAX), seq(RMAX), len(SLOTS), token(RMAX + 8);
+    for (size_t i = 0; i < blocks.size(); ++i) blocks[i] = (int)((i * 7919 + 13) % blocks.size());   // (7919 is prime: a permutation)
+    for (int i = 0; i < RMAX; ++i) {
+        prompt[i] = i / 512;
+        in_prompt[i] = i % 512;
+        seq[i] = i % SLOTS;
+    }
+    for (int i = 0; i < SLOTS; ++i) len[i] = 300 + i * 37 % 1200;
+    for (int i = 0; i < RMAX + 8; ++i) {
+        id[i] = i;
+        token[i] = i * 977 % 150000;
+    }
+    auto up = [](const std::vector<int32_t> &v) {
+        int32_t *p = nullptr;
+        if (hipMalloc(&p, v.size() * 4) != hipSuccess || hipMemcpy(p, v.data(), v.size() * 4, hipMemcpyHostToDevice) != hipSuccess) exit(1);
+        return p;
+    };
+    int32_t *d_blocks = up(blocks), *d_id = up(id), *d_prompt = up(prompt), *d_in = up(in_prompt), *d_seq = up(seq), *d_len = up(len),
+            *d_token = up(token);
+    KvGeom kv{pool, 0, BS, HKV, 128, PER_SLOT, d_blocks};
+    gemm_init();
+    hipEvent_t e0, e1;
+    CK(hipEventCreate(&e0));
+    CK(hipEventCreate(&e1));
+    struct Launch { const char *name; int epi, N, K, hq = 0, hkv = 0; };
+    std::vector<Launch> launches = {
+        {"qkv1.5", EPI_QKV, 2048, 1536, 12, 2}, {"qkv8", EPI_QKV, 6144, 4096, 32, 8}, {"qkv14", EPI_QKV, 7168, 5120, 40, 8},
+        {"qkv1k", EPI_QKV, 1536, 1024, 8, 2}, {"qkv2.5k", EPI_QKV, 4096, 2560, 16, 8}, {"o1.5", EPI_RESID_F32, 1536, 1536},
+        {"o8", EPI_RESID_F32, 4096, 4096}, {"o14", EPI_RESID_F32, 5120, 5120}, {"down1.5", EPI_RESID_F32, 1536, 8960},
+        {"down8", EPI_RESID_F32, 4096, 12288}, {"down14", EPI_RESID_F32, 5120, 17408}, {"o2.5k", EPI_RESID_F32, 2560, 2048},
+        {"down2.5k", EPI_RESID_F32, 2560, 9728}, {"gu1.5", EPI_SWIGLU, 17920, 1536}, {"gu8", EPI_SWIGLU, 24576, 4096},
+        {"gu14", EPI_SWIGLU, 34816, 5120}, {"gu2.5k", EPI_SWIGLU, 19456, 2560}, {"head1.5", EPI_STORE_F32, 151936, 1536},
+        {"head8", EPI_STORE_F32, 151936, 4096}, {"head14", EPI_STORE_F32, 151936, 5120}, {"head32k", EPI_STORE_F32, 32000, 2048},
+        {"lp1.5", EPI_LOGPROB, 151936, 1536}, {"lp8", EPI_LOGPROB, 151936, 4096}, {"lp32k", EPI_LOGPROB, 32000, 2048}};
+    for (int K : {128, 256, 512, 768}) {   // short reductions, as far down as these tiles are used
+        for (int N : {2368, 6400, 16384}) launches.push_back({"gu_k", EPI_SWIGLU, N, K});
+        if (K < 256) continue;
+        for (int N : {512, 2048}) launches.push_back({"o_k", EPI_RESID_F32, N, K});
+        for (int N : {32768, 65552}) launches.push_back({"head_k", EPI_STORE_F32, N, K});
+    }
+    const int rows[] = {513, 576, 640, 704, 768, 832, 896, 960, 1024, 1152, 1280, 1408, 1536, 1792, 2048, 2560, 3072, 3500, 4096, 5000,
+                        6144, 7000, 8192, 10000, 12288, 16384};
+    for (const Launch &l : launches)
+        for (int M : rows)
+            for (int decode = l.epi == EPI_QKV && M <= SLOTS; decode >= 0; --decode) {
+                const double about = 2.0 * M * l.N * l.K / 0.9e9 + (double)l.N * l.K * 2 / 4.5e6 + 8;
+                bool wanted = n_only == 0;
+                for (int i = 0; i < n_only; ++i) wanted |= !strcmp(only[i], l.name);
+                if (!wanted || about > 2500 || (l.epi == EPI_STORE_F32 && M > 1024)) continue;
+                struct Form { std::string name; int tile, S; double us; };   // tile >= 100: gemm_mfma's
+                std::vector<Form> forms;
+                for (int t = 0; t < LT_COUNT; ++t)
+                    for (int S = 1; S <= (l.epi == EPI_RESID_F32 ? 8 : 1); ++S) {
+                        const int bm = LARGE_SHAPES[t][0], bn = LARGE_SHAPES[t][1];
+                        const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((l.N + bn - 1) / bn) * S;
+                        if (!(large_tiles(l.epi) >> t & 1) || !large_slices_ok(S, l.K) || (size_t)S * M * l.N > (S > 1 ? SLICE_CAP : (size_t)-1)) continue;
+                        if ((S > 1 && tiles > 520) || (tiles > 256 * 24 && bm * bn < 192 * 192)) continue;
+                        forms.push_back({std::to_string(bm) + "x" + std::to_string(bn) + (S > 1 ? "/" + std::to_string(S) : ""), t, S, 1e9});
+                    }
+                if (l.epi == EPI_SWIGLU) forms.push_back({"m256x128", 102, 1, 1e9});
+                const GemmQkv q{decode ? d_seq : d_prompt, decode ? nullptr : d_in, d_len, table_f, table_f, kv, 0, l.hq, out};
+                kv.n_kv_heads = l.hkv;
+                const size_t strips = ((size_t)l.N + 255) / 256 * 4;
+                float *maxima = (float *)(C + strips * M * 8);
+                const GemmLogprob lp{1.0f, d_token, d_id, maxima, maxima + strips * M, (double *)C};
+                auto run = [&](const Form &f, const char *w) {
+                    if (l.epi == EPI_QKV) {
+                        GemmQkv a = q;
+                        a.kv = kv;
+                        L::launch<EPI_QKV>(f.tile, A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
+                    } else if (f.tile == 102) {
+                        G::T256x128::launch<EPI_SWIGLU>(A, w, out, M, l.N, l.K, 1, nullptr, 0, {});
+                    } else if (l.epi == EPI_LOGPROB) {
+                        L::named(f.tile, EPI_LOGPROB, A, w, nullptr, M, l.N, l.K, 1, &lp, nullptr, 0);
+                    } else {
+                        L::named(f.tile, f.S > 1 ? EPI_STORE_F32 : l.epi, A, w, f.S > 1 ? (void *)slices : l.epi == EPI_SWIGLU ? (void *)out : (void *)C,
+                                 M, l.N, l.K, f.S, nullptr, nullptr, 0);
+                    }
+                    if (l.epi == EPI_RESID_F32) launch_rmsnorm(KD_F16, (float *)C, nullptr, gain, M, l.N, 1e-6f, out, slices, f.S, nullptr, 0);
+                };
+                const size_t w_size = (size_t)l.N * l.K * 2;
+                const int ring = (int)(W_BYTES / w_size), iters = (int)std::max(3.0, std::min(30.0, 900.0 / about));
+                int at = 0;
+                for (int rep = 0; rep < 5; ++rep)
+                    for (Form &f : forms) {
+                        if (rep == 0) run(f, W + (size_t)(at++ % ring) * w_size);
+                        CK(hipEventRecord(e0, 0));
+                        for (int i = 0; i < iters; ++i) run(f, W + (size_t)(at++ % ring) * w_size);
+                        CK(hipEventRecord(e1, 0));
+                        CK(hipEventSynchronize(e1));
+                        CK(hipGetLastError());
+                        float ms;
+                        CK(hipEventElapsedTime(&ms, e0, e1));
+                        f.us = std::min(f.us, ms * 1e3 / iters);
+                    }
+                double best = 1e9;
+                for (const Form &f : forms) best = std::min(best, f.us);
+                printf("%s %d %d %d %s |", l.name, M, l.N, l.K, decode ? "dec" : "pre");
+                for (const Form &f : forms)
+                    if (f.us < 1.6 * best) printf(" %s=%.2f", f.name.c_str(), f.us);
+                printf("\n");
+                fflush(stdout);
+            }
+    return 0;
+}
+
 static int bench_copy() {
     const size_t bytes = (size_t)1 << 30, n = bytes / 16;
     float4 *src, *dst;
@@ -224,7 +359,8 @@ int main(int argc, char **argv) {
         return bench_attention(n, g, lp, gen, bs, argc > 7 && atoi(argv[7]) != 0, argc > 8 && atoi(argv[8]) != 0);
     }
     if (!strcmp(what, "gemm")) return bench_gemm();
+    if (!strcmp(what, "tiles")) return bench_tiles(argc - 2, argv + 2);
     if (!strcmp(what, "copy")) return bench_copy();
-    fprintf(stderr, "usage: kernel_bench attn|gemm|copy\n");
+    fprintf(stderr, "usage: kernel_bench attn|gemm|tiles|copy\n");
     return 2;
 }
