@@ -543,6 +543,81 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
             }
         }
         return;
+    } else if constexpr (EPI == EPI_QKV) {
+        // A wave's columns lie within one head.  q and k: columns come in blocks of 32, 16 dims and their 16 rotary partners
+        // (dim + 64): two accumulator tiles that hold the same lanes' pairs.  The rotated 16-row tiles go through the wave's
+        // piece of the idle LDS ring and leave as 16-byte pieces (eight dims: contiguous in q and in a key's cache fragment).
+        // v: a lane's four dims of one token are four places of the cache; 16 lanes hold 16 rows, so a prompt's consecutive
+        // tokens leave as runs of eight.  The fp32 q | k | v rows (134 MB per layer at 16384 rows of the 1.5B shape, written
+        // and read again by a kernel of its own) never exist.
+        static_assert(M16, "lane layout of the 16x16x32 products");
+        constexpr int WC = BN / WN, HALF = WC / 2;
+        constexpr int PITCH = WC * 2 + 16, LPR = WC / 8, PIECES = 16 * LPR;
+        static_assert(WC % 32 == 0 && 128 % WC == 0, "whole 32-column blocks of one head");
+        static_assert((size_t)NW * 16 * PITCH <= (size_t)NSTAGE * STAGE_ELEMS * sizeof(T), "staging fits the ring");
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // every wave has consumed its last fragments
+        asm volatile("" ::: "memory");
+        unsigned char *stg = smem_raw + (size_t)wave * 16 * PITCH;
+        const int ml = lane % 16, nq = 4 * (lane / 16), col0 = n0 + wn * WC;
+        if (col0 >= N) return;
+        const int hkv = extra.kv.n_kv_heads, bs = extra.kv.block_size;
+        const int qd = extra.hq * 128, kvd = hkv * 128;
+        const int part = col0 < qd ? 0 : (col0 < qd + kvd ? 1 : 2);   // q, k, v (wave-uniform)
+        const int pc0 = col0 - (part == 0 ? 0 : (part == 1 ? qd : qd + kvd));
+        const int head = pc0 / 128, in = pc0 % 128;                   // first column inside the head
+        T *pool = (T *)extra.kv.pool + (int64_t)extra.layer * extra.kv.layer_stride + (int64_t)head * extra.kv.head_elems();
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int mt = m0 + wm * (BM / WM) + i * 16, row = mt + ml;
+            int pos = 0, blk = 0;
+            if (row < M) {
+                const int slot = extra.row_slot[row];
+                pos = extra.row_pos ? extra.row_pos[row] : extra.slot_len[slot];
+                if (part) blk = extra.kv.block_table[(int64_t)slot * extra.kv.max_blocks_per_slot + pos / bs];
+            }
+            const int tin = pos % bs;
+            uint32_t *const count = row < M ? sat : nullptr;          // (rows past the end are copies of the last one)
+            if (part == 2) {
+                if (row < M) {
+                    T *vd = pool + (int64_t)blk * extra.kv.block_elems();
+#pragma unroll
+                    for (int jj = 0; jj < TN; ++jj)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            vd[extra.kv.v_index(tin, in + 16 * jj + nq + v)] = from_f32_sat<T>(acc[i][jj][v], sat);
+                }
+                continue;
+            }
+#pragma unroll
+            for (int p2 = 0; p2 < TN / 2; ++p2) {
+                const int j = in / 2 + 16 * p2 + nq;                  // first of the lane's four pair indices
+                const f32x4_t c = *(const f32x4_t *)(extra.rope_cos + (int64_t)pos * 64 + j);
+                const f32x4_t sn = *(const f32x4_t *)(extra.rope_sin + (int64_t)pos * 64 + j);
+                const acc_t &x1 = acc[i][2 * p2], &x2 = acc[i][2 * p2 + 1];
+                unsigned char *dst = stg + ml * PITCH + (16 * p2 + nq) * 2;
+                *(u32x2 *)dst = pack4_sat<T>(x1[0] * c[0] - x2[0] * sn[0], x1[1] * c[1] - x2[1] * sn[1],
+                                             x1[2] * c[2] - x2[2] * sn[2], x1[3] * c[3] - x2[3] * sn[3], count);
+                *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(x2[0] * c[0] + x1[0] * sn[0], x2[1] * c[1] + x1[1] * sn[1],
+                                                          x2[2] * c[2] + x1[2] * sn[2], x2[3] * c[3] + x1[3] * sn[3], count);
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int it = 0; it < (PIECES + 63) / 64; ++it) {
+                const int e = it * 64 + lane, r = (e / LPR) % 16, piece = e % LPR;
+                const u32x4 val = *(const u32x4 *)(stg + r * PITCH + piece * 16);
+                const int dim = in / 2 + (8 * piece) % HALF + 64 * ((8 * piece) / HALF);
+                const int rblk = __shfl(blk, r, 64), rtin = __shfl(tin, r, 64);
+                if (mt + r < M && (PIECES % 64 == 0 || e < PIECES)) {
+                    if (part == 0)
+                        *(u32x4 *)((T *)extra.q_out + ((int64_t)(mt + r) * extra.hq + head) * 128 + dim) = val;
+                    else
+                        *(u32x4 *)(pool + (int64_t)rblk * extra.kv.block_elems() + extra.kv.k_index(rtin, dim)) = val;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        return;
     } else {
     // ---- epilogue
     // The products take the weights as the row operand, so the accumulators hold the TRANSPOSED tile: a lane owns ONE
@@ -677,6 +752,7 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
         }
     }
     static void init_logprob() { set_attr<EPI_LOGPROB>(); }
+    static void init_qkv() { set_attr<EPI_QKV>(); }
     static int strips(int N) { return (N + BN - 1) / BN * WN; }
     // K slices so that the launch has about `want_blocks` blocks, each with >= 4 K tiles
     static int pick_split(int M, int N, int K, size_t slice_cap_floats, int want_blocks) {
@@ -722,6 +798,11 @@ template <typename T> struct Gemm {
         T256x128::init_logprob();
         T192x128::init_logprob();
         T128x128::init_logprob();
+        T64x128::init_qkv();
+        T128x128::init_qkv();
+        T256x128::init_qkv();
+        T256x256::init_qkv();
+        T128x128_2::init_qkv();
     }
 };
 void gemm_init() {
@@ -772,11 +853,45 @@ int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int 
 }
 
 // ---- q | k | v projection with rotary positions and cache append
+// More than 512 rows.  What a tile costs here is its epilogue rather than its products, and eight waves share it better than four:
+// while one round of blocks, one per CU, holds them, the smallest tile of gemm_mfma (us, against the best of gemm_large):
+//   64 x 128    1024 rows x 2048 x 1536  16.8, 25.0 (decode, V all over the cache: 19.9, 26.5);  640 x 1536 x 1024  11.8, 19.7
+//   128 x 128   2048 x 2048 x 1536  21.5, 25.7;  640 x 6144 x 4096  40.6, 47.4 (decode 46.6, 49.4);  1024 x 4096 x 2560  34.2, 36.9
+// Beyond that gemm_large's estimate decides between its tiles and 256 x 128 (1024 x 7168 x 5120  74.1, 95.6;  4096 x 2048 x 1536
+// 31.9, 43.8;  4096 x 6144 x 4096, three full rounds, 185, 199;  6144 x 6144 x 4096  289, 241;  700 decode rows 65.0, 56.5).  Reductions
+// below 1024 stay on eight waves (3072 x 1536 x 256  12.6, 19.0;  3072 x 4096 x 768  37.4, 36.9): 256 x 256 for two rounds and more, 128 x 128 two to a CU where
+// 256 x 128 would leave half the chip idle.
+// With few rows and a wide output a kernel of its own for the rotation is faster, behind K slices: three row blocks of 192 that
+// 128 x 128 tiles cannot replace fill two thirds of the chip (576 rows x 7168 x 5120: 62.6 us, 72.1 in 192 x 128 tiles; 640 rows: 67.8,
+// 64.9); on eight waves up to three row blocks of 256 (69.9 against 76.0 us at 513 rows x 7168, 82.9 and 84.1 at 768, 91.9 and 87.4 at 896).
+enum QkvRoute { QKV_SEPARATE, QKV_64x128, QKV_128x128, QKV_256x128, QKV_256x256, QKV_128x128_2, QKV_LARGE };
+static QkvRoute qkv_route(int M, int N, int K) {
+    const int64_t nb128 = (N + 127) / 128, mb = (M + 255) / 256;
+    if ((M + 63) / 64 * nb128 <= 256) return QKV_64x128;
+    if ((M + 127) / 128 * nb128 <= 256) return QKV_128x128;
+    if (K >= 1024) return M <= 576 ? QKV_SEPARATE : QKV_LARGE;
+    if (M <= 768 && 3 * nb128 >= 160) return QKV_SEPARATE;
+    if (mb * ((N + 255) / 256) >= 2 * 256) return QKV_256x256;
+    return mb * nb128 >= 160 ? QKV_256x128 : QKV_128x128_2;
+}
+template <typename T> static void gemm_qkv_t(QkvRoute r, const void *A, const void *W, int M, int N, int K, const GemmQkv &qkv, uint32_t *sat, hipStream_t s) {
+    typedef Gemm<T> G;
+    if (r == QKV_64x128) G::T64x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else if (r == QKV_128x128) G::T128x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else if (r == QKV_256x256) G::T256x256::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else if (r == QKV_128x128_2) G::T128x128_2::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+    else G::T256x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
+}
 bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
                      hipStream_t s) {
     const int N = (qkv.hq + 2 * qkv.kv.n_kv_heads) * qkv.kv.head_dim;
     if (dtype == KD_F32 || impl == 0 || qkv.kv.head_dim != 128 || K % 64 != 0 || M <= 512) return false;
-    return launch_gemm_large_qkv(dtype, A, W, M, N, K, qkv, sat, s);
+    const QkvRoute r = qkv_route(M, N, K);
+    if (r == QKV_SEPARATE) return false;
+    if (r == QKV_LARGE && launch_gemm_large_qkv(dtype, A, W, M, N, K, qkv, sat, s)) return true;
+    if (dtype == KD_BF16) gemm_qkv_t<bf16_t>(r, A, W, M, N, K, qkv, sat, s);
+    else gemm_qkv_t<f16_t>(r, A, W, M, N, K, qkv, sat, s);
+    return true;
 }
 
 // ---- log-probabilities straight from the vocabulary projection: a scoring pass wrote 622 MB of logits per 1024 rows of the
@@ -944,3 +1059,6 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
 }
 
 }  // namespace pc
+
+// For tests, not part of the C ABI: the QkvRoute of a q/k/v projection of more than 512 rows.
+extern "C" int pc_internal_qkv_route(int M, int N, int K) { return pc::qkv_route(M, N, K); }

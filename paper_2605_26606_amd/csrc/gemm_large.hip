@@ -585,7 +585,7 @@ constexpr int LARGE_SHAPES[LT_COUNT + 1][2] = {{256, 256}, {256, 192}, {192, 256
 constexpr unsigned large_tiles(int epi) {
     return epi == EPI_STORE_F32 || epi == EPI_RESID_F32 ? (1u << LT_COUNT) - 1
            : epi == EPI_SWIGLU                          ? 1u << LT_256x256 | 1u << LT_192x256 | 1u << LT_192x128
-           : epi == EPI_QKV                             ? 1u << LT_256x256 | 1u << LT_192x256 | 1u << LT_192x128 | 1u << LT_128x128
+           : epi == EPI_QKV                             ? 1u << LT_256x256 | 1u << LT_192x256 | 1u << LT_192x128
            : epi == EPI_SWIGLU_RS || epi == EPI_LOGPROB ? 1u << LT_256x256 | 1u << LT_192x256
                                                         : 0u;
 }
@@ -650,10 +650,10 @@ static double large_cost(int id, int S, int M, int N, int K, int epi, bool decod
     return (double)rounds * per * t.step * (1.0 + t.load * busy * busy) + t.first * e.first + (double)(rounds - 1) * t.next * e.next +
            (read_back ? 0.39 * S * mb : 0.0) + (decode ? (id == LT_EIGHT ? 10.5 : 2.1) : 0.0);
 }
-// The tiles that a launch of this epilogue chooses from.  (The eight waves win where the epilogue is much of the launch:
+// The tiles that a launch of this epilogue chooses from.  (The eight waves win where the epilogue is much of the launch: q/k/v, and
 // gate/up of short reductions, 1280 rows x 6400 x 128 7.9 us against 9.6, x 768 15.5 against 18.5.)
 static unsigned large_choice(int epi) {
-    return large_tiles(epi) | (epi == EPI_SWIGLU ? 1u << LT_EIGHT : 0u);
+    return large_tiles(epi) | (epi == EPI_SWIGLU || epi == EPI_QKV ? 1u << LT_EIGHT : 0u);
 }
 // (two steps at least to a slice: the ring reaches that far ahead)
 static bool large_slices_ok(int S, int K) {

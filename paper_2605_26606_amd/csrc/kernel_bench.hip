@@ -287,7 +287,11 @@ static int bench_tiles(int n_only, char **only) {
                         if ((S > 1 && tiles > 520) || (tiles > 256 * 24 && bm * bn < 192 * 192)) continue;
                         forms.push_back({std::to_string(bm) + "x" + std::to_string(bn) + (S > 1 ? "/" + std::to_string(S) : ""), t, S, 1e9});
                     }
-                if (l.epi == EPI_SWIGLU) forms.push_back({"m256x128", 102, 1, 1e9});
+                if (l.epi == EPI_QKV) {
+                    forms.push_back({"m64x128", 100, 1, 1e9});
+                    forms.push_back({"m128x128", 101, 1, 1e9});
+                }
+                if (l.epi == EPI_QKV || l.epi == EPI_SWIGLU) forms.push_back({"m256x128", 102, 1, 1e9});
                 const GemmQkv q{decode ? d_seq : d_prompt, decode ? nullptr : d_in, d_len, table_f, table_f, kv, 0, l.hq, out};
                 kv.n_kv_heads = l.hkv;
                 const size_t strips = ((size_t)l.N + 255) / 256 * 4;
@@ -297,7 +301,10 @@ static int bench_tiles(int n_only, char **only) {
                     if (l.epi == EPI_QKV) {
                         GemmQkv a = q;
                         a.kv = kv;
-                        L::launch<EPI_QKV>(f.tile, A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
+                        if (f.tile == 100) G::T64x128::launch<EPI_QKV>(A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
+                        else if (f.tile == 101) G::T128x128::launch<EPI_QKV>(A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
+                        else if (f.tile == 102) G::T256x128::launch<EPI_QKV>(A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
+                        else L::launch<EPI_QKV>(f.tile, A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
                     } else if (f.tile == 102) {
                         G::T256x128::launch<EPI_SWIGLU>(A, w, out, M, l.N, l.K, 1, nullptr, 0, {});
                     } else if (l.epi == EPI_LOGPROB) {

@@ -233,7 +233,7 @@ def test_fp32_plain_alu_option():
     (BF8, [12] * 6, 43, 3, 64, 0.02, "f16"),              # 258, 384 and 385 rows: each side of the long reductions' tile heights
     (BF8, [12] * 16, 24, 3, 64, 0.02, "f16"),
     (BF8, [12] * 11, 35, 3, 64, 0.02, "f16"),
-    (BF8, [12] * 105, 4, 4, 64, 0.02, "f16"),             # 420 decode rows: four 128-row blocks, BK 32
+    (BF8, [12] * 105, 4, 4, 64, 0.02, "f16"),             # 420 decode rows: gate/up on the large tiles, the rest in four 128-row blocks
     (BF8, [12] * 130, 4, 3, 64, 0.02, "f16"),             # 520 decode rows: the large-batch tiles, narrow outputs in K slices
     (BF, [70, 33, 300, 5, 256], 3, 10, 128, 0.02, "f16"), # larger KV blocks
     (BF, [70, 33, 300, 5, 256], 3, 10, 256, 0.02, "f16"), # the largest block size the cache accepts
@@ -312,22 +312,25 @@ def test_large_tiles_of_decode_batches(model, P, G, act):
     _check(model, w, prompts, out, 21, 2e-2, list(range(0, P * G, max(1, P * G // 6))) + [P * G - 1])
 
 
-@pytest.mark.parametrize("hq,hkv,lens,bs,act", [
-    (8, 2, [201, 3, 190, 128, 90], 32, "f16"),             # 612 rows x 1536 columns: one round of 128 x 128 tiles
-    (8, 2, [333, 201, 3, 300, 66, 400, 201], 32, "f16"),   # 1504 x 1536
-    (32, 8, [201, 3, 190, 128, 178], 64, "bf16"),          # 700 x 6144
-    (48, 8, [201, 3, 190, 128, 78], 32, "f16"),            # 600 x 8192
-    (48, 8, [333, 1, 300, 65, 301], 64, "f16"),           # 1000 x 8192
-    (48, 8, [700, 9, 650, 800, 777, 640, 555], 64, "f16"),    # 4131 x 8192: 256 x 256, a row tile with 35 rows
-    (48, 8, [700, 9, 650, 800, 777, 640, 555], 128, "bf16"),
+@pytest.mark.parametrize("hq,hkv,lens,bs,act,d", [
+    (8, 2, [201, 3, 190, 128, 90], 32, "f16", 128),             # 612 rows x 1536 columns: 64 x 128 tiles, eight waves
+    (8, 2, [333, 201, 3, 300, 66, 400, 201], 32, "f16", 128),   # 1504 x 1536: 128 x 128
+    (32, 8, [201, 3, 190, 128, 178], 64, "bf16", 128),          # 700 x 6144: 256 x 128
+    (48, 8, [201, 3, 190, 128, 38], 32, "f16", 128),            # 560 x 8192: rotation in a kernel of its own
+    (48, 8, [201, 3, 190, 128, 78], 32, "f16", 128),            # 600 x 8192: 256 x 128
+    (48, 8, [333, 1, 300, 65, 301], 64, "f16", 128),            # 1000 x 8192: the same, one full round
+    (48, 8, [700, 9, 650, 800, 777, 640, 555], 64, "f16", 128),   # 4131 x 8192: 192 x 128 on four waves, a row tile with 99 rows
+    (48, 8, [700, 9, 650, 800, 777, 640, 555], 128, "bf16", 128),
+    (48, 8, [333, 1, 300, 65, 601], 64, "f16", 1024),           # 1300 x 8192 x 1024: 192 x 256
+    (32, 8, [700, 9, 650, 800, 777, 640, 555], 64, "f16", 1024),  # 4131 x 6144 x 1024: 256 x 256, a row tile with 35 rows
 ])
-def test_projection_that_rotates_and_appends(hq, hkv, lens, bs, act):
+def test_projection_that_rotates_and_appends(hq, hkv, lens, bs, act, d):
     # prefill chunks of more than 512 rows: q, k and v leave the projection rotated and filed; sequences start anywhere in a
     # tile and in a KV block, and two decode steps read the cache back
     say("q/k/v projection with rotary positions, %d rows x %d columns" % (sum(lens), (hq + 2 * hkv) * 128))
-    m = workloads.scaled(C1, dtype="bf16", d_model=128, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ff=128, vocab=512,
+    m = workloads.scaled(C1, dtype="bf16", d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ff=128, vocab=512,
                          n_layers=2, rope_theta=1.0e6).model
-    w = workloads.perturb_norm_gains(workloads.make_weights(m, 3, std=0.05), 10)
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 3, std=0.05 if d == 128 else 0.02), 10)
     toks, cu = workloads.make_ragged_prompts(lens, m.vocab, 8)
     prompts = [toks[cu[i]:cu[i + 1]] for i in range(len(lens))]
     out = _run_generate(m, w, prompts, 2, 3, 21, dict(block_size=bs, kv_pool_bytes=256 << 20, max_slots=40, max_ctx=900,

@@ -22,7 +22,7 @@ TILES = {
     SWIGLU: [(256, 256), (192, 256), (192, 128)],
     SWIGLU_RS: [(256, 256), (192, 256)],
     LOGPROB: [(256, 256), (192, 256)],
-    QKV: [(256, 256), (192, 256), (192, 128), (128, 128)],
+    QKV: [(256, 256), (192, 256), (192, 128)],
 }
 CASES = [(e, t) for e, ts in TILES.items() for t in ts]
 TYPES = {"f16": (2, torch.float16, 2.0 ** -11, 2.0 ** -24), "bf16": (1, torch.bfloat16, 2.0 ** -8, 0.0)}

@@ -24,13 +24,17 @@ def _measured():
 
 
 def _chosen(lib, kind, m, n, k, mode):
+    if kind == QKV:
+        route = lib.pc_internal_qkv_route(m, n, k)
+        if route != 6:
+            return [None, "m64x128", "m128x128"][route]
     s = ctypes.c_int()
     slices = min(8, (8 << 20) // (m * n)) if kind == RESID else 0     # the context's slice buffer: 32 MB
     tile = lib.pc_internal_gemm_large_pick(kind, int(mode == "dec"), slices, m, n, k, ctypes.byref(s))
     return TILES[tile] + ("/%d" % s.value if s.value > 1 else "")
 
 
-@pytest.mark.parametrize("kind,name", [(RESID, "residual"), (SWIGLU, "gate/up"), (STORE, "head"), (LOGPROB, "scoring")])
+@pytest.mark.parametrize("kind,name", [(RESID, "residual"), (SWIGLU, "gate/up"), (STORE, "head"), (LOGPROB, "scoring"), (QKV, "q/k/v")])
 def test_the_choice_is_near_the_best_of_the_measured_forms(kind, name):
     # Bounds: two runs of one form differ by up to 4 %, on other cards the clocks under load differ as well; a wrong number of rounds
     # or slices costs 15 to 60 %.  Below K = 1024 a launch's time is its stores, of which the estimate knows nothing: there the worst
@@ -40,6 +44,8 @@ def test_the_choice_is_near_the_best_of_the_measured_forms(kind, name):
     regret = []
     for launch, _, m, n, k, mode, forms in (x for x in _measured() if x[1] == kind):
         form = _chosen(lib, kind, m, n, k, mode)
+        if form is None:      # q/k/v with the rotation in a kernel of its own is not among the forms
+            continue
         assert form in forms, "%s %d rows: %s is more than 1.6 times slower than the best of %s" % (launch, m, form, forms)
         late = forms[form] / min(forms.values())
         assert late <= (1.15 if k >= 1024 else 1.4), (launch, m, n, k, mode, form, late)
