@@ -596,10 +596,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
                 const f32x4_t sn = *(const f32x4_t *)(extra.rope_sin + (int64_t)pos * 64 + j);
                 const acc_t &x1 = acc[i][2 * p2], &x2 = acc[i][2 * p2 + 1];
                 unsigned char *dst = stg + ml * PITCH + (16 * p2 + nq) * 2;
-                *(u32x2 *)dst = pack4_sat<T>(x1[0] * c[0] - x2[0] * sn[0], x1[1] * c[1] - x2[1] * sn[1],
-                                             x1[2] * c[2] - x2[2] * sn[2], x1[3] * c[3] - x2[3] * sn[3], count);
-                *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(x2[0] * c[0] + x1[0] * sn[0], x2[1] * c[1] + x1[1] * sn[1],
-                                                          x2[2] * c[2] + x1[2] * sn[2], x2[3] * c[3] + x1[3] * sn[3], count);
+                *(u32x2 *)dst = pack4_sat<T>(rotated_first(x1[0], x2[0], c[0], sn[0]), rotated_first(x1[1], x2[1], c[1], sn[1]),
+                                             rotated_first(x1[2], x2[2], c[2], sn[2]), rotated_first(x1[3], x2[3], c[3], sn[3]), count);
+                *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(rotated_second(x1[0], x2[0], c[0], sn[0]), rotated_second(x1[1], x2[1], c[1], sn[1]),
+                                                          rotated_second(x1[2], x2[2], c[2], sn[2]), rotated_second(x1[3], x2[3], c[3], sn[3]), count);
             }
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -1060,5 +1060,17 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
 
 }  // namespace pc
 
-// For tests, not part of the C ABI: the QkvRoute of a q/k/v projection of more than 512 rows.
+// For tests, not part of the C ABI: the QkvRoute of a q/k/v projection of more than 512 rows, and one launch in the tile of a
+// route (`extra`: a GemmQkv).  1: launched; 0: not a tile of this file, or not a call that the kernels take.
 extern "C" int pc_internal_qkv_route(int M, int N, int K) { return pc::qkv_route(M, N, K); }
+extern "C" int pc_internal_gemm_qkv(int dtype, int route, const void *A, const void *W, int M, int N, int K, const void *extra, uint32_t *sat,
+                                    void *stream) {
+    using namespace pc;
+    if ((dtype != KD_BF16 && dtype != KD_F16) || route <= QKV_SEPARATE || route >= QKV_LARGE || !A || !W || !extra || M <= 0 || N <= 0 ||
+        N % 128 != 0 || K <= 0 || K % 64 != 0 || (((uintptr_t)A | (uintptr_t)W) & 15) != 0)
+        return 0;
+    gemm_init();
+    if (dtype == KD_BF16) gemm_qkv_t<bf16_t>((QkvRoute)route, A, W, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
+    else gemm_qkv_t<f16_t>((QkvRoute)route, A, W, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
+    return 1;
+}

@@ -37,6 +37,11 @@ template <> __device__ inline u32x2 pack4_sat<f16_t>(float a, float b, float c, 
     return (u32x2){pack2_sat<f16_t>(a, b, sat), pack2_sat<f16_t>(c, d, sat)};
 }
 
+// A rotary pair (x1, x2) turned by the angle of cosine c and sine s.  Which product is rounded is written out: left to the compiler,
+// it differs from kernel to kernel, and a row's q and k would depend on the tile (in 8 of 100000 values of half).
+__device__ inline float rotated_first(float x1, float x2, float c, float s) { return fmaf(x1, c, -(x2 * s)); }
+__device__ inline float rotated_second(float x1, float x2, float c, float s) { return fmaf(x1, s, x2 * c); }
+
 template <int N> __device__ inline void wait_vmcnt_le() {
     // s_waitcnt with only the vector-memory counter set (gfx9 encoding: vmcnt = bits 15:14 | 3:0)
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));

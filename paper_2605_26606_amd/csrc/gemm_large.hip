@@ -504,10 +504,10 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
 #pragma unroll
                             for (int s = 0; s < 2; ++s) {
                                 const f32x4_t &x1 = x[4 * c + 2 * s], &x2 = x[4 * c + 2 * s + 1], &k = cs[c][s], &n = sn[c][s];
-                                lo[c][s] = pack4_sat<T>(x1[0] * k[0] - x2[0] * n[0], x1[1] * k[1] - x2[1] * n[1],
-                                                        x1[2] * k[2] - x2[2] * n[2], x1[3] * k[3] - x2[3] * n[3], count);
-                                hi[c][s] = pack4_sat<T>(x2[0] * k[0] + x1[0] * n[0], x2[1] * k[1] + x1[1] * n[1],
-                                                        x2[2] * k[2] + x1[2] * n[2], x2[3] * k[3] + x1[3] * n[3], count);
+                                lo[c][s] = pack4_sat<T>(rotated_first(x1[0], x2[0], k[0], n[0]), rotated_first(x1[1], x2[1], k[1], n[1]),
+                                                        rotated_first(x1[2], x2[2], k[2], n[2]), rotated_first(x1[3], x2[3], k[3], n[3]), count);
+                                hi[c][s] = pack4_sat<T>(rotated_second(x1[0], x2[0], k[0], n[0]), rotated_second(x1[1], x2[1], k[1], n[1]),
+                                                        rotated_second(x1[2], x2[2], k[2], n[2]), rotated_second(x1[3], x2[3], k[3], n[3]), count);
                             }
                         pos = of_row(row_pos, min(16 * i2 + 16, SM - 16) + ml);
                         rotation(pos);

@@ -1,6 +1,7 @@
 """Every tile of the large projection kernel by name, in every epilogue it is built for and both 16-bit types, against 64-bit
 sums: row and column remainders, two, three and five steps of K to a tile, several output tiles per block, an uneven last K slice.
-(The library chooses a tile by an estimate of its time, so the sizes of a model test say little about which one runs.)
+(The library chooses a tile by an estimate of its time, so the sizes of a model test say little about which one runs.)  The
+q/k/v tiles on eight waves that share such batches are run alongside; all give the same bits.
 
 Tolerances.  The operands are exact in 16 bits; a product is summed in float32, K of them with at most K roundings of 2^-24 each:
 |sum - exact| <= K 2^-24 sum |a w|, called d below.  Results in the model type add their own rounding, 2^-11 of the value in half
@@ -24,6 +25,7 @@ TILES = {
     LOGPROB: [(256, 256), (192, 256)],
     QKV: [(256, 256), (192, 256), (192, 128)],
 }
+EIGHT = {(64, 128): 1, (128, 128): 2, (256, 128): 3, "256x256 on eight waves": 4, "128x128 two to a CU": 5}   # their routes
 CASES = [(e, t) for e, ts in TILES.items() for t in ts]
 TYPES = {"f16": (2, torch.float16, 2.0 ** -11, 2.0 ** -24), "bf16": (1, torch.bfloat16, 2.0 ** -8, 0.0)}
 GUARD = -77.0
@@ -56,6 +58,17 @@ def _launch(act, tile, epi, a, w, c, extra=None, slices=1, sat=None):
     assert a.is_contiguous() and w.is_contiguous() and a.shape[1] == w.shape[1]
     got = f(TYPES[act][0], tile[0], tile[1], epi, slices, a.data_ptr(), w.data_ptr(), None if c is None else c.data_ptr(), a.shape[0],
             w.shape[0], a.shape[1], None if extra is None else ctypes.addressof(extra), None if sat is None else sat.data_ptr(),
+            torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return got
+
+
+def _launch_eight(act, route, a, w, extra):
+    from paper_2605_26606_amd import binding
+    f = binding.library().pc_internal_gemm_qkv
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int] * 2 + [ctypes.c_void_p] * 2 + [ctypes.c_int] * 3 + [ctypes.c_void_p] * 3
+    got = f(TYPES[act][0], route, a.data_ptr(), w.data_ptr(), a.shape[0], w.shape[0], a.shape[1], ctypes.addressof(extra), None,
             torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     return got
@@ -297,6 +310,13 @@ def test_rotating_tiles(tile, act, decode):
         k_at, v_at = base + _k_index(tin, dim), base + _v_index(tin, dim, bs)
         assert bool(((flat[k_at].double() - kw).abs() <= kb).all())
         assert bool(((flat[v_at].double() - vw).abs() <= vb + vw.abs() * u + tiny).all())
+        q_bits, kv_bits = q.clone(), flat.clone()
         flat[k_at] = 9.0
         flat[v_at] = 9.0
         assert bool((flat == 9.0).all())   # nothing else was touched
+        for route in EIGHT.values():
+            flat.fill_(9.0)
+            q.zero_()
+            assert _launch_eight(act, route, a, w, extra)
+            assert torch.equal(q, q_bits) and torch.equal(flat, kv_bits), route
+            assert bool((whole[m:] == GUARD).all())
