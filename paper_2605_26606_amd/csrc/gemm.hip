@@ -1034,11 +1034,12 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
         // as tall as the batch needs (8B down at 60 rows: 22 us, 29 us with 128-row tiles; 14B q/k/v at 168: 25 us, 30 us
         // with 256-row ones)
         if (M <= 64) return sliced(typename G::T64x128(), 240);
-        // A shorter reduction is cheaper in few slices of smaller tiles, also for whoever adds them up (4096 x 4096 with the reading
-        // of the slices: 128 x 128 in 4 19.9 us at 256 rows, 256 x 128 in 8 28.7; 17.9 against 20.8 at 168; 27.6 against 32.3 at
-        // 512.  5120 x 5120: 27.9 against 28.9 at 256, 22.4 against 23.1 at 168); wider outputs or longer reductions want the
-        // taller tile (6144 x 4096 at 168: 22.3 for 22.2; 4096 x 12288 at 256: 41.4 for 40.8)
-        if (K <= 5120 && ((M > 128 && M <= 256 && nb128 <= 40) || (M > 384 && nb128 <= 32))) return sliced(typename G::T128x128(), 240);
+        // A shorter reduction is cheaper in few slices of smaller tiles, also for the norm that adds them up (us with that norm: 4096 x
+        // 4096 in 4 slices of 128 x 128 24.0 at 256 rows, in 8 of 256 x 128 27.3; 21.5 against 23.2 at 168; 29.2 against 30.0 at 400);
+        // wider outputs gain nothing (5120 x 5120 on two cards: 34.0 and 33.7 against 35.9 and 33.1 at 256 rows, 31.1 against 30.8 at 168,
+        // 29.3 against 28.9 at 129), nor do longer reductions (6144 x 4096 at 168: 22.3 for 22.2 without a norm; 4096 x 12288 at 256: 41.4
+        // for 40.8)
+        if (K <= 5120 && nb128 <= 32 && ((M > 128 && M <= 256) || M > 384)) return sliced(typename G::T128x128(), 240);
         if (M <= 128) return sliced(typename G::T128x128(), 240);
         if (M <= 192) return sliced(typename G::T192x128(), 240);
         if (M > 256 && M <= 384) return sliced(typename G::T192x192(), 240);   // 8B down at 380 rows: 44 us against 49 us
