@@ -292,12 +292,21 @@ VOC1 = workloads.scaled(C1, dtype="bf16", d_model=128, n_q_heads=2, n_kv_heads=1
                         n_layers=1, rope_theta=1.0e6).model
 VOC2 = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=20512, vocab=512,
                         n_layers=2, rope_theta=1.0e6).model
+# (those two with reductions too short for the large tiles up to 512 rows, these with longer ones)
+VOC3 = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ff=640, vocab=65552,
+                        n_layers=1, rope_theta=1.0e6).model
+VOC4 = workloads.scaled(C1, dtype="bf16", d_model=384, n_q_heads=3, n_kv_heads=1, head_dim=128, d_ff=20512, vocab=512,
+                        n_layers=2, rope_theta=1.0e6).model
 
 
 @pytest.mark.parametrize("model,P,G,act", [(VOC1, 48, 4, "f16"), (VOC1, 193, 1, "f16"), (VOC1, 64, 4, "bf16"), (VOC1, 257, 1, "f16"),
                                            (VOC1, 96, 4, "f16"), (VOC1, 77, 5, "f16"), (VOC1, 128, 4, "bf16"), (VOC1, 171, 3, "f16"),
                                            (VOC2, 64, 3, "f16"), (VOC2, 193, 1, "f16"), (VOC2, 64, 4, "f16"), (VOC2, 77, 5, "f16"),
-                                           (VOC2, 128, 4, "bf16"), (VOC2, 128, 4, "f16"), (WIDE1, 128, 4, "f16"), (WIDE1, 96, 4, "f16")])
+                                           (VOC2, 128, 4, "bf16"), (VOC2, 128, 4, "f16"), (WIDE1, 128, 4, "f16"), (WIDE1, 96, 4, "f16"),
+                                           (VOC3, 48, 4, "f16"), (VOC3, 193, 1, "f16"), (VOC3, 64, 4, "bf16"), (VOC3, 257, 1, "f16"),
+                                           (VOC3, 96, 4, "f16"), (VOC3, 77, 5, "f16"), (VOC3, 128, 4, "bf16"), (VOC3, 171, 3, "f16"),
+                                           (VOC4, 64, 3, "f16"), (VOC4, 96, 4, "f16"), (VOC4, 77, 5, "f16"), (VOC4, 128, 4, "bf16"),
+                                           (VOC4, 171, 3, "f16")])
 def test_large_tiles_of_decode_batches(model, P, G, act):
     # 192, 193, 256, 257, 384, 385, 512 and 513 rows: each side of the rules that send a step's projections to the large tiles;
     # gate/up of 41024 columns runs several tiles per block, each with row scales of its own

@@ -54,21 +54,25 @@ def test_scores_match_the_oracle(name, tol):
         assert err <= tol
 
 
-@pytest.mark.parametrize("vocab,n_seq,length,T,act", [
-    (2000, 5, 40, 1.0, "f16"),       # the last column tile holds 208 of 256 (80 of 128) columns, a strip of it none
-    (4112, 9, 150, 0.7, "f16"),      # row tiles with a remainder, 16 columns in the last tile
-    (33792, 14, 62, 1.3, "f16"),     # four row blocks and 132 column blocks: the large tiles
-    (33792, 14, 62, 1.3, "bf16"),
-    (2001, 3, 30, 1.0, "f16"),       # a vocabulary the matrix-core kernel does not take: through the logits
+@pytest.mark.parametrize("vocab,n_seq,length,T,act,d", [
+    (2000, 5, 40, 1.0, "f16", 256),       # the last column tile holds 208 of 256 (80 of 128) columns, a strip of it none
+    (4112, 9, 150, 0.7, "f16", 256),      # row tiles with a remainder, 16 columns in the last tile
+    (33792, 14, 62, 1.3, "f16", 256),     # four row blocks and 132 column blocks: 256 x 256 tiles on eight waves
+    (33792, 14, 62, 1.3, "bf16", 256),
+    (4112, 9, 150, 0.7, "f16", 1024),     # four waves, 192 x 256 (a row tile with 173 rows)
+    (33792, 14, 80, 1.3, "f16", 1024),    # four waves, 256 x 256 (a row tile with 56 rows), several tiles per block
+    (33792, 14, 80, 1.3, "bf16", 1024),
+    (2001, 3, 30, 1.0, "f16", 256),       # a vocabulary the matrix-core kernel does not take: through the logits
 ])
-def test_scores_at_tile_edges(vocab, n_seq, length, T, act):
+def test_scores_at_tile_edges(vocab, n_seq, length, T, act, d):
     # targets in every part of the vocabulary, its first and last id among them; the tolerance is the one of the 16-bit
     # logits (2e-2, and eight times that for bfloat16: three significand bits less) -- a wrong strip, row or target is
     # off by whole units
-    m = workloads.scaled(C1, dtype="bf16", d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=256, vocab=vocab,
+    m = workloads.scaled(C1, dtype="bf16", d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ff=256, vocab=vocab,
                          n_layers=1, rope_theta=1.0e6).model
-    say("scores at tile edges V=%d rows=%d %s" % (vocab, n_seq * length, act))
-    w = workloads.perturb_norm_gains(workloads.make_weights(m, 9, std=0.05), 2)
+    say("scores at tile edges V=%d rows=%d d=%d %s" % (vocab, n_seq * length, d, act))
+    # (the same spread of logits, 0.05 sqrt(256), at either width)
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 9, std=0.05 * (256 / d) ** 0.5), 2)
     rng = np.random.default_rng(vocab)
     seqs = [rng.integers(0, vocab, length) for _ in range(n_seq)]
     seqs[0][5], seqs[0][6], seqs[-1][-1] = 0, vocab - 1, vocab - 1
