@@ -792,8 +792,10 @@ template <typename T> struct Gemm {
     typedef MfmaCfg<T, 64, 64, 2, 2, 4> M64x64;                 // wave tile 32 x 32: many blocks for the small projections
     static void init() {
         T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
-        T128x128_2::init(); T128x192::init(); T256x160::init(); T64x128::init(); T64x192::init(); T32x64::init();
+        T128x128_2::init(); T128x192::init(); T64x128::init(); T64x192::init(); T32x64::init();
         T32x64_2::init(); T128x64::init(); T192x64::init(); M64x64::init();
+        T256x160::template set_attr<EPI_SWIGLU>();       // (gate/up only)
+        T256x160::template set_attr<EPI_SWIGLU_RS>();
         T256x256::init_logprob();
         T256x128::init_logprob();
         T192x128::init_logprob();
@@ -1014,7 +1016,11 @@ static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int 
             // Where one row block of 128 columns is more than a round, the narrowest tile that is not (34816 x 5120: 256 x 192 127 us,
             // 256 x 160 106.5; 17920 x 1536 in two row blocks of 128 x 160, 224 CUs instead of 140, is 25.8 us for 28.3 alone, but
             // decode steps on several streams, which fill the idle CUs, take 3 % longer: the same work costs more CU time)
-            if (swiglu && second_round && one_round(256, 160)) return whole(typename G::T256x160());
+            if (swiglu && second_round && one_round(256, 160)) {
+                if (epi == EPI_SWIGLU) G::T256x160::template launch<EPI_SWIGLU>(A, W, C, M, N, K, 1, sat, s, {});
+                else G::T256x160::template launch<EPI_SWIGLU_RS>(A, W, C, M, N, K, 1, sat, s, *row_scale);
+                return 1;
+            }
             return second_round ? whole(typename G::T256x192()) : whole(typename G::T256x128());   // a weight tile is fetched by exactly one block
         }
         // two 192-row blocks instead of two of 256 (380 rows: 24576 x 4096 70 us against 119 us, 17920 x 1536 27 us against 33
