@@ -6,7 +6,8 @@
 //   gemm_mfma   bf16 / f16 on the matrix cores (32x32x16 or 16x16x32 products),
 //               operands streamed global -> LDS several K tiles ahead, one
 //               barrier per K tile, output rows re-formed through LDS: up to 512
-//               rows (gemm_large.hip takes the larger batches)
+//               rows, and larger batches whose epilogue is most of the work
+//               (gemm_large.hip takes the others)
 #include <algorithm>
 
 #include <type_traits>
@@ -773,7 +774,7 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
 // The tile configurations.  All on 16x16x32 products (0 to 13 % faster than 32x32x16 at every decode shape measured) except
 // two whose wave tiles are a few 32x32 products only.
 template <typename T> struct Gemm {
-    // 256 x 128, 8 waves of 64 x 64: decode batches of 193 to 256 rows
+    // 256 x 128, 8 waves of 64 x 64: decode batches of 193 to 256 rows; q/k/v, gate/up and log-softmax of many rows
     typedef MfmaCfg<T, 256, 128, 4, 2, 3, 64, true> T256x128;
     typedef MfmaCfg<T, 256, 192, 4, 2, 2, 64, true> T256x192;
     typedef MfmaCfg<T, 256, 256, 4, 2, 4, 32, true> T256x256;   // short reductions of many rows; 64 x 128 per wave: three fragment reads per four products
