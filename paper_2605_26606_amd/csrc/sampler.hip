@@ -8,23 +8,32 @@
 // segment.  Sums are accumulated in double so that the selected token agrees
 // with an in-order double-precision CDF except within rounding of a boundary.
 //
+// A pass over a row costs its instructions about as much as its memory: 19 a token, of which the weight's exponential is eleven and its
+// way into the sum two.  With expf's range tests, a branch or a select per token for the end of the row and the EOS id and
+// a rescaling under selects they were 26: 256 rows of 151936 logits, passes on three streams, 35.3 -> 27.9 us; 1024 rows back to back
+// 154 -> 125 us (5.0 TB/s, the copy rate).
+//
 // Nucleus truncation (top_p < 1): the tokens in order of decreasing probability (ties: lower id first) until their
 // cumulative mass reaches top_p keep their weight, the rest get none; the passes above then run on the kept tokens.
 // The first pass of the scheme above gives the maximum and Z of the whole row; there are two ways from there to the cut:
-//   binned (nucleus_binned): one pass over the row files the tokens that can matter in bins of 1/32 of a scaled logit, with
+//   binned (nucleus_binned): the first pass also files the tokens that can matter in bins of 1/32 of a scaled logit, with
 //     a count and a sum of 25-bit fractions in ONE 64-bit LDS integer add; the bin in which the mass from the top crosses
 //     top_p Z is known then.  A second pass sums the float weights in front of that bin and lists the bin's own tokens in
-//     LDS, where the exact cut is found.  The row is read twice.
+//     LDS, where the exact cut is found.  It, and the pass over the kept tokens, leave out the granules (256 tokens) whose
+//     maximum is behind the cut.  The row is read once, and as much of it as has kept tokens twice more.
 //   radix (any row): a select over an order-preserving 32-bit key of the logit, four passes of 8 bits with a histogram of
 //     the mass per bucket (double, one histogram per wave, added up in wave order).  The row is read four times and the few
 //     buckets in use make the LDS adds collide.  Taken when the binned way cannot be: more than 5120 tokens in the
-//     crossing bin (logits almost all alike), scaled logits beyond 1e5.
+//     crossing bin (logits almost all alike), scaled logits beyond 1e5, more than 2^18 tokens.
 //   Both decide on the same float weights and the same Z, so they keep the same tokens.
 // The kept tokens then go through the first pass again: tokens and log-probabilities are those of plain sampling with all
 // other tokens masked, to the last bit.
-//   1024 rows of 151936 logits, T = 0.7, top_p = 0.95: 1509 us by the radix way, 615 us binned (a read of the rows at the
-//   copy rate: 121 us).  Rows that fall back have paid for a first pass over their bins, which the collisions in the radix
-//   buckets hide: logits of deviation 0.004 1549 us without it and 1496 with it, all alike 6034 and 6038.
+//   1024 rows of 151936 logits, T = 0.7, top_p = 0.95 (a read of the rows at the copy rate: 121 us): 1509 us by the radix way; 469 us binned
+//   with a binning pass of its own and no granules left out, 202 us so, where a few dozen tokens hold most of the mass; 565 and 464
+//   where the cut is in the bulk of the vocabulary.  (Filing costs the first pass 8 us a row while two share a CU, the pass it replaces
+//   was 20.)  Rows that fall back have paid for the bins: 1901 and 1859 us with logits rounded to whole numbers.
+#include <type_traits>
+
 #include "pc_internal.h"
 
 namespace pc {
@@ -64,6 +73,62 @@ __device__ inline uint32_t okey(float f) {
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+__device__ inline float key_logit(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key); }
+// Largest of the wave's 64 values, in every lane, without a trip through LDS: rows of 16 lanes, then over the rows.
+__device__ inline float wave_max_all(float v) {
+    auto fold = [&](auto ctrl) {   // (lanes without a source keep their own)
+        const int o = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false);
+        v = fmaxf(v, __int_as_float(o));
+    };
+    fold(std::integral_constant<int, 0x111>{});   // row_shr 1, 2, 4, 8
+    fold(std::integral_constant<int, 0x112>{});
+    fold(std::integral_constant<int, 0x114>{});
+    fold(std::integral_constant<int, 0x118>{});
+    fold(std::integral_constant<int, 0x142>{});   // row_bcast 15, 31
+    fold(std::integral_constant<int, 0x143>{});
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), WAVE - 1));
+}
+// exp(d) for -103 <= d <= 0, to the bit what expf gives (a test compares the two): log2(e) in two pieces, whole
+// powers of two apart.  expf also asks whether the result under- or overflows, four of its fourteen instructions; the passes over a
+// row are bound by them as much as by memory.
+__device__ inline float exp_weight_near(float d) {
+#pragma clang fp contract(off)
+    const float hi = d * 0x1.715476p+0f;
+    const float lo = fmaf(d, 0x1.4ae0bep-26f, fmaf(d, 0x1.715476p+0f, -hi));
+    const float n = rintf(hi);
+    return ldexpf(__builtin_amdgcn_exp2f((hi - n) + lo), (int)n);
+}
+__device__ inline float exp_weight(float d) {   // any d <= 0, minus infinity too
+    const float w = exp_weight_near(d);
+    return d < -103.2789306640625f ? 0.f : w;   // (the logarithm of the smallest float)
+}
+// Running sum over the wave's lanes, up to and with the own one, without LDS.
+template <int CTRL, int ROWS> __device__ inline double dpp_or_zero(double v) {
+    const unsigned long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double((long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+__device__ inline double wave_scan_d(double v) {
+    v += dpp_or_zero<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8: within rows of 16 lanes
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
+    v += dpp_or_zero<0x143, 0xc>(v);
+    return v;
+}
+__device__ inline double readlane_d(double v, int lane) {
+    const unsigned long long b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// A scaled logit, rounded: not to be contracted with what is subtracted from it, so that all ways to a weight round alike.
+__device__ inline float scale_logit(float raw, float inv_t) {
+#pragma clang fp contract(off)
+    return raw * inv_t;
+}
+
 // The kept set of a nucleus: logit key above kstar, or equal to it with an id up to tie_limit.
 struct Nucleus {
     bool on;
@@ -73,6 +138,15 @@ struct Nucleus {
 };
 __device__ inline uint32_t logit_key(float raw, int idx, int eos_id, float eos_key_add) {
     return okey(idx == eos_id ? raw + eos_key_add : raw);
+}
+
+template <int VEC> __device__ inline void load_vec(const float *__restrict__ x, float (&v)[VEC]) {
+    if (VEC == 4) {
+        const float4 t = *(const float4 *)x;
+        v[0] = t.x; v[1 % VEC] = t.y; v[2 % VEC] = t.z; v[3 % VEC] = t.w;
+    } else {
+        v[0] = *x;
+    }
 }
 
 template <int VEC>
@@ -106,18 +180,46 @@ __device__ inline void load_scaled(const float *__restrict__ x, int idx, int end
 
 __device__ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
+    // The fold of one lane: m the maximum, ref the same, or 0 while all tokens so far are masked (no weight); s the sum of
+// weights relative to ref.  A masked token counts as minus infinity.
+struct Fold {
+    float m = -INFINITY, ref = 0.f;
+    double s = 0.0;
+    // KEPT_ONLY: tokens for which ok is false count as masked, all others are within 100 of the row's maximum (the kept tokens of a
+    // nucleus: no weight underflows)
+    template <int VEC, bool KEPT_ONLY = false> __device__ void take(const float (&v)[VEC], const bool *ok = nullptr) {
+        float lm = m;
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) lm = fmaxf(lm, !KEPT_ONLY || ok[c] ? v[c] : -INFINITY);
+        const float next = lm == -INFINITY ? 0.f : lm;
+        // (no branch: some lane of the wave has a new maximum nearly always.  Without one the factor is 1, and so it is while s is 0 and
+        // ref no maximum yet, which may lie above the first)
+        s *= (double)exp_weight(fminf(ref - next, 0.f));
+        m = lm;
+        ref = next;
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+            // (of masked tokens too: a branch around each would be a chain of its own)
+            const float w = KEPT_ONLY ? exp_weight_near(v[c] - ref) : exp_weight(v[c] - ref);
+            s += (double)(!KEPT_ONLY || ok[c] ? w : 0.f);
+        }
+    }
+};
+
 // ---- the binned way to the nucleus
 static constexpr int NUC_BINS = 4096;          // four per thread
 static constexpr float NUC_PER_UNIT = 32.0f;   // bins per unit of scaled logit
 static constexpr int NUC_LIST = 5120;          // tokens of the crossing bin that fit the list (72 KB in all: two blocks per CU)
 static constexpr int NUC_COUNT_SHIFT = 44;     // a bin: count above, sum of weights as integers below (2^18 tokens fit either)
+static constexpr int NUC_GRANULE = 256;        // tokens of a wave's segment whose maximum is kept, so that later passes skip them
+static constexpr int NUC_GRANULES = 64;        // per wave
+static constexpr int NUC_MAX_VOCAB = SAMPLE_WAVES * NUC_GRANULES * NUC_GRANULE;   // 2^18
 
 struct NucleusBins {
     union {
         struct {
             unsigned long long bin[NUC_BINS];
-            uint32_t key[NUC_LIST];
-            int32_t id[NUC_LIST];
+            uint2 list[NUC_LIST];                      // key, id
         };
         struct {
             double hist[SAMPLE_WAVES][256];
@@ -130,33 +232,30 @@ struct NucleusBins {
     uint32_t wave_lo[SAMPLE_WAVES], wave_hi[SAMPLE_WAVES];
     double above;
     int sel, n;
+    uint32_t seen;                                     // key of the largest scaled logit that any wave has seen
+    float granule_max[SAMPLE_WAVES][NUC_GRANULES];     // largest scaled logit
 };
 
 // From the bins (each thread owns four, in order of falling logit): the first one at which above + the running mass reaches
-// `want` (NUC_BINS if none does) into sb.sel, and the mass in front of it into sb.above.  scale(bin) turns a bin's integer sum
-// into mass.  Every thread must call it; the bins are read before its first barrier only.
-template <typename Scale>
-__device__ inline void nucleus_cross(NucleusBins &sb, double above, double want, Scale scale) {
+// `want` (NUC_BINS if none does) into sb.sel, and the mass in front of it into sb.above.  place_of(i) is the place of bin i in that order,
+// scale(i) turns its integer sum into mass and falls by the factor `ratio` from one bin to the next.  Every thread must call it; the bins are read before its first barrier only.
+template <typename At, typename Scale>
+__device__ inline void nucleus_cross(NucleusBins &sb, double above, double want, double ratio, At place_of, Scale scale) {
     const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    double m[4], own = 0.0;
+    double m[4], own = 0.0, unit = scale(4 * tid);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const unsigned long long b = sb.bin[4 * tid + i];
-        m[i] = (b >> NUC_COUNT_SHIFT) ? (double)(b & ((1ull << NUC_COUNT_SHIFT) - 1)) * scale(4 * tid + i) : 0.0;
+        const unsigned long long b = sb.bin[place_of(4 * tid + i)];
+        m[i] = (b >> NUC_COUNT_SHIFT) ? (double)(b & ((1ull << NUC_COUNT_SHIFT) - 1)) * unit : 0.0;
         own += m[i];
+        unit *= ratio;
     }
-    double incl = own;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-        const double t = __shfl_up(incl, o, WAVE);
-        if (lane >= o) incl += t;
-    }
+    const double incl = wave_scan_d(own);
     if (tid == 0) sb.sel = NUC_BINS;
     if (lane == WAVE - 1) sb.wave_sum[wave] = incl;
     __syncthreads();
-    double run = above;
-    for (int w = 0; w < wave; ++w) run += sb.wave_sum[w];
-    run += incl - own;
+    const double front = wave_scan_d(lane < wave ? sb.wave_sum[lane % SAMPLE_WAVES] : 0.0);   // (lane 63: of all waves in front)
+    double run = above + readlane_d(front, WAVE - 1) + (incl - own);
     int mine = -1;
     double at = 0.0;
 #pragma unroll
@@ -183,110 +282,158 @@ __device__ inline int ties_to_keep(double want, double run, double comb, int c) 
     return r >= c ? -1 : r;
 }
 
-// The cut at mass `want` = top_p Z of a row with maximum M and sum Z: kstar and the number of its ties to keep (-1: all).
-// False: not found this way, nothing is left behind (the caller's arithmetic decides either way, see the end of pass 2).
+// The place of a token among the bins: its logit in bins, rounded to a whole number n by one fma, as PLACE_BASE + n (exact while
+// |n| < 2^22), so that the low bits of the word are n modulo NUC_BINS.  The bins lie in a ring: they can be filled before the
+// row's maximum is known.  (The EOS id's bias counts like in its key, so tokens with the same key have the same place.)
+static constexpr float PLACE_BASE = 12582912.0f;   // 1.5 * 2^23
+__device__ inline float place(float key_logit, float per_logit) { return fmaf(key_logit, per_logit, PLACE_BASE); }
+struct NucleusFile {
+    uint32_t at;
+    unsigned int mass;   // relative to the bin's middle, times 2^25
+    __device__ NucleusFile(float key_logit, float per_logit) {
+        const float p = place(key_logit, per_logit);
+        const float off = fmaf(key_logit, per_logit, -(p - PLACE_BASE));   // at most 1/2
+        mass = (unsigned int)__builtin_amdgcn_exp2f(fmaf(off, 1.4426950408889634f / NUC_PER_UNIT, 25.0f));
+        at = __float_as_uint(p) & (NUC_BINS - 1);
+    }
+    __device__ void add(NucleusBins &sb) const { atomicAdd(&sb.bin[at], (1ull << NUC_COUNT_SHIFT) + mass); }
+};
+
+// The granules in `mask`, four strides of a wave's segment [b, e) at a time: the lane's first token in each (at), whether it is
+// in the segment (in), its raw logits.  Strides are as load_scaled's: the lane owns VEC consecutive tokens of WAVE * VEC.
+// Returns whether the four strides are plain: all of them in the segment, none with the EOS id (wave-uniform).
 template <int VEC>
-__device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, float inv_t, float top_p, int eos_id,
-                                      float eos_bias, float eos_key_add, float M, double Z, double want, NucleusBins &sb,
-                                      uint32_t &kstar, int &keep_ties) {
-    constexpr int BLOCK = SAMPLE_WAVES * WAVE, STEP = BLOCK * VEC;
-    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    // (beyond these sizes the bins' edges are no longer exact, or an EOS logit and its bias may cancel)
-    if (vocab > (1 << 18) || !(fabsf(M) < 1e5f) || !(Z >= 0.5 && Z < 1e9)) return false;
-    if (eos_id >= 0 && !(fabsf(eos_bias) < 1e5f) && eos_bias != -INFINITY) return false;
-    auto raw_load = [&](int idx, float (&v)[VEC]) {
-        if (VEC == 4 && idx + 3 < vocab) {
-            const float4 t = *(const float4 *)(x + idx);
-            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-        } else {
+__device__ inline bool next_granules(unsigned long long &mask, const float *__restrict__ x, int b, int e, int eos_id, int lane,
+                                     int (&at)[4], bool (&in)[4], float (&raw)[4][VEC]) {
+    bool plain = true;
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) v[c] = (idx + c) < vocab ? x[idx + c] : -INFINITY;
-        }
-    };
+    for (int u = 0; u < 4; ++u) {   // (VEC 4: a stride is a granule; else four are)
+        const int first = mask ? b + __builtin_ctzll(mask) * NUC_GRANULE + (VEC == 4 ? 0 : u * WAVE) : e;
+        if (VEC == 4 || u == 3) mask &= mask - 1;   // (0 stays 0)
+        plain = plain && first + WAVE * VEC <= e && !(eos_id >= first && eos_id < first + WAVE * VEC);
+        at[u] = first + lane * VEC;
+        // (clamped, not left out: a branch around each load would make them wait for one another)
+        in[u] = at[u] < e;          // (with VEC = 4 segments end on multiples of four)
+        load_vec<VEC>(x + min(at[u], e - VEC), raw[u]);
+    }
+    return plain;
+}
+
+// The cut at mass `want` = top_p Z of a row with maximum M and sum Z: kstar and the number of its ties to keep (-1: all), and
+// which granules of the wave's segment [b, e) have a token that may be kept.  The bins hold the row's tokens above `filed`
+// unless they cannot (see below).  False: not found this way, nothing is left behind (the caller's arithmetic decides either way,
+// see the end of pass 2).
+template <int VEC>
+__device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, int b, int e, float inv_t, float top_p, int eos_id,
+                                      float eos_bias, float eos_key_add, float M, double Z, double want, float filed, float reach,
+                                      NucleusBins &sb, uint32_t &kstar, int &keep_ties, unsigned long long &granules) {
+    constexpr int BLOCK = SAMPLE_WAVES * WAVE;
+    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
+    // (beyond these sizes places are no longer exact, or an EOS logit and its bias may cancel)
+    if (vocab > NUC_MAX_VOCAB || !(fabsf(M) < 1e5f) || !(Z >= 0.5 && Z < 1e9)) return false;
+    if (eos_id >= 0 && !(fabsf(eos_bias) < 1e5f) && eos_bias != -INFINITY) return false;
+    const float per_logit = NUC_PER_UNIT * inv_t;
     auto scaled = [&](float raw, int idx) {   // as load_scaled forms it
         float v = raw * inv_t;
         if (idx == eos_id) v += eos_bias;
         return v;
     };
-    // place of a logit: (top - scaled logit) * 32, one explicit fma so that both passes round alike; the EOS id's bias counts
-    // like in its key, so tokens with the same key have the same place.  The edge lies 1 to 2 above the maximum: whatever the
-    // rounding of its scaled value, no place is negative
-    const float top = ceilf(M) + 1.0f, place_a = -NUC_PER_UNIT * inv_t, place_b = NUC_PER_UNIT * top;
-    auto place = [&](float raw, int idx) { return fmaf(idx == eos_id ? raw + eos_key_add : raw, place_a, place_b); };
-    // Tokens of a weight below half of (1 - top_p) Z / vocab lie behind the cut, all of them together: they need no bin.
-    const float reach = (float)(NUC_PER_UNIT * ((double)top - (double)M - log(0.5 * (1.0 - (double)top_p) * Z / vocab))) + 1.0f;
-    const float end = fminf(reach, (float)(NUC_BINS - 1));
-    const double edge0 = (double)top - (double)M;
+    const int top = (int)rintf(M * NUC_PER_UNIT) + 2;   // no place is above it, whatever the rounding of the scaled maximum
+    const int n_granules = (e - b + NUC_GRANULE - 1) / NUC_GRANULE;   // (b <= e)
+    auto with_place = [&](float n) {   // granules with a token at place n or above (places and maxima differ by rounding only)
+        return __ballot(lane < n_granules && sb.granule_max[wave][lane % NUC_GRANULES] * NUC_PER_UNIT >= n - 2.f);
+    };
+    // The bins were filled while the maximum was found.  Did their ring go round (block-uniform; a maximum 100 units of scaled
+    // logit above all that was seen of the row at first)?  Then once more, from what is within reach of it.
+    if (!((M - filed) * NUC_PER_UNIT < (float)(NUC_BINS - 16))) {
 #pragma unroll
-    for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
+        for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
+        __syncthreads();
+        const float from = M - reach;   // (reach is at most 32)
+        for (unsigned long long mask = with_place(from * NUC_PER_UNIT); mask;) {
+            int at[4];
+            bool in[4];
+            float raw[4][VEC];
+            (void)next_granules<VEC>(mask, x, b, e, eos_id, lane, at, in, raw);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int c = 0; c < VEC; ++c)
+                    if (in[u] && scaled(raw[u][c], at[u] + c) > from)
+                        NucleusFile(at[u] + c == eos_id ? raw[u][c] + eos_key_add : raw[u][c], per_logit).add(sb);
+        }
+        __syncthreads();
+    }
     if (tid == 0) sb.n = 0;
-    __syncthreads();
-    // ---- pass 1: count and weight per bin, weights relative to the bin's upper edge in 25 bits: which bin the cut is in
-    {
-        float cur[VEC], nxt[VEC];
-        raw_load(tid * VEC, nxt);
-        for (int base = tid * VEC; base < vocab; base += STEP) {
+    // ---- pass 1 is done: which bin the cut is in
+    nucleus_cross(sb, 0.0, want, 0.96923323447634408185 /* exp(-1/32) */, [&](int i) { return (top - i) & (NUC_BINS - 1); },
+                  [&](int i) { return (1.0 / 33554432.0) * exp((double)(top - i) / (double)NUC_PER_UNIT - (double)M); });
+    const int sel = sb.sel;
+    if (sel == NUC_BINS || (int)(sb.bin[(top - sel) & (NUC_BINS - 1)] >> NUC_COUNT_SHIFT) > NUC_LIST) return false;
+    // ---- pass 2: the mass in front of that bin, its tokens into the list
+    const float place_sel = PLACE_BASE + (float)(top - sel);
+    granules = with_place((float)(top - sel));
+    double s = 0.0;
+    for (unsigned long long mask = granules; mask;) {
+        int at[4];
+        bool in[4];
+        float raw[4][VEC];
+        const bool plain = next_granules<VEC>(mask, x, b, e, eos_id, lane, at, in, raw);
+        uint32_t hits = 0u;   // the lane's tokens in the bin
+        auto weigh = [&](auto is_plain) {
+            constexpr bool PLAIN = decltype(is_plain)::value;
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) cur[c] = nxt[c];
-            if (base + STEP < vocab) raw_load(base + STEP, nxt);
+            for (int u = 0; u < 4; ++u) {
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                const float p = place(cur[c], base + c);
-                if (p < end) {
-                    const int b = max((int)p, 0);
-                    const float rel = __builtin_amdgcn_exp2f(((float)b - p) * (1.4426950408889634f / NUC_PER_UNIT));
-                    atomicAdd(&sb.bin[b], (1ull << NUC_COUNT_SHIFT) + (unsigned int)(rel * 33554432.0f + 0.5f));
+                for (int c = 0; c < VEC; ++c) {
+                    float v = scale_logit(raw[u][c], inv_t), key = raw[u][c];
+                    if (!PLAIN && at[u] + c == eos_id) {
+                        v = fmaf(raw[u][c], inv_t, eos_bias);
+                        key += eos_key_add;
+                    }
+                    if (!PLAIN && !in[u]) key = -INFINITY;
+                    const float p = place(key, per_logit);
+                    hits |= p == place_sel ? 1u << (4 * u + c) : 0u;
+                    // (every token's weight, and none in place of those behind: a branch around each would be a chain of its own)
+                    const float w = exp_weight_near(v - M);
+                    s += (double)(p > place_sel ? w : 0.f);
                 }
+                __builtin_amdgcn_sched_barrier(0);   // (a stride at a time: all of them at once do not fit the registers)
+            }
+        };
+        if (plain) weigh(std::true_type{});
+        else weigh(std::false_type{});
+        if (hits) {
+            for (int k = atomicAdd(&sb.n, __popc(hits)); hits; ++k, hits &= hits - 1) {
+                const int u = __builtin_ctz(hits) / 4, c = __builtin_ctz(hits) % 4;
+                if (k < NUC_LIST) sb.list[k].y = (uint32_t)((u == 0 ? at[0] : (u == 1 ? at[1] : (u == 2 ? at[2] : at[3]))) + c);
             }
         }
     }
+    s = wave_sum_d(s);
+    if (lane == 0) sb.wave_sum[wave] = s;
+    // Behind this barrier every wave has read the first bins and filed its tokens.
     __syncthreads();
-    nucleus_cross(sb, 0.0, want, [&](int b) { return (1.0 / 33554432.0) * exp(edge0 - (double)b / (double)NUC_PER_UNIT); });
-    const int sel = sb.sel;
-    if (sel == NUC_BINS || (int)(sb.bin[sel] >> NUC_COUNT_SHIFT) > NUC_LIST) return false;
-    // ---- pass 2: the mass in front of that bin, its tokens into the list
-    double s = 0.0;
+    const int n_list = sb.n;
+    if (n_list > NUC_LIST || n_list == 0) return false;
     uint32_t lo = 0xffffffffu, hi = 0u;
-    {
-        float raw[VEC], nxt[VEC];
-        raw_load(tid * VEC, nxt);
-        for (int base = tid * VEC; base < vocab; base += STEP) {
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) raw[c] = nxt[c];
-            if (base + STEP < vocab) raw_load(base + STEP, nxt);
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                const float p = place(raw[c], base + c);
-                if (p < (float)sel) {
-                    s += (double)expf(scaled(raw[c], base + c) - M);
-                } else if (p < (float)(sel + 1)) {
-                    const int at = atomicAdd(&sb.n, 1);
-                    const uint32_t key = logit_key(raw[c], base + c, eos_id, eos_key_add);
-                    if (at < NUC_LIST) {
-                        sb.key[at] = key;
-                        sb.id[at] = base + c;
-                    }
-                    lo = min(lo, key);
-                    hi = max(hi, key);
-                }
-            }
-        }
+    for (int k = tid; k < n_list; k += BLOCK) {   // (a thread's own entries, from here on)
+        const int id = (int)sb.list[k].y;
+        const uint32_t key = logit_key(x[id], id, eos_id, eos_key_add);
+        sb.list[k].x = key;
+        lo = min(lo, key);
+        hi = max(hi, key);
     }
 #pragma unroll
     for (int o = WAVE / 2; o > 0; o >>= 1) {
         lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, WAVE));
         hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, WAVE));
     }
-    s = wave_sum_d(s);
     if (lane == 0) {
         sb.wave_lo[wave] = lo;
         sb.wave_hi[wave] = hi;
-        sb.wave_sum[wave] = s;
     }
-    // Behind this barrier every wave has read the first bins and filed its tokens.
     __syncthreads();
-    const int n_list = sb.n;
-    if (n_list > NUC_LIST || n_list == 0) return false;
     double above = 0.0;
     lo = 0xffffffffu;
     hi = 0u;
@@ -297,11 +444,11 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, fl
         above += sb.wave_sum[w];
     }
     // From here on the weights are the ones that every other way to the cut takes, expf(v - M), and their sums are exact: the
-    // list's, all within 3 % of the bin's edge, as integers of at most 2^28.  The cut is the list's if it is reached within it.
+    // list's, all within 2 % of the bin's middle, as integers of at most 2^28.  The cut is the list's if it is reached within it.
     if (!(above < want)) return false;
-    const float unit = ldexpf(1.0f, 26 - ilogbf(expf(top - (float)sel * (1.0f / NUC_PER_UNIT) - M)));
+    const float unit = ldexpf(1.0f, 26 - ilogbf(expf((float)(top - sel) * (1.0f / NUC_PER_UNIT) - M)));
     auto weight = [&](uint32_t key, int id) {
-        const float raw = id == eos_id ? x[id] : __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
+        const float raw = id == eos_id ? x[id] : key_logit(key);
         return (unsigned int)(expf(scaled(raw, id) - M) * unit);
     };
     // ---- the list's cut: 4096 parts of its key range, then of that part's, until a part is one key
@@ -310,31 +457,41 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, fl
 #pragma unroll
         for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
         __syncthreads();
-        for (int e = tid; e < n_list; e += BLOCK) {
-            const uint32_t key = sb.key[e];
-            if (key >= lo && key <= hi)
-                atomicAdd(&sb.bin[NUC_BINS - 1 - (int)((key - lo) >> shift)], (1ull << NUC_COUNT_SHIFT) + weight(key, sb.id[e]));
+        for (int k = tid; k < n_list; k += BLOCK) {
+            const uint2 t = sb.list[k];
+            if (t.x >= lo && t.x <= hi)
+                atomicAdd(&sb.bin[NUC_BINS - 1 - (int)((t.x - lo) >> shift)], (1ull << NUC_COUNT_SHIFT) + weight(t.x, (int)t.y));
         }
         __syncthreads();
-        nucleus_cross(sb, above, want, [&](int) { return 1.0 / (double)unit; });
+        nucleus_cross(sb, above, want, 1.0, [](int i) { return i; }, [&](int) { return 1.0 / (double)unit; });
         const int part = sb.sel;
         if (part == NUC_BINS) return false;
         above = sb.above;
         lo += (uint32_t)(NUC_BINS - 1 - part) << shift;
+        const unsigned long long bin = sb.bin[part];
+        if (shift > 0 && (bin >> NUC_COUNT_SHIFT) == 1ull) {   // (mostly) one token is left: it is the cut
+            for (int k = tid; k < n_list; k += BLOCK) {
+                const uint32_t key = sb.list[k].x;
+                if (key >= lo && key - lo < (1u << shift) && key <= hi) sb.seen = key;
+            }
+            __syncthreads();
+            kstar = sb.seen;
+            keep_ties = -1;
+            return true;
+        }
         if (shift == 0) {
-            const unsigned long long b = sb.bin[part];
             kstar = lo;
-            keep_ties = ties_to_keep(want, above, (double)(b & ((1ull << NUC_COUNT_SHIFT) - 1)) / (double)unit,
-                                     (int)(b >> NUC_COUNT_SHIFT));
+            keep_ties = ties_to_keep(want, above, (double)(bin & ((1ull << NUC_COUNT_SHIFT) - 1)) / (double)unit,
+                                     (int)(bin >> NUC_COUNT_SHIFT));
             return true;
         }
         hi = min(hi, lo + ((1u << shift) - 1u));
     }
 }
 
-// ROOMY: a launch of at most half a block per CU keeps the segment sums in registers (107 rows back to back: 17.7 us, 19.3 us
-// without); larger ones read them from LDS four at a time and fit two blocks per CU (256 rows: 34 us against 43 us, 1024 rows
-// 149 against 178).
+// ROOMY: a launch of at most half a block per CU keeps the segment sums in registers; larger ones read them from LDS four at a time and
+// fit two blocks per CU (with the longer passes of before, back to back: 107 rows 17.7 us, 19.3 without; 256 rows 34 us against 43 us, 1024
+// rows 149 against 178).
 template <int VEC, bool TOPP, bool ROOMY>
 __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kernel(
     const float *__restrict__ logits, const int32_t *__restrict__ logit_row, int vocab, float inv_t, float top_p,
@@ -369,49 +526,145 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
     Nucleus nu{false, 0u, 0x7fffffff, eos_key_add};
     // ---- level 1: online (max, sum) per contiguous wave segment
     const int seg = round_up((vocab + SAMPLE_WAVES - 1) / SAMPLE_WAVES, STRIDE);
-    auto level1 = [&]() {
-        const int b = min(vocab, wave * seg), e = min(vocab, b + seg);
-        float m = -INFINITY, ref = 0.f;   // (ref is m, or 0 while all tokens so far are masked: no weight)
-        double s = 0.0;
-        // four strides are fetched before the first is folded in (the fold is a serial chain, and a load
-        // per link would leave the memory latency exposed at every step); the order of the arithmetic is
-        // that of the plain loop
-        constexpr int AHEAD = 4;
-        for (int base = b; base < e; base += AHEAD * STRIDE) {
-            float v[AHEAD][VEC];
-            bool ok[AHEAD][VEC];
-#pragma unroll
-            for (int u = 0; u < AHEAD; ++u)
-                load_scaled<VEC>(x, base + u * STRIDE + lane * VEC, e, inv_t, eos_id, eos_bias, v[u], ok[u], nu);
-#pragma unroll
-            for (int u = 0; u < AHEAD; ++u) {
-                float lm = -INFINITY;
-#pragma unroll
-                for (int c = 0; c < VEC; ++c)
-                    if (ok[u][c]) lm = fmaxf(lm, v[u][c]);
-                if (lm > m) {
-                    s *= (double)expf(m - lm);   // m = -inf -> 0
-                    m = ref = lm;
-                }
-#pragma unroll
-                for (int c = 0; c < VEC; ++c)
-                    if (ok[u][c]) s += (double)expf(v[u][c] - ref);
-            }
-        }
-        const float wm = wave_max_f32(m);
-        const double ws = wave_sum_d(m == -INFINITY ? 0.0 : s * (double)expf(m - wm));
+    const int wb = min(vocab, wave * seg), we = min(vocab, wb + seg);
+    auto finish = [&](const Fold &f) {
+        const float wm = wave_max_f32(f.m);
+        const double ws = wave_sum_d(f.m == -INFINITY ? 0.0 : f.s * (double)expf(f.m - wm));
         if (lane == 0) {
             s_wm[wave] = wm;
             s_ws[wave] = ws;
         }
     };
-    level1();
+    // four strides are fetched before the first is folded in (the fold is a serial chain, and a load
+    // per link would leave the memory latency exposed at every step); the order of the arithmetic is
+    // that of the plain loop
+    constexpr int AHEAD = 4;
+    auto level1 = [&]() {
+        Fold f;
+        for (int base = wb; base < we; base += AHEAD * STRIDE) {
+            float v[AHEAD][VEC];
+            bool ok[AHEAD][VEC];
+            if (!nu.on && base + AHEAD * STRIDE <= we && !(eos_id >= base && eos_id < base + AHEAD * STRIDE)) {   // (wave-uniform)
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) load_vec<VEC>(x + base + u * STRIDE + lane * VEC, v[u]);
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) v[u][c] = scale_logit(v[u][c], inv_t);
+                    f.take(v[u]);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u)
+                    load_scaled<VEC>(x, base + u * STRIDE + lane * VEC, we, inv_t, eos_id, eos_bias, v[u], ok[u], nu);
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) v[u][c] = ok[u][c] ? v[u][c] : -INFINITY;
+                    f.take(v[u]);
+                }
+            }
+        }
+        finish(f);
+    };
+    if constexpr (!TOPP) level1();
     if constexpr (TOPP) {
         __shared__ NucleusBins sb;
         // ---- nucleus: the key kstar and the id limit among its ties at which the mass from the top reaches top_p Z
         __shared__ uint32_t s_prefix;
         __shared__ double s_above;
         __shared__ int s_keep_ties, s_tie_limit, s_wcount[SAMPLE_WAVES];
+        // Level 1, and in the same pass the bins: tokens of a weight below half of (1 - top_p) Z / vocab lie behind the cut, all of
+        // them together, and need no bin.  Z is at least the largest weight, and the largest logit at least the largest
+        // seen so far, by any wave: the first stride of every segment is looked at ahead, the rest is published as it comes.
+        const float reach = 1.0f - logf(0.5f * (1.0f - top_p) / (float)vocab);
+        float filed = -INFINITY;   // every token whose scaled logit is above this is in a bin
+        {
+            constexpr int BLOCK = SAMPLE_WAVES * WAVE;
+            const float per_logit = NUC_PER_UNIT * inv_t;
+#pragma unroll
+            for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
+            if (tid == 0) sb.seen = 0u;
+            __syncthreads();
+            {
+                float v[VEC], lm = -INFINITY;
+                bool ok[VEC];
+                load_scaled<VEC>(x, wb + lane * VEC, we, inv_t, eos_id, eos_bias, v, ok, nu);
+#pragma unroll
+                for (int c = 0; c < VEC; ++c)
+                    if (ok[c]) lm = fmaxf(lm, v[c]);
+                lm = wave_max_all(lm);
+                if (lane == 0) atomicMax(&sb.seen, okey(lm));
+            }
+            __syncthreads();
+            float seen = key_logit(sb.seen);
+            filed = seen - reach;
+            Fold f;
+            auto chunk = [&](auto plain, int base) {   // plain: whole strides without the EOS id
+                constexpr bool PLAIN = decltype(plain)::value;
+                float raw[AHEAD][VEC], v[AHEAD][VEC];
+                const uint32_t others = __hip_atomic_load(&sb.seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    const int idx = base + u * STRIDE + lane * VEC;
+                    if (PLAIN) load_vec<VEC>(x + idx, raw[u]);
+                    else {
+#pragma unroll
+                        for (int c = 0; c < VEC; ++c) raw[u][c] = idx + c < we ? x[idx + c] : 0.f;
+                    }
+                }
+                float top[AHEAD];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    const int idx = base + u * STRIDE + lane * VEC;
+                    top[u] = -INFINITY;
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) {
+                        v[u][c] = scale_logit(raw[u][c], inv_t);
+                        if (!PLAIN && idx + c == eos_id) {
+                            v[u][c] = fmaf(raw[u][c], inv_t, eos_bias);
+                            raw[u][c] += eos_key_add;   // (from here on: the key's logit)
+                        }
+                        if (!PLAIN && idx + c >= we) v[u][c] = -INFINITY;
+                        top[u] = fmaxf(top[u], v[u][c]);
+                    }
+                }
+                const float before = seen;
+                const int granule = (base - wb) / NUC_GRANULE;   // (beyond the last one only where the bins are not used)
+                if (VEC == 4) {
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        top[u] = wave_max_all(top[u]);
+                        seen = fmaxf(seen, top[u]);
+                        if (lane == 0 && granule + u < NUC_GRANULES) sb.granule_max[wave][granule + u] = top[u];
+                    }
+                } else {
+                    const float t = wave_max_all(fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3])));
+                    seen = fmaxf(seen, t);
+                    if (lane == 0 && granule < NUC_GRANULES) sb.granule_max[wave][granule] = t;
+                }
+                if (lane == 0 && seen > before) atomicMax(&sb.seen, okey(seen));
+                seen = fmaxf(seen, key_logit(others));
+                const float from = seen - reach;
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    f.take(v[u]);
+                    if (VEC > 1 && !(top[u] > from)) continue;   // (wave-uniform)
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) {
+                        const NucleusFile t(raw[u][c], per_logit);
+                        if (v[u][c] > from) t.add(sb);
+                    }
+                }
+            };
+            for (int base = wb; base < we; base += AHEAD * STRIDE) {
+                if (base + AHEAD * STRIDE <= we && !(eos_id >= base && eos_id < base + AHEAD * STRIDE))
+                    chunk(std::true_type{}, base);
+                else
+                    chunk(std::false_type{}, base);
+            }
+            finish(f);
+        }
         __syncthreads();
         float M0 = -INFINITY;
 #pragma unroll
@@ -421,7 +674,10 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
         for (int w = 0; w < SAMPLE_WAVES; ++w) Z0 += (s_wm[w] == -INFINITY) ? 0.0 : s_ws[w] * (double)expf(s_wm[w] - M0);
         const double want = (double)top_p * Z0;
         int keep_ties;
-        if (!nucleus_binned<VEC>(x, vocab, inv_t, top_p, eos_id, eos_bias, eos_key_add, M0, Z0, want, sb, nu.kstar, keep_ties)) {
+        unsigned long long granules = 0ull;   // of the wave's segment, those with a token that may be kept
+        const bool binned = nucleus_binned<VEC>(x, vocab, wb, we, inv_t, top_p, eos_id, eos_bias, eos_key_add, M0, Z0, want, filed,
+                                                reach, sb, nu.kstar, keep_ties, granules);
+        if (!binned) {
         auto &s_hist = sb.radix.hist;
         auto &s_cnt = sb.radix.cnt;
         auto &s_comb = sb.radix.comb;
@@ -524,7 +780,46 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
         }
         nu.on = true;
         __syncthreads();
-        level1();   // the same pass over the kept tokens only
+        // the same pass over the kept tokens only
+        if (!binned) {
+            level1();
+        } else {   // by the granules that have any: what is left out would add nothing, so the sums are level1's, to the last bit
+            Fold f;
+            const float cut = key_logit(nu.kstar);
+            const bool by_value = nu.tie_limit == 0x7fffffff && cut != 0.f;   // (the keys tell the zeros apart)
+            while (granules) {
+                int at[AHEAD];
+                bool in[AHEAD];
+                float v[AHEAD][VEC];
+                const bool plain = next_granules<VEC>(granules, x, wb, we, eos_id, lane, at, in, v);
+                if (plain && by_value) {
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        bool ok[VEC];
+#pragma unroll
+                        for (int c = 0; c < VEC; ++c) {
+                            ok[c] = v[u][c] >= cut;
+                            v[u][c] = scale_logit(v[u][c], inv_t);
+                        }
+                        f.take<VEC, true>(v[u], ok);
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        bool ok[VEC];
+#pragma unroll
+                        for (int c = 0; c < VEC; ++c) {
+                            const int idx = at[u] + c;
+                            const uint32_t key = logit_key(v[u][c], idx, eos_id, eos_key_add);
+                            ok[c] = in[u] && (key > nu.kstar || (key == nu.kstar && idx <= nu.tie_limit));
+                            v[u][c] = idx == eos_id ? fmaf(v[u][c], inv_t, eos_bias) : scale_logit(v[u][c], inv_t);
+                        }
+                        f.take<VEC, true>(v[u], ok);
+                    }
+                }
+            }
+            finish(f);
+        }
     }
     __syncthreads();
     float M = -INFINITY;
@@ -758,4 +1053,17 @@ void launch_logprob(const float *logits, int n, int vocab, float temperature, co
         logprob_kernel<1><<<n, SAMPLE_WAVES * WAVE, 0, s>>>(logits, vocab, inv_t, tokens, token_index, out);
 }
 
+// For tests: a[i] = exp_weight(d[i]), b[i] = expf(d[i])
+__global__ void exp_weight_kernel(const float *__restrict__ d, float *__restrict__ a, float *__restrict__ b, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    a[i] = exp_weight(d[i]);
+    b[i] = expf(d[i]);
+}
+
 }  // namespace pc
+
+// For tests, not part of the C ABI.
+extern "C" void pc_internal_exp_weight(const float *d, float *a, float *b, int n, void *stream) {
+    if (n > 0) pc::exp_weight_kernel<<<(n + 255) / 256, 256, 0, (hipStream_t)stream>>>(d, a, b, n);
+}

@@ -248,6 +248,54 @@ def test_top_p_forms(V, form):
     assert same >= math.floor(0.98 * tot)
 
 
+def test_weights_are_those_of_expf():
+    # every 73rd float from -0 to -210 and the ends of the range: the same bits
+    import ctypes
+    import paper_2605_26606_amd as pc
+    lo, hi = np.float32(-0.0).view(np.uint32), np.float32(-210.0).view(np.uint32)
+    bits = np.concatenate([np.arange(int(lo), int(hi), 73, dtype=np.uint32),
+                           np.array([0.0, -103.97, -104.0, -3.4e38, -np.inf], np.float32).view(np.uint32)])
+    d = torch.from_numpy(bits.view(np.float32)).cuda()
+    a, b = torch.empty_like(d), torch.empty_like(d)
+    f = pc.library().pc_internal_exp_weight
+    f.argtypes, f.restype = [ctypes.c_void_p] * 3 + [ctypes.c_int, ctypes.c_void_p], None
+    f(d.data_ptr(), a.data_ptr(), b.data_ptr(), len(bits), torch.cuda.current_stream().cuda_stream or None)
+    torch.cuda.synchronize()
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+@pytest.mark.parametrize("form", ["late", "edges", "few"])
+@pytest.mark.parametrize("V", [4100, 20484, 66571])   # (odd: one token per lane and load)
+def test_top_p_granules(V, form):
+    # late: the first tokens of every wave's segment are masked with a large negative number, so that the bins' ring goes
+    # round; edges: likely tokens at either end of granules of 256 tokens and of the row, the others too far behind to be kept;
+    # few: likely tokens here and there, others just behind the cut.  (Tolerances: test_top_p_forms.)
+    rng = np.random.default_rng(V + len(form))
+    n, T = 6, 0.9
+    x = rng.standard_normal((n, V)).astype(np.float32)
+    if form == "late":
+        seg = -(-(-(-V // 16)) // 256) * 256
+        x[:, np.arange(V) % seg < seg // 2] = -1e9
+    elif form == "edges":
+        at = np.arange(V) % 256
+        x[:, (at == 0) | (at == 255) | (np.arange(V) == V - 1)] += 14.0
+    else:
+        x[:, 3::577] += 9.0
+    uids = np.arange(n, dtype=np.int64) + 51
+    same = tot = 0
+    for top_p in (0.2, 0.9, 0.99):
+        tok, lp = _run_top_p(x, T, top_p, 5, uids, 1, V // 2, 0.25)
+        for i in range(n):
+            u = philox.sampling_uniform(5, int(uids[i]), 1)
+            want, wlp = sampler.sample_token(x[i] * np.float32(1.0 / np.float32(T)), 1.0, u, V // 2, 0.25, top_p=top_p)
+            tot += 1
+            if tok[i] == want:
+                same += 1
+                assert abs(lp[i] - wlp) <= 3e-5 * max(1.0, abs(wlp))
+    say("top-p granules %s V=%d: %d of %d" % (form, V, same, tot))
+    assert same >= math.floor(0.98 * tot)
+
+
 @pytest.mark.parametrize("V,T,top_p,eos,bias", [(32000, 0.7, 0.95, 9, 0.5), (30001, 1.0, 0.8, -1, 0.0), (700, 1.3, 0.3, -1, 0.0)])
 def test_top_p_draws_as_the_plain_sampler_on_the_kept_tokens(V, T, top_p, eos, bias):
     # Nothing but the cut distinguishes the two: with the other tokens masked, plain sampling gives the same token and the same
