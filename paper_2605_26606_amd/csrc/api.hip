@@ -104,6 +104,7 @@ struct pc_ctx {
     int kd = KD_F32;      // kernel dtype of activations, KV cache and weight copies
     void *lm_head_copy = nullptr;   // copy of lm_head: half (KD_F16), or aligned (KD_BF16)
     size_t esz = 2;
+    int lg_qkv = 0, lg_o = 0, lg_gu = 0, lg_down = 0, lg_head = 0;   // order of the weight copies (weight_row)
     // weights (library-owned fused copies, except embed / lm_head / final_norm)
     const void *tok_embed = nullptr, *lm_head = nullptr;
     const float *final_norm = nullptr;
@@ -275,7 +276,7 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
         if (fused) {
             {
                 Timed t(ctx, PC_KERNEL_GEMM_QKV, st);
-                launch_skinny_qkv(dt, ctx->a, ctx->wqkv[l], rows, m.d_model, row_slot, ctx->d_slot_len, ctx->rope_cos,
+                launch_skinny_qkv(dt, ctx->a, {ctx->wqkv[l], ctx->lg_qkv}, rows, m.d_model, row_slot, ctx->d_slot_len, ctx->rope_cos,
                                   ctx->rope_sin, m.n_q_heads, kv, l, ctx->q, sat, st);
             }
             {
@@ -287,18 +288,18 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
                                           ctx->cur_attn_scratch, ctx->attn, sat, st);
             {
                 Timed t(ctx, PC_KERNEL_GEMM_WO, st);
-                launch_skinny_o(dt, ctx->attn, ctx->wo[l], rows, m.d_model, qd, ctx->h, ctx->ffn_norm[l], ctx->h_act, ctx->ssq,
+                launch_skinny_o(dt, ctx->attn, {ctx->wo[l], ctx->lg_o}, rows, m.d_model, qd, ctx->h, ctx->ffn_norm[l], ctx->h_act, ctx->ssq,
                                 sat, st);
             }
             {
                 Timed t(ctx, PC_KERNEL_GEMM_GATE_UP, st);
                 const GemmRowScale rsc{ctx->ssq, m.d_model / 32, m.d_model, m.rms_eps};
-                launch_gemm(dt, impl, ctx->h_act, ctx->wgu[l], ctx->act, rows, 2 * m.d_ff, m.d_model, EPI_SWIGLU_RS, nullptr,
+                launch_gemm(dt, impl, ctx->h_act, {ctx->wgu[l], ctx->lg_gu}, ctx->act, rows, 2 * m.d_ff, m.d_model, EPI_SWIGLU_RS, nullptr,
                             0, sat, st, &rsc);
             }
             {
                 Timed t(ctx, PC_KERNEL_GEMM_DOWN, st);
-                pending = launch_gemm(dt, impl, ctx->act, ctx->wdown[l], ctx->h, rows, m.d_model, m.d_ff, EPI_RESID_F32,
+                pending = launch_gemm(dt, impl, ctx->act, {ctx->wdown[l], ctx->lg_down}, ctx->h, rows, m.d_model, m.d_ff, EPI_RESID_F32,
                                       ctx->cur_slices, ctx->cur_slice_cap, sat, st);
             }
             continue;
@@ -308,11 +309,11 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
         {
             Timed t(ctx, PC_KERNEL_GEMM_QKV, st);
             appended = ctx->qkv_perm &&
-                       launch_gemm_qkv(dt, impl, ctx->a, ctx->wqkv[l], rows, m.d_model,
+                       launch_gemm_qkv(dt, impl, ctx->a, {ctx->wqkv[l], ctx->lg_qkv}, rows, m.d_model,
                                        GemmQkv{row_slot, row_pos, ctx->d_slot_len, ctx->rope_cos, ctx->rope_sin, kv, l,
                                                m.n_q_heads, ctx->q}, sat, st);
             if (!appended)
-                s_qkv = launch_gemm(dt, impl, ctx->a, ctx->wqkv[l], ctx->qkv, rows, qd + 2 * kvd, m.d_model, EPI_STORE_F32,
+                s_qkv = launch_gemm(dt, impl, ctx->a, {ctx->wqkv[l], ctx->lg_qkv}, ctx->qkv, rows, qd + 2 * kvd, m.d_model, EPI_STORE_F32,
                                     ctx->cur_slices, ctx->cur_slice_cap, sat, st);
         }
         if (!appended)
@@ -338,19 +339,19 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
         int s_wo;
         {
             Timed t(ctx, PC_KERNEL_GEMM_WO, st);
-            s_wo = launch_gemm(dt, impl, ctx->attn, ctx->wo[l], ctx->h, rows, m.d_model, qd, EPI_RESID_F32, ctx->cur_slices,
+            s_wo = launch_gemm(dt, impl, ctx->attn, {ctx->wo[l], ctx->lg_o}, ctx->h, rows, m.d_model, qd, EPI_RESID_F32, ctx->cur_slices,
                                ctx->cur_slice_cap, sat, st);
         }
         launch_rmsnorm(dt, ctx->h, nullptr, ctx->ffn_norm[l], rows, m.d_model, m.rms_eps, ctx->a, ctx->cur_slices, s_wo, sat,
                        st);
         {
             Timed t(ctx, PC_KERNEL_GEMM_GATE_UP, st);
-            launch_gemm(dt, impl, ctx->a, ctx->wgu[l], ctx->act, rows, 2 * m.d_ff, m.d_model, EPI_SWIGLU, nullptr, 0, sat,
+            launch_gemm(dt, impl, ctx->a, {ctx->wgu[l], ctx->lg_gu}, ctx->act, rows, 2 * m.d_ff, m.d_model, EPI_SWIGLU, nullptr, 0, sat,
                         st);
         }
         {
             Timed t(ctx, PC_KERNEL_GEMM_DOWN, st);
-            pending = launch_gemm(dt, impl, ctx->act, ctx->wdown[l], ctx->h, rows, m.d_model, m.d_ff, EPI_RESID_F32,
+            pending = launch_gemm(dt, impl, ctx->act, {ctx->wdown[l], ctx->lg_down}, ctx->h, rows, m.d_model, m.d_ff, EPI_RESID_F32,
                                   ctx->cur_slices, ctx->cur_slice_cap, sat, st);
         }
     }
@@ -365,7 +366,7 @@ void enqueue_decode(pc_ctx *ctx, const int32_t *tokens_in, int n, float *logits,
                    ctx->d_sat, st);
     {
         Timed t(ctx, PC_KERNEL_GEMM_LM_HEAD, st);
-        launch_gemm(ctx->kd, ctx->impl(), ctx->a, ctx->lm_head, logits, n, m.vocab, m.d_model, EPI_STORE_F32, nullptr, 0,
+        launch_gemm(ctx->kd, ctx->impl(), ctx->a, {ctx->lm_head, ctx->lg_head}, logits, n, m.vocab, m.d_model, EPI_STORE_F32, nullptr, 0,
                     ctx->d_sat, st);
     }
     launch_advance_len(ctx->d_slot_len, ctx->d_dec_slot, n, st);
@@ -467,6 +468,10 @@ pc_status pc_create(const pc_model_config *model, const pc_weights *w, const pc_
     hipStream_t st = nullptr;
 
     // ---- fused weight copies
+    ctx->lg_qkv = weight_lg(ctx->kd, qd + 2 * kvd, m.d_model);
+    ctx->lg_o = weight_lg(ctx->kd, m.d_model, qd);
+    ctx->lg_gu = weight_lg(ctx->kd, 2 * m.d_ff, m.d_model);
+    ctx->lg_down = weight_lg(ctx->kd, m.d_model, m.d_ff);
     ctx->tok_embed = w->tok_embed;
     ctx->lm_head = w->lm_head;
     ctx->final_norm = (const float *)w->final_norm;
@@ -475,18 +480,18 @@ pc_status pc_create(const pc_model_config *model, const pc_weights *w, const pc_
         float *g;
         TRY(dev_alloc((char **)&p, (size_t)(qd + 2 * kvd) * m.d_model * esz));
         ctx->wqkv.push_back(p);
-        launch_pack_rows(ctx->kd, w->wq[l], p, qd, m.d_model, 0, ctx->qkv_perm ? m.head_dim : 0, st);
-        launch_pack_rows(ctx->kd, w->wk[l], p, kvd, m.d_model, qd, ctx->qkv_perm ? m.head_dim : 0, st);
-        launch_pack_rows(ctx->kd, w->wv[l], p, kvd, m.d_model, qd + kvd, 0, st);
+        launch_pack_rows(ctx->kd, w->wq[l], p, qd, m.d_model, 0, ctx->qkv_perm ? m.head_dim : 0, ctx->lg_qkv, st);
+        launch_pack_rows(ctx->kd, w->wk[l], p, kvd, m.d_model, qd, ctx->qkv_perm ? m.head_dim : 0, ctx->lg_qkv, st);
+        launch_pack_rows(ctx->kd, w->wv[l], p, kvd, m.d_model, qd + kvd, 0, ctx->lg_qkv, st);
         TRY(dev_alloc((char **)&p, (size_t)m.d_model * qd * esz));
         ctx->wo.push_back(p);
-        launch_pack_rows(ctx->kd, w->wo[l], p, m.d_model, qd, 0, 0, st);
+        launch_pack_rows(ctx->kd, w->wo[l], p, m.d_model, qd, 0, 0, ctx->lg_o, st);
         TRY(dev_alloc((char **)&p, (size_t)2 * m.d_ff * m.d_model * esz));
         ctx->wgu.push_back(p);
-        launch_pack_gate_up(ctx->kd, w->w_gate[l], w->w_up[l], p, m.d_ff, m.d_model, st);
+        launch_pack_gate_up(ctx->kd, w->w_gate[l], w->w_up[l], p, m.d_ff, m.d_model, ctx->lg_gu, st);
         TRY(dev_alloc((char **)&p, (size_t)m.d_model * m.d_ff * esz));
         ctx->wdown.push_back(p);
-        launch_pack_rows(ctx->kd, w->w_down[l], p, m.d_model, m.d_ff, 0, 0, st);
+        launch_pack_rows(ctx->kd, w->w_down[l], p, m.d_model, m.d_ff, 0, 0, ctx->lg_down, st);
         TRY(dev_alloc(&g, (size_t)m.d_model));
         ctx->attn_norm.push_back(g);
         TRY_HIP(hipMemcpyAsync(g, w->attn_norm[l], (size_t)m.d_model * 4, hipMemcpyDeviceToDevice, st));
@@ -499,7 +504,8 @@ pc_status pc_create(const pc_model_config *model, const pc_weights *w, const pc_
     // the matrix-core kernels' wide loads want
     if (ctx->kd == KD_F16 || (ctx->kd == KD_BF16 && ((uintptr_t)w->lm_head & 15) != 0)) {
         TRY(dev_alloc((char **)&ctx->lm_head_copy, (size_t)m.vocab * m.d_model * esz));
-        launch_pack_rows(ctx->kd, w->lm_head, ctx->lm_head_copy, m.vocab, m.d_model, 0, 0, st);
+        ctx->lg_head = weight_lg(ctx->kd, m.vocab, m.d_model);
+        launch_pack_rows(ctx->kd, w->lm_head, ctx->lm_head_copy, m.vocab, m.d_model, 0, 0, ctx->lg_head, st);
         ctx->lm_head = ctx->lm_head_copy;
     }
 
@@ -745,7 +751,7 @@ static pc_status forward_chunks(pc_ctx *ctx, const int32_t *prompt_tokens, const
         if (!score) {
             launch_rmsnorm(ctx->kd, ctx->h, d_last, ctx->final_norm, np, m.d_model, m.rms_eps, ctx->a, nullptr, 1,
                            ctx->d_sat, st);
-            launch_gemm(ctx->kd, ctx->impl(), ctx->a, ctx->lm_head, last_logits + (size_t)p0 * m.vocab, np, m.vocab,
+            launch_gemm(ctx->kd, ctx->impl(), ctx->a, {ctx->lm_head, ctx->lg_head}, last_logits + (size_t)p0 * m.vocab, np, m.vocab,
                         m.d_model, EPI_STORE_F32, nullptr, 0, ctx->d_sat, st);
         } else {
             // rows whose NEXT token belongs to a completion: positions prompt_len-1 .. len-2 of every sequence
@@ -771,12 +777,12 @@ static pc_status forward_chunks(pc_ctx *ctx, const int32_t *prompt_tokens, const
                     launch_rmsnorm(ctx->kd, ctx->h, d_row_slot + off, ctx->final_norm, sr, m.d_model, m.rms_eps, ctx->a,
                                    nullptr, 1, ctx->d_sat, st);
                     if (fused > 0) {
-                        launch_gemm_logprob(ctx->kd, ctx->a, ctx->lm_head, sr, m.vocab, m.d_model, score->temperature,
+                        launch_gemm_logprob(ctx->kd, ctx->a, {ctx->lm_head, ctx->lg_head}, sr, m.vocab, m.d_model, score->temperature,
                                             prompt_tokens, d_row_pos + off, ctx->score_logits, score->out + score_done + off,
                                             st);
                         continue;
                     }
-                    launch_gemm(ctx->kd, ctx->impl(), ctx->a, ctx->lm_head, ctx->score_logits, sr, m.vocab, m.d_model,
+                    launch_gemm(ctx->kd, ctx->impl(), ctx->a, {ctx->lm_head, ctx->lg_head}, ctx->score_logits, sr, m.vocab, m.d_model,
                                 EPI_STORE_F32, nullptr, 0, ctx->d_sat, st);
                     launch_logprob(ctx->score_logits, sr, m.vocab, score->temperature, prompt_tokens, d_row_pos + off,
                                    score->out + score_done + off, st);

@@ -268,40 +268,40 @@ template <typename TS, typename TD> __device__ inline TD conv(TS v) { return fro
 // head_perm > 0: rows come in heads of head_perm rows, and row j of a head goes to row qkv_packed_dim(j) of it
 template <typename TS, typename TD>
 __global__ void pack_rows_kernel(const TS *__restrict__ src, TD *__restrict__ dst, int64_t cols, int64_t dst_row0,
-                                 int head_perm) {
+                                 int head_perm, int lg) {
     int64_t r = blockIdx.x, rd = r;
     if (head_perm > 0) rd = (r / head_perm) * head_perm + qkv_packed_dim((int)(r % head_perm), head_perm);
-    for (int64_t i = threadIdx.x; i < cols; i += blockDim.x) dst[(dst_row0 + rd) * cols + i] = conv<TS, TD>(src[r * cols + i]);
+    for (int64_t i = threadIdx.x; i < cols; i += blockDim.x) dst[weight_at(dst_row0 + rd, i, cols, lg)] = conv<TS, TD>(src[r * cols + i]);
 }
-void launch_pack_rows(int kd, const void *src, void *dst, int64_t rows, int64_t cols, int64_t dst_row0, int head_perm,
+void launch_pack_rows(int kd, const void *src, void *dst, int64_t rows, int64_t cols, int64_t dst_row0, int head_perm, int lg,
                       hipStream_t s) {
     if (rows <= 0) return;
     if (kd == KD_F32)
-        pack_rows_kernel<float, float><<<(unsigned)rows, 256, 0, s>>>((const float *)src, (float *)dst, cols, dst_row0, head_perm);
+        pack_rows_kernel<float, float><<<(unsigned)rows, 256, 0, s>>>((const float *)src, (float *)dst, cols, dst_row0, head_perm, lg);
     else if (kd == KD_BF16)
-        pack_rows_kernel<bf16_t, bf16_t><<<(unsigned)rows, 256, 0, s>>>((const bf16_t *)src, (bf16_t *)dst, cols, dst_row0, head_perm);
+        pack_rows_kernel<bf16_t, bf16_t><<<(unsigned)rows, 256, 0, s>>>((const bf16_t *)src, (bf16_t *)dst, cols, dst_row0, head_perm, lg);
     else
-        pack_rows_kernel<bf16_t, f16_t><<<(unsigned)rows, 256, 0, s>>>((const bf16_t *)src, (f16_t *)dst, cols, dst_row0, head_perm);
+        pack_rows_kernel<bf16_t, f16_t><<<(unsigned)rows, 256, 0, s>>>((const bf16_t *)src, (f16_t *)dst, cols, dst_row0, head_perm, lg);
 }
 
 // dst row 32t + c      = gate row 16t + c   (c < 16)
 // dst row 32t + 16 + c = up   row 16t + c
 template <typename TS, typename TD>
-__global__ void pack_gate_up_kernel(const TS *__restrict__ gate, const TS *__restrict__ up, TD *__restrict__ dst, int d) {
+__global__ void pack_gate_up_kernel(const TS *__restrict__ gate, const TS *__restrict__ up, TD *__restrict__ dst, int d, int lg) {
     int64_t j = blockIdx.x;   // ffn row
     int64_t t = j / 16, c = j % 16;
     for (int i = threadIdx.x; i < d; i += blockDim.x) {
-        dst[(32 * t + c) * d + i] = conv<TS, TD>(gate[j * d + i]);
-        dst[(32 * t + 16 + c) * d + i] = conv<TS, TD>(up[j * d + i]);
+        dst[weight_at(32 * t + c, i, d, lg)] = conv<TS, TD>(gate[j * d + i]);
+        dst[weight_at(32 * t + 16 + c, i, d, lg)] = conv<TS, TD>(up[j * d + i]);
     }
 }
-void launch_pack_gate_up(int kd, const void *gate, const void *up, void *dst, int d_ff, int d, hipStream_t s) {
+void launch_pack_gate_up(int kd, const void *gate, const void *up, void *dst, int d_ff, int d, int lg, hipStream_t s) {
     if (kd == KD_F32)
-        pack_gate_up_kernel<float, float><<<d_ff, 256, 0, s>>>((const float *)gate, (const float *)up, (float *)dst, d);
+        pack_gate_up_kernel<float, float><<<d_ff, 256, 0, s>>>((const float *)gate, (const float *)up, (float *)dst, d, lg);
     else if (kd == KD_BF16)
-        pack_gate_up_kernel<bf16_t, bf16_t><<<d_ff, 256, 0, s>>>((const bf16_t *)gate, (const bf16_t *)up, (bf16_t *)dst, d);
+        pack_gate_up_kernel<bf16_t, bf16_t><<<d_ff, 256, 0, s>>>((const bf16_t *)gate, (const bf16_t *)up, (bf16_t *)dst, d, lg);
     else
-        pack_gate_up_kernel<bf16_t, f16_t><<<d_ff, 256, 0, s>>>((const bf16_t *)gate, (const bf16_t *)up, (f16_t *)dst, d);
+        pack_gate_up_kernel<bf16_t, f16_t><<<d_ff, 256, 0, s>>>((const bf16_t *)gate, (const bf16_t *)up, (f16_t *)dst, d, lg);
 }
 
 }  // namespace pc

@@ -24,7 +24,7 @@ template <typename T> __device__ inline void store_out(T *p, float v, uint32_t *
 // plain-ALU GEMM: 64x64 tile, BK = 16, 256 threads, 4x4 outputs per thread at stride 16
 // =====================================================================================
 template <typename T, int EPI>
-__global__ __launch_bounds__(256) void gemm_simt_kernel(const T *__restrict__ A, const T *__restrict__ W,
+__global__ __launch_bounds__(256) void gemm_simt_kernel(const T *__restrict__ A, const T *__restrict__ W, int lg,
                                                         void *__restrict__ Cv, int M, int N, int K,
                                                         uint32_t *__restrict__ sat) {
     constexpr int BM = 64, BN = 64, BK = 16;
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const T *__restrict__ A,
             int k = k0 + lk + i;
             int am = m0 + lr, wn = n0 + lr;
             As[lk + i][lr] = (am < M && k < K) ? to_f32(A[(int64_t)am * K + k]) : 0.f;
-            Ws[lk + i][lr] = (wn < N && k < K) ? to_f32(W[(int64_t)wn * K + k]) : 0.f;
+            Ws[lk + i][lr] = (wn < N && k < K) ? to_f32(W[weight_at(wn, k, K, lg)]) : 0.f;
         }
         __syncthreads();
 #pragma unroll
@@ -84,14 +84,14 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const T *__restrict__ A,
 }
 
 template <typename T>
-static void gemm_simt(const void *A, const void *W, void *C, int M, int N, int K, int epi, uint32_t *sat, hipStream_t s) {
+static void gemm_simt(const void *A, WeightRef W, void *C, int M, int N, int K, int epi, uint32_t *sat, hipStream_t s) {
     dim3 grid((N + 63) / 64, (M + 63) / 64);
-    const T *a = (const T *)A, *w = (const T *)W;
+    const T *a = (const T *)A, *w = (const T *)W.p;
     switch (epi) {
-        case EPI_STORE_F32: gemm_simt_kernel<T, EPI_STORE_F32><<<grid, 256, 0, s>>>(a, w, C, M, N, K, sat); break;
-        case EPI_RESID_F32: gemm_simt_kernel<T, EPI_RESID_F32><<<grid, 256, 0, s>>>(a, w, C, M, N, K, sat); break;
-        case EPI_SWIGLU: gemm_simt_kernel<T, EPI_SWIGLU><<<grid, 256, 0, s>>>(a, w, C, M, N, K, sat); break;
-        default: gemm_simt_kernel<T, EPI_STORE_T><<<grid, 256, 0, s>>>(a, w, C, M, N, K, sat); break;
+        case EPI_STORE_F32: gemm_simt_kernel<T, EPI_STORE_F32><<<grid, 256, 0, s>>>(a, w, W.lg, C, M, N, K, sat); break;
+        case EPI_RESID_F32: gemm_simt_kernel<T, EPI_RESID_F32><<<grid, 256, 0, s>>>(a, w, W.lg, C, M, N, K, sat); break;
+        case EPI_SWIGLU: gemm_simt_kernel<T, EPI_SWIGLU><<<grid, 256, 0, s>>>(a, w, W.lg, C, M, N, K, sat); break;
+        default: gemm_simt_kernel<T, EPI_STORE_T><<<grid, 256, 0, s>>>(a, w, W.lg, C, M, N, K, sat); break;
     }
 }
 
@@ -234,7 +234,7 @@ static constexpr int N_XCD = 8;   // MI355X: 8 accelerator dies, each with its o
 // d[v]: D[row 4*(l/16) + v][col l%16]) instead of 32x32x16: the same fragment bytes per product volume, four
 // times as many accumulator tiles per wave.
 template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK, int EPI, bool M16 = false>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__restrict__ A, const T *__restrict__ W,
+__global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__restrict__ A, const T *__restrict__ W, int lg,
                                                         void *__restrict__ Cv, int M, int N, int K, int mb, int nb,
                                                         int S, int plain, uint32_t *__restrict__ sat,
                                                         typename GemmExtra<EPI>::type extra) {
@@ -309,10 +309,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     for (int i = 0; i < W_ITERS; ++i) {
         const int row = (NW * i + wave) * RPL + lr;
         const int chunk = slot ^ ((row / SWZ_DIV) & (CPR - 1));
-        pw[i] = W + (int64_t)min(n0 + row, N - 1) * K + chunk * 8;
+        pw[i] = W + weight_row(min(n0 + row, N - 1), K, lg) + chunk * 8;
     }
     auto issue_tile = [&](int kt, int stage) {
         const int koff = min(kt, kt1 - 1) * BK;            // past the end: a redundant reload, keeps the count constant
+        const int kw = BK == 64 ? koff << lg : ((koff >> 6) << (6 + lg)) + (koff & 63);
         T *sa = smem + stage * STAGE_ELEMS;
         T *sw = sa + BM * BK;
 #pragma unroll
@@ -321,12 +322,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
                                              (__attribute__((address_space(3))) void *)(sa + (NW * i + wave) * RPL * BK), 16, 0, 0);
 #pragma unroll
         for (int i = 0; i < W_ITERS; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pw[i] + koff),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pw[i] + kw),
                                              (__attribute__((address_space(3))) void *)(sw + (NW * i + wave) * RPL * BK), 16, 0, 0);
     };
 
     auto issue_part = [&](int kt, int stage, int part, int parts) {   // the loads l of a tile with l * parts / LOADS == part
         const int koff = min(kt, kt1 - 1) * BK;            // past the end: a redundant reload, keeps the count constant
+        const int kw = BK == 64 ? koff << lg : ((koff >> 6) << (6 + lg)) + (koff & 63);
         T *sa = smem + stage * STAGE_ELEMS;
         T *sw = sa + BM * BK;
 #pragma unroll
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
 #pragma unroll
         for (int i = 0; i < W_ITERS; ++i)
             if ((A_ITERS + i) * parts / LOADS == part)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pw[i] + koff),
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pw[i] + kw),
                                                  (__attribute__((address_space(3))) void *)(sw + (NW * i + wave) * RPL * BK), 16, 0, 0);
     };
     acc_t acc[TM][TN];
@@ -726,7 +728,7 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
         }
     }
     template <int E>
-    static void launch(const void *A, const void *W, void *C, int M, int N, int K, int split, uint32_t *sat, hipStream_t s,
+    static void launch(const void *A, WeightRef W, void *C, int M, int N, int K, int split, uint32_t *sat, hipStream_t s,
                        const typename GemmExtra<E>::type &extra) {
         const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
         const int units = nb * split;
@@ -735,10 +737,10 @@ template <typename T, int BM, int BN, int WM, int WN, int NSTAGE, int BK = 64, b
         const int plain = (split == 1 && mb > 4) ? ((mb % N_XCD == 0) ? 2 : (E == EPI_LOGPROB ? 0 : 1)) : 0;
         const unsigned grid = plain ? (unsigned)(mb * nb) : (unsigned)((units + N_XCD - 1) / N_XCD * N_XCD * mb);
         gemm_mfma_kernel<T, BM, BN, WM, WN, NSTAGE, BK, E, M16><<<grid, 64 * WM * WN, smem, s>>>(
-            (const T *)A, (const T *)W, C, M, N, K, mb, nb, split, plain, sat, extra);
+            (const T *)A, (const T *)W.p, W.lg, C, M, N, K, mb, nb, split, plain, sat, extra);
     }
     // split > 1 only with EPI_STORE_F32, C then being the slice buffer [split][M][N]
-    static void run(const void *A, const void *W, void *C, int M, int N, int K, int epi, int split, uint32_t *sat, hipStream_t s,
+    static void run(const void *A, WeightRef W, void *C, int M, int N, int K, int epi, int split, uint32_t *sat, hipStream_t s,
                     const GemmRowScale *row_scale = nullptr) {
         switch (epi) {
             case EPI_STORE_F32: launch<EPI_STORE_F32>(A, W, C, M, N, K, split, sat, s, {}); break;
@@ -815,15 +817,15 @@ void gemm_init() {
 }
 
 template <typename T>
-static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices,
+static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N, int K, int epi, float *slices,
                               size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale);
 static int large_min_k(bool swiglu) { return swiglu ? 128 : 256; }   // the shortest reduction that gemm_large.hip gets above 512 rows
 
-int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int M, int N, int K, int epi,
+int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M, int N, int K, int epi,
                 float *slices, size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
     if (M <= 0 || N <= 0) return 1;
     if (dtype == KD_F32) {
-        if (impl != 0 && gemm_f32_ok(A, W, N, K, epi)) gemm_f32((const float *)A, (const float *)W, (float *)C, M, N, K, epi, s);
+        if (impl != 0 && gemm_f32_ok(A, W.p, N, K, epi)) gemm_f32((const float *)A, (const float *)W.p, (float *)C, M, N, K, epi, s);
         else gemm_simt<float>(A, W, C, M, N, K, epi, sat, s);
         return 1;
     }
@@ -877,7 +879,7 @@ static QkvRoute qkv_route(int M, int N, int K) {
     if (mb * ((N + 255) / 256) >= 2 * 256) return QKV_256x256;
     return mb * nb128 >= 160 ? QKV_256x128 : QKV_128x128_2;
 }
-template <typename T> static void gemm_qkv_t(QkvRoute r, const void *A, const void *W, int M, int N, int K, const GemmQkv &qkv, uint32_t *sat, hipStream_t s) {
+template <typename T> static void gemm_qkv_t(QkvRoute r, const void *A, WeightRef W, int M, int N, int K, const GemmQkv &qkv, uint32_t *sat, hipStream_t s) {
     typedef Gemm<T> G;
     if (r == QKV_64x128) G::T64x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
     else if (r == QKV_128x128) G::T128x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
@@ -885,7 +887,7 @@ template <typename T> static void gemm_qkv_t(QkvRoute r, const void *A, const vo
     else if (r == QKV_128x128_2) G::T128x128_2::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
     else G::T256x128::template launch<EPI_QKV>(A, W, nullptr, M, N, K, 1, sat, s, qkv);
 }
-bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
+bool launch_gemm_qkv(int dtype, int impl, const void *A, WeightRef W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
                      hipStream_t s) {
     const int N = (qkv.hq + 2 * qkv.kv.n_kv_heads) * qkv.kv.head_dim;
     if (dtype == KD_F32 || impl == 0 || qkv.kv.head_dim != 128 || K % 64 != 0 || M <= 512) return false;
@@ -943,7 +945,7 @@ __global__ __launch_bounds__(1024) void logprob_merge_kernel(GemmLogprob lpa, in
 }
 
 template <typename T>
-static void gemm_logprob_t(const void *A, const void *W, int M, int N, int K, GemmLogprob lpa, float *out, hipStream_t s) {
+static void gemm_logprob_t(const void *A, WeightRef W, int M, int N, int K, GemmLogprob lpa, float *out, hipStream_t s) {
     typedef Gemm<T> G;
     int strips = 0;
     auto run = [&](auto cfg) {
@@ -962,7 +964,7 @@ static void gemm_logprob_t(const void *A, const void *W, int M, int N, int K, Ge
     logprob_merge_kernel<<<(M + 15) / 16, 1024, 0, s>>>(lpa, M, N, strips, out);
 }
 
-void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, int K, float temperature,
+void launch_gemm_logprob(int dtype, const void *A, WeightRef W, int M, int N, int K, float temperature,
                          const int32_t *tokens, const int32_t *token_index, void *scratch, float *out, hipStream_t s) {
     if (M <= 0) return;
     const size_t strips = ((size_t)N + 255) / 256 * (256 / LOGPROB_STRIP);
@@ -974,7 +976,7 @@ void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, 
 }
 
 template <typename T>
-static int gemm_mfma_dispatch(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices,
+static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N, int K, int epi, float *slices,
                               size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
     // Rules from sweeps of the configurations over the projection shapes of the 1.5B, 8B and 14B models at 3 to 16384 rows.
     typedef Gemm<T> G;

@@ -91,7 +91,7 @@ PC_HD inline int large_row(int order, int j, int r) {
 // run over the first loads of the next, so only a block's first tile waits for memory; a tile after that costs its products and
 // its epilogue.  (Rows past the end read as zero through the buffer's bounds, stores past the end are dropped by them.)
 template <typename T, int TMH, int TNH, int NP, int EPI>
-__global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict__ A, const T *__restrict__ W,
+__global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict__ A, const T *__restrict__ W, int lg,
                                                             void *__restrict__ Cv, int M, int N, int K, int mb, int nb,
                                                             int S, int bh, int run, uint32_t *__restrict__ sat,
                                                             typename GemmExtra<EPI>::type extra) {
@@ -125,9 +125,9 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
         const int k0 = t.z * per;
         t.kt = min(KT, k0 + per) - k0;
         t.a = A + (int64_t)t.m0 * K + (int64_t)k0 * BK;
-        t.w = W + (int64_t)t.n0 * K + (int64_t)k0 * BK;
+        t.w = W + (int64_t)t.n0 * K + (((int64_t)k0 * BK) << lg);   // (whole slabs)
         t.a_bytes = ((uint32_t)min(M - t.m0, BM) * (uint32_t)K - (uint32_t)(k0 * BK)) * 2u;   // up to the end of the last row
-        t.w_bytes = ((uint32_t)min(N - t.n0, BN) * (uint32_t)K - (uint32_t)(k0 * BK)) * 2u;
+        t.w_bytes = ((uint32_t)min(N - t.n0, BN) * (uint32_t)K - ((uint32_t)(k0 * BK) << lg)) * 2u;
         return true;
     };
 
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
             const int u = 32 * i + 8 * wave + lr;
             const int in = h * (SN / 2) + u % (SN / 2);
             const int row = (u / (SN / 2)) * SN + large_row(ORDER, in / 16, in % 16);
-            vw[h][i] = (uint32_t)row * (uint32_t)K * 2u + (uint32_t)(slot8 ^ ((u / 2) & 7)) * 16u;
+            vw[h][i] = (uint32_t)weight_row(row, K, lg) * 2u + (uint32_t)(slot8 ^ ((u / 2) & 7)) * 16u;
         }
     }
     Tile cur, nxt;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256, 1) void gemm_large_kernel(const T *__restrict_
         const int off = in ? t : (more ? t - cur.kt : 0);
         __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            r, (__attribute__((address_space(3))) void *)(smem + slot * PAIR + UA + (32 * q + 8 * wave) * BK), 16, vw[h][q], off * (BK * 2), 0, 0);
+            r, (__attribute__((address_space(3))) void *)(smem + slot * PAIR + UA + (32 * q + 8 * wave) * BK), 16, vw[h][q], off * (BK * 2) << lg, 0, 0);
     };
 
     // ---- LDS -> registers
@@ -600,12 +600,12 @@ template <typename T, int TMH, int TNH> struct LargeCfg {
         (void)hipFuncSetAttribute((const void *)gemm_large_kernel<T, TMH, TNH, NP, E>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem<E>());
     }
     template <int E>
-    static void launch(const void *A, const void *W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s,
+    static void launch(const void *A, WeightRef W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s,
                        const typename GemmExtra<E>::type &extra) {
         const int mb = (M + BM - 1) / BM, nb = (N + BN - 1) / BN;
         int bh, run;
         const unsigned grid = gemm_band_grid(mb, nb, S, &bh, &run);
-        gemm_large_kernel<T, TMH, TNH, NP, E><<<grid, 256, smem<E>(), s>>>((const T *)A, (const T *)W, C, M, N, K, mb, nb, S, bh, run, sat, extra);
+        gemm_large_kernel<T, TMH, TNH, NP, E><<<grid, 256, smem<E>(), s>>>((const T *)A, (const T *)W.p, W.lg, C, M, N, K, mb, nb, S, bh, run, sat, extra);
     }
 };
 
@@ -683,10 +683,10 @@ static int large_pick(int max_slices, int M, int N, int K, int epi, int *S, bool
     return best;
 }
 
-static bool large_ok(const void *A, const void *W, const void *C, int M, int N, int K, int epi) {
+static bool large_ok(const void *A, WeightRef W, const void *C, int M, int N, int K, int epi) {
     // (two steps of K at least, the ring reaches that far ahead; rows of operands and results in whole 16-byte pieces, but fp32
     // results may start at any float: the logits are the caller's; a tile's bytes within a buffer descriptor's 32 bits)
-    return K % 64 == 0 && K >= 128 && N % 16 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0 && ((uintptr_t)C & (epi == EPI_STORE_F32 ? 3 : 15)) == 0 &&
+    return K % 64 == 0 && K >= 128 && N % 16 == 0 && (((uintptr_t)A | (uintptr_t)W.p) & 15) == 0 && ((uintptr_t)C & (epi == EPI_STORE_F32 ? 3 : 15)) == 0 &&
            K <= (1 << 21) && N <= (1 << 21);
 }
 
@@ -717,13 +717,13 @@ template <typename T> struct Large {
         init_epilogue<EPI_SWIGLU_RS>(); init_epilogue<EPI_QKV>(); init_epilogue<EPI_LOGPROB>();
     }
     template <int E>
-    static void launch(int id, const void *A, const void *W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s,
+    static void launch(int id, const void *A, WeightRef W, void *C, int M, int N, int K, int S, uint32_t *sat, hipStream_t s,
                        const typename GemmExtra<E>::type &extra) {
         with_tile(id, [&](auto cfg) {
             if constexpr (built<E, decltype(cfg)>()) decltype(cfg)::template launch<E>(A, W, C, M, N, K, S, sat, s, extra);
         });
     }
-    static int gemm(const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap, uint32_t *sat,
+    static int gemm(const void *A, WeightRef W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap, uint32_t *sat,
                     hipStream_t s, const GemmRowScale *row_scale) {
         int S = 1;
         if (epi == EPI_SWIGLU_RS || epi == EPI_SWIGLU) {
@@ -746,20 +746,20 @@ template <typename T> struct Large {
         else launch<EPI_STORE_F32>(id, A, W, C, M, N, K, 1, sat, s, {});
         return S;
     }
-    static bool qkv(const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
+    static bool qkv(const void *A, WeightRef W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
         int S = 1;
         const int id = large_pick(1, M, N, K, EPI_QKV, &S, !q.row_pos);
         if (id == LT_EIGHT) return false;
         launch<EPI_QKV>(id, A, W, nullptr, M, N, K, 1, sat, s, q);
         return true;
     }
-    static int logprob(const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
+    static int logprob(const void *A, WeightRef W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
         int S = 1;
         launch<EPI_LOGPROB>(large_pick(1, M, N, K, EPI_LOGPROB, &S), A, W, nullptr, M, N, K, 1, nullptr, s, lp);
         return (N + 255) / 256 * 2;   // strips of 128 columns
     }
     // `extra`: the epilogue's own arguments, if it has any
-    static void named(int id, int epi, const void *A, const void *W, void *C, int M, int N, int K, int S, const void *extra, uint32_t *sat,
+    static void named(int id, int epi, const void *A, WeightRef W, void *C, int M, int N, int K, int S, const void *extra, uint32_t *sat,
                       hipStream_t s) {
         switch (epi) {
             case EPI_STORE_F32: launch<EPI_STORE_F32>(id, A, W, C, M, N, K, S, sat, s, {}); break;
@@ -777,7 +777,7 @@ void gemm_large_init() {
     Large<f16_t>::init();
 }
 
-int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap,
+int launch_gemm_large(int dtype, const void *A, WeightRef W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap,
                       uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
     const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS;
     if ((epi != EPI_STORE_F32 && epi != EPI_RESID_F32 && !swiglu) || !large_ok(A, W, C, M, N, K, epi) || ((uintptr_t)slices & 15) != 0 ||
@@ -787,12 +787,12 @@ int launch_gemm_large(int dtype, const void *A, const void *W, void *C, int M, i
     return Large<f16_t>::gemm(A, W, C, M, N, K, epi, slices, slice_cap, sat, s, row_scale);
 }
 
-bool launch_gemm_large_qkv(int dtype, const void *A, const void *W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
+bool launch_gemm_large_qkv(int dtype, const void *A, WeightRef W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s) {
     if (!large_ok(A, W, nullptr, M, N, K, EPI_QKV)) return false;
     return dtype == KD_BF16 ? Large<bf16_t>::qkv(A, W, M, N, K, q, sat, s) : Large<f16_t>::qkv(A, W, M, N, K, q, sat, s);
 }
 
-int launch_gemm_large_logprob(int dtype, const void *A, const void *W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
+int launch_gemm_large_logprob(int dtype, const void *A, WeightRef W, int M, int N, int K, const GemmLogprob &lp, hipStream_t s) {
     if (!large_ok(A, W, nullptr, M, N, K, EPI_LOGPROB)) return 0;
     return dtype == KD_BF16 ? Large<bf16_t>::logprob(A, W, M, N, K, lp, s) : Large<f16_t>::logprob(A, W, M, N, K, lp, s);
 }

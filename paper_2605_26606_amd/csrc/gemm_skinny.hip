@@ -59,7 +59,7 @@ template <typename T> __device__ inline typename Mma<T>::frag sk_ld(const T *p) 
 //         16 dims of the first half of the head and their 16 rotation partners, see pack_qkv_rows)
 // MODE 1: residual update + activation copy + sums of squares
 template <typename T, int MODE, int BM>
-__global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__restrict__ A, const T *__restrict__ W,
+__global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__restrict__ A, const T *__restrict__ W, int lg,
                                                                   int M, int N, int K, int mb, int nb, SkinnyQkv qa,
                                                                   SkinnyO oa, uint32_t *__restrict__ sat) {
     constexpr int SK_BM = BM, SK_NS = SkinnyTile<BM>::NS, SK_STEP_ELEMS = SkinnyTile<BM>::STEP_ELEMS,
@@ -83,15 +83,15 @@ __global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(const T *__r
     for (int l = 0; l < SK_LOADS; ++l) {
         const int row = 8 * l + lr;                    // rows 0..BM-1: A, then 32 of W
         const int chunk = lslot ^ ((row / 2) & 7);
-        src[l] = (row < SK_BM ? A + (int64_t)min(m0 + row, M - 1) * K : W + (int64_t)(n0 + row - SK_BM) * K) + kwave +
-                 chunk * 8;
+        src[l] = (row < SK_BM ? A + (int64_t)min(m0 + row, M - 1) * K + kwave
+                              : W + weight_row(n0 + row - SK_BM, K, lg) + ((int64_t)kwave << lg)) + chunk * 8;
     }
     auto issue = [&](int st, int stage) {
         const int koff = min(st, steps - 1) * SK_BK;   // past the end: a redundant reload that keeps the count constant
         T *dst = ring + stage * SK_STEP_ELEMS;
 #pragma unroll
         for (int l = 0; l < SK_LOADS; ++l)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[l] + koff),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[l] + (8 * l < SK_BM ? koff : koff << lg)),
                                              (__attribute__((address_space(3))) void *)(dst + 8 * l * SK_BK), 16, 0, 0);
     };
 
@@ -248,21 +248,21 @@ void skinny_init() {   // once per device: the kernels use more dynamic LDS than
 }
 
 template <typename T, int MODE, int BM>
-static void skinny_launch_bm(const void *A, const void *W, int M, int N, int K, const SkinnyQkv &qa, const SkinnyO &oa,
+static void skinny_launch_bm(const void *A, WeightRef W, int M, int N, int K, const SkinnyQkv &qa, const SkinnyO &oa,
                              uint32_t *sat, hipStream_t s) {
     const int mb = (M + BM - 1) / BM, nb = N / SK_BN;
     const unsigned grid = (unsigned)((nb + 7) / 8 * 8 * mb);
-    gemm_skinny_kernel<T, MODE, BM><<<grid, 64 * SK_WAVES, SkinnyTile<BM>::SMEM, s>>>((const T *)A, (const T *)W, M, N, K, mb, nb, qa, oa, sat);
+    gemm_skinny_kernel<T, MODE, BM><<<grid, 64 * SK_WAVES, SkinnyTile<BM>::SMEM, s>>>((const T *)A, (const T *)W.p, W.lg, M, N, K, mb, nb, qa, oa, sat);
 }
 template <typename T, int MODE>
-static void skinny_launch(const void *A, const void *W, int M, int N, int K, const SkinnyQkv &qa, const SkinnyO &oa,
+static void skinny_launch(const void *A, WeightRef W, int M, int N, int K, const SkinnyQkv &qa, const SkinnyO &oa,
                           uint32_t *sat, hipStream_t s) {
     if (M <= 16) skinny_launch_bm<T, MODE, 16>(A, W, M, N, K, qa, oa, sat, s);
     else if (M <= 32) skinny_launch_bm<T, MODE, 32>(A, W, M, N, K, qa, oa, sat, s);
     else skinny_launch_bm<T, MODE, 64>(A, W, M, N, K, qa, oa, sat, s);
 }
 
-void launch_skinny_qkv(int dtype, const void *A, const void *W, int M, int K, const int32_t *row_slot,
+void launch_skinny_qkv(int dtype, const void *A, WeightRef W, int M, int K, const int32_t *row_slot,
                        const int32_t *slot_len, const float *rope_cos, const float *rope_sin, int hq, KvGeom kv, int layer,
                        void *q_out, uint32_t *sat, hipStream_t s) {
     SkinnyQkv qa{row_slot, slot_len, rope_cos, rope_sin, kv, layer, hq, q_out};
@@ -272,7 +272,7 @@ void launch_skinny_qkv(int dtype, const void *A, const void *W, int M, int K, co
     else skinny_launch<f16_t, 0>(A, W, M, N, K, qa, oa, sat, s);
 }
 
-void launch_skinny_o(int dtype, const void *A, const void *W, int M, int N, int K, float *h, const float *gain, void *h_act,
+void launch_skinny_o(int dtype, const void *A, WeightRef W, int M, int N, int K, float *h, const float *gain, void *h_act,
                      float *ssq, uint32_t *sat, hipStream_t s) {
     SkinnyQkv qa{};
     SkinnyO oa{h, gain, h_act, ssq};

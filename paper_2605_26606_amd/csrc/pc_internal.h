@@ -196,6 +196,15 @@ struct GemmQkv {
     void *q_out;
 };
 
+// A weight matrix as the projections take it: where it is and the order of its elements (lg of weight_row).
+struct WeightRef {
+    const void *p;
+    int lg;
+    WeightRef(const void *p, int lg = 0) : p(p), lg(lg) {}
+};
+// 16-bit copies lie in slabs where the matrix is made of whole ones; lm_heads read in place and fp32 models have plain rows.
+inline int weight_lg(int kd, int64_t N, int64_t K) { return kd != KD_F32 && N % 32 == 0 && K % 64 == 0 ? WEIGHT_SLAB : 0; }
+
 // ---------------------------------------------------------------- kernel launchers
 // (each validates nothing: callers pass shapes that the context has checked; `dtype` is a KernelDtype)
 void launch_embed(int dtype, const void *table, const int32_t *tokens, int rows, int d, int vocab, float *h,
@@ -212,28 +221,28 @@ void gemm_init();   // once per device: raises the dynamic-LDS limit of the matr
 // and `slices` holds S fp32 partial products [S][M][N]; the consumer adds them in slice order (and, for
 // EPI_RESID_F32, adds that sum to the residual stream).
 // `sat`: counter of half-range clamps of the epilogues that store activations (may be NULL).
-int launch_gemm(int dtype, int impl, const void *A, const void *W, void *C, int M, int N, int K, int epi,
+int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M, int N, int K, int epi,
                 float *slices, size_t slice_cap_floats, uint32_t *sat, hipStream_t s,
                 const GemmRowScale *row_scale = nullptr);
 // out[r] = log softmax(A[r] W^T * inv_t)[tokens[token_index[r] + 1]] without the logits ever reaching memory (16-bit types on
 // the matrix cores).  logprob_fused_rows: how many rows a call may have with `scratch_bytes` of scratch; 0: not a shape the
 // kernels take (the caller then goes through the logits).
 int logprob_fused_rows(int dtype, int impl, int N, int K, size_t scratch_bytes);
-void launch_gemm_logprob(int dtype, const void *A, const void *W, int M, int N, int K, float temperature,
+void launch_gemm_logprob(int dtype, const void *A, WeightRef W, int M, int N, int K, float temperature,
                          const int32_t *tokens, const int32_t *token_index, void *scratch, float *out, hipStream_t s);
 // C = A W^T as EPI_QKV leaves it, for batches of more than 512 rows; false: not a shape it takes, or one that a kernel of its
 // own for the rotation serves better; nothing launched.
-bool launch_gemm_qkv(int dtype, int impl, const void *A, const void *W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
+bool launch_gemm_qkv(int dtype, int impl, const void *A, WeightRef W, int M, int K, const GemmQkv &qkv, uint32_t *sat,
                      hipStream_t s);
 // Fused decode projections (gemm_skinny.hip); skinny_ok says whether the shape is one they take.
 bool skinny_ok(int M, int N, int K, int head_dim);
 void skinny_init();   // once per device, like gemm_init
-void launch_skinny_qkv(int dtype, const void *A, const void *W, int M, int K, const int32_t *row_slot,
+void launch_skinny_qkv(int dtype, const void *A, WeightRef W, int M, int K, const int32_t *row_slot,
                        const int32_t *slot_len, const float *rope_cos, const float *rope_sin, int hq, KvGeom kv, int layer,
                        void *q_out, uint32_t *sat, hipStream_t s);
 // h += A W^T; h_act = (new h) * gain in the activation type (the next RMSNorm without its scale);
 // ssq[N/32][M]: partial sums of squares of the new rows
-void launch_skinny_o(int dtype, const void *A, const void *W, int M, int N, int K, float *h, const float *gain, void *h_act,
+void launch_skinny_o(int dtype, const void *A, WeightRef W, int M, int N, int K, float *h, const float *gain, void *h_act,
                      float *ssq, uint32_t *sat, hipStream_t s);
 // Rotates q and k at each row's position, writes q (model dtype) and appends k, v to the cache.
 //   qkv fp32 [S][rows, (hq+2hkv)*hd] (S >= 1 K slices, summed here); row_slot [rows];
@@ -285,8 +294,9 @@ void launch_advantages(const float *rewards, const int32_t *off, int P, float ep
 // weight repacking at context creation; the source has the model's dtype, the copy the kernel dtype `kd`
 // dst[dst_row0 + r'] = src[r]; head_perm > 0: r' = r with its place inside its head of head_perm rows moved to
 // qkv_packed_dim
-void launch_pack_rows(int kd, const void *src, void *dst, int64_t rows, int64_t cols, int64_t dst_row0, int head_perm,
+// (lg: the order of dst's elements, as in weight_row)
+void launch_pack_rows(int kd, const void *src, void *dst, int64_t rows, int64_t cols, int64_t dst_row0, int head_perm, int lg,
                       hipStream_t s);
-void launch_pack_gate_up(int kd, const void *gate, const void *up, void *dst, int d_ff, int d, hipStream_t s);
+void launch_pack_gate_up(int kd, const void *gate, const void *up, void *dst, int d_ff, int d, int lg, hipStream_t s);
 
 }  // namespace pc

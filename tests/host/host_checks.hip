@@ -228,6 +228,23 @@ static int run_maps() {
                             }
                         }
         }
+    // weight matrices: every element has a place of its own in either order, a wave-wide load (8 rows x 64 k from a multiple of 8) is one
+    // kilobyte, the steps of 64 k of a row lie 64 << lg apart, and rows from a multiple of 32 start where plain rows do
+    for (int lg : {0, WEIGHT_SLAB})
+        for (int N : {32, 96, 224})
+            for (int K : {64, 192, 1024}) {
+                std::vector<int> seen((size_t)N * K, 0);
+                for (int r = 0; r < N; ++r)
+                    for (int k = 0; k < K; ++k) {
+                        const int64_t at = weight_at(r, k, K, lg);
+                        REQUIRE(at >= 0 && at < (int64_t)N * K && at == weight_row(r, K, lg) + (int64_t)(k / 64) * (64 << lg) + k % 64);
+                        if (lg == 0) REQUIRE(at == (int64_t)r * K + k);
+                        else REQUIRE(at == weight_at(r / 8 * 8, k / 64 * 64, K, lg) + (r % 8) * 64 + k % 64);
+                        if (r % 32 == 0 && k == 0) REQUIRE(at == (int64_t)r * K);
+                        seen[(size_t)at]++;
+                    }
+                for (int x : seen) REQUIRE(x == 1);
+            }
     int checked = 0;
     for (int mb : {8, 16, 24, 32, 40, 64, 128})
         for (int nb : {1, 3, 6, 7, 8, 9, 12, 16, 70, 594, 1187}) {
