@@ -1,6 +1,8 @@
 // Row-wise kernels of the decoder forward (Section 3.1 policy pi_theta):
 // embedding gather, RMSNorm, rotary positions + KV append, and the small
 // bookkeeping kernels of the paged cache.  All are HBM/latency bound.
+#include <algorithm>
+
 #include "pc_internal.h"
 
 namespace pc {
@@ -50,7 +52,7 @@ void launch_embed(int dtype, const void *table, const int32_t *tokens, int rows,
 // ------------------------------------------------------------------ RMSNorm
 // out = h * rsqrt(mean(h^2) + eps) * gain; one block per row, statistics in fp32.
 // Pending split-K slices of the previous projection are folded into h first (slice order).
-// VEC4: d % 4 == 0 and d <= 4 * 256 * RMS_MAXV: the row lives in registers between the two passes.
+// Rows of up to 4 * 256 * RMS_MAXV values (a multiple of 4) live in registers between the two passes.
 static constexpr int RMS_MAXV = 6;
 
 template <typename T> __device__ inline void store4(T *p, float4 v, uint32_t *sat);
@@ -64,7 +66,7 @@ template <> __device__ inline void store4<f16_t>(f16_t *p, float4 v, uint32_t *s
     *(uint2 *)p = u;
 }
 
-template <typename T, bool VEC4>
+template <typename T>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(float *__restrict__ h, const int32_t *__restrict__ src_row,
                                                       const float *__restrict__ gain, int rows, int d, float eps,
                                                       T *__restrict__ out, const float *__restrict__ slices, int S,
@@ -73,40 +75,72 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float *__restrict__ h, con
     const int r = blockIdx.x, tid = threadIdx.x;
     float *x = h + (int64_t)(src_row ? src_row[r] : r) * d;
     float ss = 0.f;
+    for (int i = tid; i < d; i += 256) {
+        float v = x[i];
+        if (S > 1) {
+            float add = 0.f;
+            for (int z = 0; z < S; ++z) add += slices[((int64_t)z * rows + r) * d + i];
+            v += add;
+            x[i] = v;
+        }
+        ss += v * v;
+    }
+    ss = wave_sum(ss);
+    if (tid % WAVE == 0) part[tid / WAVE] = ss;
+    __syncthreads();
+    const float tot = part[0] + part[1] + part[2] + part[3];
+    const float rs = 1.0f / sqrtf(tot / (float)d + eps);
+    T *o = out + (int64_t)r * d;
+    for (int i = tid; i < d; i += 256) o[i] = from_f32_sat<T>(x[i] * rs * gain[i], sat);
+}
+
+// The same for rows that fit the registers, S slices known.  A decode step's launch is a few hundred rows, one trip to memory long: the
+// loads of J pieces of a row and of all their slices are in flight at once, clamped past the row's end and not left out (a
+// branch or a loop around them made a trip of every piece and of every fourth slice: rows x d x slices 256 x 1536 x 5 5.5 -> 5.1 us, 3
+// x 1536 x 8 5.1 -> 4.2, 168 x 5120 x 6 10.3 -> 8.9; 8 slices of 256 x 4096, 34 MB, take 10.2).
+template <typename T, int S>
+__global__ __launch_bounds__(256) void rmsnorm4_kernel(float *__restrict__ h, const int32_t *__restrict__ src_row,
+                                                       const float *__restrict__ gain, int rows, int d, float eps,
+                                                       T *__restrict__ out, const float *__restrict__ slices,
+                                                       uint32_t *__restrict__ sat) {
+    constexpr int J = S == 1 ? RMS_MAXV : (S <= 4 ? 3 : 2);
+    static_assert(RMS_MAXV % J == 0, "whole groups");
+    __shared__ float part[4];
+    const int r = blockIdx.x, tid = threadIdx.x, n4 = d / 4, wave0 = __builtin_amdgcn_readfirstlane(tid / WAVE) * WAVE;
+    float4 *x = (float4 *)(h + (int64_t)(src_row ? src_row[r] : r) * d);
+    const float4 *sp = (const float4 *)(slices + (int64_t)r * d);
+    const int64_t zs = (int64_t)rows * n4;
+    float ss = 0.f;
     float4 keep[RMS_MAXV];
-    if (VEC4) {
-        const int n4 = d / 4;
 #pragma unroll
-        for (int j = 0; j < RMS_MAXV; ++j) {
-            const int i = tid + 256 * j;
-            if (i < n4) {
-                float4 v = ((const float4 *)x)[i];
-                if (S > 1) {
-                    const float4 *sp = (const float4 *)(slices + (int64_t)r * d) + i;
-                    const int64_t zs = (int64_t)rows * d / 4;
-                    float4 add = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-                    for (int z = 0; z < S; ++z) {
-                        const float4 t = sp[z * zs];
-                        add.x += t.x; add.y += t.y; add.z += t.z; add.w += t.w;
-                    }
-                    v.x += add.x; v.y += add.y; v.z += add.z; v.w += add.w;
-                    ((float4 *)x)[i] = v;
-                }
-                keep[j] = v;
-                ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    for (int j0 = 0; j0 < RMS_MAXV; j0 += J) {
+        if (256 * j0 >= n4) break;   // (block-uniform)
+        float4 t[J][S];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if (wave0 + 256 * (j0 + j) >= n4) continue;   // (wave-uniform)
+            const int i = min(tid + 256 * (j0 + j), n4 - 1);
+            keep[j0 + j] = x[i];
+            if (S > 1) {
+#pragma unroll
+                for (int z = 0; z < S; ++z) t[j][z] = sp[z * zs + i];
             }
         }
-    } else {
-        for (int i = tid; i < d; i += 256) {
-            float v = x[i];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if (wave0 + 256 * (j0 + j) >= n4) continue;
+            const int i = tid + 256 * (j0 + j);
+            float4 &v = keep[j0 + j];
             if (S > 1) {
-                float add = 0.f;
-                for (int z = 0; z < S; ++z) add += slices[((int64_t)z * rows + r) * d + i];
-                v += add;
-                x[i] = v;
+                float4 add = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int z = 0; z < S; ++z) {
+                    add.x += t[j][z].x; add.y += t[j][z].y; add.z += t[j][z].z; add.w += t[j][z].w;
+                }
+                v.x += add.x; v.y += add.y; v.z += add.z; v.w += add.w;
+                if (i < n4) x[i] = v;
             }
-            ss += v * v;
+            if (i < n4) ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
         }
     }
     ss = wave_sum(ss);
@@ -115,36 +149,35 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float *__restrict__ h, con
     const float tot = part[0] + part[1] + part[2] + part[3];
     const float rs = 1.0f / sqrtf(tot / (float)d + eps);
     T *o = out + (int64_t)r * d;
-    if (VEC4) {
-        const int n4 = d / 4;
 #pragma unroll
-        for (int j = 0; j < RMS_MAXV; ++j) {
-            const int i = tid + 256 * j;
-            if (i < n4) {
-                const float4 g = ((const float4 *)gain)[i];
-                float4 v = keep[j];
-                v.x = v.x * rs * g.x; v.y = v.y * rs * g.y; v.z = v.z * rs * g.z; v.w = v.w * rs * g.w;
-                store4<T>(o + 4 * i, v, sat);
-            }
+    for (int j = 0; j < RMS_MAXV; ++j) {
+        const int i = tid + 256 * j;
+        if (i < n4) {
+            const float4 g = ((const float4 *)gain)[i];
+            float4 v = keep[j];
+            v.x = v.x * rs * g.x; v.y = v.y * rs * g.y; v.z = v.z * rs * g.z; v.w = v.w * rs * g.w;
+            store4<T>(o + 4 * i, v, sat);
         }
-    } else {
-        for (int i = tid; i < d; i += 256) o[i] = from_f32_sat<T>(x[i] * rs * gain[i], sat);
     }
 }
 
+template <typename T>
+static void rmsnorm_t(float *h, const int32_t *src_row, const float *gain, int rows, int d, float eps, void *out, const float *slices, int S,
+                      uint32_t *sat, hipStream_t s) {
+    T *o = (T *)out;
+#define PC_RMS(N) case N: rmsnorm4_kernel<T, N><<<rows, 256, 0, s>>>(h, src_row, gain, rows, d, eps, o, slices, sat); return
+    if (d % 4 == 0 && d <= 4 * 256 * RMS_MAXV) {
+        switch (std::max(S, 1)) { PC_RMS(1); PC_RMS(2); PC_RMS(3); PC_RMS(4); PC_RMS(5); PC_RMS(6); PC_RMS(7); PC_RMS(8); }
+    }
+#undef PC_RMS
+    rmsnorm_kernel<T><<<rows, 256, 0, s>>>(h, src_row, gain, rows, d, eps, o, slices, S, sat);
+}
 void launch_rmsnorm(int dtype, float *h, const int32_t *src_row, const float *gain, int rows, int d, float eps,
                     void *out, const float *slices, int S, uint32_t *sat, hipStream_t s) {
     if (rows <= 0) return;
-    const bool vec = (d % 4 == 0) && d <= 4 * 256 * RMS_MAXV;
-#define PC_RMS(T)                                                                                              \
-    do {                                                                                                       \
-        if (vec) rmsnorm_kernel<T, true><<<rows, 256, 0, s>>>(h, src_row, gain, rows, d, eps, (T *)out, slices, S, sat);  \
-        else rmsnorm_kernel<T, false><<<rows, 256, 0, s>>>(h, src_row, gain, rows, d, eps, (T *)out, slices, S, sat);     \
-    } while (0)
-    if (dtype == KD_F32) PC_RMS(float);
-    else if (dtype == KD_BF16) PC_RMS(bf16_t);
-    else PC_RMS(f16_t);
-#undef PC_RMS
+    if (dtype == KD_F32) rmsnorm_t<float>(h, src_row, gain, rows, d, eps, out, slices, S, sat, s);
+    else if (dtype == KD_BF16) rmsnorm_t<bf16_t>(h, src_row, gain, rows, d, eps, out, slices, S, sat, s);
+    else rmsnorm_t<f16_t>(h, src_row, gain, rows, d, eps, out, slices, S, sat, s);
 }
 
 // ------------------------------------------------------------------ RoPE + KV append
@@ -206,21 +239,89 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float *__restric
     }
 }
 
+// The same with four pairs (four dims of v) to a thread and S slices known: 16-byte loads of all slices in flight at once, where the kernel
+// above waits for one slice after another (256 rows of the 8B shape 12.8 -> 11.8 us, 168 of 14B 9.7 -> 8.5).  Heads of a multiple of 16 (packed rows: 32),
+// qkv on 16 bytes.
+template <typename T, int S>
+__global__ __launch_bounds__(256) void rope_append4_kernel(const float *__restrict__ qkv, int rows, const int32_t *__restrict__ row_slot,
+                                                           const int32_t *__restrict__ row_pos, const int32_t *__restrict__ slot_len,
+                                                           const float *__restrict__ rope_cos, const float *__restrict__ rope_sin, int hq,
+                                                           KvGeom kv, int layer, T *__restrict__ q_out, uint32_t *__restrict__ sat, int perm) {
+    const int r = blockIdx.x;
+    const int hd = kv.head_dim, half = hd / 2, hkv = kv.n_kv_heads, bs = kv.block_size;
+    const int nq = hq * half / 4, nk = hkv * half / 4, nv = hkv * hd / 4;
+    const int item = blockIdx.y * 256 + threadIdx.x;
+    if (item >= nq + nk + nv) return;
+    const int width = (hq + 2 * hkv) * hd;
+    const float *row = qkv + (int64_t)r * width;
+    const int64_t zs = (int64_t)rows * width;
+    const bool is_v = item >= nq + nk;
+    // columns of the first and the second values of the pairs (v: of the four dims, twice)
+    const int per = is_v ? hd / 4 : half / 4;
+    const int i = is_v ? item - nq - nk : (item < nq ? item : item - nq);
+    const int head = i / per, j = 4 * (i % per);
+    const int base = (is_v ? (hq + hkv) * hd : (item < nq ? 0 : hq * hd)) + head * hd;
+    const int c1 = base + (is_v || !perm ? j : qkv_packed_dim(j, hd)), c2 = is_v ? c1 : base + (perm ? qkv_packed_dim(j + half, hd) : j + half);
+    float4 a[S], b[S];
+#pragma unroll
+    for (int z = 0; z < S; ++z) {
+        a[z] = *(const float4 *)(row + z * zs + c1);
+        b[z] = *(const float4 *)(row + z * zs + c2);
+    }
+    const int slot = row_slot[r];
+    const int pos = row_pos ? row_pos[r] : slot_len[slot];
+    const int blk = item < nq ? 0 : kv.block_table[(int64_t)slot * kv.max_blocks_per_slot + pos / bs];
+    const int tin = pos % bs;
+    float4 cs = {}, sn = {};
+    if (!is_v) {
+        cs = *(const float4 *)(rope_cos + (int64_t)pos * half + j);
+        sn = *(const float4 *)(rope_sin + (int64_t)pos * half + j);
+    }
+    float4 x1 = a[0], x2 = b[0];
+#pragma unroll
+    for (int z = 1; z < S; ++z) {
+        x1.x += a[z].x; x1.y += a[z].y; x1.z += a[z].z; x1.w += a[z].w;
+        x2.x += b[z].x; x2.y += b[z].y; x2.z += b[z].z; x2.w += b[z].w;
+    }
+    T *pool = (T *)kv.pool + (int64_t)layer * kv.layer_stride + (int64_t)blk * kv.block_elems() + (int64_t)head * kv.head_elems();
+    if (is_v) {
+        pool[kv.v_index(tin, j)] = from_f32_sat<T>(x1.x, sat);
+        pool[kv.v_index(tin, j + 1)] = from_f32_sat<T>(x1.y, sat);
+        pool[kv.v_index(tin, j + 2)] = from_f32_sat<T>(x1.z, sat);
+        pool[kv.v_index(tin, j + 3)] = from_f32_sat<T>(x1.w, sat);
+        return;
+    }
+    const float4 y1 = {x1.x * cs.x - x2.x * sn.x, x1.y * cs.y - x2.y * sn.y, x1.z * cs.z - x2.z * sn.z, x1.w * cs.w - x2.w * sn.w};
+    const float4 y2 = {x2.x * cs.x + x1.x * sn.x, x2.y * cs.y + x1.y * sn.y, x2.z * cs.z + x1.z * sn.z, x2.w * cs.w + x1.w * sn.w};
+    T *q = q_out + (int64_t)r * hq * hd + head * hd;
+    store4<T>(item < nq ? q + j : pool + kv.k_index(tin, j), y1, sat);                 // (four dims of a token are neighbours in K)
+    store4<T>(item < nq ? q + j + half : pool + kv.k_index(tin, j + half), y2, sat);
+}
+
+template <typename T>
+static void rope_append_t(const float *qkv, int S, const int32_t *row_slot, const int32_t *row_pos, const int32_t *slot_len, const float *rope_cos,
+                          const float *rope_sin, int rows, int hq, KvGeom kv, int layer, T *q_out, uint32_t *sat, int perm, hipStream_t s) {
+    const int hd = kv.head_dim, items = (hq + kv.n_kv_heads) * (hd / 2) + kv.n_kv_heads * hd;
+    if (hd % 16 == 0 && (!perm || hd % 32 == 0) && (((uintptr_t)qkv) & 15) == 0) {
+        const dim3 grid(rows, (items / 4 + 255) / 256);
+#define PC_ROPE(N) \
+    case N: rope_append4_kernel<T, N><<<grid, 256, 0, s>>>(qkv, rows, row_slot, row_pos, slot_len, rope_cos, rope_sin, hq, kv, layer, q_out, sat, perm); return
+        switch (std::max(S, 1)) { PC_ROPE(1); PC_ROPE(2); PC_ROPE(3); PC_ROPE(4); PC_ROPE(5); PC_ROPE(6); PC_ROPE(7); PC_ROPE(8); }
+#undef PC_ROPE
+    }
+    rope_append_kernel<T><<<dim3(rows, (items + 255) / 256), 256, 0, s>>>(qkv, S, rows, row_slot, row_pos, slot_len, rope_cos, rope_sin, hq, kv, layer,
+                                                                          q_out, sat, perm);
+}
 void launch_rope_append(int dtype, const float *qkv, int S, const int32_t *row_slot, const int32_t *row_pos,
                         const int32_t *slot_len, const float *rope_cos, const float *rope_sin, int rows, int hq,
                         KvGeom kv, int layer, void *q_out, uint32_t *sat, int perm, hipStream_t s) {
     if (rows <= 0) return;
-    const int items = hq * (kv.head_dim / 2) + kv.n_kv_heads * (kv.head_dim / 2) + kv.n_kv_heads * kv.head_dim;
-    const dim3 grid(rows, (items + 255) / 256);
     if (dtype == KD_F32)
-        rope_append_kernel<float><<<grid, 256, 0, s>>>(qkv, S, rows, row_slot, row_pos, slot_len, rope_cos, rope_sin, hq, kv,
-                                                       layer, (float *)q_out, sat, perm);
+        rope_append_t<float>(qkv, S, row_slot, row_pos, slot_len, rope_cos, rope_sin, rows, hq, kv, layer, (float *)q_out, sat, perm, s);
     else if (dtype == KD_BF16)
-        rope_append_kernel<bf16_t><<<grid, 256, 0, s>>>(qkv, S, rows, row_slot, row_pos, slot_len, rope_cos, rope_sin, hq, kv,
-                                                        layer, (bf16_t *)q_out, sat, perm);
+        rope_append_t<bf16_t>(qkv, S, row_slot, row_pos, slot_len, rope_cos, rope_sin, rows, hq, kv, layer, (bf16_t *)q_out, sat, perm, s);
     else
-        rope_append_kernel<f16_t><<<grid, 256, 0, s>>>(qkv, S, rows, row_slot, row_pos, slot_len, rope_cos, rope_sin, hq, kv,
-                                                       layer, (f16_t *)q_out, sat, perm);
+        rope_append_t<f16_t>(qkv, S, row_slot, row_pos, slot_len, rope_cos, rope_sin, rows, hq, kv, layer, (f16_t *)q_out, sat, perm, s);
 }
 
 // ------------------------------------------------------------------ bookkeeping
@@ -242,23 +343,30 @@ void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
     fill_i32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, v, n);
 }
 
-// copies whole KV blocks (all layers, all kv heads): pairs[2i] -> pairs[2i+1]
-template <typename T>
-__global__ void copy_block_kernel(KvGeom kv, const int32_t *__restrict__ pairs) {
-    int pair = blockIdx.x, layer = blockIdx.y;
-    int src = pairs[2 * pair], dst = pairs[2 * pair + 1];
-    int64_t n = kv.block_elems();
-    const T *s = (const T *)kv.pool + (int64_t)layer * kv.layer_stride + (int64_t)src * n;
-    T *d = (T *)kv.pool + (int64_t)layer * kv.layer_stride + (int64_t)dst * n;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) d[i] = s[i];
+// copies whole KV blocks (all layers, all kv heads): pairs[2i] -> pairs[2i+1], 16 bytes a thread and 16 KB a workgroup (the block of a
+// prompt's last tokens for each of 256 sequences, 3 layers of the 8B shape: 256 us two bytes a thread and
+// a workgroup to a block of a layer, 70 so)
+static constexpr int COPY_PIECES = 1024;   // of 16 bytes, per workgroup
+__global__ __launch_bounds__(256) void copy_block_kernel(uint4 *__restrict__ pool, int64_t layer_pieces, int64_t block_pieces,
+                                                         const int32_t *__restrict__ pairs) {
+    const int pair = blockIdx.x, layer = blockIdx.y;
+    const uint4 *src = pool + layer * layer_pieces + pairs[2 * pair] * block_pieces;
+    uint4 *dst = pool + layer * layer_pieces + pairs[2 * pair + 1] * block_pieces;
+    const int64_t first = (int64_t)blockIdx.z * COPY_PIECES + threadIdx.x;
+    uint4 v[COPY_PIECES / 256];
+#pragma unroll
+    for (int u = 0; u < COPY_PIECES / 256; ++u)
+        if (first + 256 * u < block_pieces) v[u] = src[first + 256 * u];
+#pragma unroll
+    for (int u = 0; u < COPY_PIECES / 256; ++u)
+        if (first + 256 * u < block_pieces) dst[first + 256 * u] = v[u];
 }
 void launch_copy_block(int dtype, KvGeom kv, int n_layers, const int32_t *pairs, int n_pairs, hipStream_t s) {
     if (n_pairs <= 0) return;
-    dim3 grid(n_pairs, n_layers);
-    if (dtype == KD_F32)
-        copy_block_kernel<float><<<grid, 256, 0, s>>>(kv, pairs);
-    else   // both 16-bit kernel dtypes: raw 16-bit payload
-        copy_block_kernel<bf16_t><<<grid, 256, 0, s>>>(kv, pairs);
+    const int64_t size = dtype == KD_F32 ? 4 : 2;   // (blocks hold a multiple of 32 tokens, K and V: whole pieces)
+    const int64_t pieces = kv.block_elems() * size / 16;
+    const dim3 grid(n_pairs, n_layers, (unsigned)((pieces + COPY_PIECES - 1) / COPY_PIECES));
+    copy_block_kernel<<<grid, 256, 0, s>>>((uint4 *)kv.pool, kv.layer_stride * size / 16, pieces, pairs);
 }
 
 // ------------------------------------------------------------------ weight repacking

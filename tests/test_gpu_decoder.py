@@ -195,6 +195,21 @@ def test_fp32_gemm_forms(d, hq, hkv, hd, dff, V, lens, G):
     _check(m, w, prompts, out, 11, 1e-4, range(0, len(lens) * G, 2))
 
 
+@pytest.mark.parametrize("P,G", [(3, 1), (11, 4), (35, 4)])   # up to eight K slices; rows of 704 pieces of 16 bytes
+def test_slices_of_heads_of_64(P, G):
+    # norm and rotation add up the K slices of projections wide enough to be cut, in heads whose rows lie in plain order (attention on
+    # the plain ALU); forks copy blocks of 32 KB with a few tokens in them
+    say("heads of 64, %d rows" % (P * G))
+    m = workloads.scaled(C1, dtype="bf16", d_model=2816, n_q_heads=32, n_kv_heads=8, head_dim=64, d_ff=2816, vocab=512,
+                         n_layers=1, rope_theta=1.0e6).model
+    w = workloads.perturb_norm_gains(workloads.make_weights(m, 3, std=0.02), 10)
+    toks, cu = workloads.make_ragged_prompts([5 + 3 * i % 40 for i in range(P)], m.vocab, 8)
+    prompts = [toks[cu[i]:cu[i + 1]] for i in range(P)]
+    out = _run_generate(m, w, prompts, G, 3, 21, dict(block_size=32, kv_pool_bytes=256 << 20, max_slots=P * (G + 1) + 8, max_ctx=128,
+                                                     max_batch_rows=1024, act_dtype="f16"))
+    _check(m, w, prompts, out, 21, 2e-2, range(0, P * G, max(1, P * G // 6)))
+
+
 def test_bf16_plain_alu_path():
     say("bf16 small model, plain-ALU kernels")
     import paper_2605_26606_amd as pc
