@@ -436,9 +436,20 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
 
     // tile kt lives in stage (kt - kt0) % NSTAGE; the tile being consumed sits in registers, the next one in LDS,
     // NSTAGE-1 more are in flight
+    // q/k/v: a lane keeps slot and position of one of the wave's rows, asked for around the first tile loads.  Looked up per row tile
+    // behind the products, the chain slot -> length -> block or rotation -> store was a third of the launch (1024 decode rows x 2048 x
+    // 1536 19.8 -> 16.4 us, 600 rows 18.6 -> 14.7).
+    constexpr int WROWS = BM / WM;
+    int row_slot = 0, row_pos = 0;
+    [[maybe_unused]] const int own_row = min(m0 + wm * WROWS + lane % WROWS, M - 1);
+    if constexpr (EPI == EPI_QKV) {
+        static_assert(WROWS <= 64, "a lane per row");
+        row_slot = extra.row_slot[own_row];
+    }
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s) issue_tile(kt0 + s, s);
     if constexpr (XT) issue_part(kt0 + NSTAGE - 1, NSTAGE - 1, 0, KK);   // (its other parts: the first tile's steps)
+    if constexpr (EPI == EPI_QKV) row_pos = extra.row_pos ? extra.row_pos[own_row] : extra.slot_len[row_slot];
     // (behind the first tile loads, so that the pipeline is already filling while the statistics arrive; these are
     // ordinary loads, younger than the tile loads: once they are back, so are the tiles.  Loads beyond the last partial sum
     // are clamped, not left out: a branch around each made them wait for one another, which cost gate/up 2.5 us at 96 rows of
@@ -550,67 +561,76 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
         // A wave's columns lie within one head.  q and k: columns come in blocks of 32, 16 dims and their 16 rotary partners
         // (dim + 64): two accumulator tiles that hold the same lanes' pairs.  The rotated 16-row tiles go through the wave's
         // piece of the idle LDS ring and leave as 16-byte pieces (eight dims: contiguous in q and in a key's cache fragment).
-        // v: a lane's four dims of one token are four places of the cache; 16 lanes hold 16 rows, so a prompt's consecutive
-        // tokens leave as runs of eight.  The fp32 q | k | v rows (134 MB per layer at 16384 rows of the 1.5B shape, written
-        // and read again by a kernel of its own) never exist.
+        // v: a token's dims lie 16 bytes apart in the cache; rows re-formed in LDS leave with neighbouring lanes on neighbouring
+        // dims, 8 cache lines to a store instead of up to 64.  The fp32 q | k | v rows (134 MB per layer at 16384 rows of the 1.5B
+        // shape, written and read again by a kernel of its own) never exist.
         static_assert(M16, "lane layout of the 16x16x32 products");
         constexpr int WC = BN / WN, HALF = WC / 2;
         constexpr int PITCH = WC * 2 + 16, LPR = WC / 8, PIECES = 16 * LPR;
         static_assert(WC % 32 == 0 && 128 % WC == 0, "whole 32-column blocks of one head");
         static_assert((size_t)NW * 16 * PITCH <= (size_t)NSTAGE * STAGE_ELEMS * sizeof(T), "staging fits the ring");
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();   // every wave has consumed its last fragments
-        asm volatile("" ::: "memory");
-        unsigned char *stg = smem_raw + (size_t)wave * 16 * PITCH;
         const int ml = lane % 16, nq = 4 * (lane / 16), col0 = n0 + wn * WC;
-        if (col0 >= N) return;
         const int hkv = extra.kv.n_kv_heads, bs = extra.kv.block_size;
         const int qd = extra.hq * 128, kvd = hkv * 128;
         const int part = col0 < qd ? 0 : (col0 < qd + kvd ? 1 : 2);   // q, k, v (wave-uniform)
         const int pc0 = col0 - (part == 0 ? 0 : (part == 1 ? qd : qd + kvd));
         const int head = pc0 / 128, in = pc0 % 128;                   // first column inside the head
+        const int row_tin = row_pos % bs;
+        int row_blk = 0;
+        if (part) row_blk = extra.kv.block_table[(int64_t)row_slot * extra.kv.max_blocks_per_slot + row_pos / bs];
+        f32x4_t cs[TN / 2], sn[TN / 2];                               // of the lane's four pair indices per block, for the row tile to come
+        auto rotation = [&](int i) {
+            const int64_t at = (int64_t)__shfl(row_pos, 16 * i + ml, 64) * 64 + in / 2 + nq;
+#pragma unroll
+            for (int p2 = 0; p2 < TN / 2; ++p2) {
+                cs[p2] = *(const f32x4_t *)(extra.rope_cos + at + 16 * p2);
+                sn[p2] = *(const f32x4_t *)(extra.rope_sin + at + 16 * p2);
+            }
+        };
+        if (part != 2) rotation(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // every wave has consumed its last fragments
+        asm volatile("" ::: "memory");
+        if (col0 >= N) return;
+        unsigned char *stg = smem_raw + (size_t)wave * 16 * PITCH;
         T *pool = (T *)extra.kv.pool + (int64_t)extra.layer * extra.kv.layer_stride + (int64_t)head * extra.kv.head_elems();
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int mt = m0 + wm * (BM / WM) + i * 16, row = mt + ml;
-            int pos = 0, blk = 0;
-            if (row < M) {
-                const int slot = extra.row_slot[row];
-                pos = extra.row_pos ? extra.row_pos[row] : extra.slot_len[slot];
-                if (part) blk = extra.kv.block_table[(int64_t)slot * extra.kv.max_blocks_per_slot + pos / bs];
-            }
-            const int tin = pos % bs;
+            const int mt = m0 + wm * WROWS + i * 16, row = mt + ml;
             uint32_t *const count = row < M ? sat : nullptr;          // (rows past the end are copies of the last one)
             if (part == 2) {
-                if (row < M) {
-                    T *vd = pool + (int64_t)blk * extra.kv.block_elems();
 #pragma unroll
-                    for (int jj = 0; jj < TN; ++jj)
+                for (int jj = 0; jj < TN; ++jj)
+                    *(u32x2 *)(stg + ml * PITCH + (16 * jj + nq) * 2) = pack4_sat<T>(acc[i][jj][0], acc[i][jj][1], acc[i][jj][2], acc[i][jj][3], count);
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            vd[extra.kv.v_index(tin, in + 16 * jj + nq + v)] = from_f32_sat<T>(acc[i][jj][v], sat);
+                for (int it = 0; it < 16 * WC / 64; ++it) {
+                    const int e = it * 64 + lane, r = e / WC, dim = e % WC;
+                    const int rblk = __shfl(row_blk, 16 * i + r, 64), rtin = __shfl(row_tin, 16 * i + r, 64);
+                    if (mt + r < M)
+                        pool[(int64_t)rblk * extra.kv.block_elems() + extra.kv.v_index(rtin, in + dim)] = *(const T *)(stg + r * PITCH + dim * 2);
                 }
+                __builtin_amdgcn_wave_barrier();
                 continue;
             }
 #pragma unroll
             for (int p2 = 0; p2 < TN / 2; ++p2) {
-                const int j = in / 2 + 16 * p2 + nq;                  // first of the lane's four pair indices
-                const f32x4_t c = *(const f32x4_t *)(extra.rope_cos + (int64_t)pos * 64 + j);
-                const f32x4_t sn = *(const f32x4_t *)(extra.rope_sin + (int64_t)pos * 64 + j);
+                const f32x4_t &c = cs[p2], &n = sn[p2];
                 const acc_t &x1 = acc[i][2 * p2], &x2 = acc[i][2 * p2 + 1];
                 unsigned char *dst = stg + ml * PITCH + (16 * p2 + nq) * 2;
-                *(u32x2 *)dst = pack4_sat<T>(rotated_first(x1[0], x2[0], c[0], sn[0]), rotated_first(x1[1], x2[1], c[1], sn[1]),
-                                             rotated_first(x1[2], x2[2], c[2], sn[2]), rotated_first(x1[3], x2[3], c[3], sn[3]), count);
-                *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(rotated_second(x1[0], x2[0], c[0], sn[0]), rotated_second(x1[1], x2[1], c[1], sn[1]),
-                                                          rotated_second(x1[2], x2[2], c[2], sn[2]), rotated_second(x1[3], x2[3], c[3], sn[3]), count);
+                *(u32x2 *)dst = pack4_sat<T>(rotated_first(x1[0], x2[0], c[0], n[0]), rotated_first(x1[1], x2[1], c[1], n[1]),
+                                             rotated_first(x1[2], x2[2], c[2], n[2]), rotated_first(x1[3], x2[3], c[3], n[3]), count);
+                *(u32x2 *)(dst + HALF * 2) = pack4_sat<T>(rotated_second(x1[0], x2[0], c[0], n[0]), rotated_second(x1[1], x2[1], c[1], n[1]),
+                                                          rotated_second(x1[2], x2[2], c[2], n[2]), rotated_second(x1[3], x2[3], c[3], n[3]), count);
             }
+            if (i + 1 < TM) rotation(i + 1);
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int it = 0; it < (PIECES + 63) / 64; ++it) {
                 const int e = it * 64 + lane, r = (e / LPR) % 16, piece = e % LPR;
                 const u32x4 val = *(const u32x4 *)(stg + r * PITCH + piece * 16);
                 const int dim = in / 2 + (8 * piece) % HALF + 64 * ((8 * piece) / HALF);
-                const int rblk = __shfl(blk, r, 64), rtin = __shfl(tin, r, 64);
+                const int rblk = __shfl(row_blk, 16 * i + r, 64), rtin = __shfl(row_tin, 16 * i + r, 64);
                 if (mt + r < M && (PIECES % 64 == 0 || e < PIECES)) {
                     if (part == 0)
                         *(u32x4 *)((T *)extra.q_out + ((int64_t)(mt + r) * extra.hq + head) * 128 + dim) = val;
@@ -859,7 +879,8 @@ int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M,
 
 // ---- q | k | v projection with rotary positions and cache append
 // More than 512 rows.  What a tile costs here is its epilogue rather than its products, and eight waves share it better than four:
-// while one round of blocks, one per CU, holds them, the smallest tile of gemm_mfma (us, against the best of gemm_large):
+// while one round of blocks, one per CU, holds them, the smallest tile of gemm_mfma (us, against the best of gemm_large; since then its
+// lookups moved ahead of the products: 1024 decode rows x 2048 x 1536 16.4, 600 rows 14.7 where it took 18.6; 128 x 128 21.9 and 19.8):
 //   64 x 128    1024 rows x 2048 x 1536  16.8, 25.0 (decode, V all over the cache: 19.9, 26.5);  640 x 1536 x 1024  11.8, 19.7
 //   128 x 128   2048 x 2048 x 1536  21.5, 25.7;  640 x 6144 x 4096  40.6, 47.4 (decode 46.6, 49.4);  1024 x 4096 x 2560  34.2, 36.9
 // Beyond that gemm_large's estimate decides between its tiles and 256 x 128 (1024 x 7168 x 5120  74.1, 95.6;  4096 x 2048 x 1536
