@@ -809,6 +809,8 @@ template <typename T> struct Gemm {
     typedef MfmaCfg<T, 64, 192, 4, 2, 4, 64, true> T64x192;
     typedef MfmaCfg<T, 32, 64, 1, 4, 4, 64, true> T32x64;       // 48 KB of LDS: three blocks per CU
     typedef MfmaCfg<T, 32, 64, 1, 2, 4, 64, true> T32x64_2;     // the same with whole gate/up chunks per wave
+    typedef MfmaCfg<T, 64, 64, 4, 2, 4, 64, true> T64x64;       // 8 waves of 16 x 32: residual projections of some hundred rows
+    typedef MfmaCfg<T, 128, 64, 4, 2, 3, 64, true> T128x64_3;   // 8 waves of 32 x 32, 72 KB of LDS: the same for some more rows
     typedef MfmaCfg<T, 256, 160, 4, 1, 3, 64, true> T256x160;   // 4 waves of 64 x 160
     typedef MfmaCfg<T, 128, 64, 4, 2, 4, 64, true> T128x64;     // 8 waves of 32 x 32: long-K projections cut into K slices
     typedef MfmaCfg<T, 192, 64, 4, 2, 4, 64, true> T192x64;     // the same in wave tiles of 48 x 32
@@ -816,7 +818,7 @@ template <typename T> struct Gemm {
     static void init() {
         T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
         T128x128_2::init(); T128x192::init(); T64x128::init(); T64x192::init(); T32x64::init();
-        T32x64_2::init(); T128x64::init(); T192x64::init(); M64x64::init();
+        T32x64_2::init(); T64x64::init(); T128x64_3::init(); T128x64::init(); T192x64::init(); M64x64::init();
         T256x160::template set_attr<EPI_SWIGLU>();       // (gate/up only)
         T256x160::template set_attr<EPI_SWIGLU_RS>();
         T256x256::init_logprob();
@@ -840,6 +842,18 @@ template <typename T>
 static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N, int K, int epi, float *slices,
                               size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale);
 static int large_min_k(bool swiglu) { return swiglu ? 128 : 256; }   // the shortest reduction that gemm_large.hip gets above 512 rows
+
+// Residual projections of more than 512 rows whose blocks of 128 x 64 all run at once, one per CU: eight waves with little to do each
+// and the whole reduction in one block, no slices for the norm behind to add up.  In 64 x 64 while there are no more than 320 of those
+// (two fit a CU).  With that norm, us alone and as one of three streams, the best of gemm_large.hip's tiles and slices against these:
+//   64 x 64    600 rows x 1536 x 1536  17.8 / 10.8, 13.7 / 8.5;  600 x 1024 x 2048  16.1 / 9.9, 14.4 / 7.8;  1024 x 512 x 256  10.5 / 6.2, 7.8 / 6.2
+//              2000 x 512 x 2048  18.1 / 12.1, 16.7 / 10.3;  600 x 2048 x 1536 (320 blocks)  19.6 / 12.2, 16.7 / 9.9 (128 x 64: 17.8 / 10.4)
+//   128 x 64   1024 x 1536 x 1536  20.7 / 14.1, 18.4 / 12.1 (64 x 64: 20.1 / 12.0);  768 x 2560 x 2048  23.0 / 17.1, 21.9 / 15.1;
+//              2000 x 1024 x 1536  21.0 / 15.7, 18.6 / 13.6;  1024 x 2048 x 2048  22.8 / 18.1, 22.4 / 16.5
+// Longer reductions are faster in slices of larger tiles: 1024 x 1536 x 3072  23.9 / 18.5, 26.2 / 18.8.
+static bool resid_small_tiles(int M, int N, int K, int epi) {
+    return epi == EPI_RESID_F32 && K >= 256 && K <= 2048 && (int64_t)((M + 127) / 128) * ((N + 63) / 64) <= 256;
+}
 
 int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M, int N, int K, int epi,
                 float *slices, size_t slice_cap_floats, uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale) {
@@ -865,7 +879,7 @@ int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M,
     // against 10.3, K = 384 8.9 against 8.4; 384 x 65552 fp32, K = 128 28.2 against 31.8, K = 256 37.5 against 34.5.
     const int nb128 = (N + 127) / 128;
     const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS;
-    const bool large = M > 512   ? K >= large_min_k(swiglu)
+    const bool large = M > 512   ? K >= large_min_k(swiglu) && !resid_small_tiles(M, N, K, epi)
                        : swiglu  ? M > 384 && K >= 384
                                  : (M > 384 && nb128 >= 96) ||
                                        (M > 192 && nb128 >= 512 && epi == EPI_STORE_F32 && K >= 256 && (M > 256 || K <= 4096));
@@ -1015,6 +1029,7 @@ static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N,
         return split;
     };
     if (M > 512) {
+        if (resid_small_tiles(M, N, K, epi)) return (int64_t)((M + 63) / 64) * ((N + 63) / 64) <= 320 ? whole(typename G::T64x64()) : whole(typename G::T128x64_3());
         if (K >= large_min_k(swiglu)) return whole(typename G::T256x128());   // (gate/up that gemm_large.hip left to this tile; widths beyond its limit)
         // 256 x 256 tiles where they still come in several rounds per CU, 256 x 128 below that
         if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) return whole(typename G::T256x256());

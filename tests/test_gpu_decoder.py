@@ -370,7 +370,11 @@ def test_projection_that_rotates_and_appends(hq, hkv, lens, bs, act, d):
     (192, 6400, 528, [700, 9, 650, 800, 777, 640, 555], "bf16"),
     (320, 320, 8208, [513], "f16"),                               # one row beyond the small batches, 5 steps
     (128, 1184, 8208, [190] * 70 + [257], "f16"),                 # two steps to a tile; 13557 rows in chunks; 80 last rows
-    (2048, 384, 528, [333, 201, 300], "f16"),                     # 834 rows of a wide model: K slices in the large tiles
+    (2048, 384, 528, [333, 201, 300], "f16"),                     # 834 rows of a wide model: residual projections in 128 x 64 tiles
+    (2048, 2112, 528, [333, 201, 300], "f16"),                    # down just beyond those: K slices in the large tiles
+    (208, 320, 528, [513], "f16"),                                # 64 x 64 tiles: one row and 16 columns in the last ones
+    (960, 2048, 528, [700, 9, 650, 577], "bf16"),                 # 1936 rows in 240 blocks of 128 x 64; their longest reduction
+    (2560, 256, 528, [190, 323], "f16"),                          # 513 rows x 2560: 360 blocks of 64 x 64, 200 of 128 x 64
     # short reductions, eight waves: gate/up (K = 64) in 256 x 256 tiles, q/k/v in 128 x 128 two to a CU; down (K = 128) in 256 x 256
     (64, 6400, 528, [700, 9, 650, 800, 777, 640, 555], "f16"),
     (8192, 128, 528, [700, 9, 650, 800, 777, 640, 555], "f16"),
