@@ -78,6 +78,15 @@ def generate(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, first_
     return out
 
 
+def _upload(t: torch.Tensor, dev, stream) -> torch.Tensor:
+    """A small host tensor on the device.  From pageable memory the copy waits for everything in flight on its stream (75 us a piece in
+    a pass of the small fp32 model); from pinned memory it is ordered behind it.  Calls for a stream of their own, which need not be
+    torch's current one, keep the copy that is complete when it returns."""
+    if t.device.type != "cpu" or stream is not None:
+        return t.to(dev)
+    return t.pin_memory().to(dev, non_blocking=True)
+
+
 def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, first_logits: torch.Tensor,
              seq_uids: np.ndarray, new_tokens: int, temperature: float, seed: int, eos_id: int = -1,
              eos_logit_bias: float = 0.0, stream=None, keep_logits_rows: Optional[np.ndarray] = None,
@@ -113,16 +122,16 @@ def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, f
     if n == 0 or T == 0:
         return out
     seqs = B.pc_fork(ctx, handles, T, stream)
-    uid_d = torch.from_numpy(np.ascontiguousarray(seq_uids, dtype=np.int64)).to(dev)
-    rows_d = torch.from_numpy(np.ascontiguousarray(logit_rows, dtype=np.int32)).to(dev)
+    uid_d = _upload(torch.from_numpy(np.ascontiguousarray(seq_uids, dtype=np.int64)), dev, stream)
+    rows_d = _upload(torch.from_numpy(np.ascontiguousarray(logit_rows, dtype=np.int32)), dev, stream)
     cur = torch.zeros(n, dtype=torch.int32, device=dev)
     logits = torch.empty((n, V), dtype=torch.float32, device=dev)
     finished = torch.zeros(n, dtype=torch.uint8, device=dev) if eos_id >= 0 else None
-    keep = None if keep_logits_rows is None else torch.as_tensor(keep_logits_rows, dtype=torch.long, device=dev)
-    keep_mask = None
-    if keep is not None:
-        keep_mask = torch.zeros(n, dtype=torch.bool, device=dev)
-        keep_mask[keep] = True
+    keep = keep_mask = None
+    if keep_logits_rows is not None:
+        keep = _upload(torch.as_tensor(keep_logits_rows, dtype=torch.long), dev, stream)
+        keep_at = torch.where(keep < 0, keep + n, keep)        # (index_select does not count from the end)
+        keep_each = keep.expand(T, *keep.shape).clone()        # what each step says it kept
     active = None                      # original index of each batch row (int32, device); None = identity
     lp_hist = torch.zeros((T, n), dtype=torch.float32, device=dev) if keep_logprobs else None
     # the sampler itself files every token (and its log-probability) under [step][original index]: no copy
@@ -132,8 +141,8 @@ def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, f
     keep_steps = None if keep_logits_steps is None else set(int(x) for x in keep_logits_steps)
     out["logits_steps"] = []
     if keep is not None and (keep_steps is None or 0 in keep_steps):
-        out["logits"].append(first_logits[rows_d.long()[keep]].clone())
-        out["logits_rows"].append(keep.clone())
+        out["logits"].append(first_logits[rows_d.long()[keep]])
+        out["logits_rows"].append(keep_each[0])
         out["logits_steps"].append(0)
     steps, rows_decoded = 1, 0
     for t in range(1, T):
@@ -161,14 +170,17 @@ def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, f
         rows_decoded += m
         if keep is not None and (keep_steps is None or t in keep_steps):
             out["logits_steps"].append(t)
-            if active is None:
-                out["logits"].append(logits[keep].clone())
-                out["logits_rows"].append(keep.clone())
+            if active is None:      # (rows are taken out once: an indexed tensor is a copy already)
+                out["logits"].append(logits.index_select(0, keep_at) if keep.dim() == 1 else logits[keep])
+                out["logits_rows"].append(keep_each[t])
             else:
+                if keep_mask is None:
+                    keep_mask = torch.zeros(n, dtype=torch.bool, device=dev)
+                    keep_mask[keep] = True
                 act_l = active.long()
                 sel = keep_mask[act_l]
-                out["logits"].append(logits[sel].clone())
-                out["logits_rows"].append(act_l[sel].clone())
+                out["logits"].append(logits[sel])
+                out["logits_rows"].append(act_l[sel])
         B.pc_sample(logits, None, m, V, temperature, seed, uid_d, None, t, eos_id, eos_logit_bias, cur, None,
                     finished, stream, top_p=top_p, hist_tokens=hist[t],
                     hist_logprob=None if lp_hist is None else lp_hist[t], hist_index=active)

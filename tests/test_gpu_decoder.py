@@ -606,6 +606,29 @@ def test_ragged_stop_shrinks_the_batch(name):
     _check(m, w, prompts, a, 3, 1e-4 if name == "fp32" else 2e-2, range(0, 32, 3), eos_id=eos, bias=bias)
 
 
+@pytest.mark.parametrize("kept", [[2, 0], [-1, 0, 2, 2], [[0, 1], [5, -2]], []])
+def test_kept_logits_of_any_index_form(kept):
+    import paper_2605_26606_amd as pc
+    w = workloads.make_weights(C1.model, 3)
+    ctx = make_ctx(C1.model, w, block_size=32, kv_pool_bytes=16 << 20, max_slots=32, max_ctx=64, max_batch_rows=64)
+    rows = np.repeat(np.arange(2, dtype=np.int32), 3)
+    toks = torch.arange(24, dtype=torch.int32, device="cuda")
+    got = []
+    with torch.cuda.stream(side_stream()):
+        last = torch.empty((2, C1.model.vocab), device="cuda")
+        handles = pc.pc_prefill_shared(ctx, toks, np.array([0, 9, 24], np.int32), last)
+        for keep in (np.arange(6), np.array(kept, np.int64)):
+            g = pc.generate(ctx, handles[rows], rows, last, rows.astype(np.int64) * 65536 + np.arange(6), 4, 1.0, 5, keep_logits_rows=keep)
+            got.append(g)
+    torch.cuda.synchronize()
+    at = torch.as_tensor(kept, dtype=torch.long)
+    assert torch.equal(got[0]["tokens"], got[1]["tokens"])
+    for t in range(4):
+        assert torch.equal(got[1]["logits_rows"][t].cpu(), at)
+        assert torch.equal(got[1]["logits"][t].cpu(), got[0]["logits"][t].cpu()[at])
+    ctx.close()
+
+
 def test_error_paths_leave_state_unchanged():
     import paper_2605_26606_amd as pc
     m = C1.model
