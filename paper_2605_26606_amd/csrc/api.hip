@@ -270,9 +270,16 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
                        skinny_ok(rows, m.d_model, qd, m.head_dim) &&
                        (int64_t)(qd + 2 * kvd) * m.d_model <= ((int64_t)8 << 20) &&
                        (2 * m.d_ff) % 64 == 0;   // the gate/up epilogue with the norm scale exists on the matrix-core kernel only
+    // (no slices are ever pending in an fp32 model)
+    auto takes_norm = [&](const float *gain, const void *w, int cols, int epi) {
+        return ctx->fuse_decode && gemm_f32_norm_ok(dt, impl, ctx->h, gain, w, cols, m.d_model, epi);
+    };
     for (int l = 0; l < m.n_layers; ++l) {
-        launch_rmsnorm(dt, ctx->h, nullptr, ctx->attn_norm[l], rows, m.d_model, m.rms_eps, ctx->a, ctx->cur_slices, pending,
-                       sat, st);
+        const bool qkv_norm = takes_norm(ctx->attn_norm[l], ctx->wqkv[l], qd + 2 * kvd, EPI_STORE_F32);
+        const bool gu_norm = takes_norm(ctx->ffn_norm[l], ctx->wgu[l], 2 * m.d_ff, EPI_SWIGLU);
+        if (!qkv_norm)
+            launch_rmsnorm(dt, ctx->h, nullptr, ctx->attn_norm[l], rows, m.d_model, m.rms_eps, ctx->a, ctx->cur_slices, pending,
+                           sat, st);
         if (fused) {
             {
                 Timed t(ctx, PC_KERNEL_GEMM_QKV, st);
@@ -304,7 +311,7 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
             }
             continue;
         }
-        int s_qkv = 0;
+        int s_qkv = 1;
         bool appended;   // (the large batches' projection rotates and appends by itself)
         {
             Timed t(ctx, PC_KERNEL_GEMM_QKV, st);
@@ -312,7 +319,9 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
                        launch_gemm_qkv(dt, impl, ctx->a, {ctx->wqkv[l], ctx->lg_qkv}, rows, m.d_model,
                                        GemmQkv{row_slot, row_pos, ctx->d_slot_len, ctx->rope_cos, ctx->rope_sin, kv, l,
                                                m.n_q_heads, ctx->q}, sat, st);
-            if (!appended)
+            if (qkv_norm)
+                launch_gemm_f32_norm(ctx->h, ctx->attn_norm[l], m.rms_eps, ctx->wqkv[l], ctx->qkv, rows, qd + 2 * kvd, m.d_model, EPI_STORE_F32, st);
+            else if (!appended)
                 s_qkv = launch_gemm(dt, impl, ctx->a, {ctx->wqkv[l], ctx->lg_qkv}, ctx->qkv, rows, qd + 2 * kvd, m.d_model, EPI_STORE_F32,
                                     ctx->cur_slices, ctx->cur_slice_cap, sat, st);
         }
@@ -342,11 +351,15 @@ int enqueue_layers(pc_ctx *ctx, int rows, const int32_t *row_slot, const int32_t
             s_wo = launch_gemm(dt, impl, ctx->attn, {ctx->wo[l], ctx->lg_o}, ctx->h, rows, m.d_model, qd, EPI_RESID_F32, ctx->cur_slices,
                                ctx->cur_slice_cap, sat, st);
         }
-        launch_rmsnorm(dt, ctx->h, nullptr, ctx->ffn_norm[l], rows, m.d_model, m.rms_eps, ctx->a, ctx->cur_slices, s_wo, sat,
-                       st);
+        if (!gu_norm)
+            launch_rmsnorm(dt, ctx->h, nullptr, ctx->ffn_norm[l], rows, m.d_model, m.rms_eps, ctx->a, ctx->cur_slices, s_wo, sat,
+                           st);
         {
             Timed t(ctx, PC_KERNEL_GEMM_GATE_UP, st);
-            launch_gemm(dt, impl, ctx->a, {ctx->wgu[l], ctx->lg_gu}, ctx->act, rows, 2 * m.d_ff, m.d_model, EPI_SWIGLU, nullptr, 0, sat,
+            if (gu_norm)
+                launch_gemm_f32_norm(ctx->h, ctx->ffn_norm[l], m.rms_eps, ctx->wgu[l], (float *)ctx->act, rows, 2 * m.d_ff, m.d_model, EPI_SWIGLU, st);
+            else
+                launch_gemm(dt, impl, ctx->a, {ctx->wgu[l], ctx->lg_gu}, ctx->act, rows, 2 * m.d_ff, m.d_model, EPI_SWIGLU, nullptr, 0, sat,
                         st);
         }
         {

@@ -228,6 +228,9 @@ int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M,
 // the matrix cores).  logprob_fused_rows: how many rows a call may have with `scratch_bytes` of scratch; 0: not a shape the
 // kernels take (the caller then goes through the logits).
 int logprob_fused_rows(int dtype, int impl, int N, int K, size_t scratch_bytes);
+// C = rmsnorm(h) W^T (EPI_STORE_F32 or EPI_SWIGLU) in one launch, for fp32 models where gemm_f32_norm_ok says so.
+bool gemm_f32_norm_ok(int dtype, int impl, const float *h, const float *gain, const void *W, int N, int K, int epi);
+void launch_gemm_f32_norm(const float *h, const float *gain, float eps, const void *W, float *C, int M, int N, int K, int epi, hipStream_t s);
 void launch_gemm_logprob(int dtype, const void *A, WeightRef W, int M, int N, int K, float temperature,
                          const int32_t *tokens, const int32_t *token_index, void *scratch, float *out, hipStream_t s);
 // C = A W^T as EPI_QKV leaves it, for batches of more than 512 rows; false: not a shape it takes, or one that a kernel of its
