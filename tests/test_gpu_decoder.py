@@ -205,8 +205,8 @@ def test_fp32_gemm_forms(d, hq, hkv, hd, dff, V, lens, G):
 ])
 def test_fp32_norm_inside_the_projection(d, dff, n, scale):
     # against the launches with a norm kernel of their own: each side rounds its normalised rows and sums at most 1376 products of
-    # order 0.02 in float32, whose errors are some 2^-24 sqrt(1376) = 2e-6 of the result, a few times that behind two layers.  A prompt's logits are the same bits
-    # alone and among others.
+    # order 0.02 in float32, whose errors are some 2^-24 sqrt(1376) = 2e-6 of the result, a few times that behind two layers.
+    # A prompt's logits are the same bits alone and among others.
     say("fp32 norm in the projection, d=%d n=%d scale=%g" % (d, n, scale))
     import paper_2605_26606_amd as pc
     m = workloads.scaled(C1, d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=16, d_ff=dff, vocab=300).model
@@ -216,19 +216,22 @@ def test_fp32_norm_inside_the_projection(d, dff, n, scale):
     toks = torch.from_numpy(np.ascontiguousarray(toks, dtype=np.int32)).cuda()
     head = max(1, n // 9)
 
-    def prefill(fuse, cu):
+    def logits_of(fuse, cu):   # behind the prompts, and a token later
         ctx = make_ctx(m, w, block_size=32, kv_pool_bytes=64 << 20, max_slots=16, max_ctx=1024, max_batch_rows=1024)
         pc.pc_set_option(ctx, pc.PC_OPT_FUSE_DECODE, fuse)
         last = torch.empty((len(cu) - 1, m.vocab), device="cuda")
-        pc.pc_prefill_shared(ctx, toks[:cu[-1]], np.array(cu, np.int32), last)
-        out = last.cpu()
+        handles = pc.pc_prefill_shared(ctx, toks[:cu[-1]], np.array(cu, np.int32), last)
+        seqs = pc.pc_fork(ctx, handles, 1)
+        logits = torch.empty_like(last)      # (a vocabulary of 300: the last column tile is a ragged one)
+        pc.pc_decode_step(ctx, seqs, toks[:len(cu) - 1], logits)
+        out = last.cpu(), logits.cpu()
         ctx.close()
         return out
 
     cu = [0, head, n] if n > head else [0, n]
-    a, b = prefill(1, cu), prefill(0, cu)
-    assert torch.isfinite(a).all() and float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
-    assert torch.equal(prefill(1, [0, head])[0], a[0])
+    for a, b in zip(logits_of(1, cu), logits_of(0, cu)):
+        assert torch.isfinite(a).all() and float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
+    assert torch.equal(logits_of(1, [0, head])[0][0], logits_of(1, cu)[0][0])
 
 
 @pytest.mark.parametrize("P,G", [(3, 1), (11, 4), (35, 4)])   # up to eight K slices; rows of 704 pieces of 16 bytes
