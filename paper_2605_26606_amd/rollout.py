@@ -87,6 +87,12 @@ def _upload(t: torch.Tensor, dev, stream) -> torch.Tensor:
     return t.pin_memory().to(dev, non_blocking=True)
 
 
+def _rows_of(x: torch.Tensor, at: torch.Tensor) -> torch.Tensor:
+    """Rows of a buffer that will be written again, in memory of their own.  Indexing copies, except with a single number: that is a
+    view."""
+    return x[at].clone() if at.dim() == 0 else x[at]
+
+
 def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, first_logits: torch.Tensor,
              seq_uids: np.ndarray, new_tokens: int, temperature: float, seed: int, eos_id: int = -1,
              eos_logit_bias: float = 0.0, stream=None, keep_logits_rows: Optional[np.ndarray] = None,
@@ -141,7 +147,7 @@ def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, f
     keep_steps = None if keep_logits_steps is None else set(int(x) for x in keep_logits_steps)
     out["logits_steps"] = []
     if keep is not None and (keep_steps is None or 0 in keep_steps):
-        out["logits"].append(first_logits[rows_d.long()[keep]])
+        out["logits"].append(_rows_of(first_logits, rows_d.long()[keep]))
         out["logits_rows"].append(keep_each[0])
         out["logits_steps"].append(0)
     steps, rows_decoded = 1, 0
@@ -170,8 +176,8 @@ def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, f
         rows_decoded += m
         if keep is not None and (keep_steps is None or t in keep_steps):
             out["logits_steps"].append(t)
-            if active is None:      # (rows are taken out once: an indexed tensor is a copy already)
-                out["logits"].append(logits.index_select(0, keep_at) if keep.dim() == 1 else logits[keep])
+            if active is None:
+                out["logits"].append(logits.index_select(0, keep_at) if keep.dim() == 1 else _rows_of(logits, keep))
                 out["logits_rows"].append(keep_each[t])
             else:
                 if keep_mask is None:

@@ -645,7 +645,7 @@ def test_ragged_stop_shrinks_the_batch(name):
     _check(m, w, prompts, a, 3, 1e-4 if name == "fp32" else 2e-2, range(0, 32, 3), eos_id=eos, bias=bias)
 
 
-@pytest.mark.parametrize("kept", [[2, 0], [-1, 0, 2, 2], [[0, 1], [5, -2]], []])
+@pytest.mark.parametrize("kept", [[2, 0], [-1, 0, 2, 2], [[0, 1], [5, -2]], [], 2, -1])
 def test_kept_logits_of_any_index_form(kept):
     import paper_2605_26606_amd as pc
     w = workloads.make_weights(C1.model, 3)
