@@ -134,21 +134,22 @@ def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, f
     logits = torch.empty((n, V), dtype=torch.float32, device=dev)
     finished = torch.zeros(n, dtype=torch.uint8, device=dev) if eos_id >= 0 else None
     keep = keep_mask = None
+    keep_steps = None if keep_logits_steps is None else set(int(x) for x in keep_logits_steps)
     if keep_logits_rows is not None:
         keep = _upload(torch.as_tensor(keep_logits_rows, dtype=torch.long), dev, stream)
         keep_at = torch.where(keep < 0, keep + n, keep)        # (index_select does not count from the end)
-        keep_each = keep.expand(T, *keep.shape).clone()        # what each step says it kept
+        kept = T if keep_steps is None else sum(0 <= x < T for x in keep_steps)
+        keep_each = list(keep.expand(kept, *keep.shape).clone())   # what each of those steps says it kept
     active = None                      # original index of each batch row (int32, device); None = identity
     lp_hist = torch.zeros((T, n), dtype=torch.float32, device=dev) if keep_logprobs else None
     # the sampler itself files every token (and its log-probability) under [step][original index]: no copy
     # kernel per step, also after the batch has shrunk
     B.pc_sample(first_logits, rows_d, n, V, temperature, seed, uid_d, None, 0, eos_id, eos_logit_bias, cur, None,
                 finished, stream, top_p=top_p, hist_tokens=hist[0], hist_logprob=None if lp_hist is None else lp_hist[0])
-    keep_steps = None if keep_logits_steps is None else set(int(x) for x in keep_logits_steps)
     out["logits_steps"] = []
     if keep is not None and (keep_steps is None or 0 in keep_steps):
         out["logits"].append(_rows_of(first_logits, rows_d.long()[keep]))
-        out["logits_rows"].append(keep_each[0])
+        out["logits_rows"].append(keep_each.pop())
         out["logits_steps"].append(0)
     steps, rows_decoded = 1, 0
     for t in range(1, T):
@@ -178,7 +179,7 @@ def generate_wave(ctx: B.Context, handles: np.ndarray, logit_rows: np.ndarray, f
             out["logits_steps"].append(t)
             if active is None:
                 out["logits"].append(logits.index_select(0, keep_at) if keep.dim() == 1 else _rows_of(logits, keep))
-                out["logits_rows"].append(keep_each[t])
+                out["logits_rows"].append(keep_each.pop())
             else:
                 if keep_mask is None:
                     keep_mask = torch.zeros(n, dtype=torch.bool, device=dev)

@@ -47,3 +47,11 @@ def test_every_step_keeps_its_own_rows(loop, keep):
     for t in range(T):
         assert torch.equal(out["logits"][t], (100.0 * t + want)[at])
         assert torch.equal(out["logits_rows"][t], at)
+
+
+def test_only_kept_steps_take_memory(loop):
+    # one step of a long pass: nothing is allocated for the steps that keep nothing
+    out = _generate(np.arange(N), keep_logits_steps=[3])
+    assert out["logits_steps"] == [3] and len(out["logits"]) == 1
+    rows = out["logits_rows"][0]
+    assert torch.equal(rows, torch.arange(N)) and rows.untyped_storage().nbytes() == N * 8
