@@ -233,6 +233,7 @@ struct NucleusBins {
     double above;
     int sel, n;
     uint32_t seen;                                     // key of the largest scaled logit that any wave has seen
+    uint32_t opening;                                  // the same of the first strides only: not written to while the waves read it
     float granule_max[SAMPLE_WAVES][NUC_GRANULES];     // largest scaled logit
 };
 
@@ -584,7 +585,7 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
             const float per_logit = NUC_PER_UNIT * inv_t;
 #pragma unroll
             for (int i = 0; i < NUC_BINS / BLOCK; ++i) sb.bin[tid + i * BLOCK] = 0ull;
-            if (tid == 0) sb.seen = 0u;
+            if (tid == 0) sb.seen = sb.opening = okey(-INFINITY);
             __syncthreads();
             {
                 float v[VEC], lm = -INFINITY;
@@ -594,10 +595,12 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
                 for (int c = 0; c < VEC; ++c)
                     if (ok[c]) lm = fmaxf(lm, v[c]);
                 lm = wave_max_all(lm);
-                if (lane == 0) atomicMax(&sb.seen, okey(lm));
+                if (lane == 0) atomicMax(&sb.opening, okey(lm));
             }
             __syncthreads();
-            float seen = key_logit(sb.seen);
+            // (all waves have to agree on `filed`, which decides whether the bins are filled again; no barrier keeps a fast wave from
+            // publishing what it sees next before a slow one is here, so that goes to another word)
+            float seen = key_logit(sb.opening);
             filed = seen - reach;
             Fold f;
             auto chunk = [&](auto plain, int base) {   // plain: whole strides without the EOS id
