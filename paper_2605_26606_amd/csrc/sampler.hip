@@ -231,6 +231,7 @@ struct NucleusBins {
     double wave_sum[SAMPLE_WAVES];
     uint32_t wave_lo[SAMPLE_WAVES], wave_hi[SAMPLE_WAVES];
     double above;
+    unsigned long long sel_bin;
     int sel, n;
     uint32_t seen;                                     // key of the largest scaled logit that any wave has seen
     uint32_t opening;                                  // the same of the first strides only: not written to while the waves read it
@@ -238,8 +239,9 @@ struct NucleusBins {
 };
 
 // From the bins (each thread owns four, in order of falling logit): the first one at which above + the running mass reaches
-// `want` (NUC_BINS if none does) into sb.sel, and the mass in front of it into sb.above.  place_of(i) is the place of bin i in that order,
-// scale(i) turns its integer sum into mass and falls by the factor `ratio` from one bin to the next.  Every thread must call it; the bins are read before its first barrier only.
+// `want` (NUC_BINS if none does) into sb.sel, its word into sb.sel_bin and the mass in front of it into sb.above.  place_of(i) is the
+// place of bin i in that order, scale(i) turns its integer sum into mass and falls by the factor `ratio` from one bin to the next.  Every
+// thread must call it; nobody reads the bins behind its last barrier, they may be cleared there.
 template <typename At, typename Scale>
 __device__ inline void nucleus_cross(NucleusBins &sb, double above, double want, double ratio, At place_of, Scale scale) {
     const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
@@ -269,7 +271,10 @@ __device__ inline void nucleus_cross(NucleusBins &sb, double above, double want,
     }
     if (mine >= 0) atomicMin(&sb.sel, mine);
     __syncthreads();
-    if (mine >= 0 && mine == sb.sel) sb.above = at;
+    if (mine >= 0 && mine == sb.sel) {
+        sb.above = at;
+        sb.sel_bin = sb.bin[place_of(mine)];
+    }
     __syncthreads();
 }
 
@@ -370,7 +375,7 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
     nucleus_cross(sb, 0.0, want, 0.96923323447634408185 /* exp(-1/32) */, [&](int i) { return (top - i) & (NUC_BINS - 1); },
                   [&](int i) { return (1.0 / 33554432.0) * exp((double)(top - i) / (double)NUC_PER_UNIT - (double)M); });
     const int sel = sb.sel;
-    if (sel == NUC_BINS || (int)(sb.bin[(top - sel) & (NUC_BINS - 1)] >> NUC_COUNT_SHIFT) > NUC_LIST) return false;
+    if (sel == NUC_BINS || (int)(sb.sel_bin >> NUC_COUNT_SHIFT) > NUC_LIST) return false;
     // ---- pass 2: the mass in front of that bin, its tokens into the list
     const float place_sel = PLACE_BASE + (float)(top - sel);
     granules = with_place((float)(top - sel));
@@ -413,7 +418,7 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
     }
     s = wave_sum_d(s);
     if (lane == 0) sb.wave_sum[wave] = s;
-    // Behind this barrier every wave has read the first bins and filed its tokens.
+    // Behind this barrier every wave has filed its tokens.
     __syncthreads();
     const int n_list = sb.n;
     if (n_list > NUC_LIST || n_list == 0) return false;
@@ -469,7 +474,7 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
         if (part == NUC_BINS) return false;
         above = sb.above;
         lo += (uint32_t)(NUC_BINS - 1 - part) << shift;
-        const unsigned long long bin = sb.bin[part];
+        const unsigned long long bin = sb.sel_bin;
         if (shift > 0 && (bin >> NUC_COUNT_SHIFT) == 1ull) {   // (mostly) one token is left: it is the cut
             for (int k = tid; k < n_list; k += BLOCK) {
                 const uint32_t key = sb.list[k].x;

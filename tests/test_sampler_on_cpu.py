@@ -93,6 +93,8 @@ def _rows(form, V, rng, n=2):
     elif form == "ties":     # few different logits: the cut falls among ties, in the list or (rows of one value) beyond it
         x = np.round(x * 2) / 2 + 0.0   # (no negative zeros: the keys order those behind the others)
         x[1] = 0.5
+    elif form == "close":    # all in one bin: it is cut into parts, and the part with the cut, of several tokens, once more
+        x = np.float32(1) + np.float32(2.0 ** -22) * rng.integers(0, 8000, (n, V)).astype(np.float32)
     elif form == "peaked":
         x[:, 3::97] += 9.0
     return x.astype(np.float32)
@@ -100,7 +102,7 @@ def _rows(form, V, rng, n=2):
 
 @pytest.mark.parametrize("order", [0, 1, 5])
 @pytest.mark.parametrize("V,top_p", [(4100, 1.0), (4100, 0.9), (2051, 0.7), (6144, 0.999)])
-@pytest.mark.parametrize("form", ["bulk", "peaked", "late", "outlier", "ties"])
+@pytest.mark.parametrize("form", ["bulk", "peaked", "late", "outlier", "ties", "close"])
 def test_no_races_between_waves_and_the_oracles_tokens(program, form, V, top_p, order):
     # (tolerances as on the GPU: the weights are float32, a uniform on the rounding of a boundary may go either way)
     rng = np.random.default_rng(V + len(form))
