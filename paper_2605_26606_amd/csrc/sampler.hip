@@ -128,6 +128,10 @@ __device__ inline float scale_logit(float raw, float inv_t) {
 #pragma clang fp contract(off)
     return raw * inv_t;
 }
+// The same with the EOS id's bias, rounded once.
+__device__ inline float scale_logit(float raw, int idx, float inv_t, int eos_id, float eos_bias) {
+    return idx == eos_id ? fmaf(raw, inv_t, eos_bias) : scale_logit(raw, inv_t);
+}
 
 // The kept set of a nucleus: logit key above kstar, or equal to it with an id up to tie_limit.
 struct Nucleus {
@@ -149,12 +153,10 @@ template <int VEC> __device__ inline void load_vec(const float *__restrict__ x, 
     }
 }
 
-template <int VEC>
-__device__ inline void load_scaled(const float *__restrict__ x, int idx, int end, float inv_t, int eos_id,
-                                   float eos_bias, float (&v)[VEC], bool (&ok)[VEC], const Nucleus &nu) {
+// The logits of VEC tokens from idx on; those from `end` on are not there (ok false, 0).
+template <int VEC> __device__ inline void load_raw(const float *__restrict__ x, int idx, int end, float (&v)[VEC], bool (&ok)[VEC]) {
     if (VEC == 4 && idx + 3 < end) {
-        const float4 t = *(const float4 *)(x + idx);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        load_vec<VEC>(x + idx, v);
 #pragma unroll
         for (int c = 0; c < VEC; ++c) ok[c] = true;
     } else {
@@ -164,6 +166,11 @@ __device__ inline void load_scaled(const float *__restrict__ x, int idx, int end
             v[c] = ok[c] ? x[idx + c] : 0.f;
         }
     }
+}
+template <int VEC>
+__device__ inline void load_scaled(const float *__restrict__ x, int idx, int end, float inv_t, int eos_id,
+                                   float eos_bias, float (&v)[VEC], bool (&ok)[VEC], const Nucleus &nu) {
+    load_raw<VEC>(x, idx, end, v, ok);
     if (nu.on) {
 #pragma unroll
         for (int c = 0; c < VEC; ++c) {
@@ -172,10 +179,7 @@ __device__ inline void load_scaled(const float *__restrict__ x, int idx, int end
         }
     }
 #pragma unroll
-    for (int c = 0; c < VEC; ++c) {
-        v[c] = v[c] * inv_t;
-        if (idx + c == eos_id) v[c] += eos_bias;
-    }
+    for (int c = 0; c < VEC; ++c) v[c] = scale_logit(v[c], idx + c, inv_t, eos_id, eos_bias);
 }
 
 __device__ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
@@ -339,11 +343,7 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
     if (vocab > NUC_MAX_VOCAB || !(fabsf(M) < 1e5f) || !(Z >= 0.5 && Z < 1e9)) return false;
     if (eos_id >= 0 && !(fabsf(eos_bias) < 1e5f) && eos_bias != -INFINITY) return false;
     const float per_logit = NUC_PER_UNIT * inv_t;
-    auto scaled = [&](float raw, int idx) {   // as load_scaled forms it
-        float v = raw * inv_t;
-        if (idx == eos_id) v += eos_bias;
-        return v;
-    };
+    auto scaled = [&](float raw, int idx) { return scale_logit(raw, idx, inv_t, eos_id, eos_bias); };
     const int top = (int)rintf(M * NUC_PER_UNIT) + 2;   // no place is above it, whatever the rounding of the scaled maximum
     const int n_granules = (e - b + NUC_GRANULE - 1) / NUC_GRANULE;   // (b <= e)
     auto with_place = [&](float n) {   // granules with a token at place n or above (places and maxima differ by rounding only)
@@ -392,11 +392,9 @@ __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, in
             for (int u = 0; u < 4; ++u) {
 #pragma unroll
                 for (int c = 0; c < VEC; ++c) {
-                    float v = scale_logit(raw[u][c], inv_t), key = raw[u][c];
-                    if (!PLAIN && at[u] + c == eos_id) {
-                        v = fmaf(raw[u][c], inv_t, eos_bias);
-                        key += eos_key_add;
-                    }
+                    const float v = PLAIN ? scale_logit(raw[u][c], inv_t) : scaled(raw[u][c], at[u] + c);
+                    float key = raw[u][c];
+                    if (!PLAIN && at[u] + c == eos_id) key += eos_key_add;
                     if (!PLAIN && !in[u]) key = -INFINITY;
                     const float p = place(key, per_logit);
                     hits |= p == place_sel ? 1u << (4 * u + c) : 0u;
@@ -628,11 +626,8 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
                     top[u] = -INFINITY;
 #pragma unroll
                     for (int c = 0; c < VEC; ++c) {
-                        v[u][c] = scale_logit(raw[u][c], inv_t);
-                        if (!PLAIN && idx + c == eos_id) {
-                            v[u][c] = fmaf(raw[u][c], inv_t, eos_bias);
-                            raw[u][c] += eos_key_add;   // (from here on: the key's logit)
-                        }
+                        v[u][c] = PLAIN ? scale_logit(raw[u][c], inv_t) : scale_logit(raw[u][c], idx + c, inv_t, eos_id, eos_bias);
+                        if (!PLAIN && idx + c == eos_id) raw[u][c] += eos_key_add;   // (from here on: the key's logit)
                         if (!PLAIN && idx + c >= we) v[u][c] = -INFINITY;
                         top[u] = fmaxf(top[u], v[u][c]);
                     }
@@ -820,7 +815,7 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
                             const int idx = at[u] + c;
                             const uint32_t key = logit_key(v[u][c], idx, eos_id, eos_key_add);
                             ok[c] = in[u] && (key > nu.kstar || (key == nu.kstar && idx <= nu.tie_limit));
-                            v[u][c] = idx == eos_id ? fmaf(v[u][c], inv_t, eos_bias) : scale_logit(v[u][c], inv_t);
+                            v[u][c] = scale_logit(v[u][c], idx, inv_t, eos_id, eos_bias);
                         }
                         f.take<VEC, true>(v[u], ok);
                     }
@@ -958,7 +953,7 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
     }
     if (token < 0) {
         token = last_pos >= 0 ? last_pos : max(0, je - 1);
-        tok_x = x[token] * inv_t + (token == eos_id ? eos_bias : 0.f);
+        tok_x = scale_logit(x[token], token, inv_t, eos_id, eos_bias);
     }
     if (lane == 0) {
         tokens_out[row] = token;
@@ -1018,7 +1013,9 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE) void logprob_kernel(const float
     for (int base = tid * VEC; base < vocab; base += SAMPLE_WAVES * WAVE * VEC) {
         float v[VEC];
         bool ok[VEC];
-        load_scaled<VEC>(x, base, vocab, inv_t, -1, 0.f, v, ok, Nucleus{false, 0u, 0, 0.f});
+        load_raw<VEC>(x, base, vocab, v, ok);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) v[c] *= inv_t;
         float lm = -INFINITY;
 #pragma unroll
         for (int c = 0; c < VEC; ++c)

@@ -1,7 +1,6 @@
 """The sampler's kernel source (csrc/sampler.hip) run on the CPU, a workgroup of 1024 fibers at a time (host/simt.h): every access to LDS
 is recorded, and two waves that touch a word without a barrier in between fail the test, whatever the result was.  The waves run one
 after the other from barrier to barrier, in several orders, so that what no barrier orders really happens out of order.  Needs g++, no GPU."""
-import math
 import os
 import shutil
 import subprocess
@@ -112,3 +111,20 @@ def test_no_races_between_waves_and_the_oracles_tokens(program, form, V, top_p, 
         u = philox.sampling_uniform(5, 51 + i, 1)
         want, wlp = sampler.sample_token(x[i] * np.float32(1.0 / np.float32(T)), 1.0, u, eos, bias, top_p=top_p)
         assert tok[i] == want and abs(lp[i] - wlp) <= 3e-5 * max(1.0, abs(wlp))
+
+
+@pytest.mark.parametrize("V", [4100, 2051])
+def test_one_rounding_of_the_biased_logit_on_every_way(program, V):
+    # Nothing but the cut distinguishes the nucleus from plain sampling with the other tokens masked: the same bits, also where the EOS id has
+    # the largest logit and is drawn.
+    rng = np.random.default_rng(V)
+    x = rng.standard_normal((8, V)).astype(np.float32)
+    T, top_p, eos, bias = 0.7, 0.9, V // 3, 0.3
+    x[:, eos] = 6.0 + rng.random(8).astype(np.float32)
+    tok, lp = _run(program, x, T, top_p, 5, 2, eos, bias, 0)
+    y = x.astype(np.float64) / T
+    y[:, eos] += bias
+    w = np.exp(y - y.max(1, keepdims=True))
+    keep = np.stack([sampler.nucleus(r, top_p) for r in w])
+    want = _run(program, np.where(keep, x, -np.inf).astype(np.float32), T, 1.0, 5, 2, eos, bias, 0)
+    assert (tok, lp) == want and eos in tok
