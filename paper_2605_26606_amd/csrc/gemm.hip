@@ -1155,17 +1155,30 @@ static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N,
 
 }  // namespace pc
 
+// For tests, not part of the C ABI: a projection of 16-bit operands in the tile that the library chooses, W in slabs or in plain rows.  The
+// number of K slices, 1: the result is in C; 0: not such a call.
+extern "C" int pc_internal_gemm(int dtype, int epi, const void *A, const void *W, int slabs, void *C, int M, int N, int K, float *slices,
+                                size_t slice_cap_floats, uint32_t *sat, void *stream) {
+    using namespace pc;
+    if ((dtype != KD_BF16 && dtype != KD_F16) || (epi != EPI_STORE_F32 && epi != EPI_RESID_F32 && epi != EPI_SWIGLU) || !A || !W || !C || M <= 0 ||
+        N <= 0 || N % 64 != 0 || K <= 0 || K % 64 != 0 || (((uintptr_t)A | (uintptr_t)W | (uintptr_t)C | (uintptr_t)slices) & 15) != 0)
+        return 0;
+    gemm_init();
+    return launch_gemm(dtype, 1, A, WeightRef(W, slabs ? WEIGHT_SLAB : 0), C, M, N, K, epi, slices, slice_cap_floats, sat, (hipStream_t)stream, nullptr);
+}
 // For tests, not part of the C ABI: the QkvRoute of a q/k/v projection of more than 512 rows, and one launch in the tile of a
-// route (`extra`: a GemmQkv).  1: launched; 0: not a tile of this file, or not a call that the kernels take.
+// route (`slabs`: W is in the order of the 16-bit copies; `extra`: a GemmQkv).  1: launched; 0: not a tile of this file, or not a call that
+// the kernels take.
 extern "C" int pc_internal_qkv_route(int M, int N, int K) { return pc::qkv_route(M, N, K); }
-extern "C" int pc_internal_gemm_qkv(int dtype, int route, const void *A, const void *W, int M, int N, int K, const void *extra, uint32_t *sat,
-                                    void *stream) {
+extern "C" int pc_internal_gemm_qkv(int dtype, int route, const void *A, const void *W, int slabs, int M, int N, int K, const void *extra,
+                                    uint32_t *sat, void *stream) {
     using namespace pc;
     if ((dtype != KD_BF16 && dtype != KD_F16) || route <= QKV_SEPARATE || route >= QKV_LARGE || !A || !W || !extra || M <= 0 || N <= 0 ||
         N % 128 != 0 || K <= 0 || K % 64 != 0 || (((uintptr_t)A | (uintptr_t)W) & 15) != 0)
         return 0;
+    const WeightRef w(W, slabs ? WEIGHT_SLAB : 0);
     gemm_init();
-    if (dtype == KD_BF16) gemm_qkv_t<bf16_t>((QkvRoute)route, A, W, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
-    else gemm_qkv_t<f16_t>((QkvRoute)route, A, W, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
+    if (dtype == KD_BF16) gemm_qkv_t<bf16_t>((QkvRoute)route, A, w, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
+    else gemm_qkv_t<f16_t>((QkvRoute)route, A, w, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
     return 1;
 }

@@ -799,21 +799,23 @@ int launch_gemm_large_logprob(int dtype, const void *A, WeightRef W, int M, int 
 
 }   // namespace pc
 
-// For tests and tuning, not part of the C ABI: one launch in the tile of bm rows x bn columns (`extra`: the GemmRowScale, GemmQkv
-// or GemmLogprob of such an epilogue).  1: launched; 0: no such tile with this epilogue, or not a call that the kernels take.
-extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int slices, const void *A, const void *W, void *C, int M, int N,
-                                      int K, const void *extra, uint32_t *sat, void *stream) {
+// For tests and tuning, not part of the C ABI: one launch in the tile of bm rows x bn columns (`slabs`: W is in the order of the 16-bit
+// copies; `extra`: the GemmRowScale, GemmQkv or GemmLogprob of such an epilogue).  1: launched; 0: no such tile with this epilogue, or not a
+// call that the kernels take.
+extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int slices, const void *A, const void *W, int slabs, void *C, int M,
+                                      int N, int K, const void *extra, uint32_t *sat, void *stream) {
     using namespace pc;
     const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS, own = epi == EPI_SWIGLU_RS || epi == EPI_QKV || epi == EPI_LOGPROB;
+    const WeightRef w(W, slabs ? WEIGHT_SLAB : 0);
     for (int id = 0; id < LT_COUNT; ++id) {
         if (LARGE_SHAPES[id][0] != bm || LARGE_SHAPES[id][1] != bn || epi < 0 || !(large_tiles(epi) >> id & 1)) continue;
         if ((dtype != KD_BF16 && dtype != KD_F16) || !A || !W || (!C && epi != EPI_QKV && epi != EPI_LOGPROB) || (own && !extra) || M <= 0 ||
-            N <= 0 || !large_ok(A, W, C, M, N, K, epi) || (swiglu && N % 64 != 0) || (epi == EPI_QKV && N % 128 != 0) || slices < 1 ||
-            (slices > 1 && epi != EPI_STORE_F32) || !large_slices_ok(slices, K))
+            N <= 0 || (slabs && !weight_lg(dtype, N, K)) || !large_ok(A, w, C, M, N, K, epi) || (swiglu && N % 64 != 0) ||
+            (epi == EPI_QKV && N % 128 != 0) || slices < 1 || (slices > 1 && epi != EPI_STORE_F32) || !large_slices_ok(slices, K))
             return 0;
         gemm_large_init();
-        if (dtype == KD_BF16) Large<bf16_t>::named(id, epi, A, W, C, M, N, K, slices, extra, sat, (hipStream_t)stream);
-        else Large<f16_t>::named(id, epi, A, W, C, M, N, K, slices, extra, sat, (hipStream_t)stream);
+        if (dtype == KD_BF16) Large<bf16_t>::named(id, epi, A, w, C, M, N, K, slices, extra, sat, (hipStream_t)stream);
+        else Large<f16_t>::named(id, epi, A, w, C, M, N, K, slices, extra, sat, (hipStream_t)stream);
         return 1;
     }
     return 0;

@@ -155,11 +155,12 @@ static int run_gemm(const char *name, int M, int N, int K, int epi, int split, s
     CK(hipEventCreate(&e0));
     CK(hipEventCreate(&e1));
     const int ring = (int)Ws.size();
-    for (int i = 0; i < 3; ++i) Cfg::run(A, Ws[i % ring], split > 1 ? (void *)slices : C, M, N, K, epi, split, nullptr, 0);
+    const int lg = weight_lg(KD_F16, N, K);   // (the order of a model's copies; the values are the same everywhere)
+    for (int i = 0; i < 3; ++i) Cfg::run(A, {Ws[i % ring], lg}, split > 1 ? (void *)slices : C, M, N, K, epi, split, nullptr, 0);
     CK(hipDeviceSynchronize());
     const int iters = 24;
     CK(hipEventRecord(e0, 0));
-    for (int i = 0; i < iters; ++i) Cfg::run(A, Ws[i % ring], split > 1 ? (void *)slices : C, M, N, K, epi, split, nullptr, 0);
+    for (int i = 0; i < iters; ++i) Cfg::run(A, {Ws[i % ring], lg}, split > 1 ? (void *)slices : C, M, N, K, epi, split, nullptr, 0);
     CK(hipEventRecord(e1, 0));
     CK(hipEventSynchronize(e1));
     float ms;
@@ -173,7 +174,7 @@ static int run_gemm(const char *name, int M, int N, int K, int epi, int split, s
 // the tile that the library's own dispatch picks
 struct Dispatched {
     static void init() { gemm_init(); }
-    static void run(const void *A, const void *W, void *C, int M, int N, int K, int epi, int, uint32_t *sat, hipStream_t s) {
+    static void run(const void *A, WeightRef W, void *C, int M, int N, int K, int epi, int, uint32_t *sat, hipStream_t s) {
         launch_gemm(KD_F16, 1, A, W, C, M, N, K, epi, nullptr, 0, sat, s);
     }
 };
@@ -297,7 +298,8 @@ static int bench_tiles(int n_only, char **only) {
                 const size_t strips = ((size_t)l.N + 255) / 256 * 4;
                 float *maxima = (float *)(C + strips * M * 8);
                 const GemmLogprob lp{1.0f, d_token, d_id, maxima, maxima + strips * M, (double *)C};
-                auto run = [&](const Form &f, const char *w) {
+                auto run = [&](const Form &f, const char *rows) {
+                    const WeightRef w(rows, weight_lg(KD_F16, l.N, l.K));   // the order of a model's copies
                     if (l.epi == EPI_QKV) {
                         GemmQkv a = q;
                         a.kv = kv;

@@ -200,7 +200,7 @@ struct GemmQkv {
 struct WeightRef {
     const void *p;
     int lg;
-    WeightRef(const void *p, int lg = 0) : p(p), lg(lg) {}
+    WeightRef(const void *p, int lg) : p(p), lg(lg) {}   // (no default: plain rows are the exception)
 };
 // 16-bit copies lie in slabs where the matrix is made of whole ones; lm_heads read in place and fp32 models have plain rows.
 inline int weight_lg(int kd, int64_t N, int64_t K) { return kd != KD_F32 && N % 32 == 0 && K % 64 == 0 ? WEIGHT_SLAB : 0; }
