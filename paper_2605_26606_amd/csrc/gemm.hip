@@ -900,8 +900,10 @@ static int large_min_k(bool swiglu) { return swiglu ? 128 : 256; }   // the shor
 //   128 x 64   1024 x 1536 x 1536  20.7 / 14.1, 18.4 / 12.1 (64 x 64: 20.1 / 12.0);  768 x 2560 x 2048  23.0 / 17.1, 21.9 / 15.1;
 //              2000 x 1024 x 1536  21.0 / 15.7, 18.6 / 13.6;  1024 x 2048 x 2048  22.8 / 18.1, 22.4 / 16.5
 // Longer reductions are faster in slices of larger tiles: 1024 x 1536 x 3072  23.9 / 18.5, 26.2 / 18.8.
-static bool resid_small_tiles(int M, int N, int K, int epi) {
-    return epi == EPI_RESID_F32 && K >= 256 && K <= 2048 && (int64_t)((M + 127) / 128) * ((N + 63) / 64) <= 256;
+enum ResidTile { RESID_LARGE, RESID_64x64, RESID_128x64 };
+static ResidTile resid_tile(int M, int N, int K, int epi) {
+    if (epi != EPI_RESID_F32 || K < 256 || K > 2048 || (int64_t)((M + 127) / 128) * ((N + 63) / 64) > 256) return RESID_LARGE;
+    return (int64_t)((M + 63) / 64) * ((N + 63) / 64) <= 320 ? RESID_64x64 : RESID_128x64;
 }
 
 int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M, int N, int K, int epi,
@@ -928,7 +930,7 @@ int launch_gemm(int dtype, int impl, const void *A, WeightRef W, void *C, int M,
     // against 10.3, K = 384 8.9 against 8.4; 384 x 65552 fp32, K = 128 28.2 against 31.8, K = 256 37.5 against 34.5.
     const int nb128 = (N + 127) / 128;
     const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS;
-    const bool large = M > 512   ? K >= large_min_k(swiglu) && !resid_small_tiles(M, N, K, epi)
+    const bool large = M > 512   ? K >= large_min_k(swiglu) && resid_tile(M, N, K, epi) == RESID_LARGE
                        : swiglu  ? M > 384 && K >= 384
                                  : (M > 384 && nb128 >= 96) ||
                                        (M > 192 && nb128 >= 512 && epi == EPI_STORE_F32 && K >= 256 && (M > 256 || K <= 4096));
@@ -1078,7 +1080,8 @@ static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N,
         return split;
     };
     if (M > 512) {
-        if (resid_small_tiles(M, N, K, epi)) return (int64_t)((M + 63) / 64) * ((N + 63) / 64) <= 320 ? whole(typename G::T64x64()) : whole(typename G::T128x64_3());
+        const ResidTile resid = resid_tile(M, N, K, epi);
+        if (resid != RESID_LARGE) return resid == RESID_64x64 ? whole(typename G::T64x64()) : whole(typename G::T128x64_3());
         if (K >= large_min_k(swiglu)) return whole(typename G::T256x128());   // (gate/up that gemm_large.hip left to this tile; widths beyond its limit)
         // 256 x 256 tiles where they still come in several rounds per CU, 256 x 128 below that
         if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) return whole(typename G::T256x256());
@@ -1166,9 +1169,10 @@ extern "C" int pc_internal_gemm(int dtype, int epi, const void *A, const void *W
     gemm_init();
     return launch_gemm(dtype, 1, A, WeightRef(W, slabs ? WEIGHT_SLAB : 0), C, M, N, K, epi, slices, slice_cap_floats, sat, (hipStream_t)stream, nullptr);
 }
-// For tests, not part of the C ABI: the QkvRoute of a q/k/v projection of more than 512 rows, and one launch in the tile of a
-// route (`slabs`: W is in the order of the 16-bit copies; `extra`: a GemmQkv).  1: launched; 0: not a tile of this file, or not a call that
+// For tests, not part of the C ABI: the ResidTile of a residual projection and the QkvRoute of a q/k/v projection of more than 512 rows, and
+// one launch in the tile of a q/k/v route (`slabs`: W is in the order of the 16-bit copies; `extra`: a GemmQkv).  1: launched; 0: not a tile of this file, or not a call that
 // the kernels take.
+extern "C" int pc_internal_resid_tile(int M, int N, int K) { return pc::resid_tile(M, N, K, pc::EPI_RESID_F32); }
 extern "C" int pc_internal_qkv_route(int M, int N, int K) { return pc::qkv_route(M, N, K); }
 extern "C" int pc_internal_gemm_qkv(int dtype, int route, const void *A, const void *W, int slabs, int M, int N, int K, const void *extra,
                                     uint32_t *sat, void *stream) {

@@ -293,6 +293,11 @@ static int bench_tiles(int n_only, char **only) {
                     forms.push_back({"m128x128", 101, 1, 1e9});
                 }
                 if (l.epi == EPI_QKV || l.epi == EPI_SWIGLU) forms.push_back({"m256x128", 102, 1, 1e9});
+                if (l.epi == EPI_RESID_F32 && l.K <= 3072) {   // (blocks that run in two rounds at most)
+                    auto blocks = [&](int bm) { return (int64_t)((M + bm - 1) / bm) * ((l.N + 63) / 64); };
+                    if (blocks(64) <= 1024) forms.push_back({"m64x64", 103, 1, 1e9});
+                    if (blocks(128) <= 512) forms.push_back({"m128x64", 104, 1, 1e9});
+                }
                 const GemmQkv q{decode ? d_seq : d_prompt, decode ? nullptr : d_in, d_len, table_f, table_f, kv, 0, l.hq, out};
                 kv.n_kv_heads = l.hkv;
                 const size_t strips = ((size_t)l.N + 255) / 256 * 4;
@@ -307,6 +312,10 @@ static int bench_tiles(int n_only, char **only) {
                         else if (f.tile == 101) G::T128x128::launch<EPI_QKV>(A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
                         else if (f.tile == 102) G::T256x128::launch<EPI_QKV>(A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
                         else L::launch<EPI_QKV>(f.tile, A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
+                    } else if (f.tile == 103) {
+                        G::T64x64::launch<EPI_RESID_F32>(A, w, C, M, l.N, l.K, 1, nullptr, 0, {});
+                    } else if (f.tile == 104) {
+                        G::T128x64_3::launch<EPI_RESID_F32>(A, w, C, M, l.N, l.K, 1, nullptr, 0, {});
                     } else if (f.tile == 102) {
                         G::T256x128::launch<EPI_SWIGLU>(A, w, out, M, l.N, l.K, 1, nullptr, 0, {});
                     } else if (l.epi == EPI_LOGPROB) {
