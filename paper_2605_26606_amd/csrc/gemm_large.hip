@@ -614,11 +614,12 @@ template <typename T, int TMH, int TNH> struct LargeCfg {
 // each further tile of a block cost beside their steps, plus the fp32 results' way to the kernel that reads them.  A step takes
 // longer the more CUs are busy (`load`: the clock falls under the matrix cores' power, 2.0 PFLOP/s on operands of zeros and 1.45 on
 // random ones).  The constants are a least-squares fit, then moved a little for least regret, to the times of 1094 launches of 513 to
-// 16384 rows x 512 to 151936 columns x 128 to 17408, each in every tile and up to 8 slices, with weights in plain rows.  Held against
-// the times on weights in slabs and, for residual projections, with the eight-wave tiles among the forms (profiles/large_tile_times.txt, taken by
-// kernel_bench tiles; tests/test_tile_choice.py) what runs takes 1.0 % longer on average than the fastest form, 12 % at worst from K = 1024 up
-// (q/k/v of 8192 x 1536 x 1024, 46.7 us for 41.7) and 39 % below (16384 x 2368 x 256, 33 us for 24).  (One set of constants for all epilogues, fitted without the norm that reads the slices and to K of 1536 and more, was up to 28 % off there and
-// 60 % below: 640 rows x 2560 x 9728 58.2 us for 44.5.)
+// 16384 rows x 512 to 151936 columns x 128 to 17408, each in every tile and up to 8 slices, with weights in plain rows whose values repeated (and let
+// the clock rise).  Held against times on mixed values in slabs and, for residual projections, with the eight-wave tiles among the forms
+// (profiles/large_tile_times.txt, taken by kernel_bench tiles; tests/test_tile_choice.py) what runs takes 1.0 % longer on average than the
+// fastest form, 9 % at worst from K = 1024 up (640 x 24576 x 4096, 138 us for 126) and 31 % below (16384 x 2368 x 256, 35 us for 27).  (One
+// set of constants for all epilogues, fitted without the norm that reads the slices and to K of 1536 and more, was up to 28 % off there
+// and 60 % below: 640 rows x 2560 x 9728 58.2 us for 44.5.)
 struct LargeTime {
     double step, load, first, next;
 };

@@ -38,7 +38,13 @@ using namespace pc;
 __global__ void fill_half_kernel(uint16_t *p, size_t n, uint32_t seed) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) {
-        uint32_t h = (uint32_t)(i * 2654435761u) ^ seed;
+        // (well mixed: of values that repeat every 1024, as a product alone gives them, fewer bits change from one product to the next, the
+        // matrix cores draw less power and the chip holds a higher clock, by an amount that depends on the order of the weights)
+        uint32_t h = (uint32_t)i ^ seed;
+        for (int r = 0; r < 3; ++r) {
+            h *= 2654435761u;
+            h ^= h >> 15;
+        }
         p[i] = 0x2800 | (h & 0x3FF) | ((h >> 3) & 0x8000);   // +-(0.03 .. 0.06) as IEEE half
     }
 }

@@ -42,7 +42,7 @@ def _chosen(lib, kind, m, n, k, mode):
 def test_the_choice_is_near_the_best_of_the_measured_forms(kind, name):
     # Bounds: two runs of one form differ by up to 4 %, on other cards the clocks under load differ as well; a wrong number of rounds
     # or slices costs 15 to 60 %.  Below K = 1024 a launch's time is its stores, of which the estimate knows nothing: there the worst
-    # choice is 39 % behind the best form (and still ahead of the eight-wave kernel that it would go to otherwise).
+    # choice is 31 % behind the best form (and still ahead of the eight-wave kernel that it would go to otherwise).
     from paper_2605_26606_amd import binding
     lib = binding.library()
     regret = []
