@@ -111,8 +111,8 @@ typedef struct {
                                   RMSNorm's inputs; that norm's scale applied by the gate/up epilogue): six launches per
                                   layer instead of eight; larger models keep one kernel per operation, which is faster
                                   there.  fp32 models: the layer's two RMSNorms run inside the projections behind
-                                  them, in prefill, scoring and decode alike (default 1; 0 keeps one kernel per operation
-                                  everywhere) */
+                                  them, in prefill, scoring and decode alike, and a decode step's last norm inside the
+                                  vocabulary projection (default 1; 0 keeps one kernel per operation everywhere) */
 #define PC_OPT_TIME_NEXT_STEP 3 /* value = a PC_KERNEL_* class: the next pc_decode_step runs eagerly (no graph)
                                    with a HIP event pair around every launch of that class; -1 disarms */
 

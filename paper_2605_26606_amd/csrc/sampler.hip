@@ -88,9 +88,11 @@ __device__ inline float wave_max_all(float v) {
     fold(std::integral_constant<int, 0x143>{});
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), WAVE - 1));
 }
-// exp(d) for -103 <= d <= 0, to the bit what expf gives (a test compares the two): log2(e) in two pieces, whole
-// powers of two apart.  expf also asks whether the result under- or overflows, four of its fourteen instructions; the passes over a
-// row are bound by them as much as by memory.
+// exp(d) for -103 <= d <= 0 as 2^(d log2 e), with Cody and Waite's two-piece constant: log2 e is a float and the float nearest to what that one
+// leaves; the product with the first is split exactly into its rounded value and the rest of it (fma), the nearest whole number goes into the
+// exponent, and what is left, at most 1/2 and a little, is the argument of the hardware's 2^x.  To the bit what expf gives (a test compares
+// the two).  expf also asks whether the result under- or overflows, four of its fourteen instructions; the passes over a row are bound by
+// them as much as by memory.
 __device__ inline float exp_weight_near(float d) {
 #pragma clang fp contract(off)
     const float hi = d * 0x1.715476p+0f;
@@ -184,7 +186,7 @@ __device__ inline void load_scaled(const float *__restrict__ x, int idx, int end
 
 __device__ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
-    // The fold of one lane: m the maximum, ref the same, or 0 while all tokens so far are masked (no weight); s the sum of
+// The fold of one lane: m the maximum, ref the same, or 0 while all tokens so far are masked (no weight); s the sum of
 // weights relative to ref.  A masked token counts as minus infinity.
 struct Fold {
     float m = -INFINITY, ref = 0.f;
@@ -213,7 +215,8 @@ struct Fold {
 // ---- the binned way to the nucleus
 static constexpr int NUC_BINS = 4096;          // four per thread
 static constexpr float NUC_PER_UNIT = 32.0f;   // bins per unit of scaled logit
-static constexpr int NUC_LIST = 5120;          // tokens of the crossing bin that fit the list (72 KB in all: two blocks per CU)
+static constexpr int NUC_LIST = 5120;          // tokens of the crossing bin that fit the list (with the bins 72 KB, 78.6 of the kernel's all: two blocks
+                                               // fit the 160 KB of a CU)
 static constexpr int NUC_COUNT_SHIFT = 44;     // a bin: count above, sum of weights as integers below (2^18 tokens fit either)
 static constexpr int NUC_GRANULE = 256;        // tokens of a wave's segment whose maximum is kept, so that later passes skip them
 static constexpr int NUC_GRANULES = 64;        // per wave
@@ -330,9 +333,9 @@ __device__ inline bool next_granules(unsigned long long &mask, const float *__re
 }
 
 // The cut at mass `want` = top_p Z of a row with maximum M and sum Z: kstar and the number of its ties to keep (-1: all), and
-// which granules of the wave's segment [b, e) have a token that may be kept.  The bins hold the row's tokens above `filed`
-// unless they cannot (see below).  False: not found this way, nothing is left behind (the caller's arithmetic decides either way,
-// see the end of pass 2).
+// which granules of the wave's segment [b, e) have a token that may be kept.  The bins hold the tokens within `reach` of M, some of those
+// further down, and none at or below `filed`, so that their ring has not gone round if M is not too far above that (else see below).
+// False: not found this way, nothing is left behind (the caller's arithmetic decides either way, see the end of pass 2).
 template <int VEC>
 __device__ inline bool nucleus_binned(const float *__restrict__ x, int vocab, int b, int e, float inv_t, float top_p, int eos_id,
                                       float eos_bias, float eos_key_add, float M, double Z, double want, float filed, float reach,
@@ -582,7 +585,9 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
         // them together, and need no bin.  Z is at least the largest weight, and the largest logit at least the largest
         // seen so far, by any wave: the first stride of every segment is looked at ahead, the rest is published as it comes.
         const float reach = 1.0f - logf(0.5f * (1.0f - top_p) / (float)vocab);
-        float filed = -INFINITY;   // every token whose scaled logit is above this is in a bin
+        // No token whose scaled logit is at or below this is in a bin.  Those above it are if they were within reach of the largest logit
+        // seen when their turn came; the others lie behind the cut.
+        float filed = -INFINITY;
         {
             constexpr int BLOCK = SAMPLE_WAVES * WAVE;
             const float per_logit = NUC_PER_UNIT * inv_t;
