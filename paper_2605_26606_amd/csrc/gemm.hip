@@ -398,6 +398,20 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
         for (int jj = 0; jj < TN; ++jj)
 #pragma unroll
             for (int v = 0; v < AV; ++v) acc[i][jj][v] = 0.f;
+    // sums of the K slices behind the block, the current one's is in acc
+    constexpr bool SLICES = EPI == EPI_RESID_SLICES;
+    [[maybe_unused]] acc_t front[SLICES ? TM : 1][SLICES ? TN : 1] = {};
+    auto end_slice = [&]() {
+        if constexpr (SLICES) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int jj = 0; jj < TN; ++jj) {
+                    front[i][jj] += acc[i][jj];
+                    acc[i][jj] = acc_t{};
+                }
+        }
+    };
 
     // fragment addressing: lane (fr, fg) reads chunk CG*kk + fg of its row, stored at slot chunk ^ swz(row)
     const int fr = lane % RT, fg = lane / RT;
@@ -537,7 +551,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     }
     int stage = 0;
     if constexpr (KK % 2 == 0) {   // an even number of steps per tile: the two fragment sets alternate within a tile
+        int slice_end = kt1;
+        if constexpr (SLICES) slice_end = kt0 + extra.per;
         for (int kt = kt0; kt < kt1; ++kt) {
+            if constexpr (SLICES)
+                if (kt == slice_end) {
+                    end_slice();
+                    slice_end += extra.per;
+                }
 #pragma unroll
             for (int kk = 0; kk < KK; kk += 2) {
                 kstep(fa[0], fb[0], fa[1], fb[1], kt, stage, kk);
@@ -545,7 +566,16 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
             }
             stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
         }
+        if constexpr (SLICES)
+            if (kt0 + extra.per < kt1) {
+                end_slice();
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int jj = 0; jj < TN; ++jj) acc[i][jj] = front[i][jj];
+            }
     } else {                       // one step per tile: they alternate from tile to tile
+        static_assert(!SLICES, "ends of slices");
         static_assert(KK == 1 || KK % 2 == 0, "steps per tile");
         int kt = kt0;
         for (; kt + 1 < kt1; kt += 2) {
@@ -699,7 +729,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
     // fifth of the decode gate/up kernel).  Instead each wave turns RT output rows at a time into whole rows through
     // a private piece of the now idle LDS ring and stores them 16 bytes per lane, neighbouring lanes on
     // neighbouring addresses.  LDS instructions of one wave execute in order, so the hand-over needs no barrier.
-    typedef typename std::conditional<(EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32), float, T>::type OutT;
+    typedef typename std::conditional<(EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32 || SLICES), float, T>::type OutT;
     constexpr int WCOLS = SWIGLU ? (BN / WN) / 2 : BN / WN;        // output columns of one wave
     constexpr int RB = WCOLS * (int)sizeof(OutT);                 // bytes of one output row of the wave
     constexpr int LPR = RB / 16;                                  // 16-byte pieces of one row
@@ -767,7 +797,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const T *__rest
             const int gm = m0 + wm * (BM / WM) + i * RT + row, col = colbase + piece * EPC;
             if (gm < M && col < ldc) {
                 OutT *dst = Cbase + (int64_t)gm * ldc + col;
-                if constexpr (EPI == EPI_RESID_F32) {
+                if constexpr (EPI == EPI_RESID_F32 || SLICES) {
                     const f32x4_t old = *(const f32x4_t *)dst, add = __builtin_bit_cast(f32x4_t, val);
                     *(f32x4_t *)dst = (f32x4_t){old[0] + add[0], old[1] + add[1], old[2] + add[2], old[3] + add[3]};
                 } else {
@@ -867,9 +897,11 @@ template <typename T> struct Gemm {
     static void init() {
         T256x128::init(); T256x192::init(); T256x256::init(); T192x128::init(); T192x192::init(); T128x128::init();
         T128x128_2::init(); T128x192::init(); T64x128::init(); T64x192::init(); T32x64::init();
-        T32x64_2::init(); T64x64::init(); T128x64_3::init(); T128x64::init(); T192x64::init(); M64x64::init();
+        T32x64_2::init(); T128x64::init(); T192x64::init(); M64x64::init();
         T256x160::template set_attr<EPI_SWIGLU>();       // (gate/up only)
         T256x160::template set_attr<EPI_SWIGLU_RS>();
+        T64x64::template set_attr<EPI_RESID_SLICES>();
+        T128x64_3::template set_attr<EPI_RESID_SLICES>();
         T256x256::init_logprob();
         T256x128::init_logprob();
         T192x128::init_logprob();
@@ -893,7 +925,9 @@ static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N,
 static int large_min_k(bool swiglu) { return swiglu ? 128 : 256; }   // the shortest reduction that gemm_large.hip gets above 512 rows
 
 // Residual projections of more than 512 rows whose blocks of 128 x 64 all run at once, one per CU: eight waves with little to do each
-// and the whole reduction in one block, no slices for the norm behind to add up.  In 64 x 64 while there are no more than 320 of those
+// and the whole reduction in one block, no slices for the norm behind to add up.  A block forms the sums of the slices that
+// gemm_large.hip would cut and adds them in their order: the same bits (summed in one go, the logits of 1024 rows of the 1.5B shape, four
+// layers, are 5.5e-4 of their size away, through the roundings to half that follow, and as far from 64-bit ones).  In 64 x 64 while there are no more than 320 of those
 // (two fit a CU).  With that norm, us alone and as one of three streams, the best of gemm_large.hip's tiles and slices against these:
 //   64 x 64    600 rows x 1536 x 1536  17.8 / 10.8, 13.7 / 8.5;  600 x 1024 x 2048  16.1 / 9.9, 14.4 / 7.8;  1024 x 512 x 256  10.5 / 6.2, 7.8 / 6.2
 //              2000 x 512 x 2048  18.1 / 12.1, 16.7 / 10.3;  600 x 2048 x 1536 (320 blocks)  19.6 / 12.2, 16.7 / 9.9 (128 x 64: 17.8 / 10.4)
@@ -1081,7 +1115,13 @@ static int gemm_mfma_dispatch(const void *A, WeightRef W, void *C, int M, int N,
     };
     if (M > 512) {
         const ResidTile resid = resid_tile(M, N, K, epi);
-        if (resid != RESID_LARGE) return resid == RESID_64x64 ? whole(typename G::T64x64()) : whole(typename G::T128x64_3());
+        if (resid != RESID_LARGE) {
+            const int S = gemm_large_resid_slices(M, N, K, slices, slice_cap_floats);
+            const GemmSlices sums{(K / 64 + S - 1) / S};
+            if (resid == RESID_64x64) G::T64x64::template launch<EPI_RESID_SLICES>(A, W, C, M, N, K, 1, sat, s, sums);
+            else G::T128x64_3::template launch<EPI_RESID_SLICES>(A, W, C, M, N, K, 1, sat, s, sums);
+            return 1;
+        }
         if (K >= large_min_k(swiglu)) return whole(typename G::T256x128());   // (gate/up that gemm_large.hip left to this tile; widths beyond its limit)
         // 256 x 256 tiles where they still come in several rounds per CU, 256 x 128 below that
         if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 2 * 256) return whole(typename G::T256x256());

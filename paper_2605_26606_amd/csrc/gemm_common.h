@@ -53,12 +53,14 @@ template <int EPI> struct GemmExtra { typedef NoExtra type; };
 template <> struct GemmExtra<EPI_SWIGLU_RS> { typedef GemmRowScale type; };
 template <> struct GemmExtra<EPI_LOGPROB> { typedef GemmLogprob type; };
 template <> struct GemmExtra<EPI_QKV> { typedef GemmQkv type; };
+template <> struct GemmExtra<EPI_RESID_SLICES> { typedef GemmSlices type; };
 
 // gemm_large.hip: large batches.  Each launches nothing and says so (0, false) if it does not take the call, or if the 256 x 128
 // tile of gemm.hip is the faster one for it.
 void gemm_large_init();   // once per device, like gemm_init
 int launch_gemm_large(int dtype, const void *A, WeightRef W, void *C, int M, int N, int K, int epi, float *slices, size_t slice_cap,
                       uint32_t *sat, hipStream_t s, const GemmRowScale *row_scale);   // the number of K slices, as launch_gemm
+int gemm_large_resid_slices(int M, int N, int K, const float *slices, size_t slice_cap);   // how many it would cut such a launch into
 bool launch_gemm_large_qkv(int dtype, const void *A, WeightRef W, int M, int N, int K, const GemmQkv &q, uint32_t *sat, hipStream_t s);
 int launch_gemm_large_logprob(int dtype, const void *A, WeightRef W, int M, int N, int K, const GemmLogprob &lp,
                               hipStream_t s);          // the number of column strips

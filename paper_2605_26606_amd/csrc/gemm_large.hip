@@ -684,6 +684,17 @@ static int large_pick(int max_slices, int M, int N, int K, int epi, int *S, bool
     return best;
 }
 
+// The tile and the slices of a projection whose consumer adds up the latter, if there is room for them.
+static int large_pick_sliced(int M, int N, int K, int epi, const float *slices, size_t slice_cap, int *S) {
+    const int max_slices = slices ? (int)std::min<size_t>(8, slice_cap / ((size_t)M * N)) : 1;
+    return large_pick(std::max(1, max_slices), M, N, K, epi, S, false, epi == EPI_RESID_F32 || slices);
+}
+int gemm_large_resid_slices(int M, int N, int K, const float *slices, size_t slice_cap) {
+    int S = 1;
+    (void)large_pick_sliced(M, N, K, EPI_RESID_F32, slices, slice_cap, &S);
+    return S;
+}
+
 static bool large_ok(const void *A, WeightRef W, const void *C, int M, int N, int K, int epi) {
     // (two steps of K at least, the ring reaches that far ahead; rows of operands and results in whole 16-byte pieces, but fp32
     // results may start at any float: the logits are the caller's; a tile's bytes within a buffer descriptor's 32 bits)
@@ -740,8 +751,7 @@ template <typename T> struct Large {
             launch<EPI_STORE_F32>(M <= 256 ? LT_256x128 : (M <= 384 ? LT_192x256 : LT_256x256), A, W, C, M, N, K, 1, sat, s, {});
             return 1;
         }
-        const int max_slices = slices ? (int)std::min<size_t>(8, slice_cap / ((size_t)M * N)) : 1;
-        const int id = large_pick(std::max(1, max_slices), M, N, K, epi, &S, false, epi == EPI_RESID_F32 || slices);
+        const int id = large_pick_sliced(M, N, K, epi, slices, slice_cap, &S);
         if (S > 1) launch<EPI_STORE_F32>(id, A, W, slices, M, N, K, S, sat, s, {});
         else if (epi == EPI_RESID_F32) launch<EPI_RESID_F32>(id, A, W, C, M, N, K, 1, sat, s, {});
         else launch<EPI_STORE_F32>(id, A, W, C, M, N, K, 1, sat, s, {});

@@ -304,6 +304,8 @@ static int bench_tiles(int n_only, char **only) {
                     if (blocks(64) <= 1024) forms.push_back({"m64x64", 103, 1, 1e9});
                     if (blocks(128) <= 512) forms.push_back({"m128x64", 104, 1, 1e9});
                 }
+                const int slices_of = gemm_large_resid_slices(M, l.N, l.K, slices, SLICE_CAP);
+                const GemmSlices sums{(l.K / 64 + slices_of - 1) / slices_of};
                 const GemmQkv q{decode ? d_seq : d_prompt, decode ? nullptr : d_in, d_len, table_f, table_f, kv, 0, l.hq, out};
                 kv.n_kv_heads = l.hkv;
                 const size_t strips = ((size_t)l.N + 255) / 256 * 4;
@@ -319,9 +321,9 @@ static int bench_tiles(int n_only, char **only) {
                         else if (f.tile == 102) G::T256x128::launch<EPI_QKV>(A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
                         else L::launch<EPI_QKV>(f.tile, A, w, nullptr, M, l.N, l.K, 1, nullptr, 0, a);
                     } else if (f.tile == 103) {
-                        G::T64x64::launch<EPI_RESID_F32>(A, w, C, M, l.N, l.K, 1, nullptr, 0, {});
+                        G::T64x64::launch<EPI_RESID_SLICES>(A, w, C, M, l.N, l.K, 1, nullptr, 0, sums);
                     } else if (f.tile == 104) {
-                        G::T128x64_3::launch<EPI_RESID_F32>(A, w, C, M, l.N, l.K, 1, nullptr, 0, {});
+                        G::T128x64_3::launch<EPI_RESID_SLICES>(A, w, C, M, l.N, l.K, 1, nullptr, 0, sums);
                     } else if (f.tile == 102) {
                         G::T256x128::launch<EPI_SWIGLU>(A, w, out, M, l.N, l.K, 1, nullptr, 0, {});
                     } else if (l.epi == EPI_LOGPROB) {

@@ -169,6 +169,7 @@ enum Epilogue {
                          // of the scaled product, and the product at the row's target column (GemmLogprob)
     EPI_QKV = 6,         // the fused q | k | v projection: rotary positions applied to q and k, q written in the model dtype,
                          // k and v appended to the cache (GemmQkv; heads of 128, rows of W in the order of qkv_packed_dim)
+    EPI_RESID_SLICES = 7,   // EPI_RESID_F32 to the bits of a product cut into K slices that its consumer adds up (GemmSlices)
 };
 
 // Per-row RMSNorm statistics for EPI_SWIGLU_RS: ssq[t][row], t < tiles, are partial sums of squares of the row (as the fused output projection leaves them); scale = rsqrt(sum_t ssq / d + eps).
@@ -176,6 +177,11 @@ struct GemmRowScale {
     const float *ssq;
     int tiles, d;
     float eps;
+};
+
+// EPI_RESID_SLICES: K tiles of 64 to a slice; their sums are added in slice order, the total to the residual stream.
+struct GemmSlices {
+    int per;
 };
 
 // EPI_LOGPROB: part_max / part_sum [strip][M] hold max and sum of exp(x - max) of x = product * inv_t over the strip's columns;

@@ -394,3 +394,43 @@ def test_rotating_tiles(tile, act, decode, slabs):
             assert _launch_eight(act, route, a, w, extra, slabs)
             assert torch.equal(q, q_bits) and torch.equal(flat, kv_bits), route
             assert bool((whole[m:] == GUARD).all())
+
+
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+@pytest.mark.parametrize("m,n,k", [
+    (1024, 1536, 1536),     # 128 x 64 blocks
+    (577, 1600, 1536), (2000, 512, 2048), (513, 2048, 1472),       # 64 x 64 (23 steps of K: an uneven last slice)
+    (600, 512, 256),        # short: one sum
+])
+def test_residual_blocks_give_the_bits_of_the_slices_they_stand_for(m, n, k, act):
+    # The blocks of 64 rows that residual projections of some hundred rows run in, against the large tile and the K slices that they replace,
+    # added up as the norm behind does: the slices in order, their sum to the residual.  With and without room for slices.
+    from paper_2605_26606_amd import binding
+    lib = binding.library()
+    assert lib.pc_internal_resid_tile(m, n, k) > 0
+    f = lib.pc_internal_gemm
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int] * 2 + [ctypes.c_void_p] * 2 + [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_size_t] + \
+        [ctypes.c_void_p] * 2
+    a, w, exact, d = _operands(act, m, n, k, m + k)
+    old = torch.randn((m, n), device="cuda")
+    order, cut = _slabs(w), 0
+    for cap in (8 << 20, 0):
+        s = ctypes.c_int()
+        tile = lib.pc_internal_gemm_large_pick(RESID, 0, min(8, cap // (m * n)), m, n, k, ctypes.byref(s))
+        cut += s.value > 1
+        say("residual blocks, %s: %d x %d x %d, %d slices" % (act, m, n, k, s.value))
+        parts = torch.empty((s.value, m, n), device="cuda")
+        assert _launch(act, TILES[RESID][tile], STORE, a, w, parts, slices=s.value, slabs=True)
+        want = torch.zeros((m, n), device="cuda")
+        for part in parts:
+            want += part
+        want = old + want
+        whole, c = _guarded((m, n), torch.float32, old)
+        buffer = torch.empty(max(cap, 4), device="cuda")
+        assert f(TYPES[act][0], RESID, a.data_ptr(), order.data_ptr(), 1, c.data_ptr(), m, n, k, buffer.data_ptr() if cap else None, cap, None,
+                 torch.cuda.current_stream().cuda_stream) == 1
+        torch.cuda.synchronize()
+        assert torch.equal(c, want) and bool((whole[m:] == GUARD).all())
+        assert bool(((c.double() - exact - old.double()).abs() <= d + 2.0 ** -23 * want.abs()).all())
+    assert cut == (0 if k == 256 else 1)
