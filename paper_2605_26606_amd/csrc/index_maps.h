@@ -30,10 +30,11 @@ PC_HD inline int kv_v_index_frag(int tin, int d, int head_dim) {
 
 // ---- Weight matrices [N][K] of the 16-bit projections.  lg = 0: plain rows.  lg = WEIGHT_SLAB: slabs of 32 rows x 64 k (4 KB), a
 // row's 128 bytes behind the previous row's, the slabs of 32 rows one after another along K: the eight rows x 64 k that a
-// wave-wide load of the GEMMs takes are one contiguous kilobyte, the loads that follow it the same slab's and the next one's: a
-// decode step of 256 sequences x 28 layers of the 1.5B shape 31.65 -> 30.98 ms, 1024 sequences 17.93 -> 17.42, three 9.45 -> 9.20, 168
-// of the 14B shape in bfloat16 (whose lm_head stays in plain rows) 17.01 -> 16.81 ms, 8B steps and prefills as before; gate/up alone
-// 27.7 -> 25.2 us, the head 149 -> 142.
+// wave-wide load of the GEMMs takes are one contiguous kilobyte, the loads that follow it the same slab's and the next one's.  Both orders
+// timed in turn, several passes side by side: 16 decode steps of 256 sequences x 28 layers of the 1.5B shape 31.17 -> 30.14 ms, of 1024 x 4 layers 17.74
+// -> 17.19, 32 of three x 8 layers 9.44 -> 9.18, 16 of 168 x 3 layers of the 14B shape in bfloat16 (whose lm_head stays in plain rows) 16.83 ->
+// 16.64, 8B steps and prefills as before; gate/up alone 26.2 -> 23.5 us (19.3 in either order if the weights lie in the last-level cache), the head
+// 149 -> 142.
 // weight_row: element offset of the first 64 k of row r; the next 64 lie 64 << lg elements on.
 constexpr int WEIGHT_SLAB = 5;
 PC_HD inline int64_t weight_row(int64_t r, int64_t K, int lg) { return ((r >> lg) << lg) * K + (r & ((1 << lg) - 1)) * 64; }
