@@ -610,68 +610,74 @@ __global__ __launch_bounds__(SAMPLE_WAVES *WAVE, ROOMY ? 4 : 8) void sample_kern
             // publishing what it sees next before a slow one is here, so that goes to another word)
             float seen = key_logit(sb.opening);
             filed = seen - reach;
-            Fold f;
-            auto chunk = [&](auto plain, int base) {   // plain: whole strides without the EOS id
-                constexpr bool PLAIN = decltype(plain)::value;
-                float raw[AHEAD][VEC], v[AHEAD][VEC];
-                const uint32_t others = __hip_atomic_load(&sb.seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-#pragma unroll
-                for (int u = 0; u < AHEAD; ++u) {
-                    const int idx = base + u * STRIDE + lane * VEC;
-                    if (PLAIN) load_vec<VEC>(x + idx, raw[u]);
-                    else {
-#pragma unroll
-                        for (int c = 0; c < VEC; ++c) raw[u][c] = idx + c < we ? x[idx + c] : 0.f;
-                    }
-                }
-                float top[AHEAD];
-#pragma unroll
-                for (int u = 0; u < AHEAD; ++u) {
-                    const int idx = base + u * STRIDE + lane * VEC;
-                    top[u] = -INFINITY;
-#pragma unroll
-                    for (int c = 0; c < VEC; ++c) {
-                        v[u][c] = PLAIN ? scale_logit(raw[u][c], inv_t) : scale_logit(raw[u][c], idx + c, inv_t, eos_id, eos_bias);
-                        if (!PLAIN && idx + c == eos_id) raw[u][c] += eos_key_add;   // (from here on: the key's logit)
-                        if (!PLAIN && idx + c >= we) v[u][c] = -INFINITY;
-                        top[u] = fmaxf(top[u], v[u][c]);
-                    }
-                }
-                const float before = seen;
-                const int granule = (base - wb) / NUC_GRANULE;   // (beyond the last one only where the bins are not used)
-                if (VEC == 4) {
+            // Rows that nucleus_binned refuses whatever the bins hold: too long, or a maximum beyond 1e5 at the first look (block-uniform).
+            // (1024 x 151936 beyond 1e5: 3803 us with the bins filled, 3720 without; 256 rows of 300000 tokens 770, 727)
+            if (vocab > NUC_MAX_VOCAB || !(seen < 1e5f)) {
+                level1();
+            } else {
+                Fold f;
+                auto chunk = [&](auto plain, int base) {   // plain: whole strides without the EOS id
+                    constexpr bool PLAIN = decltype(plain)::value;
+                    float raw[AHEAD][VEC], v[AHEAD][VEC];
+                    const uint32_t others = __hip_atomic_load(&sb.seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) {
-                        top[u] = wave_max_all(top[u]);
-                        seen = fmaxf(seen, top[u]);
-                        if (lane == 0 && granule + u < NUC_GRANULES) sb.granule_max[wave][granule + u] = top[u];
-                    }
-                } else {
-                    const float t = wave_max_all(fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3])));
-                    seen = fmaxf(seen, t);
-                    if (lane == 0 && granule < NUC_GRANULES) sb.granule_max[wave][granule] = t;
-                }
-                if (lane == 0 && seen > before) atomicMax(&sb.seen, okey(seen));
-                seen = fmaxf(seen, key_logit(others));
-                const float from = seen - reach;
+                        const int idx = base + u * STRIDE + lane * VEC;
+                        if (PLAIN) load_vec<VEC>(x + idx, raw[u]);
+                        else {
 #pragma unroll
-                for (int u = 0; u < AHEAD; ++u) {
-                    f.take(v[u]);
-                    if (VEC > 1 && !(top[u] > from)) continue;   // (wave-uniform)
-#pragma unroll
-                    for (int c = 0; c < VEC; ++c) {
-                        const NucleusFile t(raw[u][c], per_logit);
-                        if (v[u][c] > from) t.add(sb);
+                            for (int c = 0; c < VEC; ++c) raw[u][c] = idx + c < we ? x[idx + c] : 0.f;
+                        }
                     }
+                    float top[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        const int idx = base + u * STRIDE + lane * VEC;
+                        top[u] = -INFINITY;
+#pragma unroll
+                        for (int c = 0; c < VEC; ++c) {
+                            v[u][c] = PLAIN ? scale_logit(raw[u][c], inv_t) : scale_logit(raw[u][c], idx + c, inv_t, eos_id, eos_bias);
+                            if (!PLAIN && idx + c == eos_id) raw[u][c] += eos_key_add;   // (from here on: the key's logit)
+                            if (!PLAIN && idx + c >= we) v[u][c] = -INFINITY;
+                            top[u] = fmaxf(top[u], v[u][c]);
+                        }
+                    }
+                    const float before = seen;
+                    const int granule = (base - wb) / NUC_GRANULE;   // (beyond the last one only where the bins are not used)
+                    if (VEC == 4) {
+#pragma unroll
+                        for (int u = 0; u < AHEAD; ++u) {
+                            top[u] = wave_max_all(top[u]);
+                            seen = fmaxf(seen, top[u]);
+                            if (lane == 0 && granule + u < NUC_GRANULES) sb.granule_max[wave][granule + u] = top[u];
+                        }
+                    } else {
+                        const float t = wave_max_all(fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3])));
+                        seen = fmaxf(seen, t);
+                        if (lane == 0 && granule < NUC_GRANULES) sb.granule_max[wave][granule] = t;
+                    }
+                    if (lane == 0 && seen > before) atomicMax(&sb.seen, okey(seen));
+                    seen = fmaxf(seen, key_logit(others));
+                    const float from = seen - reach;
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        f.take(v[u]);
+                        if (VEC > 1 && !(top[u] > from)) continue;   // (wave-uniform)
+#pragma unroll
+                        for (int c = 0; c < VEC; ++c) {
+                            const NucleusFile t(raw[u][c], per_logit);
+                            if (v[u][c] > from) t.add(sb);
+                        }
+                    }
+                };
+                for (int base = wb; base < we; base += AHEAD * STRIDE) {
+                    if (base + AHEAD * STRIDE <= we && !(eos_id >= base && eos_id < base + AHEAD * STRIDE))
+                        chunk(std::true_type{}, base);
+                    else
+                        chunk(std::false_type{}, base);
                 }
-            };
-            for (int base = wb; base < we; base += AHEAD * STRIDE) {
-                if (base + AHEAD * STRIDE <= we && !(eos_id >= base && eos_id < base + AHEAD * STRIDE))
-                    chunk(std::true_type{}, base);
-                else
-                    chunk(std::false_type{}, base);
+                finish(f);
             }
-            finish(f);
         }
         __syncthreads();
         float M0 = -INFINITY;

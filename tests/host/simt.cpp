@@ -12,6 +12,7 @@
 #include "simt_run.h"
 
 simt_dim threadIdx, blockIdx, blockDim;
+long simt_word_adds;
 
 namespace {
 const int STACK = 128 << 10;

@@ -12,6 +12,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 struct simt_dim { int x; };
 extern simt_dim threadIdx, blockIdx, blockDim;
@@ -20,6 +21,7 @@ void simt_barrier(int line);
 const uint64_t *simt_exchange(uint64_t mine, uint64_t *live);   // every live lane's value, 64 of them
 enum { SIMT_READ = 0, SIMT_WRITE = 1, SIMT_ATOMIC = 2 };
 void simt_access(const void *p, int bytes, int kind);
+extern long simt_word_adds;   // atomic adds to 64-bit integers
 
 #define __global__
 #define __device__
@@ -48,7 +50,7 @@ inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 inline int __ffsll(long long v) { return __builtin_ffsll(v); }
 inline float __builtin_amdgcn_exp2f(float x) { return exp2f(x); }
 
-template <typename T> SIMT_UNSEEN T atomicAdd(T *p, T v) { simt_access(p, sizeof(T), SIMT_ATOMIC); const T old = *p; *p = old + v; return old; }
+template <typename T> SIMT_UNSEEN T atomicAdd(T *p, T v) { simt_access(p, sizeof(T), SIMT_ATOMIC); simt_word_adds += sizeof(T) == 8 && std::is_integral<T>::value; const T old = *p; *p = old + v; return old; }
 template <typename T> SIMT_UNSEEN T atomicMax(T *p, T v) { simt_access(p, sizeof(T), SIMT_ATOMIC); const T old = *p; *p = old < v ? v : old; return old; }
 template <typename T> SIMT_UNSEEN T atomicMin(T *p, T v) { simt_access(p, sizeof(T), SIMT_ATOMIC); const T old = *p; *p = v < old ? v : old; return old; }
 template <typename T> SIMT_UNSEEN T __hip_atomic_load(const T *p, int, int) { simt_access(p, sizeof(T), SIMT_ATOMIC); return *p; }

@@ -43,6 +43,7 @@ int main(int, char **a) {
         }
         printf("%d %a\\n", tok[r], (double)lp[r]);
     }
+    fprintf(stderr, "%ld tokens put in bins\\n", simt_word_adds);
     return 0;
 }
 """
@@ -69,7 +70,7 @@ def program(tmp_path_factory):
     return os.path.join(d, "run")
 
 
-def _run(program, x, T, top_p, seed, step, eos, bias, order):
+def _run(program, x, T, top_p, seed, step, eos, bias, order, said=None):
     n, V = x.shape
     inv_t = np.float32(1.0) / np.float32(T)
     key_add = np.float32(bias) * np.float32(T) if eos >= 0 else np.float32(0)
@@ -79,6 +80,8 @@ def _run(program, x, T, top_p, seed, step, eos, bias, order):
     out = p.stdout.decode()
     assert p.returncode == 0, "%s%s" % (out[-500:], p.stderr.decode()[-500:])
     lines = [l.split() for l in out.splitlines()]
+    if said is not None:
+        said.append(p.stderr.decode())
     return [int(t) for t, _ in lines], [float.fromhex(lp) for _, lp in lines]
 
 
@@ -128,3 +131,15 @@ def test_one_rounding_of_the_biased_logit_on_every_way(program, V):
     keep = np.stack([sampler.nucleus(r, top_p) for r in w])
     want = _run(program, np.where(keep, x, -np.inf).astype(np.float32), T, 1.0, 5, 2, eos, bias, 0)
     assert (tok, lp) == want and eos in tok
+
+
+@pytest.mark.parametrize("V,shift", [(4100, 2.0e5), (4097, 2.0e5), (262152, 0.0), (4100, 9.9e4)])
+def test_rows_beyond_the_bins_are_not_put_in_them(program, V, shift):
+    # Scaled logits beyond 1e5 and rows of more than 2^18 tokens go to the other search whatever the bins hold.
+    rng = np.random.default_rng(V)
+    x = (rng.standard_normal((1, V)) + shift).astype(np.float32)
+    said = []
+    tok, lp = _run(program, x, 1.0, 0.9, 5, 1, V // 2, 0.25, 0, said)
+    want, wlp = sampler.sample_token(x[0], 1.0, philox.sampling_uniform(5, 51, 1), V // 2, 0.25, top_p=0.9)
+    assert tok[0] == want and abs(lp[0] - wlp) <= 3e-5 * max(1.0, abs(wlp))
+    assert said[0].startswith("0 tokens") == (shift > 1e5 or V > 1 << 18)
