@@ -1210,19 +1210,26 @@ extern "C" int pc_internal_gemm(int dtype, int epi, const void *A, const void *W
     return launch_gemm(dtype, 1, A, WeightRef(W, slabs ? WEIGHT_SLAB : 0), C, M, N, K, epi, slices, slice_cap_floats, sat, (hipStream_t)stream, nullptr);
 }
 // For tests, not part of the C ABI: the ResidTile of a residual projection and the QkvRoute of a q/k/v projection of more than 512 rows, and
-// one launch in the tile of a q/k/v route (`slabs`: W is in the order of the 16-bit copies; `extra`: a GemmQkv).  1: launched; 0: not a tile of this file, or not a call that
-// the kernels take.
+// one launch in the tile of a q/k/v route, W in plain rows or (_slabs) in the order of the 16-bit copies (`extra`: a GemmQkv).  1: launched;
+// 0: not a tile of this file, or not a call that the kernels take.
 extern "C" int pc_internal_resid_tile(int M, int N, int K) { return pc::resid_tile(M, N, K, pc::EPI_RESID_F32); }
 extern "C" int pc_internal_qkv_route(int M, int N, int K) { return pc::qkv_route(M, N, K); }
-extern "C" int pc_internal_gemm_qkv(int dtype, int route, const void *A, const void *W, int slabs, int M, int N, int K, const void *extra,
-                                    uint32_t *sat, void *stream) {
-    using namespace pc;
-    if ((dtype != KD_BF16 && dtype != KD_F16) || route <= QKV_SEPARATE || route >= QKV_LARGE || !A || !W || !extra || M <= 0 || N <= 0 ||
-        N % 128 != 0 || K <= 0 || K % 64 != 0 || (((uintptr_t)A | (uintptr_t)W) & 15) != 0)
+namespace pc {
+static int qkv_by_route(int dtype, int route, const void *A, WeightRef w, int M, int N, int K, const void *extra, uint32_t *sat, void *stream) {
+    if ((dtype != KD_BF16 && dtype != KD_F16) || route <= QKV_SEPARATE || route >= QKV_LARGE || !A || !w.p || !extra || M <= 0 || N <= 0 ||
+        N % 128 != 0 || K <= 0 || K % 64 != 0 || (((uintptr_t)A | (uintptr_t)w.p) & 15) != 0)
         return 0;
-    const WeightRef w(W, slabs ? WEIGHT_SLAB : 0);
     gemm_init();
     if (dtype == KD_BF16) gemm_qkv_t<bf16_t>((QkvRoute)route, A, w, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
     else gemm_qkv_t<f16_t>((QkvRoute)route, A, w, M, N, K, *(const GemmQkv *)extra, sat, (hipStream_t)stream);
     return 1;
+}
+}  // namespace pc
+extern "C" int pc_internal_gemm_qkv(int dtype, int route, const void *A, const void *W, int M, int N, int K, const void *extra, uint32_t *sat,
+                                    void *stream) {
+    return pc::qkv_by_route(dtype, route, A, pc::WeightRef(W, 0), M, N, K, extra, sat, stream);
+}
+extern "C" int pc_internal_gemm_qkv_slabs(int dtype, int route, const void *A, const void *W, int M, int N, int K, const void *extra,
+                                          uint32_t *sat, void *stream) {
+    return pc::qkv_by_route(dtype, route, A, pc::WeightRef(W, pc::WEIGHT_SLAB), M, N, K, extra, sat, stream);
 }

@@ -616,7 +616,7 @@ template <typename T, int TMH, int TNH> struct LargeCfg {
 // random ones).  The constants are a least-squares fit, then moved a little for least regret, to the times of 1094 launches of 513 to
 // 16384 rows x 512 to 151936 columns x 128 to 17408, each in every tile and up to 8 slices, with weights in plain rows whose values repeated (and let
 // the clock rise).  Held against times on mixed values in slabs and, for residual projections, with the eight-wave tiles among the forms
-// (profiles/large_tile_times.txt, taken by kernel_bench tiles; tests/test_tile_choice.py) what runs takes 1.0 % longer on average than the
+// (profiles/large_tile_times.txt and resid_tile_times.txt, taken by kernel_bench tiles; tests/test_tile_choice.py) what runs takes 1.0 % longer on average than the
 // fastest form, 9 % at worst from K = 1024 up (640 x 24576 x 4096, 138 us for 126) and 31 % below (16384 x 2368 x 256, 35 us for 27).  (One
 // set of constants for all epilogues, fitted without the norm that reads the slices and to K of 1536 and more, was up to 28 % off there
 // and 60 % below: 640 rows x 2560 x 9728 58.2 us for 44.5.)
@@ -810,18 +810,14 @@ int launch_gemm_large_logprob(int dtype, const void *A, WeightRef W, int M, int 
 
 }   // namespace pc
 
-// For tests and tuning, not part of the C ABI: one launch in the tile of bm rows x bn columns (`slabs`: W is in the order of the 16-bit
-// copies; `extra`: the GemmRowScale, GemmQkv or GemmLogprob of such an epilogue).  1: launched; 0: no such tile with this epilogue, or not a
-// call that the kernels take.
-extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int slices, const void *A, const void *W, int slabs, void *C, int M,
-                                      int N, int K, const void *extra, uint32_t *sat, void *stream) {
-    using namespace pc;
+namespace pc {
+static int large_by_name(int dtype, int bm, int bn, int epi, int slices, const void *A, WeightRef w, void *C, int M, int N, int K, const void *extra,
+                         uint32_t *sat, void *stream) {
     const bool swiglu = epi == EPI_SWIGLU || epi == EPI_SWIGLU_RS, own = epi == EPI_SWIGLU_RS || epi == EPI_QKV || epi == EPI_LOGPROB;
-    const WeightRef w(W, slabs ? WEIGHT_SLAB : 0);
     for (int id = 0; id < LT_COUNT; ++id) {
         if (LARGE_SHAPES[id][0] != bm || LARGE_SHAPES[id][1] != bn || epi < 0 || !(large_tiles(epi) >> id & 1)) continue;
-        if ((dtype != KD_BF16 && dtype != KD_F16) || !A || !W || (!C && epi != EPI_QKV && epi != EPI_LOGPROB) || (own && !extra) || M <= 0 ||
-            N <= 0 || (slabs && !weight_lg(dtype, N, K)) || !large_ok(A, w, C, M, N, K, epi) || (swiglu && N % 64 != 0) ||
+        if ((dtype != KD_BF16 && dtype != KD_F16) || !A || !w.p || (!C && epi != EPI_QKV && epi != EPI_LOGPROB) || (own && !extra) || M <= 0 ||
+            N <= 0 || (w.lg && !weight_lg(dtype, N, K)) || !large_ok(A, w, C, M, N, K, epi) || (swiglu && N % 64 != 0) ||
             (epi == EPI_QKV && N % 128 != 0) || slices < 1 || (slices > 1 && epi != EPI_STORE_F32) || !large_slices_ok(slices, K))
             return 0;
         gemm_large_init();
@@ -830,6 +826,18 @@ extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int sl
         return 1;
     }
     return 0;
+}
+}   // namespace pc
+// For tests, not part of the C ABI: one launch in the tile of bm rows x bn columns, W in plain rows or (_slabs) in the order of the 16-bit
+// copies (`extra`: the GemmRowScale, GemmQkv or GemmLogprob of such an epilogue).  1: launched; 0: no such tile with this epilogue, or not a
+// call that the kernels take.
+extern "C" int pc_internal_gemm_large(int dtype, int bm, int bn, int epi, int slices, const void *A, const void *W, void *C, int M, int N,
+                                      int K, const void *extra, uint32_t *sat, void *stream) {
+    return pc::large_by_name(dtype, bm, bn, epi, slices, A, pc::WeightRef(W, 0), C, M, N, K, extra, sat, stream);
+}
+extern "C" int pc_internal_gemm_large_slabs(int dtype, int bm, int bn, int epi, int slices, const void *A, const void *W, void *C, int M, int N,
+                                            int K, const void *extra, uint32_t *sat, void *stream) {
+    return pc::large_by_name(dtype, bm, bn, epi, slices, A, pc::WeightRef(W, pc::WEIGHT_SLAB), C, M, N, K, extra, sat, stream);
 }
 // The tile (its place in the list above; LT_EIGHT: gemm_mfma's) and the number of K slices that the estimate chooses, up to
 // max_slices where there is room for slices (0: there is none).

@@ -1,9 +1,7 @@
 """Every tile of the large projection kernel by name, in every epilogue it is built for and both 16-bit types, against 64-bit
-sums: row and column remainders, two, three and five steps of K to a tile, several output tiles per block, an uneven last K slice,
-the weights in slabs (the order of the library's 16-bit copies) and in plain rows (an lm_head read in place).
+sums: row and column remainders, two, three and five steps of K to a tile, several output tiles per block, an uneven last K slice.
 (The library chooses a tile by an estimate of its time, so the sizes of a model test say little about which one runs.)  The
-q/k/v tiles on eight waves that share such batches are run alongside; all give the same bits.  The tiles of smaller batches are run in the
-sizes that they are chosen for, once in either order of the weights.
+q/k/v tiles on eight waves that share such batches are run alongside; all give the same bits.
 
 Tolerances.  The operands are exact in 16 bits; a product is summed in float32, K of them with at most K roundings of 2^-24 each:
 |sum - exact| <= K 2^-24 sum |a w|, called d below.  Results in the model type add their own rounding, 2^-11 of the value in half
@@ -52,33 +50,25 @@ class Qkv(ctypes.Structure):
                 ("rope_sin", ctypes.c_void_p), ("kv", KvGeom), ("layer", ctypes.c_int), ("hq", ctypes.c_int), ("q_out", ctypes.c_void_p)]
 
 
-def _slabs(w):
-    # slabs of 32 rows x 64 columns, a row's 64 values behind the previous row's, slabs one after another along a row
-    n, k = w.shape
-    return w.reshape(n // 32, 32, k // 64, 64).permute(0, 2, 1, 3).contiguous().reshape(n, k)
-
-
-def _launch(act, tile, epi, a, w, c, extra=None, slices=1, sat=None, slabs=False):
+def _launch(act, tile, epi, a, w, c, extra=None, slices=1, sat=None):
     from paper_2605_26606_amd import binding
     f = binding.library().pc_internal_gemm_large
     f.restype = ctypes.c_int
-    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_void_p] * 2 + [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int] * 3 + [ctypes.c_void_p] * 3
+    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_void_p] * 3 + [ctypes.c_int] * 3 + [ctypes.c_void_p] * 3
     assert a.is_contiguous() and w.is_contiguous() and a.shape[1] == w.shape[1]
-    w = _slabs(w) if slabs else w
-    got = f(TYPES[act][0], tile[0], tile[1], epi, slices, a.data_ptr(), w.data_ptr(), int(slabs), None if c is None else c.data_ptr(),
-            a.shape[0], w.shape[0], a.shape[1], None if extra is None else ctypes.addressof(extra), None if sat is None else sat.data_ptr(),
+    got = f(TYPES[act][0], tile[0], tile[1], epi, slices, a.data_ptr(), w.data_ptr(), None if c is None else c.data_ptr(), a.shape[0],
+            w.shape[0], a.shape[1], None if extra is None else ctypes.addressof(extra), None if sat is None else sat.data_ptr(),
             torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     return got
 
 
-def _launch_eight(act, route, a, w, extra, slabs):
+def _launch_eight(act, route, a, w, extra):
     from paper_2605_26606_amd import binding
     f = binding.library().pc_internal_gemm_qkv
     f.restype = ctypes.c_int
-    f.argtypes = [ctypes.c_int] * 2 + [ctypes.c_void_p] * 2 + [ctypes.c_int] * 4 + [ctypes.c_void_p] * 3
-    w = _slabs(w) if slabs else w
-    got = f(TYPES[act][0], route, a.data_ptr(), w.data_ptr(), int(slabs), a.shape[0], w.shape[0], a.shape[1], ctypes.addressof(extra), None,
+    f.argtypes = [ctypes.c_int] * 2 + [ctypes.c_void_p] * 2 + [ctypes.c_int] * 3 + [ctypes.c_void_p] * 3
+    got = f(TYPES[act][0], route, a.data_ptr(), w.data_ptr(), a.shape[0], w.shape[0], a.shape[1], ctypes.addressof(extra), None,
             torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     return got
@@ -100,13 +90,11 @@ def _guarded(shape, dtype, fill):
     return whole, whole[:shape[0]]
 
 
-def _sizes(epi, tile, slabs):
+def _sizes(epi, tile):
     """(rows, columns, K): less than a tile and a bit more than one, the reductions of odd and even step counts; then more than
     256 tiles, so that blocks compute several"""
     bm, bn = tile
     unit = 64 if epi in (SWIGLU, SWIGLU_RS) else (128 if epi == QKV else 16)
-    if slabs:
-        unit = max(unit, 32)
     few = (bn * 2 + bn // 3 + unit) // unit * unit
     many = (90 * bn - 7 * bn // 16) // unit * unit
     return [(bm - 19, max(unit, few // 4 // unit * unit), 128), (bm + 37, few, 320), (2 * bm + 37, many, 192), (2 * bm + 1, many, 128)]
@@ -119,100 +107,40 @@ def _pairs(n):
     return torch.cat([gate, gate + 16])
 
 
-@pytest.mark.parametrize("slabs", [True, False])
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("epi,tile", [c for c in CASES if c[0] in (STORE, RESID)])
-def test_plain_tiles(epi, tile, act, slabs):
-    for m, n, k in _sizes(epi, tile, slabs):
-        say("large tile%s %dx%d, epilogue %d, %s: %d x %d x %d" % (" on slabs" if slabs else "", *tile, epi, act, m, n, k))
+def test_plain_tiles(epi, tile, act):
+    for m, n, k in _sizes(epi, tile):
+        say("large tile %dx%d, epilogue %d, %s: %d x %d x %d" % (*tile, epi, act, m, n, k))
         a, w, exact, d = _operands(act, m, n, k, m + k)
         old = torch.randn((m, n), device="cuda") if epi == RESID else torch.zeros((m, n), device="cuda")
         whole, c = _guarded((m, n), torch.float32, old)
-        assert _launch(act, tile, epi, a, w, c, slabs=slabs)
+        assert _launch(act, tile, epi, a, w, c)
         want = exact + old.double()
         assert bool(((c.double() - want).abs() <= d + 2.0 ** -23 * want.abs()).all())
         assert bool((whole[m:] == GUARD).all())
     if epi == STORE:   # results that start at any float
-        m, n, k = tile[0] + 3, tile[1] + (32 if slabs else 48), 128
+        m, n, k = tile[0] + 3, tile[1] + 48, 128
         a, w, exact, d = _operands(act, m, n, k, 6)
         flat = torch.full((m * n + 8,), GUARD, device="cuda")
-        assert _launch(act, tile, epi, a, w, flat[1:], slabs=slabs)
+        assert _launch(act, tile, epi, a, w, flat[1:])
         assert bool(((flat[1:1 + m * n].double().reshape(m, n) - exact).abs() <= d).all())
         assert bool((flat[1 + m * n:] == GUARD).all()) and float(flat[0]) == GUARD
     if epi == STORE:   # K slices: 4 + 4 + 3 steps; the sum of the slices is the product
-        m, n, k, s = tile[0] + 5, tile[1] + (32 if slabs else 16), 704, 3
+        m, n, k, s = tile[0] + 5, tile[1] + 16, 704, 3
         a, w, exact, d = _operands(act, m, n, k, 5)
         out = torch.full((s + 1, m, n), GUARD, device="cuda")
-        assert _launch(act, tile, epi, a, w, out, slices=s, slabs=slabs)
+        assert _launch(act, tile, epi, a, w, out, slices=s)
         assert bool(((out[:s].double().sum(0) - exact).abs() <= d).all())
         assert bool((out[s] == GUARD).all())
 
 
-# (columns, K, epilogue, rows): the tiles of up to 512 rows for wide, very wide, mid-width, long and small projections, the eight-wave ones
-# above; last tiles of 32 or 64 columns
-CHOSEN = [
-    (12352, 192, STORE, [3, 50, 100, 170, 250, 300, 400]),
-    (33088, 128, STORE, [3, 50, 100, 170, 250]),
-    (12352, 192, SWIGLU, [3, 50, 100, 170, 250, 300, 400]),
-    (33088, 128, SWIGLU, [50, 100, 170, 250]),
-    (4160, 2112, RESID, [3, 50, 100, 170, 250, 300, 400]),
-    (1600, 5504, RESID, [3, 50, 200, 300, 400]),
-    (1600, 576, STORE, [3, 50, 250]),
-    (1600, 1536, RESID, [577, 1000]),
-    (512, 128, RESID, [600]),
-    (12352, 128, STORE, [600, 6000]),
-]
-
-
-@pytest.mark.parametrize("act", ["f16", "bf16"])
-@pytest.mark.parametrize("n,k,epi,rows", CHOSEN)
-def test_chosen_tiles_give_the_same_bits_on_slabs_and_rows(n, k, epi, rows, act):
-    from paper_2605_26606_amd import binding
-    f = binding.library().pc_internal_gemm
-    f.restype = ctypes.c_int
-    f.argtypes = [ctypes.c_int] * 2 + [ctypes.c_void_p] * 2 + [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_size_t] + \
-        [ctypes.c_void_p] * 2
-    _, dtype, u, tiny = TYPES[act]
-    cap = 8 << 20
-    buffer = torch.empty(cap, device="cuda")
-    for m in rows:
-        say("chosen tile, epilogue %d, %s: %d x %d x %d" % (epi, act, m, n, k))
-        a, w, exact, d = _operands(act, m, n, k, m + k)
-        old = torch.randn((m, n), device="cuda")
-        results = []
-        for order in (w, _slabs(w)):
-            whole, c = _guarded((m, n // 2) if epi == SWIGLU else (m, n), dtype if epi == SWIGLU else torch.float32, old if epi == RESID else 0)
-            sat = torch.zeros(1, dtype=torch.int32, device="cuda")
-            s = f(TYPES[act][0], epi, a.data_ptr(), order.data_ptr(), int(order is not w), c.data_ptr(), m, n, k,
-                  buffer.data_ptr() if epi == RESID else None, cap if epi == RESID else 0, sat.data_ptr(), torch.cuda.current_stream().cuda_stream)
-            torch.cuda.synchronize()
-            assert s >= 1 and bool((whole[m:] == GUARD).all())
-            results.append(buffer[:s * m * n].reshape(s, m, n).clone() if s > 1 else c.clone())
-        assert torch.equal(results[0], results[1])
-        got = results[1].double()
-        if epi == SWIGLU:
-            at = _pairs(n).cuda()
-            g, up, dg, du = exact[:, at[:n // 2]], exact[:, at[n // 2:]], d[:, at[:n // 2]], d[:, at[n // 2:]]
-            sig = torch.sigmoid(g)
-            want = g * sig * up
-            bound = 1.1 * up.abs() * dg + (g * sig).abs() * du + 1.1 * dg * du + want.abs() * (u + (2 + g.abs()) * 2.0 ** -21) + tiny
-            if act == "f16":
-                want = want.clamp(-65504, 65504)
-            assert bool(((got - want).abs() <= bound).all())
-        elif got.dim() == 3:
-            assert bool(((got.sum(0) - exact).abs() <= d).all())
-        else:
-            want = exact + old.double() if epi == RESID else exact
-            assert bool(((got - want).abs() <= d + 2.0 ** -23 * want.abs()).all())
-
-
-@pytest.mark.parametrize("slabs", [True, False])
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("epi,tile", [c for c in CASES if c[0] in (SWIGLU, SWIGLU_RS)])
-def test_gate_up_tiles(epi, tile, act, slabs):
+def test_gate_up_tiles(epi, tile, act):
     _, dtype, u, tiny = TYPES[act]
-    for m, n, k in _sizes(epi, tile, slabs):
-        say("large tile%s %dx%d, epilogue %d, %s: %d x %d x %d" % (" on slabs" if slabs else "", *tile, epi, act, m, n, k))
+    for m, n, k in _sizes(epi, tile):
+        say("large tile %dx%d, epilogue %d, %s: %d x %d x %d" % (*tile, epi, act, m, n, k))
         a, w, exact, d = _operands(act, m, n, k, m + k)
         extra = None
         if epi == SWIGLU_RS:   # partial sums of squares of 32 columns each; one row is tiny, so that its scale is large
@@ -230,7 +158,7 @@ def test_gate_up_tiles(epi, tile, act, slabs):
         bound = 1.1 * up.abs() * dg + (g * sig).abs() * du + 1.1 * dg * du + want.abs() * (u + (2 + g.abs()) * 2.0 ** -21) + tiny
         whole, c = _guarded((m, n // 2), dtype, 0)
         sat = torch.zeros(1, dtype=torch.int32, device="cuda")
-        assert _launch(act, tile, epi, a, w, c, extra, sat=sat, slabs=slabs)
+        assert _launch(act, tile, epi, a, w, c, extra, sat=sat)
         if act == "f16":   # beyond the half range: clamped, and counted once each
             over = want.abs() > 65504 * (1 + 2.0 ** -10)
             near = (want.abs() > 65504 * (1 - 2.0 ** -10)) & ~over
@@ -253,19 +181,18 @@ def test_gate_up_tiles(epi, tile, act, slabs):
             extra = RowScale(ssq.data_ptr(), k // 32, k, 0.0)
         whole, c = _guarded((m, n // 2), dtype, 0)
         sat = torch.zeros(1, dtype=torch.int32, device="cuda")
-        assert _launch(act, tile, epi, a, w, c, extra, sat=sat, slabs=slabs)
+        assert _launch(act, tile, epi, a, w, c, extra, sat=sat)
         want = torch.zeros((m, n // 2), device="cuda")
         for r in (0, m - 1):
             want[r, cols] = -65504.0
         assert torch.equal(c.float(), want) and int(sat) == 4
 
 
-@pytest.mark.parametrize("slabs", [True, False])
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("tile", TILES[LOGPROB])
-def test_log_softmax_tiles(tile, act, slabs):
-    for m, n, k in _sizes(LOGPROB, tile, slabs):
-        say("large tile%s %dx%d, log-softmax, %s: %d x %d x %d" % (" on slabs" if slabs else "", *tile, act, m, n, k))
+def test_log_softmax_tiles(tile, act):
+    for m, n, k in _sizes(LOGPROB, tile):
+        say("large tile %dx%d, log-softmax, %s: %d x %d x %d" % (*tile, act, m, n, k))
         a, w, exact, d = _operands(act, m, n, k, m + k)
         strips = (n + 255) // 256 * 2
         rng = np.random.default_rng(m)
@@ -277,7 +204,7 @@ def test_log_softmax_tiles(tile, act, slabs):
         sm_all, sm = _guarded((strips, m), torch.float64, 3.0)
         target = torch.full((m,), GUARD, device="cuda")
         extra = Logprob(inv_t, tokens.data_ptr(), index.data_ptr(), mx.data_ptr(), target.data_ptr(), sm.data_ptr())
-        assert _launch(act, tile, LOGPROB, a, w, None, extra, slabs=slabs)
+        assert _launch(act, tile, LOGPROB, a, w, None, extra)
         col = tokens[1:].long()
         inside = col < n
         assert bool((target[~inside] == GUARD).all())
@@ -314,17 +241,16 @@ def _v_index(tin, d, bs):
     return bs * 128 + frag * 512 + (((tin % 32) // 8) * 16 + d % 16) * 8 + tin % 8
 
 
-@pytest.mark.parametrize("slabs", [True, False])
 @pytest.mark.parametrize("act", ["f16", "bf16"])
 @pytest.mark.parametrize("tile", TILES[QKV])
 @pytest.mark.parametrize("decode", [False, True])
-def test_rotating_tiles(tile, act, decode, slabs):
+def test_rotating_tiles(tile, act, decode):
     _, dtype, u, tiny = TYPES[act]
     # enough heads for more than 256 tiles at two row blocks and a remainder in the last size
     many = -(-260 * tile[1] // (3 * 128))
     for m, hq, hkv, k, bs in [(tile[0] - 19, 2, 1, 128, 32), (tile[0] + 37, 3, 3, 320, 64), (2 * tile[0] + 37, many - 6, 3, 192, 128)]:
         n = (hq + 2 * hkv) * 128
-        say("large tile%s %dx%d, q/k/v, %s, %s: %d x %d x %d" % (" on slabs" if slabs else "", *tile, act, "decode" if decode else "prefill", m, n, k))
+        say("large tile %dx%d, q/k/v, %s, %s: %d x %d x %d" % (*tile, act, "decode" if decode else "prefill", m, n, k))
         a, w, exact, d = _operands(act, m, n, k, m + k)
         # weight rows in the order of the packed heads (the values are those of the natural order)
         order = torch.arange(n)
@@ -360,7 +286,7 @@ def test_rotating_tiles(tile, act, decode, slabs):
         whole, q = _guarded((m, hq * 128), dtype, 0)
         extra = Qkv(d_slot.data_ptr(), None if decode else d_pos.data_ptr(), d_len.data_ptr(), cos.data_ptr(), sin.data_ptr(),
                     KvGeom(pool.data_ptr(), slots * per_slot * block_elems, bs, hkv, 128, per_slot, d_table.data_ptr()), layer, hq, q.data_ptr())
-        assert _launch(act, tile, QKV, a, w, None, extra, slabs=slabs)
+        assert _launch(act, tile, QKV, a, w, None, extra)
         c, s = cos[d_pos.long()].double()[:, None], sin[d_pos.long()].double()[:, None]
 
         def rotated(x, e):
@@ -391,46 +317,6 @@ def test_rotating_tiles(tile, act, decode, slabs):
         for route in EIGHT.values():
             flat.fill_(9.0)
             q.zero_()
-            assert _launch_eight(act, route, a, w, extra, slabs)
+            assert _launch_eight(act, route, a, w, extra)
             assert torch.equal(q, q_bits) and torch.equal(flat, kv_bits), route
             assert bool((whole[m:] == GUARD).all())
-
-
-@pytest.mark.parametrize("act", ["f16", "bf16"])
-@pytest.mark.parametrize("m,n,k", [
-    (1024, 1536, 1536),     # 128 x 64 blocks
-    (577, 1600, 1536), (2000, 512, 2048), (513, 2048, 1472),       # 64 x 64 (23 steps of K: an uneven last slice)
-    (600, 512, 256),        # short: one sum
-])
-def test_residual_blocks_give_the_bits_of_the_slices_they_stand_for(m, n, k, act):
-    # The blocks of 64 rows that residual projections of some hundred rows run in, against the large tile and the K slices that they replace,
-    # added up as the norm behind does: the slices in order, their sum to the residual.  With and without room for slices.
-    from paper_2605_26606_amd import binding
-    lib = binding.library()
-    assert lib.pc_internal_resid_tile(m, n, k) > 0
-    f = lib.pc_internal_gemm
-    f.restype = ctypes.c_int
-    f.argtypes = [ctypes.c_int] * 2 + [ctypes.c_void_p] * 2 + [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_size_t] + \
-        [ctypes.c_void_p] * 2
-    a, w, exact, d = _operands(act, m, n, k, m + k)
-    old = torch.randn((m, n), device="cuda")
-    order, cut = _slabs(w), 0
-    for cap in (8 << 20, 0):
-        s = ctypes.c_int()
-        tile = lib.pc_internal_gemm_large_pick(RESID, 0, min(8, cap // (m * n)), m, n, k, ctypes.byref(s))
-        cut += s.value > 1
-        say("residual blocks, %s: %d x %d x %d, %d slices" % (act, m, n, k, s.value))
-        parts = torch.empty((s.value, m, n), device="cuda")
-        assert _launch(act, TILES[RESID][tile], STORE, a, w, parts, slices=s.value, slabs=True)
-        want = torch.zeros((m, n), device="cuda")
-        for part in parts:
-            want += part
-        want = old + want
-        whole, c = _guarded((m, n), torch.float32, old)
-        buffer = torch.empty(max(cap, 4), device="cuda")
-        assert f(TYPES[act][0], RESID, a.data_ptr(), order.data_ptr(), 1, c.data_ptr(), m, n, k, buffer.data_ptr() if cap else None, cap, None,
-                 torch.cuda.current_stream().cuda_stream) == 1
-        torch.cuda.synchronize()
-        assert torch.equal(c, want) and bool((whole[m:] == GUARD).all())
-        assert bool(((c.double() - exact - old.double()).abs() <= d + 2.0 ** -23 * want.abs()).all())
-    assert cut == (0 if k == 256 else 1)

@@ -1,5 +1,5 @@
 """The tile and the number of K slices that the library chooses for a projection of more than 512 rows, held against the measured
-times of every form that computes it on weights in slabs (profiles/large_tile_times.txt).  Host code of the built library; no GPU."""
+times of every form that computes it (profiles/large_tile_times.txt).  Host code of the built library; no GPU."""
 import ctypes
 import os
 
@@ -28,10 +28,6 @@ def _chosen(lib, kind, m, n, k, mode):
         route = lib.pc_internal_qkv_route(m, n, k)
         if route != 6:
             return [None, "m64x128", "m128x128"][route]
-    if kind == RESID:
-        route = lib.pc_internal_resid_tile(m, n, k)
-        if route:
-            return [None, "m64x64", "m128x64"][route]
     s = ctypes.c_int()
     slices = min(8, (8 << 20) // (m * n)) if kind == RESID else 0     # the context's slice buffer: 32 MB
     tile = lib.pc_internal_gemm_large_pick(kind, int(mode == "dec"), slices, m, n, k, ctypes.byref(s))
@@ -42,7 +38,7 @@ def _chosen(lib, kind, m, n, k, mode):
 def test_the_choice_is_near_the_best_of_the_measured_forms(kind, name):
     # Bounds: two runs of one form differ by up to 4 %, on other cards the clocks under load differ as well; a wrong number of rounds
     # or slices costs 15 to 60 %.  Below K = 1024 a launch's time is its stores, of which the estimate knows nothing: there the worst
-    # choice is 31 % behind the best form (and still ahead of the eight-wave kernel that it would go to otherwise).
+    # choice is 39 % behind the best form (and still ahead of the eight-wave kernel that it would go to otherwise).
     from paper_2605_26606_amd import binding
     lib = binding.library()
     regret = []
